@@ -314,13 +314,17 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dkv_kernel(const AttnArg
         char *const out = (char *)(j ? a.dk : a.dv);
         const int64_t ost = j ? a.dk_st : a.dv_st, osh = j ? a.dk_sh : a.dv_sh;
         const float mul = j ? a.scale : 1.0f;
-        if (SHARD && (a.grad_f32 & 2)) {  // added to the partial sums the rows hold
-            if (kvrow < sk) add_rowT_f32<DB>((float *)out + (ktok0 + kvrow) * ost + (int64_t)g * osh, accT, mul, hl);
-        } else if (a.grad_f32) {
-            if (kvrow < sk) store_rowT<DB>(out + ((ktok0 + kvrow) * ost + (int64_t)g * osh) * 4, true, accT, mul, hl);
-        } else if (wk_lo < sk) {
-            // through the Q/dO buffer the last step did not use (every wavefront is past its barriers)
-            store_rowT_bf16_lds<DB>(smem + (n & 1) * STEP + wave * (32 * L::ROWB),
+        if (wk_lo >= sk) continue;
+        char *const stage = smem + (n & 1) * STEP + wave * (32 * L::ROWB);  // the Q/dO buffer the last step did not use (every wavefront is past its barriers)
+        if (a.grad_f32) {
+            float *const rows = (float *)out + (ktok0 + wk_lo) * ost + (int64_t)g * osh;
+            RowsF32<DB> f;
+            if (SHARD && (a.grad_f32 & 2))  // added to the partial sums the rows hold
+                f.add(stage, rows, ost, min(32, sk - wk_lo), accT, mul, lane);
+            else
+                f.store(stage, rows, ost, min(32, sk - wk_lo), accT, mul, lane);
+        } else {
+            store_rowT_bf16_lds<DB>(stage,
                                     (uint16_t *)out + (ktok0 + wk_lo) * ost + (int64_t)g * osh, ost,
                                     min(32, sk - wk_lo), accT, mul, lane);
         }
@@ -544,16 +548,17 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(const AttnArgs
             for (int p = 0; p < nparts; p++)
                 split_sum<DB>(a.pq.split_scratch + (int64_t)(slot + p) * kPartialBytes, dqT, 1.0f, tid);
         }
-        if (SHARD && (a.grad_f32 & 2)) {  // added to the partial sum the rows hold
-            if (qok)
-                add_rowT_f32<DB>((float *)a.dq + (tok0 + qrow) * a.dq_st + (int64_t)h * a.dq_sh, dqT, a.scale, hl);
-        } else if (a.grad_f32) {
-            if (qok)
-                store_rowT<DB>((char *)a.dq + ((tok0 + qrow) * a.dq_st + (int64_t)h * a.dq_sh) * 4, true, dqT,
-                               a.scale, hl);
-        } else if (wq_lo < s) {
-            // through the tile buffer the last step did not use (see the forward kernel)
-            store_rowT_bf16_lds<DB>(smem + (ntiles & 1) * 2 * TILE + wave * (32 * L::ROWB),
+        if (wq_lo >= s) continue;
+        char *const stage = smem + (ntiles & 1) * 2 * TILE + wave * (32 * L::ROWB);  // the tile buffer the last step did not use (see the forward kernel)
+        if (a.grad_f32) {
+            float *const rows = (float *)a.dq + (tok0 + wq_lo) * a.dq_st + (int64_t)h * a.dq_sh;
+            RowsF32<DB> f;
+            if (SHARD && (a.grad_f32 & 2))  // added to the partial sum the rows hold
+                f.add(stage, rows, a.dq_st, min(32, s - wq_lo), dqT, a.scale, lane);
+            else
+                f.store(stage, rows, a.dq_st, min(32, s - wq_lo), dqT, a.scale, lane);
+        } else {
+            store_rowT_bf16_lds<DB>(stage,
                                     (uint16_t *)a.dq + (tok0 + wq_lo) * a.dq_st + (int64_t)h * a.dq_sh, a.dq_st,
                                     min(32, s - wq_lo), dqT, a.scale, lane);
         }

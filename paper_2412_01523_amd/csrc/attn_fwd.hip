@@ -509,8 +509,14 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs a)
                 // (o_acc, lse_acc) <- merge((o_acc, lse_acc), (O, LSE)), the row's two half-wave lanes each
                 // taking their head-dim elements of the row; a part that counts nothing is silenced even
                 // if it holds rubbish (a running result is started with lse_acc = -inf over anything).
-                if (qrow < s) {
-                    const int64_t li = (int64_t)h * a.T + tok0 + qrow;
+                if (wq_lo < s) {
+                    const int nrows = min(32, s - wq_lo);
+                    float *const rows = (float *)a.dq + (tok0 + wq_lo) * a.dq_st + (int64_t)h * a.dq_sh;
+                    RowsF32<DB> acc32;
+                    int lane_ = lane;
+                    asm volatile("" : "+v"(lane_));  // (address arithmetic stays in the epilogue)
+                    acc32.load(rows, a.dq_st, nrows, lane_);
+                    const int64_t li = (int64_t)h * a.T + tok0 + min(qrow, s - 1);
                     const float la = a.delta_out[li];
                     const float lb = l_tot > 0.f ? m_run * a.scale + __logf(l_tot) : -INFINITY;
                     const float m = fmaxf(la, lb);
@@ -522,25 +528,19 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs a)
                         wb = l_tot > 0.f ? eb * inv / l_tot : 0.f;  // (with the row's normalisation)
                         lse = m + __logf(ea + eb);
                     }
-                    float *row = (float *)a.dq + (tok0 + qrow) * a.dq_st + (int64_t)h * a.dq_sh;
+                    uint16_t *const o16 = a.out_o ? a.out_o + (tok0 + wq_lo) * a.o_st + (int64_t)h * a.o_sh : nullptr;  // the merged rows rounded to bf16, if asked for
+                    acc32.each(smem + wave * (32 * L::ROWB), 32, oacc, wb, lane_, [&](int half, int n, int row, int col, f32x4 w) {
+                        const float wr = __shfl(wa, row);  // the weight of the piece's row
+                        const f32x4 o = acc32.old[half][n];
 #pragma unroll
-                    for (int db = 0; db < DB; db++)
-#pragma unroll
-                        for (int i4 = 0; i4 < 4; i4++) {
-                            f32x4 *p = (f32x4 *)(row + db * 32 + 8 * i4 + 4 * hl);
-                            f32x4 w = *p;
-#pragma unroll
-                            for (int e = 0; e < 4; e++) {
-                                w[e] = (wa > 0.f ? wa * w[e] : 0.f) + wb * oacc[db][4 * i4 + e];
-                                oacc[db][4 * i4 + e] = w[e];
-                            }
-                            *p = w;
+                        for (int e = 0; e < 4; e++) w[e] += wr > 0.f ? wr * o[e] : 0.f;
+                        if (row < nrows) {
+                            *(f32x4 *)(rows + (int64_t)row * a.dq_st + col) = w;
+                            if (o16) *(u32x2 *)(o16 + (int64_t)row * a.o_st + col) = u32x2{pack_bf16x2(w[0], w[1]), pack_bf16x2(w[2], w[3])};
                         }
-                    if (hl == 0) a.delta_out[li] = lse;  // (after both lanes of the row have read it: one wavefront)
+                    });
+                    if (qrow < s && hl == 0) a.delta_out[li] = lse;  // (after both lanes of the row have read it: one wavefront)
                 }
-                if (a.out_o && wq_lo < s)  // the merged rows rounded to bf16, if asked for
-                    store_rowT_bf16_lds<DB>(smem + wave * (32 * L::ROWB), a.out_o + (tok0 + wq_lo) * a.o_st + (int64_t)h * a.o_sh,
-                                            a.o_st, min(32, s - wq_lo), oacc, 1.0f, lane);
                 continue;
             }
         }
