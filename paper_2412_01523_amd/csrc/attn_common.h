@@ -539,6 +539,11 @@ __device__ __forceinline__ flexsp_shard_item load_shard_item(const flexsp_shard_
 // word and the barrier that ends an item anyway.  The last workgroup to leave zeroes the
 // counters, so a launch (or a graph replay of it) always finds them clear; launches that share
 // a plan's counters must not overlap.
+// A pass of no more items than workgroups that can be resident is launched with one workgroup per item (`direct`):
+// workgroup w runs items[w] and leaves.  Nothing is dealt then, so none of the above is paid for: the queue boundaries
+// in front of the descriptor, the ticket, the look at all counters at the end, the count of those that left are
+// four trips to memory one after the other in a kernel that otherwise takes a dozen.  Measured, forward
+// and backward: 436 tokens in four sequences, 4 heads, D = 64: 30.8 -> 25.7 us; batches of 80 and 92 us: 6 and 8 % less.
 struct ItemDealer {
     const int32_t *offsets;
     int32_t *counters;  // kCounterStride apart (a line of their own each: they are hammered from all
@@ -546,6 +551,7 @@ struct ItemDealer {
     int *slot;          // LDS word
     int nq, q, wave, lane;
     int pending;        // wavefront 0, lane 0: ticket drawn ahead (offset from W of queue q)
+    bool direct;        // one workgroup per item
 
     __device__ __forceinline__ int wgs_of(int qq) const { return ((int)gridDim.x - qq + nq - 1) / nq; }
     __device__ __forceinline__ int draw(int qq)  // wavefront 0 only; waits for the answer
@@ -599,6 +605,8 @@ struct ItemDealer {
     }
     __device__ __forceinline__ int first(const PassQueues &pq, int *lds_word, int wave_, int lane_)
     {
+        direct = pq.direct != 0;
+        if (direct) return (int)blockIdx.x;
         offsets = pq.offsets;
         counters = pq.counters;
         slot = lds_word;
@@ -617,11 +625,13 @@ struct ItemDealer {
     // call when an item starts: draws the ticket of the item after it
     __device__ __forceinline__ void prefetch()
     {
+        if (direct) return;
         if (wave == 0 && lane == 0) pending = atomicAdd(counters + q * kCounterStride, 1);
     }
     // call when an item is done (all of the workgroup's LDS reads issued): next item or -1
     __device__ __forceinline__ int advance()
     {
+        if (direct) return -1;
         int idx = -1;
         if (wave == 0) {
             idx = offsets[q] + wgs_of(q) + __builtin_amdgcn_readfirstlane(pending);
@@ -637,6 +647,7 @@ struct ItemDealer {
     // leaving workgroup: the workgroups still running then find their tiles gone from the cache.)
     __device__ __forceinline__ void finish()
     {
+        if (direct) return;
         if (wave == 0 && lane == 0) {
             if (atomicAdd(counters + nq * kCounterStride, 1) == (int)gridDim.x - 1)
                 for (int i = 0; i <= nq; i++) __hip_atomic_store(counters + i * kCounterStride, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -51,6 +51,7 @@ struct HostPass {
     int64_t offsets[kMaxQueues + 1];    // queue boundaries
     int tile_rows;
     int32_t records = 0;                // partial-result records of split tiles
+    std::vector<int32_t> direct;        // items in workgroup order, if the pass is launched with one workgroup per item
 };
 
 struct flexsp_plan {
@@ -415,6 +416,23 @@ void distribute(std::vector<Work> &work, const std::vector<int64_t> &group_cost,
     out.tile_rows = tile_rows;
 }
 
+// A pass whose items can all be resident at once is launched with one workgroup per item (see ItemDealer).  This is the
+// workgroups' order: workgroup w runs on XCD w % nq and takes the next item of that queue, or of the queue with the
+// most items left where that one has run out.
+void direct_order(HostPass &p, int nq, int n_wg)
+{
+    p.direct.clear();
+    if (p.items.empty() || p.items.size() > (size_t)n_wg) return;
+    std::vector<int64_t> at(p.offsets, p.offsets + nq);
+    for (size_t w = 0; w < p.items.size(); w++) {
+        int q = (int)(w % nq);
+        if (at[q] >= p.offsets[q + 1])
+            for (int x = 0; x < nq; x++)
+                if (p.offsets[x + 1] - at[x] > p.offsets[q + 1] - at[q]) q = x;
+        p.direct.push_back((int32_t)at[q]++);
+    }
+}
+
 int check_attn_common(flexsp_ctx *ctx, flexsp_plan *plan, const int32_t *cu_dev, int32_t head_begin,
                       int32_t head_count, int32_t kv_head_begin, int32_t kv_head_count, int causal)
 {
@@ -479,11 +497,13 @@ int plan_upload(flexsp_ctx *ctx, flexsp_plan *p)
         char *stage = (char *)p->slab.host;
         std::memset(stage, 0, head_bytes);  // also the ticket counters: every plan starts with them clear
         for (int i = 0; i < 3; i++) {
+            const std::vector<int32_t> &order = p->pass[i].direct;
+            const bool direct = !order.empty();
             if (p->kvshard) {
                 // the host list names a sequence by its index (seq_start); the device item carries its ranges
                 flexsp_shard_item *d = (flexsp_shard_item *)(stage + item_off[i]);
                 for (size_t n = 0; n < p->pass[i].items.size(); n++) {
-                    const flexsp_item &it = p->pass[i].items[n];
+                    const flexsp_item &it = p->pass[i].items[direct ? order[n] : n];
                     const int b = it.seq_start;
                     // a part of a cut tile: the keys of its steps only, positions counted from its first key
                     const int32_t np = it.parts & 0xffff, part = it.parts >> 16;  // (whole tiles only in the dK/dV pass)
@@ -493,6 +513,9 @@ int plan_upload(flexsp_ctx *ctx, flexsp_plan *p)
                     d[n] = flexsp_shard_item{p->cu[b], p->cu[b + 1] - p->cu[b], p->cu_k[b] + skip, k_len - skip,
                                              p->shift[b] - skip, it.tile, it.head | (part << 16) | (np << 24), it.slot};
                 }
+            } else if (direct) {
+                flexsp_item *d = (flexsp_item *)(stage + item_off[i]);
+                for (size_t n = 0; n < order.size(); n++) d[n] = p->pass[i].items[order[n]];
             } else if (!p->pass[i].items.empty()) {
                 std::memcpy(stage + item_off[i], p->pass[i].items.data(),
                             p->pass[i].items.size() * sizeof(flexsp_item));
@@ -503,6 +526,7 @@ int plan_upload(flexsp_ctx *ctx, flexsp_plan *p)
             p->dq[i].offsets = (const int32_t *)((char *)p->dev_base + offs_off[i]);
             p->dq[i].counters = (int32_t *)((char *)p->dev_base + ctr_off[i]);
             p->dq[i].nq = nq;
+            p->dq[i].direct = direct ? 1 : 0;
             p->dq[i].split_flags = (int32_t *)((char *)p->dev_base + flag_off[i]);
             p->dq[i].split_scratch = (char *)p->dev_base + part_off[i];
         }
@@ -528,10 +552,8 @@ int plan_upload(flexsp_ctx *ctx, flexsp_plan *p)
 
 int grid_for(const flexsp_ctx *ctx, const HostPass &p, int per_cu)
 {
-    int64_t n = (int64_t)p.items.size();
-    int64_t g = (int64_t)ctx->num_cu * per_cu;
-    if (n < g) g = ((n + ctx->num_xcd - 1) / ctx->num_xcd) * ctx->num_xcd;
-    return (int)std::max<int64_t>(g, 1);
+    if (!p.direct.empty()) return (int)p.direct.size();
+    return p.items.empty() ? 1 : ctx->num_cu * per_cu;
 }
 
 }  // namespace
@@ -701,6 +723,7 @@ int flexsp_plan_create(flexsp_ctx *ctx, const int32_t *cu, int32_t B, int32_t Hq
         build_pass(p->cu, B, Hq, 1, kFwdBq, kFwdBk, causal != 0, false, nq, n_wg, p->pass[FLEXSP_PASS_FWD]);
         build_pass(p->cu, B, Hkv, Hq / Hkv, kDkvBk, kDkvBq, causal != 0, true, nq, n_wg, p->pass[FLEXSP_PASS_BWD_DKV]);
         build_pass(p->cu, B, Hq, 1, kDqBq, kDqBk, causal != 0, false, nq, n_wg, p->pass[FLEXSP_PASS_BWD_DQ]);
+        for (HostPass &hp : p->pass) direct_order(hp, nq, n_wg);
     } catch (const std::bad_alloc &) {
         delete p;
         return FLEXSP_OUT_OF_MEMORY;
@@ -807,6 +830,7 @@ int flexsp_plan_create_kvshard(flexsp_ctx *ctx, const int32_t *cu_q, const int32
             // (one "workgroup" whose share no tile exceeds: nothing is cut)
             distribute(work, group_cost, ctx->num_xcd, 1, kDkvBk, p->pass[FLEXSP_PASS_BWD_DKV], 1);
         }
+        for (HostPass &hp : p->pass) direct_order(hp, ctx->num_xcd, workgroups_of(ctx));
     } catch (const std::bad_alloc &) {
         delete p;
         return FLEXSP_OUT_OF_MEMORY;

@@ -53,6 +53,7 @@ struct PassQueues {
     int32_t nq;
     int32_t *split_flags;      // device, one arrival counter per partial-result record (a tile uses its first record's)
     char *split_scratch;       // device, kPartialBytes per record
+    int32_t direct;            // the launch has one workgroup per item: workgroup w runs items[w] and leaves (see ItemDealer)
 };
 
 // Arguments of the attention kernels.  Strides are in elements; pointers already include
