@@ -120,7 +120,8 @@ void flexsp_plan_destroy(flexsp_plan *plan);
  * sequence-parallel group), the plan cuts such a tile's inner loop into `nparts` consecutive ranges,
  * one work item each; every part leaves its partial result (fp32) in the plan's scratch and the part
  * that finishes last adds them up in part order and writes the tile, so results do not depend on
- * which part that is. */
+ * which part that is.  (A backward of so few items that compute units would be left without work cuts
+ * its tiles into shorter parts than listed here, when it is launched.) */
 typedef struct flexsp_item {
     int32_t seq_start; /* first token of the sequence in the packed stream            */
     int32_t seq_len;   /* its length                                                   */
@@ -397,7 +398,7 @@ enum {
     FLEXSP_K_UNPACK = 1,
     FLEXSP_K_FWD = 2,
     FLEXSP_K_BWD_DELTA = 3, /* reserved: the row-dot preprocessing is part of the dQ kernel, never launched */
-    FLEXSP_K_BWD_DKV = 4,
+    FLEXSP_K_BWD_DKV = 4,   /* a small backward runs both passes in one launch, counted here            */
     FLEXSP_K_BWD_DQ = 5,
     FLEXSP_K_COUNT = 6
 };

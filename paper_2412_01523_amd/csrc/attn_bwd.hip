@@ -26,6 +26,17 @@ namespace {
 constexpr int kReadAhead = 4;
 
 
+template <int D>
+constexpr int dkv_lds()  // bytes of LDS of the dK/dV pass: two steps (Q | dO | 64 log-sum-exp, 64 delta), four exchange slots
+{
+    return 2 * (2 * kDkvBq * LdsTile<D>::ROWB + 512) + 4 * 2048;
+}
+template <int D>
+constexpr int dq_lds()  // ... of the dQ pass: two steps (K | V)
+{
+    return 4 * kDqBk * LdsTile<D>::ROWB;
+}
+
 // ------------------------------------------------------------------------------ dK / dV
 // One work item = 64 keys of one (sequence, kv head).  The accumulators of 32 keys x D for both
 // dK and dV, next to the K and V fragments, would take more than half of the register file and
@@ -42,8 +53,11 @@ constexpr int kReadAhead = 4;
 // an item names 64 keys of the shard and the query rows of its sequence on this device, key j is
 // visible to query row i iff j <= i + shift, the rows' log-sum-exp and delta are those of the COMPLETE
 // attention, and the gradients may be added to what dK / dV hold.  Tiles are not cut into parts.
-template <int D, bool SHARD>
-__global__ __launch_bounds__(kThreads, 2) void attn_bwd_dkv_kernel(const AttnArgs a)
+//
+// SELF = true: the log-sum-exp read is the forward's own and the workgroup forms delta = dO . O of a step's rows itself,
+// from rows of O and dO requested with the step's tiles, so that the pass does not have to come after the dQ pass.
+template <int D, bool SHARD, bool SELF>
+__device__ __forceinline__ void dkv_pass(const AttnArgs &a, const PassQueues &pq, const int first_wg, char *const smem, int &deal_word, int &split_word)
 {
     typedef LdsTile<D> L;
     constexpr int KS = D / 16;
@@ -52,7 +66,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dkv_kernel(const AttnArg
     constexpr int QTILE = BQ * L::ROWB;
     constexpr int STEP = 2 * QTILE + 512;       // Q | dO | lse2[64] delta[64]
     constexpr int XSLOT = 2048;                 // one 32 x 32 bf16 block (P or dS)
-    __shared__ __attribute__((aligned(1024))) char smem[2 * STEP + 4 * XSLOT];
+    static_assert(dkv_lds<D>() == 2 * STEP + 4 * XSLOT, "LDS of the pass");
     char *const exch = smem + 2 * STEP;
 
     const int tid = threadIdx.x;
@@ -71,16 +85,15 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dkv_kernel(const AttnArg
         lo.tr[db][0] += j ? 0 : QTILE;
         lo.tr[db][1] += j ? 0 : QTILE;
     }
-    __shared__ int deal_word, split_word;
     ItemDealer deal;
 
-    for (int item = deal.first(a.pq, &deal_word, wave, lane0); item >= 0; item = deal.advance()) {
+    for (int item = deal.first(pq, first_wg, &deal_word, wave, lane0); item >= 0; item = deal.advance()) {
         // s: query rows of the sequence; sk: its keys; sh: position of the first query minus position of
         // the first key (0 unless SHARD); tok0 / ktok0: their first rows in q, dO / k, v
         int s, sk, sh, g, kv0, first, total, nparts, part, slot, qfirst, nsteps;
         int64_t tok0, ktok0;
         if constexpr (SHARD) {
-            const flexsp_shard_item it = load_shard_item((const flexsp_shard_item *)a.pq.items, item);
+            const flexsp_shard_item it = load_shard_item((const flexsp_shard_item *)pq.items, item);
             s = it.q_len; sk = it.k_len; sh = it.shift; g = it.head_parts & 0xffff; kv0 = it.tile * kDkvBk;
             tok0 = it.q_start; ktok0 = it.k_start;
             // the first query row that sees the tile's first key, rounded down to a step boundary; no
@@ -89,7 +102,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dkv_kernel(const AttnArg
             nsteps = max(0, (s - qfirst + BQ - 1) / BQ);
             first = 0; total = nsteps * a.G; nparts = 1; part = 0; slot = -1;
         } else {
-            const flexsp_item it = load_item(a.pq.items, item);
+            const flexsp_item it = load_item(pq.items, item);
             s = it.seq_len; sk = s; sh = 0; g = it.head; kv0 = it.tile * kDkvBk;
             tok0 = it.seq_start; ktok0 = tok0;
             qfirst = a.causal ? kv0 : 0;  // kv0 is a multiple of BQ
@@ -126,6 +139,9 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dkv_kernel(const AttnArg
                 h_nxt++;
             }
         };
+        // SELF: 16 rows of O and dO per wavefront and step, whole rows (LPR lanes each), for delta
+        constexpr int LPR = D / 8, RPI = 64 / LPR, NI = 16 / RPI;
+        u32x4 o_raw[SELF ? NI : 1], g_raw[SELF ? NI : 1];
         auto prefetch = [&](int h, int qs, int buf) {
             char *base = smem + buf * STEP;
             const uint16_t *qb = a.q + tok0 * a.q_st + (int64_t)h * a.q_sh;
@@ -137,9 +153,32 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dkv_kernel(const AttnArg
                 load_tile_async<D, BQ>(base, qb, a.q_st, qs, s - 1, wave, lane);
                 load_tile_async<D, BQ>(base + QTILE, gb, a.do_st, qs, s - 1, wave, lane);
             }
-            if (wave < 2) {  // wavefront 0: lse2 of the 64 rows, wavefront 1: delta
+            if constexpr (SELF) {
+#pragma unroll
+                for (int i = 0; i < NI; i++) {
+                    const int64_t row = tok0 + min(qs + wave * 16 + i * RPI + lane / LPR, s - 1);
+                    o_raw[i] = *(const u32x4 *)(a.o + row * a.o_st + (int64_t)h * a.o_sh + (lane % LPR) * 8);
+                    g_raw[i] = *(const u32x4 *)(a.dO + row * a.do_st + (int64_t)h * a.do_sh + (lane % LPR) * 8);
+                }
+                if (wave == 0) global_to_lds4(a.lse_in + (int64_t)h * a.T + tok0 + min(qs + lane, s - 1), base + 2 * QTILE);
+            } else if (wave < 2) {  // wavefront 0: lse2 of the 64 rows, wavefront 1: delta
                 const float *src = (wave ? a.delta_in : a.lse_in) + (int64_t)h * a.T + tok0 + min(qs + lane, s - 1);
                 global_to_lds4(src, base + 2 * QTILE + wave * 256);
+            }
+        };
+        // SELF: -delta of the rows requested last, left where the step in buffer `buf` reads it
+        auto put_delta = [&](int buf) {
+            float *to = (float *)(smem + buf * STEP + 2 * QTILE + 256) + wave * 16;
+#pragma unroll
+            for (int i = 0; i < NI; i++) {
+                float d = 0.f;
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    const uint32_t gw = g_raw[i][e], ow = o_raw[i][e];
+                    d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, gw), __builtin_bit_cast(bf16x2, ow), d, false);
+                }
+                d = group_sum<LPR>(d);
+                if (lane % LPR == 0) to[i * RPI + lane / LPR] = -d;
             }
         };
         if (n > 0) prefetch(h_cur, q_cur, 0);
@@ -178,6 +217,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dkv_kernel(const AttnArg
                 return lo_ >= s || (a.causal && lo_ + 31 + sh < wk_lo);
             };
             lo.pin();
+            if constexpr (SELF) put_delta(BUF);
             wait_vmem();
             __syncthreads();  // tile `step` is in LDS; the previous step's exchange slots are free
             // (the copies of the next tiles go out after phase 1's matrix instructions, not here: a
@@ -229,7 +269,11 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dkv_kernel(const AttnArg
                     constexpr bool MASK = decltype(maskc)::value;
 #pragma unroll
                     for (int i4 = 0; i4 < 4; i4++) {
-                        const f32x4 l4 = *(const f32x4 *)(sL + j * 32 + 8 * i4 + 4 * hl);
+                        f32x4 l4 = *(const f32x4 *)(sL + j * 32 + 8 * i4 + 4 * hl);
+                        if constexpr (SELF) {  // to base 2, as the dQ pass leaves it
+#pragma unroll
+                            for (int e = 0; e < 4; e++) l4[e] = SHARD && l4[e] == -INFINITY ? INFINITY : l4[e] * 1.4426950408889634f;
+                        }
                         float p[4], ds[4];
 #pragma unroll
                         for (int e = 0; e < 4; e++) {
@@ -300,14 +344,14 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dkv_kernel(const AttnArg
         }
         if (n >= kLateTicketSteps) deal.prefetch();
         if (nparts > 1) {
-            split_store<DB>(a.pq.split_scratch + (int64_t)(slot + part) * kPartialBytes, accT, tid);
-            if (!split_arrive(a.pq.split_flags + slot, nparts, &split_word, tid)) continue;  // a later part finishes the tile
+            split_store<DB>(pq.split_scratch + (int64_t)(slot + part) * kPartialBytes, accT, tid);
+            if (!split_arrive(pq.split_flags + slot, nparts, &split_word, tid)) continue;  // a later part finishes the tile
 #pragma unroll
             for (int d = 0; d < DB; d++)
 #pragma unroll
                 for (int i = 0; i < 16; i++) accT[d][i] = 0.f;
             for (int p = 0; p < nparts; p++)
-                split_sum<DB>(a.pq.split_scratch + (int64_t)(slot + p) * kPartialBytes, accT, 1.0f, tid);
+                split_sum<DB>(pq.split_scratch + (int64_t)(slot + p) * kPartialBytes, accT, 1.0f, tid);
         }
 
         // role 0 writes dV rows, role 1 writes dK rows (scaled)
@@ -333,41 +377,48 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dkv_kernel(const AttnArg
     deal.finish();
 }
 
+template <int D, bool SHARD>
+__global__ __launch_bounds__(kThreads, 2) void attn_bwd_dkv_kernel(const AttnArgs a)
+{
+    __shared__ __attribute__((aligned(1024))) char smem[dkv_lds<D>()];
+    __shared__ int deal_word, split_word;
+    dkv_pass<D, SHARD, false>(a, a.pq, 0, smem, deal_word, split_word);
+}
+
 // ------------------------------------------------------------------------------ dQ
 // SHARD = true: the rows' share of dQ that comes from one shard of the keys (see the dK/dV kernel): the
 // log-sum-exp read here is that of the complete attention and `o` the complete output, so delta is the
 // complete one; a part of a cut tile comes as an item of its own with its key range and shift.
 template <int D, bool SHARD>
-__global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(const AttnArgs a)
+__device__ __forceinline__ void dq_pass(const AttnArgs &a, const PassQueues &pq, const int first_wg, char *const smem, int &deal_word, int &split_word)
 {
     typedef LdsTile<D> L;
     constexpr int KS = D / 16;
     constexpr int DB = D / 32;
     constexpr int TILE = kDqBk * L::ROWB;
-    __shared__ __attribute__((aligned(1024))) char smem[4 * TILE];  // [buffer][K | V]
+    static_assert(dq_lds<D>() == 4 * TILE, "LDS of the pass");  // [buffer][K | V]
 
     const int tid = threadIdx.x;
     const int lane0 = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     LaneOffsets<D> lo;
     lo.init(lane0);
-    __shared__ int deal_word, split_word;
     ItemDealer deal;
 
-    for (int item = deal.first(a.pq, &deal_word, wave, lane0); item >= 0; item = deal.advance()) {
+    for (int item = deal.first(pq, first_wg, &deal_word, wave, lane0); item >= 0; item = deal.advance()) {
         // s: query rows of the sequence; sk: keys counted from the item's first one; rel: position of a
         // row among those keys minus its row index; tok0 / ktok0: first rows in q, o, dO / k, v
         int s, sk, rel, h, q0, ntiles, nparts, part, slot;
         int64_t tok0, ktok0;
         if constexpr (SHARD) {
-            const flexsp_shard_item it = load_shard_item((const flexsp_shard_item *)a.pq.items, item);
+            const flexsp_shard_item it = load_shard_item((const flexsp_shard_item *)pq.items, item);
             s = it.q_len; sk = it.k_len; rel = it.shift; h = it.head_parts & 0xffff; q0 = it.tile * kDqBq;
             tok0 = it.q_start; ktok0 = it.k_start;
             part = (it.head_parts >> 16) & 0xff; nparts = it.head_parts >> 24; slot = it.slot;
             const int kv_end = a.causal ? max(0, min(sk, q0 + kDqBq + rel)) : sk;  // keys some row of the tile sees
             ntiles = (kv_end + kDqBk - 1) / kDqBk;
         } else {
-            const flexsp_item it = load_item(a.pq.items, item);
+            const flexsp_item it = load_item(pq.items, item);
             s = it.seq_len; h = it.head; q0 = it.tile * kDqBq;
             tok0 = it.seq_start;
             // The item walks key tiles step_begin .. step_end-1 (all of them unless the tile was cut: then it
@@ -539,14 +590,14 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(const AttnArgs
             a.lse_out[(int64_t)h * a.T + tok0 + qrow] = lse2;
         }
         if (nparts > 1) {
-            split_store<DB>(a.pq.split_scratch + (int64_t)(slot + part) * kPartialBytes, dqT, tid);
-            if (!split_arrive(a.pq.split_flags + slot, nparts, &split_word, tid)) continue;  // a later part finishes the tile
+            split_store<DB>(pq.split_scratch + (int64_t)(slot + part) * kPartialBytes, dqT, tid);
+            if (!split_arrive(pq.split_flags + slot, nparts, &split_word, tid)) continue;  // a later part finishes the tile
 #pragma unroll
             for (int db = 0; db < DB; db++)
 #pragma unroll
                 for (int i = 0; i < 16; i++) dqT[db][i] = 0.f;
             for (int p = 0; p < nparts; p++)
-                split_sum<DB>(a.pq.split_scratch + (int64_t)(slot + p) * kPartialBytes, dqT, 1.0f, tid);
+                split_sum<DB>(pq.split_scratch + (int64_t)(slot + p) * kPartialBytes, dqT, 1.0f, tid);
         }
         if (wq_lo >= s) continue;
         char *const stage = smem + (ntiles & 1) * 2 * TILE + wave * (32 * L::ROWB);  // the tile buffer the last step did not use (see the forward kernel)
@@ -567,11 +618,55 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(const AttnArgs
     deal.finish();
 }
 
+template <int D, bool SHARD>
+__global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(const AttnArgs a)
+{
+    __shared__ __attribute__((aligned(1024))) char smem[dq_lds<D>()];
+    __shared__ int deal_word, split_word;
+    dq_pass<D, SHARD>(a, a.pq, 0, smem, deal_word, split_word);
+}
+
+// ------------------------------------------------------------------------------ both at once
+// Small backwards, whose two passes have a workgroup per item each (see ItemDealer) and leave most of the chip idle:
+// workgroups 0 .. dq_wg-1 run the dK/dV pass, the rest the dQ pass.  One launch less, and the passes' chains of
+// memory trips and short steps run side by side instead of one after the other; the price is that the dK/dV pass reads
+// O as well.  Forward and backward, two launches -> one: 635 tokens, 1 head 29.6 -> 22.2 us; 808 tokens, 4 heads 42.8 -> 31.7 us;
+// 1 141 tokens, 16 heads on 2 94 -> 76 us; 5 630 tokens, 2 heads 45.0 -> 38.8 us.
+// PER_CU: with D = 128 the rows of O and dO that wait for a step do not fit beside the rest in half the register file (35
+// spills).  A launch of at most one workgroup per compute unit takes the kernel that has all of it (808 tokens, 4 heads:
+// 31.7 against 34.3 us), a larger one the kernel that two workgroups can share a compute unit with (5 630 tokens, 2 heads:
+// 38.8 against 43.4 us).
+template <int D, bool SHARD, int PER_CU>
+__global__ __launch_bounds__(kThreads, PER_CU) void attn_bwd_both_kernel(const AttnArgs a)
+{
+    constexpr int LDS = dkv_lds<D>() > dq_lds<D>() ? dkv_lds<D>() : dq_lds<D>();
+    __shared__ __attribute__((aligned(1024))) char smem[LDS];
+    __shared__ int deal_word, split_word;
+    if ((int)blockIdx.x >= a.dq_wg)
+        dq_pass<D, SHARD>(a, a.dq_pq, a.dq_wg, smem, deal_word, split_word);
+    else if ((int)blockIdx.x < a.dkv_items)
+        dkv_pass<D, SHARD, true>(a, a.pq, 0, smem, deal_word, split_word);
+}
+
+template <bool SHARD>
+void start_both(const AttnArgs &a, int D, int grid, hipStream_t s)
+{
+    auto start = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, s, a); };
+    if (D == 64)
+        start(attn_bwd_both_kernel<64, SHARD, 2>);
+    else if (a.per_cu == 1)
+        start(attn_bwd_both_kernel<128, SHARD, 1>);
+    else
+        start(attn_bwd_both_kernel<128, SHARD, 2>);
+}
+
 }  // namespace
 
 hipError_t launch_attn_bwd_dkv(const AttnArgs &a, int D, int grid, hipStream_t s)
 {
-    if (D == 128)
+    if (a.dq_wg)
+        start_both<false>(a, D, grid, s);
+    else if (D == 128)
         hipLaunchKernelGGL((attn_bwd_dkv_kernel<128, false>), dim3(grid), dim3(kThreads), 0, s, a);
     else
         hipLaunchKernelGGL((attn_bwd_dkv_kernel<64, false>), dim3(grid), dim3(kThreads), 0, s, a);
@@ -589,7 +684,9 @@ hipError_t launch_attn_bwd_dq(const AttnArgs &a, int D, int grid, hipStream_t s)
 
 hipError_t launch_attn_bwd_dkv_kvshard(const AttnArgs &a, int D, int grid, hipStream_t s)
 {
-    if (D == 128)
+    if (a.dq_wg)
+        start_both<true>(a, D, grid, s);
+    else if (D == 128)
         hipLaunchKernelGGL((attn_bwd_dkv_kernel<128, true>), dim3(grid), dim3(kThreads), 0, s, a);
     else
         hipLaunchKernelGGL((attn_bwd_dkv_kernel<64, true>), dim3(grid), dim3(kThreads), 0, s, a);

@@ -310,6 +310,24 @@ __device__ __forceinline__ float halves_sum(float x)
     return lo + hi;
 }
 
+// sum over the lane's group of N = 8 or 16 consecutive lanes, in every one of them: lane ^ 1, lane ^ 2, the mirrored half
+// row, the mirrored row (cross-lane operands of the additions: no trip through LDS)
+template <int CTRL>
+__device__ __forceinline__ float add_dpp(float x)
+{
+    const int y = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true);
+    return x + __builtin_bit_cast(float, y);
+}
+template <int N>
+__device__ __forceinline__ float group_sum(float x)
+{
+    static_assert(N == 8 || N == 16, "half a row or a row of lanes");
+    x = add_dpp<0xB1>(x);
+    x = add_dpp<0x4E>(x);
+    x = add_dpp<0x141>(x);
+    return N == 16 ? add_dpp<0x140>(x) : x;
+}
+
 // (Outputs are written with non-temporal stores here and below: they are not read again by the
 // kernel that writes them, and the K/V and Q/dO tiles the workgroups share keep their place in L2;
 // worth about 1 % on batches of short sequences.  The same hint on the per-item row loads cost up
@@ -603,10 +621,10 @@ struct ItemDealer {
         const int v = *(volatile int *)slot;
         return __builtin_amdgcn_readfirstlane(v);
     }
-    __device__ __forceinline__ int first(const PassQueues &pq, int *lds_word, int wave_, int lane_)
+    __device__ __forceinline__ int first(const PassQueues &pq, int first_wg, int *lds_word, int wave_, int lane_)  // first_wg: the launch's first workgroup of this pass
     {
         direct = pq.direct != 0;
-        if (direct) return (int)blockIdx.x;
+        if (direct) return (int)blockIdx.x - first_wg;
         offsets = pq.offsets;
         counters = pq.counters;
         slot = lds_word;

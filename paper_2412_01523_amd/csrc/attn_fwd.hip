@@ -57,7 +57,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs a)
     __shared__ int deal_word, split_word;
     ItemDealer deal;
 
-    int item = deal.first(a.pq, &deal_word, wave, lane0);
+    int item = deal.first(a.pq, 0, &deal_word, wave, lane0);
     for (; item >= 0; item = deal.advance()) {
         // s: query rows of the sequence; sk: its keys; tok0 / ktok0: their first rows in q / k, v
         int s, sk, shift, h, q0;

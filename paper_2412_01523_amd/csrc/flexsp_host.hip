@@ -51,7 +51,7 @@ struct HostPass {
     int64_t offsets[kMaxQueues + 1];    // queue boundaries
     int tile_rows;
     int32_t records = 0;                // partial-result records of split tiles
-    std::vector<int32_t> direct;        // items in workgroup order, if the pass is launched with one workgroup per item
+    std::vector<flexsp_item> direct;    // items in workgroup order, if the pass is launched with one workgroup per item
 };
 
 struct flexsp_plan {
@@ -270,6 +270,23 @@ void build_pass(const std::vector<int32_t> &cu, int B, int heads, int group_mult
 // finishes no earlier than the longest item, which for a batch of few heads and one dominant
 // sequence is several times the even share: the compute units that run out of work wait for it.
 // `spare`: tiles of up to this many even shares are left whole (0: every tile longer than a part is cut).
+int64_t part_length(int64_t share)
+{
+    return std::min(share * 3 / 4, std::max<int64_t>(share * 35 / 100, kLongPartSteps));
+}
+// Parts a tile of c steps is cut into: about `target` steps each, none of fewer than `shortest`.
+int part_count(int64_t c, int64_t target, int64_t shortest)
+{
+    if (c < 2 * shortest || c <= target) return 1;
+    return (int)std::min<int64_t>(std::min<int64_t>(cdiv(c, target), kMaxParts), c / shortest);
+}
+void cut_part(flexsp_item &it, int64_t c, int p, int k, int32_t slot)
+{
+    it.step_begin = (int32_t)((int64_t)p * c / k);
+    it.step_end = (int32_t)((int64_t)(p + 1) * c / k);
+    it.slot = slot;
+    it.parts = (p << 16) | k;
+}
 void split_long_items(std::vector<Work> &work, int n_wg, int spare, HostPass &out)
 {
     out.records = 0;
@@ -282,22 +299,18 @@ void split_long_items(std::vector<Work> &work, int n_wg, int spare, HostPass &ou
         total += w.cost;
     }
     const int64_t share = total / std::max(n_wg, 1);
-    const int64_t target = std::max<int64_t>(
-        std::min(share * 3 / 4, std::max<int64_t>(share * 35 / 100, kLongPartSteps)), kMinPartSteps);
+    const int64_t target = std::max<int64_t>(part_length(share), kMinPartSteps);
     const size_t n0 = work.size();
     for (size_t i = 0; i < n0; i++) {
         const int64_t c = work[i].cost;
-        if (c < 2 * kMinPartSteps || c <= target || c <= spare * share) continue;
-        int k = (int)std::min<int64_t>(std::min<int64_t>(cdiv(c, target), kMaxParts), c / kMinPartSteps);
+        if (c <= spare * share) continue;
+        const int k = part_count(c, target, kMinPartSteps);
         if (k < 2 || out.records + k > kMaxSplitRecords) continue;
         const int32_t slot = out.records;
         out.records += k;
         for (int p = 0; p < k; p++) {
             Work w = work[i];
-            w.it.step_begin = (int32_t)((int64_t)p * c / k);
-            w.it.step_end = (int32_t)((int64_t)(p + 1) * c / k);
-            w.it.slot = slot;
-            w.it.parts = (p << 16) | k;
+            cut_part(w.it, c, p, k, slot);
             w.cost = w.it.step_end - w.it.step_begin;
             if (p == 0)
                 work[i] = w;
@@ -416,20 +429,69 @@ void distribute(std::vector<Work> &work, const std::vector<int64_t> &group_cost,
     out.tile_rows = tile_rows;
 }
 
-// A pass whose items can all be resident at once is launched with one workgroup per item (see ItemDealer).  This is the
-// workgroups' order: workgroup w runs on XCD w % nq and takes the next item of that queue, or of the queue with the
-// most items left where that one has run out.
-void direct_order(HostPass &p, int nq, int n_wg)
+// A pass whose items can all be resident at once is launched with one workgroup per item (see ItemDealer).  This lists its
+// items in the order of the workgroups: workgroup w runs on XCD w % nq and takes the next item of that queue, or of the
+// queue with the most items left where that one has run out.
+// Such a pass lasts as long as its longest item, whatever an even share is, so where compute units would be left without
+// work its tiles are cut into shorter parts than the plan lists (none when `lowest` is 0): of `lowest` steps or more while
+// there is at most one item per compute unit (n_wg counts two), of half of kMinPartSteps or more while all items are resident at
+// once and the longest outlasts three shares.  Forward and backward, without -> with: 926 tokens, 8 heads on 4
+// 44.5 -> 33.4 us; 440 tokens, 16 heads on 4 62 -> 34 us; 7 616 tokens, 3 heads 159 -> 134 us; 14 938 tokens, 2 heads
+// 129 -> 118 us.  (Without the bound on shares 1 480 tokens with 16 heads, which keep the chip busy as they are, took 132
+// instead of 124 us.)  The forward's tiles stay as listed: a batch that the plan does not cut gives the same bits as
+// flexsp_attn_varlen_fwd_static, and cutting them too is worth 10 % at 7 616 tokens with 3 heads, 0 to 3 % elsewhere.
+void direct_list(HostPass &p, int nq, int n_wg, int spare, int64_t lowest)
 {
     p.direct.clear();
     if (p.items.empty() || p.items.size() > (size_t)n_wg) return;
-    std::vector<int64_t> at(p.offsets, p.offsets + nq);
-    for (size_t w = 0; w < p.items.size(); w++) {
-        int q = (int)(w % nq);
-        if (at[q] >= p.offsets[q + 1])
+    // the tiles, whole, in the order of the queues (a cut one where its first part stands)
+    std::vector<int64_t> steps(p.records, 0);
+    int64_t total = 0, longest = 0;
+    for (const flexsp_item &it : p.items)
+        if (it.slot >= 0) steps[it.slot] = std::max<int64_t>(steps[it.slot], it.step_end);
+    auto tile_steps = [&](const flexsp_item &it) { return it.slot >= 0 ? steps[it.slot] : (int64_t)it.step_end; };
+    auto first_part = [](const flexsp_item &it) { return (it.parts >> 16) == 0; };
+    for (const flexsp_item &it : p.items)
+        if (first_part(it)) {
+            total += tile_steps(it);
+            longest = std::max(longest, tile_steps(it));
+        }
+    const int64_t share = total / n_wg;
+    int64_t shortest = 0;
+    auto parts_of = [&](int64_t c, int64_t m) { return c <= spare * share ? 1 : part_count(c, std::max(part_length(share), m), m); };
+    for (int tier = 0; lowest && !shortest && tier < (longest > 3 * share ? 2 : 1); tier++)
+        for (int64_t m = tier == 0 ? lowest : kMinPartSteps / 2; !shortest && m < kMinPartSteps; m += 2) {
+            int64_t n = 0;
+            for (const flexsp_item &it : p.items)
+                if (first_part(it)) n += parts_of(tile_steps(it), m);
+            if (n <= (tier == 0 ? n_wg / 2 : n_wg)) shortest = m;
+        }
+    std::vector<std::vector<flexsp_item>> queue(nq);
+    int32_t records = 0;
+    for (int x = 0; x < nq; x++)
+        for (int64_t i = p.offsets[x]; i < p.offsets[x + 1]; i++) {
+            flexsp_item it = p.items[i];
+            if (!shortest) {
+                queue[x].push_back(it);
+            } else if (first_part(it)) {
+                const int64_t c = tile_steps(it);
+                const int k = parts_of(c, shortest);
+                for (int part = 0; part < k; part++) {
+                    cut_part(it, c, part, k, k > 1 ? records : -1);
+                    queue[x].push_back(it);
+                }
+                if (k > 1) records += k;
+            }
+        }
+    if (shortest) p.records = records;
+    std::vector<size_t> at(nq, 0);
+    for (;;) {
+        int q = (int)(p.direct.size() % nq);
+        if (at[q] >= queue[q].size())
             for (int x = 0; x < nq; x++)
-                if (p.offsets[x + 1] - at[x] > p.offsets[q + 1] - at[q]) q = x;
-        p.direct.push_back((int32_t)at[q]++);
+                if (queue[x].size() - at[x] > queue[q].size() - at[q]) q = x;
+        if (at[q] >= queue[q].size()) break;
+        p.direct.push_back(queue[q][at[q]++]);
     }
 }
 
@@ -464,7 +526,7 @@ int plan_upload(flexsp_ctx *ctx, flexsp_plan *p)
         auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
         for (int i = 0; i < 3; i++) {
             item_off[i] = off;
-            off = align(off + p->pass[i].items.size() * item_bytes);
+            off = align(off + std::max(p->pass[i].items.size(), p->pass[i].direct.size()) * item_bytes);
         }
         for (int i = 0; i < 3; i++) {
             offs_off[i] = off;
@@ -497,13 +559,13 @@ int plan_upload(flexsp_ctx *ctx, flexsp_plan *p)
         char *stage = (char *)p->slab.host;
         std::memset(stage, 0, head_bytes);  // also the ticket counters: every plan starts with them clear
         for (int i = 0; i < 3; i++) {
-            const std::vector<int32_t> &order = p->pass[i].direct;
-            const bool direct = !order.empty();
+            const bool direct = !p->pass[i].direct.empty();
+            const std::vector<flexsp_item> &items = direct ? p->pass[i].direct : p->pass[i].items;
             if (p->kvshard) {
                 // the host list names a sequence by its index (seq_start); the device item carries its ranges
                 flexsp_shard_item *d = (flexsp_shard_item *)(stage + item_off[i]);
-                for (size_t n = 0; n < p->pass[i].items.size(); n++) {
-                    const flexsp_item &it = p->pass[i].items[direct ? order[n] : n];
+                for (size_t n = 0; n < items.size(); n++) {
+                    const flexsp_item &it = items[n];
                     const int b = it.seq_start;
                     // a part of a cut tile: the keys of its steps only, positions counted from its first key
                     const int32_t np = it.parts & 0xffff, part = it.parts >> 16;  // (whole tiles only in the dK/dV pass)
@@ -513,12 +575,8 @@ int plan_upload(flexsp_ctx *ctx, flexsp_plan *p)
                     d[n] = flexsp_shard_item{p->cu[b], p->cu[b + 1] - p->cu[b], p->cu_k[b] + skip, k_len - skip,
                                              p->shift[b] - skip, it.tile, it.head | (part << 16) | (np << 24), it.slot};
                 }
-            } else if (direct) {
-                flexsp_item *d = (flexsp_item *)(stage + item_off[i]);
-                for (size_t n = 0; n < order.size(); n++) d[n] = p->pass[i].items[order[n]];
-            } else if (!p->pass[i].items.empty()) {
-                std::memcpy(stage + item_off[i], p->pass[i].items.data(),
-                            p->pass[i].items.size() * sizeof(flexsp_item));
+            } else if (!items.empty()) {
+                std::memcpy(stage + item_off[i], items.data(), items.size() * sizeof(flexsp_item));
             }
             int32_t *o = (int32_t *)(stage + offs_off[i]);
             for (int x = 0; x <= nq; x++) o[x] = (int32_t)p->pass[i].offsets[x];
@@ -548,6 +606,23 @@ int plan_upload(flexsp_ctx *ctx, flexsp_plan *p)
         p->delta = (float *)((char *)p->dev_base + delta_off);
     }
     return FLEXSP_OK;
+}
+
+// Backwards that run their two passes in one launch (see attn_bwd_both_kernel): those whose items can all be resident at
+// once.  (Up to twice as many: 3 500 tokens with 3 heads 156 -> 152 us, but 1 480 tokens with 16 heads 125 -> 132 us.)
+// Fills in what such a launch needs and returns its grid (each pass's workgroups keep to their XCD: the dQ pass starts at a
+// multiple of the number of queues), or 0.
+int both_at_once(const flexsp_ctx *ctx, const flexsp_plan *p, AttnArgs &a)
+{
+    const int dkv = (int)p->pass[FLEXSP_PASS_BWD_DKV].direct.size(), dq = (int)p->pass[FLEXSP_PASS_BWD_DQ].direct.size();
+    if (!dkv || !dq || dkv + dq > workgroups_of(ctx)) return 0;
+    a.pq = p->dq[FLEXSP_PASS_BWD_DKV];
+    a.dq_pq = p->dq[FLEXSP_PASS_BWD_DQ];
+    a.dkv_items = dkv;
+    a.dq_wg = (int)cdiv(dkv, ctx->num_xcd) * ctx->num_xcd;
+    const int grid = a.dq_wg + dq;
+    a.per_cu = grid <= ctx->num_cu ? 1 : 2;
+    return grid;
 }
 
 int grid_for(const flexsp_ctx *ctx, const HostPass &p, int per_cu)
@@ -723,7 +798,7 @@ int flexsp_plan_create(flexsp_ctx *ctx, const int32_t *cu, int32_t B, int32_t Hq
         build_pass(p->cu, B, Hq, 1, kFwdBq, kFwdBk, causal != 0, false, nq, n_wg, p->pass[FLEXSP_PASS_FWD]);
         build_pass(p->cu, B, Hkv, Hq / Hkv, kDkvBk, kDkvBq, causal != 0, true, nq, n_wg, p->pass[FLEXSP_PASS_BWD_DKV]);
         build_pass(p->cu, B, Hq, 1, kDqBq, kDqBk, causal != 0, false, nq, n_wg, p->pass[FLEXSP_PASS_BWD_DQ]);
-        for (HostPass &hp : p->pass) direct_order(hp, nq, n_wg);
+        for (int i = 0; i < 3; i++) direct_list(p->pass[i], nq, n_wg, 0, i == FLEXSP_PASS_FWD ? 0 : kShortPartSteps);
     } catch (const std::bad_alloc &) {
         delete p;
         return FLEXSP_OUT_OF_MEMORY;
@@ -830,7 +905,8 @@ int flexsp_plan_create_kvshard(flexsp_ctx *ctx, const int32_t *cu_q, const int32
             // (one "workgroup" whose share no tile exceeds: nothing is cut)
             distribute(work, group_cost, ctx->num_xcd, 1, kDkvBk, p->pass[FLEXSP_PASS_BWD_DKV], 1);
         }
-        for (HostPass &hp : p->pass) direct_order(hp, ctx->num_xcd, workgroups_of(ctx));
+        for (int i = 0; i < 3; i++)  // (whole tiles only in the dK/dV pass)
+            direct_list(p->pass[i], ctx->num_xcd, workgroups_of(ctx), 2, i == FLEXSP_PASS_BWD_DQ ? kShortPartSteps : 0);
     } catch (const std::bad_alloc &) {
         delete p;
         return FLEXSP_OUT_OF_MEMORY;
@@ -1170,11 +1246,16 @@ int flexsp_attn_varlen_bwd_kvshard(flexsp_ctx *ctx, flexsp_plan *plan, flexsp_te
     a.scale = scale; a.scale_l2 = scale * 1.4426950408889634f;
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipSuccess;
-    // as in flexsp_attn_varlen_bwd: the dQ kernel leaves delta and the base-2 log-sum-exp of its rows in
-    // the plan's scratch for the dK/dV kernel
     a.lse_in = lse;
     a.lse_out = lse2;
     a.delta_out = plan->delta;
+    if (const int grid = both_at_once(ctx, plan, a)) {
+        Timed tm(ctx, FLEXSP_K_BWD_DKV, s);
+        e = launch_attn_bwd_dkv_kvshard(a, plan->D, grid, s);
+        return e == hipSuccess ? FLEXSP_OK : hip_fail(e);
+    }
+    // as in flexsp_attn_varlen_bwd: the dQ kernel leaves delta and the base-2 log-sum-exp of its rows in
+    // the plan's scratch for the dK/dV kernel
     a.pq = plan->dq[FLEXSP_PASS_BWD_DQ];
     if (!plan->pass[FLEXSP_PASS_BWD_DQ].items.empty()) {
         Timed tm(ctx, FLEXSP_K_BWD_DQ, s);
@@ -1272,12 +1353,17 @@ int flexsp_attn_varlen_bwd(flexsp_ctx *ctx, flexsp_plan *plan, flexsp_tensor q, 
     a.scale = scale; a.scale_l2 = scale * 1.4426950408889634f;
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
-    // The dQ kernel runs first: it holds every query row's dO in registers, so it also computes
-    // delta = dO . O and the log-sum-exp in base 2 for its rows and leaves both in the plan's
-    // scratch for the dK/dV kernel (no separate preprocessing launch).
     a.lse_in = lse;
     a.lse_out = lse2;
     a.delta_out = plan->delta;
+    if (const int grid = both_at_once(ctx, plan, a)) {
+        Timed tm(ctx, FLEXSP_K_BWD_DKV, s);
+        e = launch_attn_bwd_dkv(a, plan->D, grid, s);
+        return e == hipSuccess ? FLEXSP_OK : hip_fail(e);
+    }
+    // The dQ kernel runs first: it holds every query row's dO in registers, so it also computes
+    // delta = dO . O and the log-sum-exp in base 2 for its rows and leaves both in the plan's
+    // scratch for the dK/dV kernel (no separate preprocessing launch).
     a.pq = plan->dq[FLEXSP_PASS_BWD_DQ];
     {
         Timed tm(ctx, FLEXSP_K_BWD_DQ, s);

@@ -31,6 +31,7 @@ constexpr int kLateTicketSteps = 16;  // items of at least this many steps draw 
 // kMaxSplitRecords records per pass.
 constexpr int kPartialBytes = 64 * kThreads * 4 + 2 * kThreads * 4;  // 67 584 B
 constexpr int kMinPartSteps = 16;
+constexpr int kShortPartSteps = 4;  // ... where a backward would leave compute units without work (see direct_list)
 constexpr int kGroupMajorSteps = 24;  // sequences whose longest tile has at most this many steps are queued tile beside tile
 constexpr int kLongPartSteps = 160;  // parts at least this long are aimed at 35 % of an even share instead of 75 %
 constexpr int kMaxParts = 8;
@@ -75,6 +76,10 @@ struct AttnArgs {
     float scale;     // softmax scale
     float scale_l2;  // scale * log2(e)
     PassQueues pq;
+    // a launch that runs both backward passes (launch_attn_bwd_dkv*, both passes direct, lse_in as the caller gave it): the
+    // dQ pass's queues, its first workgroup (0: the dK/dV pass alone), the dK/dV pass's items, workgroups per compute unit
+    PassQueues dq_pq;
+    int32_t dq_wg, dkv_items, per_cu;
 };
 
 // Launchers implemented next to their kernels.  All are asynchronous on `s`.

@@ -1,5 +1,5 @@
-"""Launches of few items, where the kernels are started one workgroup per item, and the sizes around the line where
-they become persistent (two workgroups per compute unit): against the CPU fp64 oracle, twice through one plan."""
+"""Launches of few items: one workgroup per item, both backward passes in one launch, tiles cut into short parts; and the
+sizes around the lines where each of these ends: against the CPU fp64 oracle, twice."""
 import numpy as np
 import pytest
 
@@ -25,18 +25,33 @@ def case_lengths(items, head_items):
     return [1 + (7 * i) % 5 for i in range(n - 1)] + [61]
 
 
-@pytest.mark.parametrize("around,heads,D", [(-2, 1, 64), (0, 1, 64), (1, 1, 64), (0, 4, 128), (4, 4, 128), (None, 1, 128), (None, 3, 64)])
-@pytest.mark.parametrize("causal", [True, False])
-def test_items_around_the_persistent_line(ctx, around, heads, D, causal):
-    lens = [300, 70] if around is None else case_lengths(2 * ctx.num_cu + around, heads)
-    print(f"launch shape: {len(lens)} sequences x {heads} heads, D={D}, causal={causal}", flush=True)
+def check(ctx, lens, hq, hkv, D, causal, grad_f32=True):
+    print(f"launch shape: {len(lens)} sequences, {hq} heads on {hkv}, D={D}, causal={causal}", flush=True)
     cu = wl.cu_seqlens(lens)
     T = int(cu[-1])
-    q, k, v, dO = (wl.normal_bf16(911, tid, (T, heads, D)) for tid in (wl.TID_Q, wl.TID_K, wl.TID_V, wl.TID_DO))
+    q, dO = (wl.normal_bf16(911, tid, (T, hq, D)) for tid in (wl.TID_Q, wl.TID_DO))
+    k, v = (wl.normal_bf16(911, tid, (T, hkv, D)) for tid in (wl.TID_K, wl.TID_V))
     o, lse, dq, dk, dv = oracle.attn_fwd_bwd(q, k, v, dO, cu, causal)
     ref = {"O": o, "dQ": dq, "dK": dk, "dV": dv}
-    runs = [GpuAttn(ctx).run(q, k, v, dO, cu, causal=causal, grad_f32=True) for _ in range(2)]
-    check_against_budget(f"{len(lens)} sequences", runs[0], ref, q, k, v, dO, cu, causal, None, True)
+    runs = [GpuAttn(ctx).run(q, k, v, dO, cu, causal=causal, grad_f32=grad_f32) for _ in range(2)]
+    check_against_budget(f"{len(lens)} sequences", runs[0], ref, q, k, v, dO, cu, causal, None, grad_f32)
     assert np.abs(runs[0]["LSE"] - lse).max() < 1e-3
     for name in runs[0]:
         assert np.array_equal(runs[0][name], runs[1][name]), name
+
+
+# items per pass: half a chip, one and two workgroups per compute unit, and one more than each
+@pytest.mark.parametrize("per_cu,more,heads,D", [(0.5, 0, 1, 128), (0.5, 1, 1, 128), (1, 0, 4, 128), (1, 1, 1, 128), (1, 1, 1, 64),
+                                                 (2, -2, 1, 64), (2, 0, 1, 64), (2, 1, 1, 64), (2, 0, 4, 128), (2, 4, 4, 128)])
+def test_items_around_the_lines(ctx, per_cu, more, heads, D):
+    check(ctx, case_lengths(int(per_cu * ctx.num_cu) + more, heads), heads, heads, D, True)
+
+
+@pytest.mark.parametrize("lens,hq,hkv,D,causal", [
+    ([1], 1, 1, 128, True), ([300, 70], 1, 1, 128, False), ([300, 70], 3, 3, 64, True), ([513, 31], 8, 2, 128, True),
+    ([511, 257], 8, 2, 64, False), ([1030], 4, 1, 128, True), ([1025, 64, 129], 2, 2, 128, False), ([1500], 2, 2, 64, True),
+])
+@pytest.mark.parametrize("grad_f32", [True, False])
+def test_few_long_items(ctx, lens, hq, hkv, D, causal, grad_f32):
+    check(ctx, lens, hq, hkv, D, causal, grad_f32)
+
