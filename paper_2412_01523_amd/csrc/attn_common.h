@@ -450,9 +450,8 @@ __device__ __forceinline__ void store_rowT_bf16_lds(char *stage, uint16_t *g, in
 // list), so without the readfirstlane every quantity derived from the descriptor - sequence
 // length, tile bounds, loop trip counts, base addresses - would live in vector registers and
 // every branch on them would be compiled as a divergent one.
-__device__ __forceinline__ flexsp_item load_item(const flexsp_item *items, int idx)
+__device__ __forceinline__ flexsp_item uniform_item(const flexsp_item &v)
 {
-    const flexsp_item v = items[idx];
     flexsp_item it;
     it.seq_start = __builtin_amdgcn_readfirstlane(v.seq_start);
     it.seq_len = __builtin_amdgcn_readfirstlane(v.seq_len);
@@ -463,6 +462,10 @@ __device__ __forceinline__ flexsp_item load_item(const flexsp_item *items, int i
     it.slot = __builtin_amdgcn_readfirstlane(v.slot);
     it.parts = __builtin_amdgcn_readfirstlane(v.parts);
     return it;
+}
+__device__ __forceinline__ flexsp_item load_item(const flexsp_item *items, int idx)
+{
+    return uniform_item(items[idx]);
 }
 
 // ------------------------------------------------------------------------------------------

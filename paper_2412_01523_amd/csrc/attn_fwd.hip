@@ -31,12 +31,56 @@ namespace {
 template <int V>
 using ic = std::integral_constant<int, V>;
 
+// The n-th item of a batch, items counted by query tile of the packed sequences and then by head, as wave-uniform values; every
+// wavefront looks for itself, 64 sequences at a time.  False if there are fewer items or the lengths are not 0 = cu[0] <=
+// cu[1] <= ... <= cu[B] <= T.
+__device__ __forceinline__ bool find_item(const int32_t *cu, int B, int T, int heads, int causal, int n, int lane, flexsp_item &it)
+{
+    const int pair = n / heads;
+    int before = 0, start = 0, len = 0, tile = -1;
+    bool bad = cu[0] != 0;
+    for (int b0 = 0; b0 < B; b0 += 64) {
+        const int b = b0 + lane;
+        const int lo = b < B ? cu[b] : 0, hi = b < B ? cu[b + 1] : 0;
+        const bool wrong = lo < 0 || hi < lo || hi > T;
+        bad = bad || wrong;
+        const int nt = wrong ? 0 : (hi - lo + kFwdBq - 1) / kFwdBq;
+        int upto = nt;  // tiles of this and the earlier lanes
+#pragma unroll
+        for (int d = 1; d < 64; d *= 2) {
+            const int x = __shfl_up(upto, d);
+            if (lane >= d) upto += x;
+        }
+        const uint64_t mine = __builtin_amdgcn_ballot_w64(pair >= before + upto - nt && pair < before + upto);
+        if (mine) {
+            const int l = __builtin_ctzll(mine);
+            start = __builtin_amdgcn_readlane(lo, l);
+            len = __builtin_amdgcn_readlane(hi, l) - start;
+            tile = pair - before - __builtin_amdgcn_readlane(upto - nt, l);
+        }
+        before += __builtin_amdgcn_readlane(upto, 63);
+    }
+    if (tile < 0 || __builtin_amdgcn_ballot_w64(bad) != 0) return false;
+    it.seq_start = start;
+    it.seq_len = len;
+    it.tile = tile;
+    it.head = n - pair * heads;
+    it.step_begin = 0;
+    it.step_end = ((causal ? min(len, (tile + 1) * kFwdBq) : len) + kFwdBk - 1) / kFwdBk;
+    it.slot = -1;
+    it.parts = 1;
+    return true;
+}
+
 // SHARD = true is the variant for one shard of the keys (context parallelism): a work item then
 // names separate query and key ranges and an offset `shift` between their positions, key j is
 // visible to query row i iff j <= i + shift (when causal), rows may see no key at all (O = 0,
 // LSE = -inf), and up to three 32-key blocks of a wavefront need masking (the diagonal crosses two
 // when shift is not a multiple of 32, plus the ragged end of the shard).
-template <int D, bool SHARD>
+//
+// FIND = true is the variant without a list of items: workgroup w finds the w-th (query tile, head) of the batch in the
+// lengths and leaves when it is done.
+template <int D, bool SHARD, bool FIND>
 __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs a)
 {
     typedef LdsTile<D> L;
@@ -57,7 +101,14 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs a)
     __shared__ int deal_word, split_word;
     ItemDealer deal;
 
-    int item = deal.first(a.pq, 0, &deal_word, wave, lane0);
+    flexsp_item found;
+    int item;
+    if constexpr (FIND) {
+        deal.direct = true;
+        item = find_item(a.cu, a.B, a.T, a.Hq, a.causal, (int)blockIdx.x, lane0, found) ? 0 : -1;
+    } else {
+        item = deal.first(a.pq, 0, &deal_word, wave, lane0);
+    }
     for (; item >= 0; item = deal.advance()) {
         // s: query rows of the sequence; sk: its keys; tok0 / ktok0: their first rows in q / k, v
         int s, sk, shift, h, q0;
@@ -70,7 +121,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs a)
             // (a part of a cut tile comes with its own key range and shift: nothing else differs)
             part = (it.head_parts >> 16) & 0xff; nparts = it.head_parts >> 24; slot = it.slot;
         } else {
-            const flexsp_item it = load_item(a.pq.items, item);
+            flexsp_item it;
+            if constexpr (FIND) it = uniform_item(found); else it = load_item(a.pq.items, item);
             s = it.seq_len; sk = s; shift = 0; h = it.head; q0 = it.tile * kFwdBq;
             tok0 = it.seq_start; ktok0 = tok0;
             part = it.parts >> 16; nparts = it.parts & 0xffff; slot = it.slot;
@@ -561,19 +613,23 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs a)
 
 hipError_t launch_attn_fwd(const AttnArgs &a, int D, int grid, hipStream_t s)
 {
-    if (D == 128)
-        hipLaunchKernelGGL((attn_fwd_kernel<128, false>), dim3(grid), dim3(kThreads), 0, s, a);
+    if (D == 128 && a.cu)
+        hipLaunchKernelGGL((attn_fwd_kernel<128, false, true>), dim3(grid), dim3(kThreads), 0, s, a);
+    else if (a.cu)
+        hipLaunchKernelGGL((attn_fwd_kernel<64, false, true>), dim3(grid), dim3(kThreads), 0, s, a);
+    else if (D == 128)
+        hipLaunchKernelGGL((attn_fwd_kernel<128, false, false>), dim3(grid), dim3(kThreads), 0, s, a);
     else
-        hipLaunchKernelGGL((attn_fwd_kernel<64, false>), dim3(grid), dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL((attn_fwd_kernel<64, false, false>), dim3(grid), dim3(kThreads), 0, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_attn_fwd_kvshard(const AttnArgs &a, int D, int grid, hipStream_t s)
 {
     if (D == 128)
-        hipLaunchKernelGGL((attn_fwd_kernel<128, true>), dim3(grid), dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL((attn_fwd_kernel<128, true, false>), dim3(grid), dim3(kThreads), 0, s, a);
     else
-        hipLaunchKernelGGL((attn_fwd_kernel<64, true>), dim3(grid), dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL((attn_fwd_kernel<64, true, false>), dim3(grid), dim3(kThreads), 0, s, a);
     return hipGetLastError();
 }
 

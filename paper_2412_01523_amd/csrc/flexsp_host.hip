@@ -466,32 +466,36 @@ void direct_list(HostPass &p, int nq, int n_wg, int spare, int64_t lowest)
                 if (first_part(it)) n += parts_of(tile_steps(it), m);
             if (n <= (tier == 0 ? n_wg / 2 : n_wg)) shortest = m;
         }
-    std::vector<std::vector<flexsp_item>> queue(nq);
+    std::vector<flexsp_item> list;  // the same queues, tiles cut
+    list.reserve((size_t)n_wg);
+    size_t at[kMaxQueues], end[kMaxQueues];
     int32_t records = 0;
-    for (int x = 0; x < nq; x++)
+    for (int x = 0; x < nq; x++) {
+        at[x] = list.size();
         for (int64_t i = p.offsets[x]; i < p.offsets[x + 1]; i++) {
             flexsp_item it = p.items[i];
             if (!shortest) {
-                queue[x].push_back(it);
+                list.push_back(it);
             } else if (first_part(it)) {
                 const int64_t c = tile_steps(it);
                 const int k = parts_of(c, shortest);
                 for (int part = 0; part < k; part++) {
                     cut_part(it, c, part, k, k > 1 ? records : -1);
-                    queue[x].push_back(it);
+                    list.push_back(it);
                 }
                 if (k > 1) records += k;
             }
         }
+        end[x] = list.size();
+    }
     if (shortest) p.records = records;
-    std::vector<size_t> at(nq, 0);
-    for (;;) {
-        int q = (int)(p.direct.size() % nq);
-        if (at[q] >= queue[q].size())
+    p.direct.reserve(list.size());
+    for (size_t w = 0; w < list.size(); w++) {
+        int q = (int)(w % nq);
+        if (at[q] == end[q])
             for (int x = 0; x < nq; x++)
-                if (queue[x].size() - at[x] > queue[q].size() - at[q]) q = x;
-        if (at[q] >= queue[q].size()) break;
-        p.direct.push_back(queue[q][at[q]++]);
+                if (end[x] - at[x] > end[q] - at[q]) q = x;
+        p.direct.push_back(list[at[q]++]);
     }
 }
 

@@ -1,0 +1,71 @@
+"""The forward without a plan finds its work on the device: in a list for batches that do not fit the chip at once, every
+workgroup for itself for those that do.  Same bits as the plan's forward around that line and at odd lengths."""
+import numpy as np
+import pytest
+
+from paper_2412_01523_amd import workloads as wl
+
+from gpu_util import to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2412_01523_amd import binding as fx
+    c = fx.Context(0)
+    yield c
+    c.close()
+
+
+def both(ctx, lens, hq, hkv, D, causal):
+    import torch
+    from paper_2412_01523_amd import binding as fx
+    print(f"static forward: {len(lens)} sequences, {sum(lens)} tokens, {hq} heads on {hkv}, D={D}, causal={causal}", flush=True)
+    cu, T = wl.cu_seqlens(lens), sum(lens)
+    q, k, v = (to_dev(wl.normal_bf16(771, tid, (T, h, D))) for tid, h in ((0, hq), (1, hkv), (2, hkv)))
+    cud = torch.from_numpy(cu).cuda()
+    outs = []
+    for planned in (True, False):
+        o = torch.full((T, hq, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+        lse = torch.full((hq, T), float("nan"), dtype=torch.float32, device="cuda")
+        if planned:
+            with_plan = fx.Plan(ctx, cu, hq, hkv, D, causal)
+            assert int(with_plan.items(fx.PASS_FWD)[0]["nparts"].max()) == 1
+            fx.flexsp_attn_varlen_fwd(ctx, with_plan, q, k, v, cud, o, lse, causal=causal)
+            torch.cuda.synchronize()
+            with_plan.close()
+        else:
+            fx.flexsp_attn_varlen_fwd_static(ctx, q, k, v, cud, o, lse, causal=causal)
+            torch.cuda.synchronize()
+        outs.append((o.view(torch.int16), lse.view(torch.int32)))
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+
+
+# (ceil(T / 128) + B) x heads is the bound the choice is made by: 512 items and one more sequence
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 127, 253, 254, 255, 256, 600])
+@pytest.mark.parametrize("causal", [True, False])
+def test_many_sequences(ctx, n, causal):
+    both(ctx, [1 + (37 * i) % 130 if i % 5 else 0 for i in range(n - 1)] + [129], 2, 1, 64, causal)
+
+
+# (lengths whose tiles the plan leaves whole: up to 31 steps of 64 keys, or less than an even share of the pass)
+@pytest.mark.parametrize("lens,hq,hkv,D", [([1], 1, 1, 128), ([128], 16, 2, 128), ([1153, 1, 0, 640], 6, 3, 128), ([1900], 16, 2, 128),
+                                           ([0, 0, 700, 0], 4, 4, 64), ([1000] * 70, 3, 1, 64), ([9000] * 9 + [4500], 7, 7, 64)])
+def test_odd_shapes(ctx, lens, hq, hkv, D):
+    both(ctx, lens, hq, hkv, D, True)
+
+
+@pytest.mark.parametrize("T,B", [(1024, 3), (65536, 200)])
+def test_wrong_lengths_compute_nothing(ctx, T, B):
+    import torch
+    from paper_2412_01523_amd import binding as fx
+    good = [i * T // B for i in range(B + 1)]
+    for at, value in ((0, 1), (B // 2, -1), (B // 2, T + 1), (B, T + 1), (B, 0)):
+        cu = torch.tensor(good, dtype=torch.int32)
+        cu[at] = value
+        t = torch.zeros((T, 2, 64), dtype=torch.bfloat16, device="cuda")
+        o, lse = torch.full_like(t, 7.0), torch.full((2, T), 7.0, dtype=torch.float32, device="cuda")
+        fx.flexsp_attn_varlen_fwd_static(ctx, t, t, t, cu.cuda(), o, lse)
+        torch.cuda.synchronize()
+        assert bool((o == 7.0).all()) and bool((lse == 7.0).all()), (at, value)
