@@ -56,11 +56,13 @@ class Profile(Structure):
 
 
 _lib = None
+_torch = None          # set with _lib
+_pointers, _ints = {}, {}  # ctypes array types by length
 
 
 def lib() -> ctypes.CDLL:
     """Loads libflexsp.so (built in-tree by paper_2412_01523_amd.build); fails loudly if absent."""
-    global _lib
+    global _lib, _torch
     if _lib is None:
         if not LIB_PATH.exists():
             raise FileNotFoundError(
@@ -68,7 +70,7 @@ def lib() -> ctypes.CDLL:
         # torch ships its own HIP runtime (soname libamdhip64.so.7).  Load it first so that this
         # library binds to the same runtime instance that owns torch's device memory and streams;
         # two runtimes in one process do not see each other's allocations.
-        import torch  # noqa: F401
+        import torch
         L = ctypes.CDLL(str(LIB_PATH))
         L.flexsp_strerror.restype = c_char_p
         L.flexsp_strerror.argtypes = [c_int]
@@ -126,6 +128,7 @@ def lib() -> ctypes.CDLL:
         L.flexsp_min_microbatches.restype = c_int64
         L.flexsp_profile_start.argtypes = [c_void_p, c_int32]
         L.flexsp_profile_stop.argtypes = [c_void_p, POINTER(Profile)]
+        _torch = torch
         _lib = L
     return _lib
 
@@ -135,17 +138,22 @@ def _check(status: int, where: str):
         raise FlexspError(status, where)
 
 
+# What follows runs once to eight times per call, and the calls are a few microseconds of GPU work when a batch is small: the
+# handle of torch's current stream without a Stream object around it (2.1 -> 0.2 us), a view's strides in one look
+# (1.3 -> 0.7 us each).  Forward and backward of 436 tokens spent 23.5 us in here and in ctypes, and now 14.1 us.
 def _stream(stream) -> int:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        if not _torch.cuda.is_initialized():
+            return _torch.cuda.current_stream().cuda_stream
+        return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
     return int(getattr(stream, "cuda_stream", stream))
 
 
 def _view(t) -> Tensor:
     """[T, heads, D] torch tensor (2-byte elements, last dim contiguous) -> flexsp_tensor."""
-    assert t.dim() == 3 and t.stride(2) == 1 and t.element_size() in (2, 4), "need [T,H,D], D contiguous"
-    return Tensor(t.data_ptr(), t.stride(0), t.stride(1))
+    st = t.stride()
+    assert len(st) == 3 and st[2] == 1 and t.element_size() in (2, 4), "need [T,H,D], D contiguous"
+    return Tensor(t.data_ptr(), st[0], st[1])
 
 
 class Context:
@@ -197,7 +205,7 @@ class Plan:
         self.handle = c_void_p()
         self.cu = cu
         self.hq, self.hkv, self.d, self.causal = hq, hkv, d, bool(causal)
-        _check(lib().flexsp_plan_create(ctx.handle, cu.ctypes.data_as(c_void_p), len(cu) - 1, hq, hkv, d,
+        _check(lib().flexsp_plan_create(ctx.handle, cu.ctypes.data, len(cu) - 1, hq, hkv, d,
                                         int(bool(causal)), byref(self.handle)), "flexsp_plan_create")
 
     def num_items(self, which: int) -> int:
@@ -275,29 +283,36 @@ def flexsp_unpack(ctx: Context, src, dst, stream=None):
 
 def _many(fn, name, ctx, srcs, dsts, T, heads, D, P, stream):
     n = len(srcs)
-    assert n == len(dsts) and all(s.is_contiguous() and d.is_contiguous() and s.numel() == d.numel()
-                                  for s, d in zip(srcs, dsts))
+    assert n == len(dsts)
     eb = srcs[0].element_size()
-    assert all(s.element_size() == eb for s in srcs)
-    sp = (c_void_p * n)(*[s.data_ptr() for s in srcs])
-    dp = (c_void_p * n)(*[d.data_ptr() for d in dsts])
-    hh = (c_int32 * n)(*heads)
-    _check(fn(ctx.handle, n, sp, dp, T, hh, D, P, eb, _stream(stream)), name)
+    for s, d in zip(srcs, dsts):
+        assert s.is_contiguous() and d.is_contiguous() and s.numel() == d.numel() and s.element_size() == eb
+    if n not in _pointers:
+        _pointers[n], _ints[n] = c_void_p * n, c_int32 * n
+    _check(fn(ctx.handle, n, _pointers[n](*[s.data_ptr() for s in srcs]), _pointers[n](*[d.data_ptr() for d in dsts]), T,
+              _ints[n](*heads), D, P, eb, _stream(stream)), name)
 
 
 def flexsp_pack_many(ctx: Context, srcs, dsts, P: int, stream=None):
     """Several src [T,H_i,D] -> dst [P,T,H_i/P,D] in one launch (same T, D, element size)."""
-    T, _, D = srcs[0].shape
-    assert all(s.shape[0] == T and s.shape[2] == D for s in srcs)
-    _many(lib().flexsp_pack_many, "flexsp_pack_many", ctx, srcs, dsts, T, [s.shape[1] for s in srcs], D, P, stream)
+    shapes = [s.shape for s in srcs]
+    T, _, D = shapes[0]
+    heads = []
+    for s in shapes:
+        assert s[0] == T and s[2] == D
+        heads.append(s[1])
+    _many(lib().flexsp_pack_many, "flexsp_pack_many", ctx, srcs, dsts, T, heads, D, P, stream)
 
 
 def flexsp_unpack_many(ctx: Context, srcs, dsts, stream=None):
     """Several src [P,T,Hp_i,D] -> dst [T,P*Hp_i,D] in one launch."""
-    P, T, _, D = srcs[0].shape
-    assert all(s.shape[0] == P and s.shape[1] == T and s.shape[3] == D for s in srcs)
-    _many(lib().flexsp_unpack_many, "flexsp_unpack_many", ctx, srcs, dsts, T, [P * s.shape[2] for s in srcs], D, P,
-          stream)
+    shapes = [s.shape for s in srcs]
+    P, T, _, D = shapes[0]
+    heads = []
+    for s in shapes:
+        assert s[0] == P and s[1] == T and s[3] == D
+        heads.append(P * s[2])
+    _many(lib().flexsp_unpack_many, "flexsp_unpack_many", ctx, srcs, dsts, T, heads, D, P, stream)
 
 
 def flexsp_attn_varlen_fwd(ctx: Context, plan: Plan, q, k, v, cu_seqlens_dev, o, lse, *, head_begin=0,
