@@ -378,7 +378,7 @@ __device__ __forceinline__ void dkv_pass(const AttnArgs &a, const PassQueues &pq
 }
 
 template <int D, bool SHARD>
-__global__ __launch_bounds__(kThreads, 2) void attn_bwd_dkv_kernel(const AttnArgs a)
+__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dkv_kernel(const AttnArgs a)
 {
     __shared__ __attribute__((aligned(1024))) char smem[dkv_lds<D>()];
     __shared__ int deal_word, split_word;
@@ -619,7 +619,7 @@ __device__ __forceinline__ void dq_pass(const AttnArgs &a, const PassQueues &pq,
 }
 
 template <int D, bool SHARD>
-__global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(const AttnArgs a)
+__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(const AttnArgs a)
 {
     __shared__ __attribute__((aligned(1024))) char smem[dq_lds<D>()];
     __shared__ int deal_word, split_word;

@@ -51,6 +51,7 @@ struct HostPass {
     int64_t offsets[kMaxQueues + 1];    // queue boundaries
     int tile_rows;
     int32_t records = 0;                // partial-result records of split tiles
+    int64_t steps = 0, longest = 0;     // inner-loop steps of the pass and of its longest item
     std::vector<flexsp_item> direct;    // items in workgroup order, if the pass is launched with one workgroup per item
 };
 
@@ -325,6 +326,11 @@ void distribute(std::vector<Work> &work, const std::vector<int64_t> &group_cost,
                 HostPass &out, int spare)
 {
     split_long_items(work, n_wg, spare, out);
+    out.steps = out.longest = 0;
+    for (const Work &w : work) {
+        out.steps += w.cost;
+        out.longest = std::max(out.longest, w.cost);
+    }
     // groups -> queues
     std::vector<int32_t> order(group_cost.size());
     for (size_t i = 0; i < order.size(); i++) order[i] = (int32_t)i;
@@ -633,6 +639,17 @@ int grid_for(const flexsp_ctx *ctx, const HostPass &p, int per_cu)
 {
     if (!p.direct.empty()) return (int)p.direct.size();
     return p.items.empty() ? 1 : ctx->num_cu * per_cu;
+}
+
+// Workgroups per compute unit of a backward pass.  With D = 64 three fit (160 registers, 42 KB of LDS) and hide more of each
+// other's waits, but each is slower: where the longest item is most of a workgroup's share, the others wait for it.
+// Both passes, two -> three: 30 011 tokens, 12 heads on 4, not causal 1 053 -> 1 004 us with the forward (longest item a third
+// of a share); 44 560 tokens, 4 heads 4 986 -> 4 694 (a third); 59 031 tokens in 296 sequences 415 -> 394 (a third); but 21 751 tokens,
+// 4 heads 263 -> 279 and 125 824 tokens, 2 heads 710 -> 740 (three quarters).  D = 128 needs the registers of two.
+int bwd_per_cu(const flexsp_ctx *ctx, const flexsp_plan *plan, int pass)
+{
+    const HostPass &p = plan->pass[pass];
+    return plan->D == 64 && 2 * p.longest * workgroups_of(ctx) <= p.steps ? 3 : 2;
 }
 
 }  // namespace
@@ -1263,7 +1280,7 @@ int flexsp_attn_varlen_bwd_kvshard(flexsp_ctx *ctx, flexsp_plan *plan, flexsp_te
     a.pq = plan->dq[FLEXSP_PASS_BWD_DQ];
     if (!plan->pass[FLEXSP_PASS_BWD_DQ].items.empty()) {
         Timed tm(ctx, FLEXSP_K_BWD_DQ, s);
-        e = launch_attn_bwd_dq_kvshard(a, plan->D, grid_for(ctx, plan->pass[FLEXSP_PASS_BWD_DQ], 2), s);
+        e = launch_attn_bwd_dq_kvshard(a, plan->D, grid_for(ctx, plan->pass[FLEXSP_PASS_BWD_DQ], bwd_per_cu(ctx, plan, FLEXSP_PASS_BWD_DQ)), s);
     }
     if (e != hipSuccess) return hip_fail(e);
     a.lse_in = lse2;
@@ -1271,7 +1288,7 @@ int flexsp_attn_varlen_bwd_kvshard(flexsp_ctx *ctx, flexsp_plan *plan, flexsp_te
     a.pq = plan->dq[FLEXSP_PASS_BWD_DKV];
     if (!plan->pass[FLEXSP_PASS_BWD_DKV].items.empty()) {
         Timed tm(ctx, FLEXSP_K_BWD_DKV, s);
-        e = launch_attn_bwd_dkv_kvshard(a, plan->D, grid_for(ctx, plan->pass[FLEXSP_PASS_BWD_DKV], 2), s);
+        e = launch_attn_bwd_dkv_kvshard(a, plan->D, grid_for(ctx, plan->pass[FLEXSP_PASS_BWD_DKV], bwd_per_cu(ctx, plan, FLEXSP_PASS_BWD_DKV)), s);
     }
     return e == hipSuccess ? FLEXSP_OK : hip_fail(e);
 }
@@ -1371,7 +1388,7 @@ int flexsp_attn_varlen_bwd(flexsp_ctx *ctx, flexsp_plan *plan, flexsp_tensor q, 
     a.pq = plan->dq[FLEXSP_PASS_BWD_DQ];
     {
         Timed tm(ctx, FLEXSP_K_BWD_DQ, s);
-        e = launch_attn_bwd_dq(a, plan->D, grid_for(ctx, plan->pass[FLEXSP_PASS_BWD_DQ], 2), s);
+        e = launch_attn_bwd_dq(a, plan->D, grid_for(ctx, plan->pass[FLEXSP_PASS_BWD_DQ], bwd_per_cu(ctx, plan, FLEXSP_PASS_BWD_DQ)), s);
     }
     if (e != hipSuccess) return hip_fail(e);
     a.lse_in = lse2;
@@ -1379,7 +1396,7 @@ int flexsp_attn_varlen_bwd(flexsp_ctx *ctx, flexsp_plan *plan, flexsp_tensor q, 
     a.pq = plan->dq[FLEXSP_PASS_BWD_DKV];
     {
         Timed tm(ctx, FLEXSP_K_BWD_DKV, s);
-        e = launch_attn_bwd_dkv(a, plan->D, grid_for(ctx, plan->pass[FLEXSP_PASS_BWD_DKV], 2), s);
+        e = launch_attn_bwd_dkv(a, plan->D, grid_for(ctx, plan->pass[FLEXSP_PASS_BWD_DKV], bwd_per_cu(ctx, plan, FLEXSP_PASS_BWD_DKV)), s);
     }
     return e == hipSuccess ? FLEXSP_OK : hip_fail(e);
 }
