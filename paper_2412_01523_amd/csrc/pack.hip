@@ -7,6 +7,8 @@
 // access per lane of a wavefront).  Walking the head-sharded side instead would make every
 // workgroup that runs at the same time read the same 1/P-wide window of each token row, which
 // concentrates the traffic on a fraction of the memory channels.
+#include <algorithm>
+
 #include "flexsp_internal.h"
 
 namespace flexsp {
@@ -24,33 +26,38 @@ template <> struct VecOf<1> { typedef uint8_t type; };
 constexpr int kPackThreads = 256;
 constexpr int kPackMany = 4;  // tensors per launch of the multi-tensor form
 
+// x / d for 0 <= x < 2^31 and d not a power of two, as a multiplication and a shift: m = floor(2^(31+s) / d) + 1 with s = ceil(log2 d)
+// fits 32 bits, and floor(x m / 2^(31+s)) is the exact quotient (m d exceeds 2^(31+s) by at most d <= 2^s).  For powers of
+// two m is 0 and s the shift.  A division by a number the compiler does not know is a chain of some twenty vector
+// instructions, and a vector of 16 bytes needed two of them: 30 011 tokens of 24 and 6 heads over 3 devices, D = 80, fp32,
+// took 213 us, and takes 187 (6.2 TB/s).
+struct Divisor {
+    uint32_t d, m;
+    int s;
+    __device__ __forceinline__ uint32_t quotient(uint32_t x) const { return m ? __umulhi(x, m) >> (s - 1) : x >> s; }
+};
+
 // Units are vectors of VB bytes.  rc = vectors per (token, slab) run, row = vectors per
 // token on the sequence-sharded side (= P * rc), slab = T * rc vectors per slab.  One vector
 // per thread and one 4 KiB stretch per workgroup measured fastest (more vectors per thread
 // lose 5-15 %).  IDX is the integer type of a vector index (32-bit whenever the tensor has
-// fewer than 2^31 vectors); shifts replace the divisions when rc and row are powers of two.
+// fewer than 2^31 vectors, whose divisions are multiplications).
 template <int VB, bool UNPACK, typename IDX>
 __global__ __launch_bounds__(kPackThreads) void permute_kernel(
     const typename VecOf<VB>::type *__restrict__ src, typename VecOf<VB>::type *__restrict__ dst,
-    IDX total, IDX slab, IDX row, IDX rc, int row_shift, int rc_shift)
+    IDX total, IDX slab, IDX row, IDX rc, Divisor by_row, Divisor by_rc)
 {
     const IDX c = (IDX)blockIdx.x * kPackThreads + threadIdx.x;  // sequence-sharded index
     if (c >= total) return;
-    IDX t, e, r, w;
-    if (row_shift >= 0) {
-        t = c >> row_shift;
-        e = c & (row - 1);
+    IDX t, r;  // token, slab (peer)
+    if constexpr (sizeof(IDX) == 4) {
+        t = by_row.quotient(c);
+        r = by_rc.quotient(c - t * row);
     } else {
-        t = c / row;  // token
-        e = c - t * row;
+        t = c / row;
+        r = (c - t * row) / rc;
     }
-    if (rc_shift >= 0) {
-        r = e >> rc_shift;
-        w = e & (rc - 1);
-    } else {
-        r = e / rc;  // slab (peer)
-        w = e - r * rc;
-    }
+    const IDX w = c - t * row - r * rc;
     const IDX o = r * slab + t * rc + w;  // head-sharded index
     if (UNPACK)
         __builtin_nontemporal_store(__builtin_nontemporal_load(&src[o]), &dst[c]);
@@ -58,38 +65,26 @@ __global__ __launch_bounds__(kPackThreads) void permute_kernel(
         __builtin_nontemporal_store(__builtin_nontemporal_load(&src[c]), &dst[o]);
 }
 
-// Several tensors in one launch (blockIdx.y picks the tensor): the same walk, 16-byte vectors and
+// Several tensors in one launch, one tensor's workgroups after the other's: the same walk, 16-byte vectors and
 // 32-bit indices only.  Saves the launches in between and lets one tensor's last workgroups
 // overlap the next one's first.
 struct ManyArgs {
     const u32x4 *src[kPackMany];
     u32x4 *dst[kPackMany];
-    uint32_t total[kPackMany], slab[kPackMany], row[kPackMany], rc[kPackMany];
-    int row_shift[kPackMany], rc_shift[kPackMany];
+    uint32_t total[kPackMany], slab[kPackMany];
+    Divisor row[kPackMany], rc[kPackMany];
+    uint32_t first[kPackMany];  // the tensor's first workgroup
 };
 // (the tensor index is resolved by a chain of compile-time cases: indexing the by-value argument
 // arrays with a run-time value would move them to scratch memory)
 template <bool UNPACK, int Y>
-__device__ __forceinline__ void permute_one_of_many(const ManyArgs &m, uint32_t c)
+__device__ __forceinline__ void permute_one_of_many(const ManyArgs &m)
 {
+    const uint32_t c = (blockIdx.x - m.first[Y]) * kPackThreads + threadIdx.x;
     if (c >= m.total[Y]) return;
-    const uint32_t row = m.row[Y], rc = m.rc[Y];
-    uint32_t t, e, r, w;
-    if (m.row_shift[Y] >= 0) {
-        t = c >> m.row_shift[Y];
-        e = c & (row - 1);
-    } else {
-        t = c / row;
-        e = c - t * row;
-    }
-    if (m.rc_shift[Y] >= 0) {
-        r = e >> m.rc_shift[Y];
-        w = e & (rc - 1);
-    } else {
-        r = e / rc;
-        w = e - r * rc;
-    }
-    const uint32_t o = r * m.slab[Y] + t * rc + w;
+    const uint32_t t = m.row[Y].quotient(c), e = c - t * m.row[Y].d;
+    const uint32_t r = m.rc[Y].quotient(e), w = e - r * m.rc[Y].d;
+    const uint32_t o = r * m.slab[Y] + t * m.rc[Y].d + w;
     if (UNPACK)
         __builtin_nontemporal_store(__builtin_nontemporal_load(&m.src[Y][o]), &m.dst[Y][c]);
     else
@@ -99,21 +94,22 @@ template <bool UNPACK>
 __global__ __launch_bounds__(kPackThreads) void permute_many_kernel(const ManyArgs m)
 {
     static_assert(kPackMany == 4, "one case per tensor below");
-    const uint32_t c = blockIdx.x * kPackThreads + threadIdx.x;
-    switch (blockIdx.y) {
-    case 0: permute_one_of_many<UNPACK, 0>(m, c); break;
-    case 1: permute_one_of_many<UNPACK, 1>(m, c); break;
-    case 2: permute_one_of_many<UNPACK, 2>(m, c); break;
-    default: permute_one_of_many<UNPACK, 3>(m, c); break;
-    }
+    if (blockIdx.x < m.first[1])
+        permute_one_of_many<UNPACK, 0>(m);
+    else if (blockIdx.x < m.first[2])
+        permute_one_of_many<UNPACK, 1>(m);
+    else if (blockIdx.x < m.first[3])
+        permute_one_of_many<UNPACK, 2>(m);
+    else
+        permute_one_of_many<UNPACK, 3>(m);
 }
 
-inline int shift_of(int64_t x)
+inline Divisor divisor(int64_t d)  // 1 <= d < 2^31
 {
-    if (x <= 0 || (x & (x - 1)) != 0) return -1;
-    int sft = 0;
-    while (((int64_t)1 << sft) < x) sft++;
-    return sft;
+    Divisor v = {(uint32_t)d, 0, 0};
+    while (((int64_t)1 << v.s) < d) v.s++;
+    if ((d & (d - 1)) != 0) v.m = (uint32_t)(((uint64_t)1 << (31 + v.s)) / (uint64_t)d + 1);
+    return v;
 }
 
 template <int VB, typename IDX>
@@ -123,14 +119,15 @@ hipError_t launch_idx(const void *src, void *dst, int64_t total, int64_t slab, i
     typedef typename VecOf<VB>::type V;
     int64_t blocks = (total + kPackThreads - 1) / kPackThreads;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    const Divisor by_row = sizeof(IDX) == 4 ? divisor(row) : Divisor(), by_rc = sizeof(IDX) == 4 ? divisor(rc) : Divisor();
     if (unpack)
         hipLaunchKernelGGL((permute_kernel<VB, true, IDX>), dim3((unsigned)blocks), dim3(kPackThreads), 0, s,
-                           (const V *)src, (V *)dst, (IDX)total, (IDX)slab, (IDX)row, (IDX)rc, shift_of(row),
-                           shift_of(rc));
+                           (const V *)src, (V *)dst, (IDX)total, (IDX)slab, (IDX)row, (IDX)rc, by_row,
+                           by_rc);
     else
         hipLaunchKernelGGL((permute_kernel<VB, false, IDX>), dim3((unsigned)blocks), dim3(kPackThreads), 0, s,
-                           (const V *)src, (V *)dst, (IDX)total, (IDX)slab, (IDX)row, (IDX)rc, shift_of(row),
-                           shift_of(rc));
+                           (const V *)src, (V *)dst, (IDX)total, (IDX)slab, (IDX)row, (IDX)rc, by_row,
+                           by_rc);
     return hipGetLastError();
 }
 
@@ -169,7 +166,7 @@ hipError_t launch_pack_many(int n, const void *const *src, void *const *dst, int
 {
     ManyArgs m;
     bool fast = n <= kPackMany;
-    int64_t most = 0;
+    int64_t blocks = 0;
     for (int i = 0; i < n && fast; i++) {
         const int64_t run_bytes = (int64_t)(H[i] / P) * D * eb, bytes = T * P * run_bytes;
         const uintptr_t bits = (uintptr_t)src[i] | (uintptr_t)dst[i] | (uintptr_t)run_bytes;
@@ -182,13 +179,13 @@ hipError_t launch_pack_many(int n, const void *const *src, void *const *dst, int
         m.src[i] = (const u32x4 *)src[i];
         m.dst[i] = (u32x4 *)dst[i];
         m.total[i] = (uint32_t)total;
-        m.rc[i] = (uint32_t)rc;
         m.slab[i] = (uint32_t)(T * rc);
-        m.row[i] = (uint32_t)((int64_t)P * rc);
-        m.row_shift[i] = shift_of((int64_t)P * rc);
-        m.rc_shift[i] = shift_of(rc);
-        most = total > most ? total : most;
+        m.row[i] = divisor(std::max<int64_t>(P * rc, 1));
+        m.rc[i] = divisor(std::max<int64_t>(rc, 1));
+        m.first[i] = (uint32_t)blocks;
+        blocks += (total + kPackThreads - 1) / kPackThreads;
     }
+    if (blocks * kPackThreads >= ((int64_t)1 << 32)) fast = false;  // threads of a launch are counted in 32 bits
     if (!fast) {
         for (int i = 0; i < n; i++) {
             hipError_t e = launch_pack(src[i], dst[i], T, H[i], D, P, eb, unpack, s);
@@ -196,12 +193,12 @@ hipError_t launch_pack_many(int n, const void *const *src, void *const *dst, int
         }
         return hipSuccess;
     }
-    if (most == 0) return hipSuccess;
+    if (blocks == 0) return hipSuccess;
     for (int i = n; i < kPackMany; i++) {
         m.src[i] = nullptr; m.dst[i] = nullptr;
-        m.total[i] = 0; m.slab[i] = 0; m.row[i] = 1; m.rc[i] = 1; m.row_shift[i] = 0; m.rc_shift[i] = 0;
+        m.total[i] = 0; m.slab[i] = 0; m.row[i] = m.rc[i] = divisor(1); m.first[i] = (uint32_t)blocks;
     }
-    const dim3 grid((unsigned)((most + kPackThreads - 1) / kPackThreads), (unsigned)n);
+    const dim3 grid((unsigned)blocks);
     if (unpack)
         hipLaunchKernelGGL(permute_many_kernel<true>, grid, dim3(kPackThreads), 0, s, m);
     else
