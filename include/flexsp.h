@@ -93,7 +93,8 @@ int flexsp_ctx_num_xcd(const flexsp_ctx *ctx);
  * longest first (the tiles of a short sequence side by side, where its longest tile would stand),
  * in one queue per XCD, for the forward kernel and for the two backward kernels,
  * and holds the fp32 scratch the kernels need (delta and the base-2 log-sum-exp [Hq, T] for the
- * backward, one 66 KiB record per part of a cut tile), so the hot calls allocate nothing.
+ * backward, one 66 KiB record per part of a cut tile, at most 512 of them per pass where the finer cut of
+ * a small backward applies, see flexsp_item), so the hot calls allocate nothing.
  * Everything is copied before the call returns; the caller keeps ownership of
  * cu_seqlens_host.  On a device context the queues go to the GPU with an asynchronous copy on
  * a stream of the context's own, and the first forward / backward call that uses the plan

@@ -10,6 +10,7 @@
 //   dK/dV   one work item = 64 keys of one (sequence, kv head); loops over the query heads of
 //           the group and over the query rows that see those keys; dK^T, dV^T stay in
 //           registers, so grouped-query heads are summed without a reduction pass.
+// Small backwards run both as one launch (attn_bwd_both_kernel); the dK/dV pass then forms delta itself.
 // The 32x32 accumulator keeps one COLUMN per lane, and only its ROW index can be contracted
 // in a following MFMA.  Hence dK/dV computes S = Q K^T (rows = queries) and dQ computes
 // S^T = K Q^T (rows = keys).  Operands whose contraction index runs along the rows of a
