@@ -235,6 +235,8 @@ int flexsp_attn_varlen_fwd(flexsp_ctx *ctx, flexsp_plan *plan, flexsp_tensor q, 
  * type): FLEXSP_BF16 rounds the fp32 accumulators to bf16 once; FLEXSP_F32 stores them as
  * they are (useful when grouped-query sums grow past the range where bf16's spacing is fine
  * enough).  Results are deterministic (no floating-point atomics).
+ * bf16 gradients may be written over what the call does not need again: dq over o, dk and dv over k
+ * and v (the same view).  No other output may overlap an input, and no two outputs each other.
  * Errors: INVALID_ARGUMENT, UNSUPPORTED (grad_dtype), PLAN_MISMATCH, NO_DEVICE, HIP_ERROR.
  */
 int flexsp_attn_varlen_bwd(flexsp_ctx *ctx, flexsp_plan *plan, flexsp_tensor q, flexsp_tensor k,

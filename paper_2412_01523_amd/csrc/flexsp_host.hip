@@ -618,14 +618,38 @@ int plan_upload(flexsp_ctx *ctx, flexsp_plan *p)
     return FLEXSP_OK;
 }
 
+// Whether no output of a backward shares memory with one of its inputs (the views' extents: interleaved views count as
+// sharing).
+bool outputs_apart(const flexsp_plan *p, const AttnArgs &a)
+{
+    struct Bytes {
+        uintptr_t lo, hi;
+    };
+    auto view = [&](const void *first, int64_t T, int64_t st, int64_t heads, int64_t sh, int64_t eb) {
+        const uintptr_t lo = (uintptr_t)first;
+        return Bytes{lo, T > 0 ? lo + (uintptr_t)(((T - 1) * st + (heads - 1) * sh + p->D) * eb) : lo};
+    };
+    const int64_t Tk = p->kvshard ? p->Tk : p->T, gb = a.grad_f32 ? 4 : 2;
+    const Bytes in[] = {view(a.q, p->T, a.q_st, p->Hq, a.q_sh, 2),    view(a.k, Tk, a.k_st, p->Hkv, a.k_sh, 2),
+                        view(a.v, Tk, a.v_st, p->Hkv, a.v_sh, 2),     view(a.o, p->T, a.o_st, p->Hq, a.o_sh, 2),
+                        view(a.dO, p->T, a.do_st, p->Hq, a.do_sh, 2), {(uintptr_t)a.lse_in, (uintptr_t)(a.lse_in + p->T * p->Hq)}};
+    const Bytes out[] = {view(a.dq, p->T, a.dq_st, p->Hq, a.dq_sh, gb), view(a.dk, Tk, a.dk_st, p->Hkv, a.dk_sh, gb),
+                         view(a.dv, Tk, a.dv_st, p->Hkv, a.dv_sh, gb)};
+    for (const Bytes &x : in)
+        for (const Bytes &y : out)
+            if (x.lo < y.hi && y.lo < x.hi) return false;
+    return true;
+}
+
 // Backwards that run their two passes in one launch (see attn_bwd_both_kernel): those whose items can all be resident at
-// once.  (Up to twice as many: 3 500 tokens with 3 heads 156 -> 152 us, but 1 480 tokens with 16 heads 125 -> 132 us.)
+// once, and whose outputs lie apart from their inputs: side by side, one pass would read what the other has already
+// overwritten, where one after the other dq over o and dk, dv over k, v come out right.  (Up to twice as many: 3 500 tokens with 3 heads 156 -> 152 us, but 1 480 tokens with 16 heads 125 -> 132 us.)
 // Fills in what such a launch needs and returns its grid (each pass's workgroups keep to their XCD: the dQ pass starts at a
 // multiple of the number of queues), or 0.
 int both_at_once(const flexsp_ctx *ctx, const flexsp_plan *p, AttnArgs &a)
 {
     const int dkv = (int)p->pass[FLEXSP_PASS_BWD_DKV].direct.size(), dq = (int)p->pass[FLEXSP_PASS_BWD_DQ].direct.size();
-    if (!dkv || !dq || dkv + dq > workgroups_of(ctx)) return 0;
+    if (!dkv || !dq || dkv + dq > workgroups_of(ctx) || !outputs_apart(p, a)) return 0;
     a.pq = p->dq[FLEXSP_PASS_BWD_DKV];
     a.dq_pq = p->dq[FLEXSP_PASS_BWD_DQ];
     a.dkv_items = dkv;
