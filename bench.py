@@ -51,6 +51,16 @@ MEASURED_HBM_TRAFFIC = {
 }
 
 
+def kernel_flops(d, pairs_heads, launched):
+    """Algorithmic FLOPs of a launch by kernel, per (query, key) pair and head: fwd 2 products; dK/dV kernel 4 (S, dP, dV,
+    dK); dQ kernel 1 (its S and dP are recomputation, counted as zero).  A small backward runs both passes in one launch, which
+    the library counts as bwd_dkv: without a bwd_dq among the `launched` kernels all 5 products are that launch's."""
+    flops = {"fwd": 4 * d * pairs_heads, "bwd_dkv": 8 * d * pairs_heads, "bwd_dq": 2 * d * pairs_heads}
+    if "bwd_dq" not in launched:
+        flops["bwd_dkv"] += flops.pop("bwd_dq")
+    return flops
+
+
 def permute_leg(ctx, fx, wl, torch, stream):
     """Achieved HBM bandwidth of pack / unpack on the [32768, 32, 128] bf16, P = 8 shape, rotating
     over 4 distinct buffer pairs (2 GiB) so the 256 MB last-level cache cannot serve the reads;
@@ -367,7 +377,9 @@ def main() -> int:
         e = 2
         alg = {"fwd": (T * (2 * Hq + 2 * Hkv) * D) * e + 4 * Hq * T,
                "bwd_dq": (T * (4 * Hq + 2 * Hkv) * D) * e + 3 * 4 * Hq * T,
-               "bwd_dkv": (T * (2 * Hq + 4 * Hkv) * D) * e + 2 * 4 * Hq * T}
+               "bwd_dkv": (T * (2 * Hq + 4 * Hkv) * D) * e + 2 * 4 * Hq * T,
+               # a small backward's one launch: q k v o dO lse in, dq dk dv out, delta and lse2 written
+               "bwd_both": (T * (4 * Hq + 4 * Hkv) * D) * e + 3 * 4 * Hq * T}
         print(json.dumps({"traffic_probe": cfg.name, "copy_bytes_each_way": c1.tokens * c1.hq * c1.sp_degree * c1.d * 2,
                           "algorithmic_bytes_per_launch": alg}))
         return 0
@@ -482,9 +494,7 @@ def main() -> int:
         ms, n = prof[name]
         if n:
             kern[name] = {"avg_ms": ms / n, "launches_per_step": n / max(args.steps, 1)}
-    # algorithmic FLOPs per launch, per (query, key) pair and head: fwd 2 GEMMs, dK/dV kernel 4 GEMMs
-    # (S, dP, dV, dK), dQ kernel 1 GEMM (its S and dP are recomputation, counted as zero)
-    alg = {"fwd": 4 * D * pairs_heads, "bwd_dkv": 8 * D * pairs_heads, "bwd_dq": 2 * D * pairs_heads}
+    alg = kernel_flops(D, pairs_heads, kern)
     dom = max((k for k in alg if k in kern), key=lambda k: kern[k]["avg_ms"] * kern[k]["launches_per_step"])
     ach = alg[dom] / (kern[dom]["avg_ms"] * 1e-3) / 1e12
     roofline = {"kernel": dom, "bound": "mfma", "achieved": ach, "peak": BF16_MFMA_PEAK / 1e12,
