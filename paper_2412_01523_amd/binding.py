@@ -56,13 +56,13 @@ class Profile(Structure):
 
 
 _lib = None
-_torch = None          # set with _lib
+_current_stream = None  # set with _lib
 _pointers, _ints = {}, {}  # ctypes array types by length
 
 
 def lib() -> ctypes.CDLL:
     """Loads libflexsp.so (built in-tree by paper_2412_01523_amd.build); fails loudly if absent."""
-    global _lib, _torch
+    global _lib, _current_stream
     if _lib is None:
         if not LIB_PATH.exists():
             raise FileNotFoundError(
@@ -128,7 +128,7 @@ def lib() -> ctypes.CDLL:
         L.flexsp_min_microbatches.restype = c_int64
         L.flexsp_profile_start.argtypes = [c_void_p, c_int32]
         L.flexsp_profile_stop.argtypes = [c_void_p, POINTER(Profile)]
-        _torch = torch
+        _current_stream = _current_stream_of(torch)
         _lib = L
     return _lib
 
@@ -141,11 +141,25 @@ def _check(status: int, where: str):
 # What follows runs once to eight times per call, and the calls are a few microseconds of GPU work when a batch is small: the
 # handle of torch's current stream without a Stream object around it (2.1 -> 0.2 us), a view's strides in one look
 # (1.3 -> 0.7 us each).  Forward and backward of 436 tokens spent 23.5 us in here and in ctypes, and now 14.1 us.
+def _current_stream_of(torch):
+    """A function that returns the handle of torch's current stream.  The short way is not part of torch's public interface: a
+    torch that lacks it is asked the public way."""
+    raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    device = getattr(torch._C, "_cuda_getDevice", None)
+    initialized = torch.cuda.is_initialized
+
+    def public():
+        return torch.cuda.current_stream().cuda_stream
+
+    def short():
+        return raw_stream(device()) if initialized() else public()
+
+    return public if raw_stream is None or device is None else short
+
+
 def _stream(stream) -> int:
     if stream is None:
-        if not _torch.cuda.is_initialized():
-            return _torch.cuda.current_stream().cuda_stream
-        return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
+        return _current_stream()
     return int(getattr(stream, "cuda_stream", stream))
 
 
