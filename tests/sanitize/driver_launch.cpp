@@ -77,11 +77,116 @@ static int check_overlap(flexsp_ctx *ctx)
     return 0;
 }
 
+// The list a pass of few items is launched with (one workgroup per item), which plan inspection does not show: every tile's
+// steps exactly once, by one whole item or by parts with records of their own.
+static int check_list(const flexsp_plan *p, int pass, const std::vector<std::vector<int64_t>> &tiles, int heads, int lowest)
+{
+    const HostPass &hp = p->pass[pass];
+    size_t whole = 0;
+    for (const auto &b : tiles) whole += b.size() * heads;
+    if (hp.items.empty() || hp.items.size() > 512) {
+        CHECK(hp.direct.empty());
+        return 0;
+    }
+    CHECK(hp.direct.size() >= whole && hp.direct.size() <= 512);
+    std::vector<std::vector<std::vector<std::vector<flexsp_item>>>> of(tiles.size());
+    for (size_t b = 0; b < tiles.size(); b++) of[b].assign(tiles[b].size(), std::vector<std::vector<flexsp_item>>(heads));
+    for (const flexsp_item &it : hp.direct) {
+        size_t b = 0;  // plans of shards name a sequence by its index, others by its first token
+        if (p->kvshard)
+            b = (size_t)it.seq_start;
+        else
+            while (b < tiles.size() && (p->cu[b] != it.seq_start || tiles[b].empty())) b++;
+        CHECK(b < tiles.size() && it.tile >= 0 && (size_t)it.tile < tiles[b].size() && it.head >= 0 && it.head < heads);
+        of[b][it.tile][it.head].push_back(it);
+    }
+    std::vector<char> taken((size_t)hp.records, 0);
+    for (size_t b = 0; b < tiles.size(); b++)
+        for (size_t t = 0; t < tiles[b].size(); t++)
+            for (int h = 0; h < heads; h++) {
+                std::vector<flexsp_item> &v = of[b][t][h];
+                std::sort(v.begin(), v.end(), [](const flexsp_item &x, const flexsp_item &y) { return x.parts >> 16 < y.parts >> 16; });
+                CHECK(!v.empty() && v[0].step_begin == 0 && v.back().step_end == tiles[b][t]);
+                const int n = (int)v.size();
+                CHECK(n <= kMaxParts);
+                for (int i = 0; i < n; i++) {
+                    CHECK(v[i].parts == ((i << 16) | n) && v[i].slot == v[0].slot);
+                    CHECK(i == 0 || v[i].step_begin == v[i - 1].step_end);
+                    CHECK(n == 1 || v[i].step_end - v[i].step_begin >= lowest);
+                }
+                CHECK((v[0].slot >= 0) == (n > 1));
+                if (n > 1) {
+                    CHECK(v[0].slot + n <= hp.records);
+                    for (int i = 0; i < n; i++) CHECK(!taken[v[0].slot + i]++);
+                }
+            }
+    return 0;
+}
+
+static int check_direct_lists(flexsp_ctx *ctx)
+{
+    unsigned seed = 4711;
+    auto rnd = [&](int lo, int hi) { seed = seed * 1664525u + 1013904223u; return lo + (int)((seed >> 8) % (unsigned)(hi - lo + 1)); };
+    int lists = 0, finer = 0, both = 0;
+    for (int trial = 0; trial < 600; trial++) {
+        const int Hkv = rnd(1, 4), G = rnd(0, 2) ? 1 : rnd(2, 8), Hq = Hkv * G, causal = rnd(0, 3) != 0;
+        const int B = rnd(1, rnd(0, 1) ? 4 : 120), top = 1 << rnd(3, 12);
+        std::vector<int32_t> cu(B + 1, 0), cu_k(B + 1, 0), shift(B, 0);
+        for (int b = 0; b < B; b++) {
+            cu[b + 1] = cu[b] + (rnd(0, 9) ? rnd(1, top) : 0);
+            cu_k[b + 1] = cu_k[b] + (rnd(0, 9) ? rnd(1, 2 * top) : 0);
+            shift[b] = rnd(-top, 2 * top);
+        }
+        for (int shard = 0; shard < 2; shard++) {
+            flexsp_plan *p = nullptr;
+            if (shard)
+                CHECK(flexsp_plan_create_kvshard(ctx, cu.data(), cu_k.data(), shift.data(), B, Hq, Hkv, 128, causal, &p) == FLEXSP_OK);
+            else
+                CHECK(flexsp_plan_create(ctx, cu.data(), B, Hq, Hkv, 128, causal, &p) == FLEXSP_OK);
+            std::vector<std::vector<int64_t>> rows(B), keys(B);  // steps of each sequence's query tiles and key tiles
+            for (int b = 0; b < B; b++) {
+                const int64_t sq = cu[b + 1] - cu[b], sk = shard ? cu_k[b + 1] - cu_k[b] : sq, sh = shard ? shift[b] : 0;
+                for (int64_t t = 0; t * 128 < sq; t++) {
+                    const int64_t seen = causal ? std::max<int64_t>(0, std::min(sk, (t + 1) * 128 + sh)) : sk;
+                    rows[b].push_back((seen + 63) / 64 + shard);  // (a shard's tile without keys is still written)
+                }
+                for (int64_t t = 0; t * 64 < sk; t++) {
+                    const int64_t first = causal ? std::max<int64_t>(0, t * 64 - sh) / 64 * 64 : 0;
+                    keys[b].push_back(std::max<int64_t>(0, (sq - first + 63) / 64) * G + shard);
+                }
+            }
+            for (int pass = 0; pass < 3; pass++) {
+                const std::vector<std::vector<int64_t>> &steps = pass == FLEXSP_PASS_BWD_DKV ? keys : rows;
+                const int heads = pass == FLEXSP_PASS_BWD_DKV ? Hkv : Hq;
+                const HostPass &hp = p->pass[pass];
+                if (check_list(p, pass, steps, heads, pass == FLEXSP_PASS_FWD ? kMinPartSteps : kShortPartSteps)) return 1;
+                lists += !hp.direct.empty();
+                finer += hp.direct.size() > hp.items.size();
+            }
+            AttnArgs a;
+            std::memset(&a, 0, sizeof(a));
+            a.q = a.k = a.v = a.o = a.dO = (const uint16_t *)(1 << 20);  // inputs here, outputs there, all strides 0
+            a.lse_in = (const float *)(1 << 20);
+            a.dq = a.dk = a.dv = (void *)((uintptr_t)1 << 40);
+            const int grid = both_at_once(ctx, p, a);
+            if (grid) {
+                const int dkv = (int)p->pass[FLEXSP_PASS_BWD_DKV].direct.size(), dq = (int)p->pass[FLEXSP_PASS_BWD_DQ].direct.size();
+                CHECK(dkv > 0 && dq > 0 && a.dkv_items == dkv && a.dq_wg >= dkv && a.dq_wg % ctx->num_xcd == 0 && grid == a.dq_wg + dq && dkv + dq <= 512);
+                both++;
+            }
+            flexsp_plan_destroy(p);
+        }
+    }
+    std::printf("%d lists, %d cut finer than listed, %d single launches\n", lists, finer, both);
+    CHECK(lists > 500 && finer > 100 && both > 200);
+    return 0;
+}
+
 int main()
 {
     flexsp_ctx *ctx = nullptr;
     CHECK(flexsp_ctx_create(&ctx, -1) == FLEXSP_OK);
-    if (check_overlap(ctx)) return 1;
+    if (check_overlap(ctx) || check_direct_lists(ctx)) return 1;
     flexsp_ctx_destroy(ctx);
     std::puts("launch decisions: ok");
     return 0;
