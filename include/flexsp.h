@@ -93,8 +93,9 @@ int flexsp_ctx_num_xcd(const flexsp_ctx *ctx);
  * longest first (the tiles of a short sequence side by side, where its longest tile would stand),
  * in one queue per XCD, for the forward kernel and for the two backward kernels,
  * and holds the fp32 scratch the kernels need (delta and the base-2 log-sum-exp [Hq, T] for the
- * backward, one 66 KiB record per part of a cut tile, at most 512 of them per pass where the finer cut of
- * a small backward applies, see flexsp_item), so the hot calls allocate nothing.
+ * backward, one 66 KiB record per part of a cut tile), so the hot calls allocate nothing.  Where the finer
+ * cut of a small backward applies (see flexsp_item) there are at most two records per compute unit and
+ * backward pass, 69 MB for both passes on 256 compute units; a new buffer is made a quarter larger than asked.
  * Everything is copied before the call returns; the caller keeps ownership of
  * cu_seqlens_host.  On a device context the queues go to the GPU with an asynchronous copy on
  * a stream of the context's own, and the first forward / backward call that uses the plan
@@ -230,7 +231,8 @@ int flexsp_attn_varlen_fwd(flexsp_ctx *ctx, flexsp_plan *plan, flexsp_tensor q, 
  * Backward of Eq. 3 for the loss L = sum(O * dO): writes dq [T,*,D] (query heads as in q)
  * and dk, dv [T,*,D] (kv heads as in k; summed over the query heads of each group).
  * o and lse are the forward's outputs.  Softmax is recomputed from lse (no second
- * reduction); delta = rowsum(dO * O) is formed in fp32 in the plan's scratch.
+ * reduction); delta = rowsum(dO * O) is formed in fp32 and kept in the plan's scratch between the two
+ * passes (a small backward runs them in one launch, in which each forms it itself).
  * grad_dtype selects the element type of dq, dk and dv (their strides count elements of that
  * type): FLEXSP_BF16 rounds the fp32 accumulators to bf16 once; FLEXSP_F32 stores them as
  * they are (useful when grouped-query sums grow past the range where bf16's spacing is fine
@@ -333,17 +335,19 @@ int flexsp_lse_merge_acc(flexsp_ctx *ctx, flexsp_tensor o_acc, float *lse_acc, f
 /*
  * The forward for callers that cannot allocate: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc.  Same result as flexsp_attn_varlen_fwd, bit for bit, but it takes
- * no plan and calls no hipMalloc, hipFree or any other allocating routine: the work queues are built
+ * no plan and calls no hipMalloc, hipFree or any other allocating routine: the work is listed
  * on the device from `cu_seqlens_dev` (device pointer, B+1 int32 prefix sums, cu[0] = 0,
- * non-decreasing, cu[B] <= T) by a small kernel launched in front of the attention kernel, into a
+ * non-decreasing, cu[B] <= T).  A batch of more possible items, (ceil(T / 128) + B) * head_count, than
+ * two per compute unit has work queues, built by a small kernel launched in front of the attention kernel in a
  * fixed array of about 2 MiB that each GPU the library runs on holds from library load until the
- * process ends (its address on the context's device is resolved by flexsp_ctx_create).
+ * process ends (its address on the context's device is resolved by flexsp_ctx_create).  In a smaller
+ * one every workgroup of the attention kernel finds its item in the lengths itself.
  *   B, T            sequences in the batch; tokens the q / k / v / o tensors hold (rows of lse)
  *   D               head dim, 64 or 128; the remaining arguments are those of flexsp_attn_varlen_fwd
  * Limits: T <= 524 288 and (ceil(T / 128) + B) * head_count <= 65 536, else FLEXSP_UNSUPPORTED.
  * The lengths are read on the device only, so they cannot be checked by the host: if the device
  * array is not a valid prefix-sum list inside [0, T], NOTHING is computed (o and lse keep their
- * contents).  Every call on a GPU shares that GPU's array: calls that may overlap in time on one
+ * contents).  Calls with queues share the GPU's array: those that may overlap in time on one
  * GPU (different streams, or graph replays running concurrently) race; order them.  Sequences are
  * served longest tile first like a plan's queues, but without the plan's grouping of a head's tiles
  * onto one XCD, so it is somewhat slower than the plan-based call; nothing synchronises the host.

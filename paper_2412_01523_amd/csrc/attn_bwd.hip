@@ -583,7 +583,8 @@ __device__ __forceinline__ void dq_pass(const AttnArgs &a, const PassQueues &pq,
             if (t + 1 < ntiles) step_fn(std::integral_constant<int, 1>{}, t + 1);
         }
 
-        // delta and the base-2 log-sum-exp are kept for the dK/dV kernel, which runs after this one
+        // delta and the base-2 log-sum-exp are kept for the dK/dV kernel, which runs after this one (beside a
+        // dK/dV pass in one launch nobody reads them)
         // (stored here, not where they are computed: a store in flight there would be waited for by
         // the first tile's wait for its copy)
         if (qok && hl == 0) {

@@ -339,8 +339,8 @@ __device__ __forceinline__ float group_sum(float x)
 // pass through LDS half a head dim at a time, and memory sees 256 (D = 128) or 128 (D = 64) contiguous bytes per row and
 // instruction.  Measured
 // against the piece-wise accesses: one device's ring pass of a 64K-token batch over four devices (forward with the fp32
-// running result, backward with fp32 sums) 1 654 -> 1 601 us; forward and backward with fp32 gradients of an unmasked
-// D = 64 batch (30 011 tokens, 12 heads on 4 kv heads) 1 145 -> 1 089 us.
+// running result, backward with fp32 sums) 1 643 -> 1 582 us; forward and backward with fp32 gradients of an unmasked
+// D = 64 batch (30 011 tokens, 12 heads on 4 kv heads) 1 109 -> 1 090 us.
 template <int DB>
 struct RowsF32 {
     static constexpr int HB = DB / 2;            // 32-wide blocks per half
