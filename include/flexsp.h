@@ -285,7 +285,8 @@ int flexsp_attn_varlen_bwd(flexsp_ctx *ctx, flexsp_plan *plan, flexsp_tensor q, 
  *   attention; then, over the visible keys j of the shard,
  *       dQ_i = scale sum_j dS_ij k_j (this shard's part),  dK_j = scale sum_i dS_ij q_i,  dV_j = sum_i P_ij dO_i,
  *       dS_ij = P_ij (dO_i.v_j - delta_i).
- *   dq is [Tq, Hq, D], dk / dv are [Tk, Hkv, D] (rows of the shard), grad_dtype as in flexsp_attn_varlen_bwd.
+ *   dq is [Tq, Hq, D], dk / dv are [Tk, Hkv, D] (rows of the shard), grad_dtype and what
+ *   may overlap as in flexsp_attn_varlen_bwd.
  *   accumulate = 0: the three outputs are overwritten (rows and keys that see nothing get zeros);
  *   accumulate = 1 (fp32 gradients only, else UNSUPPORTED): the results are ADDED to what dq / dk / dv
  *   hold, as a ring needs it (dq gathers the shards' parts; dk / dv travel with their shard and gather
