@@ -58,7 +58,7 @@ constexpr int dq_lds()  // ... of the dQ pass: two steps (K | V)
 // SELF = true: the log-sum-exp read is the forward's own and the workgroup forms delta = dO . O of a step's rows itself,
 // from rows of O and dO requested with the step's tiles, so that the pass does not have to come after the dQ pass.
 template <int D, bool SHARD, bool SELF>
-__device__ __forceinline__ void dkv_pass(const AttnArgs &a, const PassQueues &pq, const int first_wg, char *const smem, int &deal_word, int &split_word)
+__device__ __forceinline__ void dkv_pass(KernArgs &args, KernQueues &queues, const int first_wg, char *const smem, int &deal_word, int &split_word)
 {
     typedef LdsTile<D> L;
     constexpr int KS = D / 16;
@@ -70,7 +70,7 @@ __device__ __forceinline__ void dkv_pass(const AttnArgs &a, const PassQueues &pq
     static_assert(dkv_lds<D>() == 2 * STEP + 4 * XSLOT, "LDS of the pass");
     char *const exch = smem + 2 * STEP;
 
-    const int tid = threadIdx.x;
+    const int tid = thread_id();
     const int lane0 = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kb = wave >> 1, j = wave & 1;     // key block; role: 0 accumulates dV, 1 accumulates dK
@@ -88,7 +88,9 @@ __device__ __forceinline__ void dkv_pass(const AttnArgs &a, const PassQueues &pq
     }
     ItemDealer deal;
 
-    for (int item = deal.first(pq, first_wg, &deal_word, wave, lane0); item >= 0; item = deal.advance()) {
+    for (int item = deal.first(queues, args.grid, first_wg, &deal_word, wave, lane0); item >= 0; item = deal.advance()) {
+        KernArgs &a = fresh(args);
+        KernQueues &pq = fresh(queues);
         // s: query rows of the sequence; sk: its keys; sh: position of the first query minus position of
         // the first key (0 unless SHARD); tok0 / ktok0: their first rows in q, dO / k, v
         int s, sk, sh, g, kv0, first, total, nparts, part, slot, qfirst, nsteps;
@@ -116,6 +118,7 @@ __device__ __forceinline__ void dkv_pass(const AttnArgs &a, const PassQueues &pq
         // the item instead of being hoisted out of this loop into long-lived registers
         int lane = lane0;
         asm volatile("" : "+v"(lane));
+        lane &= 63;  // (its range is known again: divisions by the pieces of a row are shifts)
         const int r = lane & 31, hl = lane >> 5;
         const int wk_lo = kv0 + kb * 32;
         const int kvrow = wk_lo + r;  // this lane's key (column of S)
@@ -343,28 +346,30 @@ __device__ __forceinline__ void dkv_pass(const AttnArgs &a, const PassQueues &pq
             step_fn(std::integral_constant<int, 0>{}, step);
             if (step + 1 < n) step_fn(std::integral_constant<int, 1>{}, step + 1);
         }
+        KernArgs &e = fresh(args);
+        KernQueues &eq = fresh(queues);
         if (n >= kLateTicketSteps) deal.prefetch();
         if (nparts > 1) {
-            split_store<DB>(pq.split_scratch + (int64_t)(slot + part) * kPartialBytes, accT, tid);
-            if (!split_arrive(pq.split_flags + slot, nparts, &split_word, tid)) continue;  // a later part finishes the tile
+            split_store<DB>(eq.split_scratch + (int64_t)(slot + part) * kPartialBytes, accT, tid);
+            if (!split_arrive(eq.split_flags + slot, nparts, &split_word, tid)) continue;  // a later part finishes the tile
 #pragma unroll
             for (int d = 0; d < DB; d++)
 #pragma unroll
                 for (int i = 0; i < 16; i++) accT[d][i] = 0.f;
             for (int p = 0; p < nparts; p++)
-                split_sum<DB>(pq.split_scratch + (int64_t)(slot + p) * kPartialBytes, accT, 1.0f, tid);
+                split_sum<DB>(eq.split_scratch + (int64_t)(slot + p) * kPartialBytes, accT, 1.0f, tid);
         }
 
         // role 0 writes dV rows, role 1 writes dK rows (scaled)
-        char *const out = (char *)(j ? a.dk : a.dv);
-        const int64_t ost = j ? a.dk_st : a.dv_st, osh = j ? a.dk_sh : a.dv_sh;
-        const float mul = j ? a.scale : 1.0f;
+        char *const out = (char *)(j ? e.dk : e.dv);
+        const int64_t ost = j ? e.dk_st : e.dv_st, osh = j ? e.dk_sh : e.dv_sh;
+        const float mul = j ? e.scale : 1.0f;
         if (wk_lo >= sk) continue;
         char *const stage = smem + (n & 1) * STEP + wave * (32 * L::ROWB);  // the Q/dO buffer the last step did not use (every wavefront is past its barriers)
-        if (a.grad_f32) {
+        if (e.grad_f32) {
             float *const rows = (float *)out + (ktok0 + wk_lo) * ost + (int64_t)g * osh;
             RowsF32<DB> f;
-            if (SHARD && (a.grad_f32 & 2))  // added to the partial sums the rows hold
+            if (SHARD && (e.grad_f32 & 2))  // added to the partial sums the rows hold
                 f.add(stage, rows, ost, min(32, sk - wk_lo), accT, mul, lane);
             else
                 f.store(stage, rows, ost, min(32, sk - wk_lo), accT, mul, lane);
@@ -379,8 +384,9 @@ __device__ __forceinline__ void dkv_pass(const AttnArgs &a, const PassQueues &pq
 }
 
 template <int D, bool SHARD>
-__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dkv_kernel(const AttnArgs a)
+__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dkv_kernel(const AttnArgs)
 {
+    KernArgs &a = kernel_args();
     __shared__ __attribute__((aligned(1024))) char smem[dkv_lds<D>()];
     __shared__ int deal_word, split_word;
     dkv_pass<D, SHARD, false>(a, a.pq, 0, smem, deal_word, split_word);
@@ -391,7 +397,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dkv_kernel
 // log-sum-exp read here is that of the complete attention and `o` the complete output, so delta is the
 // complete one; a part of a cut tile comes as an item of its own with its key range and shift.
 template <int D, bool SHARD>
-__device__ __forceinline__ void dq_pass(const AttnArgs &a, const PassQueues &pq, const int first_wg, char *const smem, int &deal_word, int &split_word)
+__device__ __forceinline__ void dq_pass(KernArgs &args, KernQueues &queues, const int first_wg, char *const smem, int &deal_word, int &split_word)
 {
     typedef LdsTile<D> L;
     constexpr int KS = D / 16;
@@ -399,14 +405,16 @@ __device__ __forceinline__ void dq_pass(const AttnArgs &a, const PassQueues &pq,
     constexpr int TILE = kDqBk * L::ROWB;
     static_assert(dq_lds<D>() == 4 * TILE, "LDS of the pass");  // [buffer][K | V]
 
-    const int tid = threadIdx.x;
+    const int tid = thread_id();
     const int lane0 = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     LaneOffsets<D> lo;
     lo.init(lane0);
     ItemDealer deal;
 
-    for (int item = deal.first(pq, first_wg, &deal_word, wave, lane0); item >= 0; item = deal.advance()) {
+    for (int item = deal.first(queues, args.grid, first_wg, &deal_word, wave, lane0); item >= 0; item = deal.advance()) {
+        KernArgs &a = fresh(args);
+        KernQueues &pq = fresh(queues);
         // s: query rows of the sequence; sk: keys counted from the item's first one; rel: position of a
         // row among those keys minus its row index; tok0 / ktok0: first rows in q, o, dO / k, v
         int s, sk, rel, h, q0, ntiles, nparts, part, slot;
@@ -434,6 +442,7 @@ __device__ __forceinline__ void dq_pass(const AttnArgs &a, const PassQueues &pq,
         // the item instead of being hoisted out of this loop into long-lived registers
         int lane = lane0;
         asm volatile("" : "+v"(lane));
+        lane &= 63;  // (its range is known again: divisions by the pieces of a row are shifts)
         const int r = lane & 31, hl = lane >> 5;
         const int g = h / a.G;
         const uint16_t *kbase = a.k + ktok0 * a.k_st + (int64_t)g * a.k_sh;
@@ -583,37 +592,39 @@ __device__ __forceinline__ void dq_pass(const AttnArgs &a, const PassQueues &pq,
             if (t + 1 < ntiles) step_fn(std::integral_constant<int, 1>{}, t + 1);
         }
 
+        KernArgs &e = fresh(args);
+        KernQueues &eq = fresh(queues);
         // delta and the base-2 log-sum-exp are kept for the dK/dV kernel, which runs after this one (beside a
         // dK/dV pass in one launch nobody reads them)
         // (stored here, not where they are computed: a store in flight there would be waited for by
         // the first tile's wait for its copy)
         if (qok && hl == 0) {
-            a.delta_out[(int64_t)h * a.T + tok0 + qrow] = -delta;  // negated: the dK/dV kernel starts its dP accumulator from it
-            a.lse_out[(int64_t)h * a.T + tok0 + qrow] = lse2;
+            e.delta_out[(int64_t)h * e.T + tok0 + qrow] = -delta;  // negated: the dK/dV kernel starts its dP accumulator from it
+            e.lse_out[(int64_t)h * e.T + tok0 + qrow] = lse2;
         }
         if (nparts > 1) {
-            split_store<DB>(pq.split_scratch + (int64_t)(slot + part) * kPartialBytes, dqT, tid);
-            if (!split_arrive(pq.split_flags + slot, nparts, &split_word, tid)) continue;  // a later part finishes the tile
+            split_store<DB>(eq.split_scratch + (int64_t)(slot + part) * kPartialBytes, dqT, tid);
+            if (!split_arrive(eq.split_flags + slot, nparts, &split_word, tid)) continue;  // a later part finishes the tile
 #pragma unroll
             for (int db = 0; db < DB; db++)
 #pragma unroll
                 for (int i = 0; i < 16; i++) dqT[db][i] = 0.f;
             for (int p = 0; p < nparts; p++)
-                split_sum<DB>(pq.split_scratch + (int64_t)(slot + p) * kPartialBytes, dqT, 1.0f, tid);
+                split_sum<DB>(eq.split_scratch + (int64_t)(slot + p) * kPartialBytes, dqT, 1.0f, tid);
         }
         if (wq_lo >= s) continue;
         char *const stage = smem + (ntiles & 1) * 2 * TILE + wave * (32 * L::ROWB);  // the tile buffer the last step did not use (see the forward kernel)
-        if (a.grad_f32) {
-            float *const rows = (float *)a.dq + (tok0 + wq_lo) * a.dq_st + (int64_t)h * a.dq_sh;
+        if (e.grad_f32) {
+            float *const rows = (float *)e.dq + (tok0 + wq_lo) * e.dq_st + (int64_t)h * e.dq_sh;
             RowsF32<DB> f;
-            if (SHARD && (a.grad_f32 & 2))  // added to the partial sum the rows hold
-                f.add(stage, rows, a.dq_st, min(32, s - wq_lo), dqT, a.scale, lane);
+            if (SHARD && (e.grad_f32 & 2))  // added to the partial sum the rows hold
+                f.add(stage, rows, e.dq_st, min(32, s - wq_lo), dqT, e.scale, lane);
             else
-                f.store(stage, rows, a.dq_st, min(32, s - wq_lo), dqT, a.scale, lane);
+                f.store(stage, rows, e.dq_st, min(32, s - wq_lo), dqT, e.scale, lane);
         } else {
             store_rowT_bf16_lds<DB>(stage,
-                                    (uint16_t *)a.dq + (tok0 + wq_lo) * a.dq_st + (int64_t)h * a.dq_sh, a.dq_st,
-                                    min(32, s - wq_lo), dqT, a.scale, lane);
+                                    (uint16_t *)e.dq + (tok0 + wq_lo) * e.dq_st + (int64_t)h * e.dq_sh, e.dq_st,
+                                    min(32, s - wq_lo), dqT, e.scale, lane);
         }
         // deal.advance() holds the barrier after which the LDS buffers are reused by the next item
     }
@@ -621,8 +632,9 @@ __device__ __forceinline__ void dq_pass(const AttnArgs &a, const PassQueues &pq,
 }
 
 template <int D, bool SHARD>
-__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(const AttnArgs a)
+__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(const AttnArgs)
 {
+    KernArgs &a = kernel_args();
     __shared__ __attribute__((aligned(1024))) char smem[dq_lds<D>()];
     __shared__ int deal_word, split_word;
     dq_pass<D, SHARD>(a, a.pq, 0, smem, deal_word, split_word);
@@ -634,32 +646,32 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
 // memory trips and short steps run side by side instead of one after the other; the price is that the dK/dV pass reads
 // O as well.  Forward and backward, two launches -> one: 635 tokens, 1 head 29.6 -> 22.2 us; 808 tokens, 4 heads 42.8 -> 31.7 us;
 // 1 141 tokens, 16 heads on 2 94 -> 76 us; 5 630 tokens, 2 heads 45.0 -> 38.8 us.
-// PER_CU: with D = 128 the rows of O and dO that wait for a step do not fit beside the rest in half the register file (35
-// spills).  A launch of at most one workgroup per compute unit takes the kernel that has all of it (808 tokens, 4 heads:
+// PER_CU: with D = 128 the rows of O and dO that wait for a step do not fit beside the rest in half the register file (8
+// to 11 spills).  A launch of at most one workgroup per compute unit takes the kernel that has all of it (808 tokens, 4 heads:
 // 31.7 against 34.3 us), a larger one the kernel that two workgroups can share a compute unit with (5 630 tokens, 2 heads:
 // 38.8 against 43.4 us).
 template <int D, bool SHARD, int PER_CU>
-__global__ __launch_bounds__(kThreads, PER_CU) void attn_bwd_both_kernel(const AttnArgs a)
+__global__ __launch_bounds__(kThreads, PER_CU) void attn_bwd_both_kernel(const AttnArgs)
 {
+    KernArgs &a = kernel_args();
     constexpr int LDS = dkv_lds<D>() > dq_lds<D>() ? dkv_lds<D>() : dq_lds<D>();
     __shared__ __attribute__((aligned(1024))) char smem[LDS];
     __shared__ int deal_word, split_word;
-    if ((int)blockIdx.x >= a.dq_wg)
+    if (workgroup_id() >= a.dq_wg)
         dq_pass<D, SHARD>(a, a.dq_pq, a.dq_wg, smem, deal_word, split_word);
-    else if ((int)blockIdx.x < a.dkv_items)
+    else if (workgroup_id() < a.dkv_items)
         dkv_pass<D, SHARD, true>(a, a.pq, 0, smem, deal_word, split_word);
 }
 
 template <bool SHARD>
 void start_both(const AttnArgs &a, int D, int grid, hipStream_t s)
 {
-    auto start = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, s, a); };
     if (D == 64)
-        start(attn_bwd_both_kernel<64, SHARD, 2>);
+        launch(attn_bwd_both_kernel<64, SHARD, 2>, a, grid, s);
     else if (a.per_cu == 1)
-        start(attn_bwd_both_kernel<128, SHARD, 1>);
+        launch(attn_bwd_both_kernel<128, SHARD, 1>, a, grid, s);
     else
-        start(attn_bwd_both_kernel<128, SHARD, 2>);
+        launch(attn_bwd_both_kernel<128, SHARD, 2>, a, grid, s);
 }
 
 }  // namespace
@@ -669,18 +681,18 @@ hipError_t launch_attn_bwd_dkv(const AttnArgs &a, int D, int grid, hipStream_t s
     if (a.dq_wg)
         start_both<false>(a, D, grid, s);
     else if (D == 128)
-        hipLaunchKernelGGL((attn_bwd_dkv_kernel<128, false>), dim3(grid), dim3(kThreads), 0, s, a);
+        launch(attn_bwd_dkv_kernel<128, false>, a, grid, s);
     else
-        hipLaunchKernelGGL((attn_bwd_dkv_kernel<64, false>), dim3(grid), dim3(kThreads), 0, s, a);
+        launch(attn_bwd_dkv_kernel<64, false>, a, grid, s);
     return hipGetLastError();
 }
 
 hipError_t launch_attn_bwd_dq(const AttnArgs &a, int D, int grid, hipStream_t s)
 {
     if (D == 128)
-        hipLaunchKernelGGL((attn_bwd_dq_kernel<128, false>), dim3(grid), dim3(kThreads), 0, s, a);
+        launch(attn_bwd_dq_kernel<128, false>, a, grid, s);
     else
-        hipLaunchKernelGGL((attn_bwd_dq_kernel<64, false>), dim3(grid), dim3(kThreads), 0, s, a);
+        launch(attn_bwd_dq_kernel<64, false>, a, grid, s);
     return hipGetLastError();
 }
 
@@ -689,18 +701,18 @@ hipError_t launch_attn_bwd_dkv_kvshard(const AttnArgs &a, int D, int grid, hipSt
     if (a.dq_wg)
         start_both<true>(a, D, grid, s);
     else if (D == 128)
-        hipLaunchKernelGGL((attn_bwd_dkv_kernel<128, true>), dim3(grid), dim3(kThreads), 0, s, a);
+        launch(attn_bwd_dkv_kernel<128, true>, a, grid, s);
     else
-        hipLaunchKernelGGL((attn_bwd_dkv_kernel<64, true>), dim3(grid), dim3(kThreads), 0, s, a);
+        launch(attn_bwd_dkv_kernel<64, true>, a, grid, s);
     return hipGetLastError();
 }
 
 hipError_t launch_attn_bwd_dq_kvshard(const AttnArgs &a, int D, int grid, hipStream_t s)
 {
     if (D == 128)
-        hipLaunchKernelGGL((attn_bwd_dq_kernel<128, true>), dim3(grid), dim3(kThreads), 0, s, a);
+        launch(attn_bwd_dq_kernel<128, true>, a, grid, s);
     else
-        hipLaunchKernelGGL((attn_bwd_dq_kernel<64, true>), dim3(grid), dim3(kThreads), 0, s, a);
+        launch(attn_bwd_dq_kernel<64, true>, a, grid, s);
     return hipGetLastError();
 }
 

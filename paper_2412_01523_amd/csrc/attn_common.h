@@ -24,6 +24,50 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c)
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// (Workgroup and thread numbers come from the builtins: HIP's threadIdx and blockIdx are functions of the device library, which these
+// files' -mno-amdgpu-ieee keeps from being inlined.)
+__device__ __forceinline__ int thread_id() { return __builtin_amdgcn_workitem_id_x(); }
+__device__ __forceinline__ int workgroup_id() { return __builtin_amdgcn_workgroup_id_x(); }
+
+// A kernel's arguments where the launch left them.  Taken as an ordinary parameter they are all loaded when the kernel starts, and
+// the dozens of scalars that only an item's first and last instructions need are kept for its whole life, most of them
+// spilled into lanes of vector registers (78 to 139 in the D = 128 kernels, 14 to 60 now).  Here a member is a scalar load where it is
+// used, and fresh() makes the compiler forget what it has loaded so far.  What an item does once is bound by the instructions it issues: a
+// wavefront has its SIMD's issue slots to itself for most of them.  With this, divisions by the pieces of a row that are shifts, and
+// epilogues through buffer stores, the start of a dK/dV item fell from 399 to 241 instructions and no forward kernel spills a
+// vector register; forward and backward, before and after: 436 tokens, 4 heads 18.3 -> 16.1 us; 49 152 tokens in short sequences, 8 heads
+// 534 -> 517 us; one device's ring pass of a 64K-token batch over four devices 1 426 -> 1 372 us; 16 384 tokens of prompts, forward
+// alone 165 -> 159 us; long sequences the same.
+typedef const __attribute__((address_space(4))) AttnArgs KernArgs;
+typedef const __attribute__((address_space(4))) PassQueues KernQueues;
+// The segment is in host memory: every line of it is asked for at once when the kernel starts, or each would cost its own trip
+// where it is first needed.
+__device__ __forceinline__ KernArgs &kernel_args()
+{
+    typedef const __attribute__((address_space(4))) uint32_t word;
+    KernArgs *p = (KernArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    constexpr int LINES = (sizeof(AttnArgs) + 63) / 64;
+    uint32_t first[LINES];
+#pragma unroll
+    for (int i = 0; i < LINES; i++) first[i] = ((word *)p)[i * 16];
+#pragma unroll
+    for (int i = 0; i < LINES; i++) asm volatile("" ::"s"(first[i]));
+    return *p;
+}
+inline void launch(void (*kernel)(const AttnArgs), const AttnArgs &a, int grid, hipStream_t s)
+{
+    AttnArgs with_grid = a;
+    with_grid.grid = grid;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, s, with_grid);
+}
+template <class T>
+__device__ __forceinline__ T &fresh(T &a)
+{
+    T *p = &a;
+    asm volatile("" : "+s"(p));
+    return *p;
+}
+
 union Frag8 {
     bf16x8 v;
     u32x4 u;
@@ -125,13 +169,13 @@ __device__ __forceinline__ void load_tile_async(char *tile, const uint16_t *g, i
     typedef LdsTile<D> L;
     constexpr int N = ROWS * L::CH / kThreads;
     static_assert(N >= 1 && ROWS * L::CH % kThreads == 0, "tile must split evenly over the workgroup");
+    static_assert((kThreads / L::CH) % 16 == 0, "rows per pass must be a multiple of the swizzle period");
+    const int row0 = first + (wave * 64 + lane) / L::CH;  // (the piece's column is the same in every pass)
+    const uint16_t *col = g + ((lane % L::CH) ^ L::sw(row0 - first)) * 8;
 #pragma unroll
     for (int n = 0; n < N; n++) {
-        const int pos = n * kThreads + wave * 64 + lane;
-        const int row = pos / L::CH;
-        const int c = (pos % L::CH) ^ L::sw(row);
-        const int grow = min(first + row, last_valid);
-        global_to_lds16(g + (int64_t)grow * stride + c * 8, tile + (n * kThreads + wave * 64) * 16);
+        const int grow = min(row0 + n * (kThreads / L::CH), last_valid);
+        global_to_lds16(col + (int64_t)grow * stride, tile + (n * kThreads + wave * 64) * 16);
     }
 }
 
@@ -143,9 +187,8 @@ template <int D>
 __device__ __forceinline__ uint32_t tile_goff(int32_t stride, int wave, int lane)
 {
     typedef LdsTile<D> L;
-    const int pos = wave * 64 + lane;
-    const int row = pos / L::CH;
-    const int c = (pos % L::CH) ^ L::sw(row);
+    const int row = (wave * 64 + lane) / L::CH;
+    const int c = (lane % L::CH) ^ L::sw(row);
     return (uint32_t)(row * (uint32_t)stride * 2u + c * 16);
 }
 template <int D, int ROWS>
@@ -274,13 +317,13 @@ struct RowBlock {
     // tile read patterns itself.
     __device__ __forceinline__ void stage(char *tile, int row0, int lane)
     {
-        char *region = tile + row0 * L::ROWB;
+        // piece n lies n * RP rows below piece 0, in the same column; the swizzle of RP * n + r is that of RP * n
+        // exclusive-or that of r (r < RP, a power of two)
+        constexpr int RP = 64 / L::CH;
+        char *region = tile + row0 * L::ROWB + (lane / L::CH) * L::ROWB;
+        const int at = ((lane % L::CH) ^ L::sw(lane / L::CH)) << 4;
 #pragma unroll
-        for (int n = 0; n < N; n++) {
-            const int pos = n * 64 + lane;
-            const int row = pos / L::CH;
-            *(u32x4 *)(region + row * L::ROWB + (((pos % L::CH) ^ L::sw(row)) << 4)) = raw[n];
-        }
+        for (int n = 0; n < N; n++) *(u32x4 *)(region + n * RP * L::ROWB + (at ^ (L::sw(n * RP) << 4))) = raw[n];
     }
 };
 
@@ -391,6 +434,7 @@ struct RowsF32 {
     __device__ __forceinline__ void store(char *stage, float *g, int64_t stride, int nrows, const f32x16 (&acc)[DB], float mul, int lane)
     {
         asm volatile("" : "+v"(lane));  // (address arithmetic stays in the epilogue)
+        lane &= 63;
         each(stage, nrows, acc, mul, lane, [&](int, int, int row, int col, const f32x4 &v) {
             __builtin_nontemporal_store(v, (f32x4 *)(g + (int64_t)row * stride + col));
         });
@@ -399,6 +443,7 @@ struct RowsF32 {
     __device__ __forceinline__ void add(char *stage, float *g, int64_t stride, int nrows, const f32x16 (&acc)[DB], float mul, int lane)
     {
         asm volatile("" : "+v"(lane));
+        lane &= 63;
         load(g, stride, nrows, lane);
         each(stage, nrows, acc, mul, lane, [&](int half, int n, int row, int col, const f32x4 &v) {
             *(f32x4 *)(g + (int64_t)row * stride + col) = old[half][n] + v;
@@ -412,18 +457,23 @@ struct RowsF32 {
 //   acc      NB blocks; lane l holds token row l % 32, head-dim elements db*32 + 8*i4 + 4*hl + e
 //   stage    wave-private LDS, 32 rows x ROWB bytes (ROWB = NB*64); chunk c of row r is kept at
 //            position c ^ (r & (CH-1)) so that the column-wise writes spread over the banks
-//   g        address of the first token row (this wavefront's row 0) + first head-dim element
-//   stride   token stride in elements;  nrows  rows of this wavefront inside the sequence
+//   g        address of the first token row (this wavefront's row 0) + first head-dim element (wave-uniform)
+//   stride   token stride in elements;  nrows  rows of this wavefront inside the sequence (at least 1)
 template <int NB>
-__device__ __forceinline__ void store_rowT_bf16_lds(char *stage, uint16_t *g, int64_t stride, int nrows,
+__device__ __forceinline__ void store_rowT_bf16_lds(char *stage, uint16_t *g, int32_t stride, int nrows,
                                                     const f32x16 (&acc)[NB], float mul, int lane)
 {
     constexpr int ROWB = NB * 64;   // bytes per staged row
     constexpr int CH = ROWB / 16;   // 16-byte chunks per row
+    constexpr int RP = 64 / CH;     // rows per store instruction
+    constexpr int N = 32 / RP;      // store instructions
     // opaque copy: keeps the address arithmetic below here, inside the epilogue, instead of being
     // hoisted to the top of the kernel where its results would occupy registers for good
     asm volatile("" : "+v"(lane));
+    lane &= 63;
     const int r = lane & 31, hl = lane >> 5;
+    char *const to = stage + r * ROWB + 8 * hl;
+    const int x = (r & (CH - 1)) << 4;
 #pragma unroll
     for (int db = 0; db < NB; db++)
 #pragma unroll
@@ -431,18 +481,22 @@ __device__ __forceinline__ void store_rowT_bf16_lds(char *stage, uint16_t *g, in
             u32x2 w;
             w[0] = pack_bf16x2(acc[db][4 * i4] * mul, acc[db][4 * i4 + 1] * mul);
             w[1] = pack_bf16x2(acc[db][4 * i4 + 2] * mul, acc[db][4 * i4 + 3] * mul);
-            const int c = (4 * db + i4) ^ (r & (CH - 1));
-            *(u32x2 *)(stage + r * ROWB + c * 16 + 8 * hl) = w;
+            *(u32x2 *)(to + (((4 * db + i4) << 4) ^ x)) = w;
         }
-    // the wavefront reads back what it wrote: no barrier, just LDS ordering within the wave
+    // the wavefront reads back what it wrote: no barrier, just LDS ordering within the wave; every read in flight before the
+    // first store (these files are compiled in source order).  Buffer stores: the descriptor knows where the rows
+    // end, so rows past the sequence are dropped by the hardware and a piece costs no address arithmetic.
+    const uint32_t rowb = (uint32_t)stride * 2u;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(g, 0, (int)((nrows - 1) * rowb + ROWB), 0x00020000);
+    const char *const from = stage + (lane / CH) * ROWB;
+    const int y = ((lane % CH) ^ (lane / CH)) << 4;
+    u32x4 v[N];
 #pragma unroll
-    for (int n = 0; n < 32 * CH / 64; n++) {
-        const int pos = n * 64 + lane;
-        const int row = pos / CH;
-        const int c = (pos % CH) ^ (row & (CH - 1));
-        const u32x4 v = *(const u32x4 *)(stage + pos * 16);
-        if (row < nrows) __builtin_nontemporal_store(v, (u32x4 *)(g + (int64_t)row * stride + c * 8));
-    }
+    for (int n = 0; n < N; n++) v[n] = *(const u32x4 *)(from + n * RP * ROWB + (y ^ (((n * RP) & (CH - 1)) << 4)));
+    const uint32_t off = (uint32_t)(lane / CH) * rowb + (uint32_t)(lane % CH) * 16u;
+#pragma unroll
+    for (int n = 0; n < N; n++)
+        __builtin_amdgcn_raw_buffer_store_b128(v[n], rsrc, off, n * RP * rowb, 2 /* non-temporal */);
 }
 
 // Descriptor of item `idx` as wave-uniform (scalar) values.  The index is uniform, but the load
@@ -570,11 +624,11 @@ struct ItemDealer {
     int32_t *counters;  // kCounterStride apart (a line of their own each: they are hammered from all
                         // compute dies at once): [q] tickets drawn beyond the static ones, [nq] workgroups that left
     int *slot;          // LDS word
-    int nq, q, wave, lane;
+    int nq, q, wave, lane, grid;
     int pending;        // wavefront 0, lane 0: ticket drawn ahead (offset from W of queue q)
     bool direct;        // one workgroup per item
 
-    __device__ __forceinline__ int wgs_of(int qq) const { return ((int)gridDim.x - qq + nq - 1) / nq; }
+    __device__ __forceinline__ int wgs_of(int qq) const { return (grid - qq + nq - 1) / nq; }
     __device__ __forceinline__ int draw(int qq)  // wavefront 0 only; waits for the answer
     {
         int tk = 0;
@@ -624,21 +678,22 @@ struct ItemDealer {
         const int v = *(volatile int *)slot;
         return __builtin_amdgcn_readfirstlane(v);
     }
-    __device__ __forceinline__ int first(const PassQueues &pq, int first_wg, int *lds_word, int wave_, int lane_)  // first_wg: the launch's first workgroup of this pass
+    __device__ __forceinline__ int first(KernQueues &pq, int grid_, int first_wg, int *lds_word, int wave_, int lane_)  // first_wg: the launch's first workgroup of this pass
     {
         direct = pq.direct != 0;
-        if (direct) return (int)blockIdx.x - first_wg;
+        if (direct) return workgroup_id() - first_wg;
         offsets = pq.offsets;
         counters = pq.counters;
         slot = lds_word;
         nq = pq.nq;
+        grid = grid_;
         wave = wave_;
         lane = lane_;
-        q = (int)(blockIdx.x % pq.nq);
+        q = workgroup_id() % pq.nq;
         pending = 0;
         int idx = -1;
         if (wave == 0) {
-            idx = offsets[q] + (int)(blockIdx.x / pq.nq);
+            idx = offsets[q] + workgroup_id() / pq.nq;
             if (idx >= offsets[q + 1]) idx = steal();
         }
         return publish(idx);
@@ -670,7 +725,7 @@ struct ItemDealer {
     {
         if (direct) return;
         if (wave == 0 && lane == 0) {
-            if (atomicAdd(counters + nq * kCounterStride, 1) == (int)gridDim.x - 1)
+            if (atomicAdd(counters + nq * kCounterStride, 1) == grid - 1)
                 for (int i = 0; i <= nq; i++) __hip_atomic_store(counters + i * kCounterStride, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }

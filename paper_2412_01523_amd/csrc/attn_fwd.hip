@@ -81,7 +81,7 @@ __device__ __forceinline__ bool find_item(const int32_t *cu, int B, int T, int h
 // FIND = true is the variant without a list of items: workgroup w finds the w-th (query tile, head) of the batch in the
 // lengths and leaves when it is done.
 template <int D, bool SHARD, bool FIND>
-__global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs a)
+__global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs)
 {
     typedef LdsTile<D> L;
     constexpr int KS = D / 16;                  // k steps of the score product
@@ -93,23 +93,25 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs a)
     // [K buffer 0 | K buffer 1 | V buffer 0 | V buffer 1]
     __shared__ __attribute__((aligned(1024))) char smem[4 * TILE];
 
-    const int tid = threadIdx.x;
+    const int tid = thread_id();
     const int lane0 = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     LaneOffsets<D> lo;
     lo.init(lane0);
     __shared__ int deal_word, split_word;
     ItemDealer deal;
+    KernArgs &args = kernel_args();
 
     flexsp_item found;
     int item;
     if constexpr (FIND) {
         deal.direct = true;
-        item = find_item(a.cu, a.B, a.T, a.Hq, a.causal, (int)blockIdx.x, lane0, found) ? 0 : -1;
+        item = find_item(args.cu, args.B, args.T, args.Hq, args.causal, workgroup_id(), lane0, found) ? 0 : -1;
     } else {
-        item = deal.first(a.pq, 0, &deal_word, wave, lane0);
+        item = deal.first(args.pq, args.grid, 0, &deal_word, wave, lane0);
     }
     for (; item >= 0; item = deal.advance()) {
+        KernArgs &a = fresh(args);
         // s: query rows of the sequence; sk: its keys; tok0 / ktok0: their first rows in q / k, v
         int s, sk, shift, h, q0;
         int64_t tok0, ktok0;
@@ -132,6 +134,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs a)
         // the item instead of being hoisted out of this loop into long-lived registers
         int lane = lane0;
         asm volatile("" : "+v"(lane));
+        lane &= 63;  // (its range is known again: divisions by the pieces of a row are shifts)
         const int r = lane & 31, hl = lane >> 5;
         const int g = h / a.G;
         // keys this item needs
@@ -238,7 +241,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs a)
         uint32_t pk[2][8];  // P of block c (bf16 pairs) in pk[c & 1]
         // Blocks are computed under conditions, so to the compiler the arrays' contents pass from item to item, 48 registers
         // of them, which SHARD stored and loaded around every item: 128 spilled vector registers with D = 128.  An item
-        // that defines them itself, as anything, leaves 29.  Shard forwards of a 64K-token batch over four devices, plain and folding,
+        // that defines them itself, as anything, left 29 of them (none by now).  Shard forwards of a 64K-token batch over four devices, plain and folding,
         // 346 -> 262 and 498 -> 310 us; of 93-token sequences over eight, 3 655 -> 1 605 and 5 050 -> 2 111 us.
 #pragma unroll
         for (int j = 0; j < 2; j++) {
@@ -526,22 +529,23 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs a)
         }
 
         // ---- epilogue: normalise, write O (bf16) and LSE (natural log)
+        KernArgs &e = fresh(args);
         float l_tot = halves_sum(l_run);
         {
             if (nparts > 1) {
                 // hand over (O unnormalised, row maximum, row sum); the part that arrives last merges
                 // all parts in part order: O = sum_p 2^((m_p - M) scale_l2) O_p, likewise the row sums
                 const int tid_ = wave * 64 + lane;  // (recomputed: keeping threadIdx alive through the tile loop costs a register)
-                char *rec = a.pq.split_scratch + (int64_t)(slot + part) * kPartialBytes;
+                char *rec = e.pq.split_scratch + (int64_t)(slot + part) * kPartialBytes;
                 split_store<DB>(rec, oacc, tid_);
                 split_put((float *)(rec + 64 * kThreads * 4) + 2 * tid_, m_run);
                 split_put((float *)(rec + 64 * kThreads * 4) + 2 * tid_ + 1, l_tot);
-                if (!split_arrive(a.pq.split_flags + slot, nparts, &split_word, tid_)) continue;
+                if (!split_arrive(e.pq.split_flags + slot, nparts, &split_word, tid_)) continue;
                 // all parts' row statistics first (one trip to memory for the lot), then the records in turn
                 float mp[kMaxParts], lp[kMaxParts];
 #pragma unroll
                 for (int p = 0; p < kMaxParts; p++) {
-                    const float *st = (const float *)(a.pq.split_scratch + (int64_t)(slot + min(p, nparts - 1)) * kPartialBytes +
+                    const float *st = (const float *)(e.pq.split_scratch + (int64_t)(slot + min(p, nparts - 1)) * kPartialBytes +
                                                       64 * kThreads * 4) + 2 * tid_;
                     mp[p] = split_get(st);
                     lp[p] = split_get(st + 1);
@@ -557,8 +561,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs a)
 #pragma unroll
                 for (int p = 0; p < kMaxParts; p++) {
                     if (p < nparts) {
-                        const float w = mp[p] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mp[p] - M) * a.scale_l2);
-                        split_sum<DB>(a.pq.split_scratch + (int64_t)(slot + p) * kPartialBytes, oacc, w, tid_);
+                        const float w = mp[p] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mp[p] - M) * e.scale_l2);
+                        split_sum<DB>(e.pq.split_scratch + (int64_t)(slot + p) * kPartialBytes, oacc, w, tid_);
                         l_tot += w * lp[p];
                     }
                 }
@@ -566,21 +570,22 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs a)
             }
         }
         if constexpr (SHARD) {
-            if (a.dq) {
+            if (e.dq) {
                 // Fold into the fp32 running result of a ring instead of writing this shard's own O and LSE:
                 // (o_acc, lse_acc) <- merge((o_acc, lse_acc), (O, LSE)), the row's two half-wave lanes each
                 // taking their head-dim elements of the row; a part that counts nothing is silenced even
                 // if it holds rubbish (a running result is started with lse_acc = -inf over anything).
                 if (wq_lo < s) {
                     const int nrows = min(32, s - wq_lo);
-                    float *const rows = (float *)a.dq + (tok0 + wq_lo) * a.dq_st + (int64_t)h * a.dq_sh;
+                    float *const rows = (float *)e.dq + (tok0 + wq_lo) * e.dq_st + (int64_t)h * e.dq_sh;
                     RowsF32<DB> acc32;
                     int lane_ = lane;
                     asm volatile("" : "+v"(lane_));  // (address arithmetic stays in the epilogue)
-                    acc32.load(rows, a.dq_st, nrows, lane_);
-                    const int64_t li = (int64_t)h * a.T + tok0 + min(qrow, s - 1);
-                    const float la = a.delta_out[li];
-                    const float lb = l_tot > 0.f ? m_run * a.scale + __logf(l_tot) : -INFINITY;
+                    lane_ &= 63;
+                    acc32.load(rows, e.dq_st, nrows, lane_);
+                    const int64_t li = (int64_t)h * e.T + tok0 + min(qrow, s - 1);
+                    const float la = e.delta_out[li];
+                    const float lb = l_tot > 0.f ? m_run * e.scale + __logf(l_tot) : -INFINITY;
                     const float m = fmaxf(la, lb);
                     float wa = 0.f, wb = 0.f, lse = -INFINITY;
                     if (m > -INFINITY) {
@@ -590,29 +595,29 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs a)
                         wb = l_tot > 0.f ? eb * inv / l_tot : 0.f;  // (with the row's normalisation)
                         lse = m + __logf(ea + eb);
                     }
-                    uint16_t *const o16 = a.out_o ? a.out_o + (tok0 + wq_lo) * a.o_st + (int64_t)h * a.o_sh : nullptr;  // the merged rows rounded to bf16, if asked for
+                    uint16_t *const o16 = e.out_o ? e.out_o + (tok0 + wq_lo) * e.o_st + (int64_t)h * e.o_sh : nullptr;  // the merged rows rounded to bf16, if asked for
                     acc32.each(smem + wave * (32 * L::ROWB), 32, oacc, wb, lane_, [&](int half, int n, int row, int col, f32x4 w) {
                         const float wr = __shfl(wa, row);  // the weight of the piece's row
                         const f32x4 o = acc32.old[half][n];
 #pragma unroll
-                        for (int e = 0; e < 4; e++) w[e] += wr > 0.f ? wr * o[e] : 0.f;
+                        for (int i = 0; i < 4; i++) w[i] += wr > 0.f ? wr * o[i] : 0.f;
                         if (row < nrows) {
-                            *(f32x4 *)(rows + (int64_t)row * a.dq_st + col) = w;
-                            if (o16) *(u32x2 *)(o16 + (int64_t)row * a.o_st + col) = u32x2{pack_bf16x2(w[0], w[1]), pack_bf16x2(w[2], w[3])};
+                            *(f32x4 *)(rows + (int64_t)row * e.dq_st + col) = w;
+                            if (o16) *(u32x2 *)(o16 + (int64_t)row * e.o_st + col) = u32x2{pack_bf16x2(w[0], w[1]), pack_bf16x2(w[2], w[3])};
                         }
                     });
-                    if (qrow < s && hl == 0) a.delta_out[li] = lse;  // (after both lanes of the row have read it: one wavefront)
+                    if (qrow < s && hl == 0) e.delta_out[li] = lse;  // (after both lanes of the row have read it: one wavefront)
                 }
                 continue;
             }
         }
-        if (qrow < s && hl == 0) a.lse_out[(int64_t)h * a.T + tok0 + qrow] = m_run * a.scale + __logf(l_tot);
+        if (qrow < s && hl == 0) e.lse_out[(int64_t)h * e.T + tok0 + qrow] = m_run * e.scale + __logf(l_tot);
         // O is staged through the K buffers without a barrier: no wavefront reads a K tile after the
         // barrier of the last window (the scores of the last blocks were issued in the window before),
         // and this wavefront is past that barrier, so every wavefront has reached it
         if (wq_lo < s)
-            store_rowT_bf16_lds<DB>(smem + wave * (32 * L::ROWB), a.out_o + (tok0 + wq_lo) * a.o_st + (int64_t)h * a.o_sh,
-                                    a.o_st, min(32, s - wq_lo), oacc,
+            store_rowT_bf16_lds<DB>(smem + wave * (32 * L::ROWB), e.out_o + (tok0 + wq_lo) * e.o_st + (int64_t)h * e.o_sh,
+                                    e.o_st, min(32, s - wq_lo), oacc,
                                     (SHARD && !(l_tot > 0.f)) ? 0.f : 1.0f / l_tot, lane);
         // deal.advance() holds the barrier after which the LDS buffers are reused by the next item
     }
@@ -624,22 +629,22 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs a)
 hipError_t launch_attn_fwd(const AttnArgs &a, int D, int grid, hipStream_t s)
 {
     if (D == 128 && a.cu)
-        hipLaunchKernelGGL((attn_fwd_kernel<128, false, true>), dim3(grid), dim3(kThreads), 0, s, a);
+        launch(attn_fwd_kernel<128, false, true>, a, grid, s);
     else if (a.cu)
-        hipLaunchKernelGGL((attn_fwd_kernel<64, false, true>), dim3(grid), dim3(kThreads), 0, s, a);
+        launch(attn_fwd_kernel<64, false, true>, a, grid, s);
     else if (D == 128)
-        hipLaunchKernelGGL((attn_fwd_kernel<128, false, false>), dim3(grid), dim3(kThreads), 0, s, a);
+        launch(attn_fwd_kernel<128, false, false>, a, grid, s);
     else
-        hipLaunchKernelGGL((attn_fwd_kernel<64, false, false>), dim3(grid), dim3(kThreads), 0, s, a);
+        launch(attn_fwd_kernel<64, false, false>, a, grid, s);
     return hipGetLastError();
 }
 
 hipError_t launch_attn_fwd_kvshard(const AttnArgs &a, int D, int grid, hipStream_t s)
 {
     if (D == 128)
-        hipLaunchKernelGGL((attn_fwd_kernel<128, true, false>), dim3(grid), dim3(kThreads), 0, s, a);
+        launch(attn_fwd_kernel<128, true, false>, a, grid, s);
     else
-        hipLaunchKernelGGL((attn_fwd_kernel<64, true, false>), dim3(grid), dim3(kThreads), 0, s, a);
+        launch(attn_fwd_kernel<64, true, false>, a, grid, s);
     return hipGetLastError();
 }
 

@@ -80,6 +80,7 @@ struct AttnArgs {
     // dQ pass's queues, its first workgroup (0: the dK/dV pass alone), the dK/dV pass's items, workgroups per compute unit
     PassQueues dq_pq;
     int32_t dq_wg, dkv_items, per_cu;
+    int32_t grid;  // workgroups of the launch (filled in by the launchers)
     // a forward without a list of items: every workgroup finds its own in the lengths (device; null: pq holds a list)
     const int32_t *cu;
     int32_t B;
