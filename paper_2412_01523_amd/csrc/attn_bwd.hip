@@ -10,6 +10,7 @@
 //   dK/dV   one work item = 64 keys of one (sequence, kv head); loops over the query heads of
 //           the group and over the query rows that see those keys; dK^T, dV^T stay in
 //           registers, so grouped-query heads are summed without a reduction pass.
+// With D = 64 and long enough walks a dK/dV item is 128 keys (attn_bwd_dkv_wide_kernel).
 // Small backwards run both as one launch (attn_bwd_both_kernel); the dK/dV pass then forms delta itself.
 // The 32x32 accumulator keeps one COLUMN per lane, and only its ROW index can be contracted
 // in a following MFMA.  Hence dK/dV computes S = Q K^T (rows = queries) and dQ computes
@@ -392,6 +393,329 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dkv_kernel
     dkv_pass<D, SHARD, false>(a, a.pq, 0, smem, deal_word, split_word);
 }
 
+// ------------------------------------------------------------------------------ dK / dV, 128 keys
+// The D = 64 kernel for all but short walks over the queries.  One work item = 128 keys of one (sequence, kv head).  With D = 64 the
+// accumulators of 32 keys for both dK and dV, their K and V fragments and a block's S and dP fit 256 registers, so a wavefront
+// does its 32 keys alone: nothing is swapped between wavefronts, a step has one barrier instead of two, each tile of Q and dO serves
+// twice the keys, and with four step buffers a tile is asked for two steps before it is read.  A wavefront walks the query rows in
+// blocks of 32 as the forward does: the matrix instructions of block c - 1's sums carry the arithmetic of block c between them, then
+// come S and dP of block c + 1.
+// The kernel of 64 keys spends its time waiting (no unit busy for more than 43 % of the cycles: its waves stand at the two
+// barriers and for LDS).  Here the matrix unit is busy for 50 %, other waits fall from 27 to 21 % of the waves' time: 30 011 tokens, 12
+// heads on 4, not causal 532 -> 465 us (counters on); forward and backward of 8 heads, 64 keys -> 128: 65 536 tokens
+// causal in sequences of 16 384 4 710 -> 4 465 us, 4 096 1 324 -> 1 251, 1 024 451 -> 443, 512 299 -> 297, 256 241 -> 244; 32 768
+// tokens not causal 4 096 1 228 -> 1 149, 1 024 351 -> 327, 256 144 -> 136.  Same bits, the sums are formed in the same order.
+// (D = 128 needs 390 registers, one wavefront per SIMD; two 64-key workgroups are as fast or faster.)
+__global__ __launch_bounds__(kThreads, 2) void attn_bwd_dkv_wide_kernel(const AttnArgs)
+{
+    constexpr int D = 64;
+    typedef LdsTile<D> L;
+    constexpr int KS = D / 16, DB = D / 32, BQ = kDkvBq;
+    constexpr int QTILE = BQ * L::ROWB;
+    constexpr int STEP = 2 * QTILE + 512;  // Q | dO | lse2[64] delta[64]
+    constexpr int NB = 4;                  // step buffers: two in use, two on their way
+    constexpr int NCP = 2 * BQ * L::CH / kThreads;  // copy instructions of a wavefront per step, the row statistics apart
+    static_assert(2 * DB * 16 * kThreads * 4 <= kPartialBytes, "a part's sums are one record");
+    __shared__ __attribute__((aligned(1024))) char smem[NB * STEP];
+    __shared__ int deal_word, split_word;
+    KernArgs &args = kernel_args();
+    KernQueues &queues = args.pq;
+
+    const int tid = thread_id();
+    const int lane0 = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    LaneOffsets<D> lo0;
+    lo0.init(lane0);
+    ItemDealer deal;
+
+    for (int item = deal.first(queues, args.grid, 0, &deal_word, wave, lane0); item >= 0; item = deal.advance()) {
+        KernArgs &a = fresh(args);
+        const flexsp_item it = load_item(a.pq.items, item);
+        const int s = it.seq_len, g = it.head, kv0 = it.tile * kDkvWideBk;
+        const int64_t tok0 = it.seq_start;
+        const int qfirst = a.causal ? kv0 : 0;
+        const int nsteps = (s - qfirst + BQ - 1) / BQ;
+        const int first = it.step_begin, n = it.step_end - first;
+        const int nparts = it.parts & 0xffff, part = it.parts >> 16, slot = it.slot;
+        int lane = lane0;
+        asm volatile("" : "+v"(lane));
+        lane &= 63;
+        const int r = lane & 31, hl = lane >> 5;
+        const int wk_lo = kv0 + wave * 32;  // the wavefront's first key
+        const int kvrow = wk_lo + r;        // this lane's key (column of S)
+        const bool causal = a.causal != 0;
+        const float scale_l2 = a.scale_l2;
+        if (n < kLateTicketSteps) deal.prefetch();
+        const int q_end = qfirst + nsteps * BQ;
+        const uint32_t goffq = tile_goff<D>(a.q_st, wave, lane), goffg = tile_goff<D>(a.do_st, wave, lane);
+        int h_f = g * a.G + first / nsteps, q_f = qfirst + (first % nsteps) * BQ;  // the step fetched next
+        int buf_f = 0, left_f = n;
+        int q_t = q_f;  // the step whose tile the window accumulates from
+        auto next_q = [&](int q) { return q + BQ >= q_end ? qfirst : q + BQ; };
+        auto fetch = [&]() {  // asks for the next step's tiles, if there is one
+            if (left_f <= 0) return;
+            char *base = smem + buf_f * STEP;
+            const uint16_t *qb = a.q + tok0 * a.q_st + (int64_t)h_f * a.q_sh;
+            const uint16_t *gb = a.dO + tok0 * a.do_st + (int64_t)h_f * a.do_sh;
+            if (wave < 2) {  // wavefront 0: lse2 of the 64 rows, wavefront 1: delta
+                const float *src = (wave ? a.delta_in : a.lse_in) + (int64_t)h_f * a.T + tok0 + min(q_f + lane, s - 1);
+                global_to_lds4(src, base + 2 * QTILE + wave * 256);
+            }
+            if (__builtin_expect(q_f + BQ <= s, 1)) {
+                load_tile_async_fast<D, BQ>(base, qb + (int64_t)q_f * a.q_st, a.q_st, goffq, wave);
+                load_tile_async_fast<D, BQ>(base + QTILE, gb + (int64_t)q_f * a.do_st, a.do_st, goffg, wave);
+            } else {
+                load_tile_async<D, BQ>(base, qb, a.q_st, q_f, s - 1, wave, lane);
+                load_tile_async<D, BQ>(base + QTILE, gb, a.do_st, q_f, s - 1, wave, lane);
+            }
+            left_f--;
+            buf_f = buf_f + 1 == NB ? 0 : buf_f + 1;
+            q_f += BQ;
+            if (q_f >= q_end) {
+                q_f = qfirst;
+                h_f++;
+            }
+        };
+        fetch();
+        // K and V fragments of the wavefront's keys, through its quarter of the last buffer, which is idle until window 0
+        bf16x8 kf[KS], vf[KS];
+        {
+            RowBlock<D> krows, vrows;
+            krows.load(a.k + tok0 * a.k_st + (int64_t)g * a.k_sh, a.k_st, wk_lo, s - 1, lane);
+            vrows.load(a.v + tok0 * a.v_st + (int64_t)g * a.v_sh, a.v_st, wk_lo, s - 1, lane);
+            char *region = smem + (NB - 1) * STEP + wave * (32 * L::ROWB);
+            krows.fragments(region, 0, lo0, kf, lane);
+            vrows.fragments(region, 0, lo0, vf, lane);
+            __builtin_amdgcn_s_waitcnt(0xC07F);
+        }
+        for (int i = 1; i < NB - 1; i++) fetch();
+        f32x16 accV[DB], accK[DB];
+#pragma unroll
+        for (int d = 0; d < DB; d++) accV[d] = accK[d] = f32x16{};
+        // block c = rows 32 * (c & 1) .. of step c / 2; S and dP - delta of the latest block in sa, pa, P and dS of block c in pp, dd[c & 1]
+        f32x16 sa, pa;
+        uint32_t pp[2][8], dd[2][8];
+        asm volatile("" : "=v"(sa), "=v"(pa));
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int i = 0; i < 8; i++) asm volatile("" : "=v"(pp[j][i]), "=v"(dd[j][i]));
+        // LDS addresses: in window t the scores read the tiles of step t + 1 (nat, st_n), the sums those of step t (tr, st_t)
+        int nat[KS], tr[DB][2], st_n = hl * 16, st_t = hl * 16;
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) nat[ks] = lo0.nat[ks];
+#pragma unroll
+        for (int db = 0; db < DB; db++) tr[db][0] = lo0.tr[db][0], tr[db][1] = lo0.tr[db][1];
+        auto empty = [&](int q) { return wk_lo >= s || q >= s || (causal && q + 31 < wk_lo); };
+        auto masked = [&](int q) { return (causal && q < wk_lo + 31) || q + 32 > s; };
+
+        auto scores = [&](int half) {
+#pragma unroll
+            for (int i4 = 0; i4 < 4; i4++) {
+                const f32x4 d4 = *(const f32x4 *)(smem + st_n + 2 * QTILE + 256 + half * 128 + 32 * i4);
+#pragma unroll
+                for (int e = 0; e < 4; e++) pa[4 * i4 + e] = d4[e];
+            }
+            constexpr int AH = kReadAhead, N = 2 * KS;
+            bf16x8 fr[N];
+            auto rd = [&](int i) { return lds_nat(smem, ((i & 1) ? QTILE : 0) + half * 32 * L::ROWB + nat[i >> 1]); };
+#pragma unroll
+            for (int i = 0; i < AH; i++) fr[i] = rd(i);
+#pragma unroll
+            for (int i = 0; i < N; i++) {
+                if (i + AH < N) fr[i + AH] = rd(i + AH);
+                if (i & 1)
+                    pa = mfma32(fr[i], vf[i >> 1], pa);
+                else
+                    sa = mfma32(fr[i], kf[i >> 1], i ? sa : f32x16{});
+            }
+        };
+        // q: the block's first row; stat: per-lane address of its step's row statistics
+        auto probs = [&](uint32_t (&p8)[8], uint32_t (&d8)[8], int q, int stat, int half) {
+            const bool mask = masked(q);
+#pragma unroll
+            for (int i4 = 0; i4 < 4; i4++) {
+                const f32x4 l4 = *(const f32x4 *)(smem + stat + 2 * QTILE + half * 128 + 32 * i4);
+                float p[4], ds[4];
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sa[4 * i4 + e], scale_l2, -l4[e]));
+                    if (mask) {
+                        const int qr = q + 8 * i4 + 4 * hl + e;
+                        p[e] = ((causal && qr < kvrow) || qr >= s) ? 0.f : p[e];
+                    }
+                    ds[e] = p[e] * pa[4 * i4 + e];
+                }
+                p8[2 * i4] = pack_bf16x2(p[0], p[1]);
+                p8[2 * i4 + 1] = pack_bf16x2(p[2], p[3]);
+                d8[2 * i4] = pack_bf16x2(ds[0], ds[1]);
+                d8[2 * i4 + 1] = pack_bf16x2(ds[2], ds[3]);
+            }
+        };
+        auto sums = [&](const uint32_t (&p8)[8], const uint32_t (&d8)[8], int half) {
+            constexpr int AH = kReadAhead, N = 4 * DB;
+            bf16x8 fr[N];
+            auto rd = [&](int i) {
+                const int k = i >> 1, at = ((i & 1) ? 0 : QTILE) + (half * 32 + (k / DB) * 16) * L::ROWB;
+                return lds_tr(smem, at + tr[k % DB][0], at + tr[k % DB][1]);
+            };
+#pragma unroll
+            for (int i = 0; i < AH; i++) fr[i] = rd(i);
+#pragma unroll
+            for (int i = 0; i < N; i++) {
+                if (i + AH < N) fr[i + AH] = rd(i + AH);
+                const int k = i >> 1, o = 4 * (k / DB);
+                Frag8 f;
+                if (i & 1) {
+                    f.u = u32x4{d8[o], d8[o + 1], d8[o + 2], d8[o + 3]};
+                    accK[k % DB] = mfma32(fr[i], f.v, accK[k % DB]);
+                } else {
+                    f.u = u32x4{p8[o], p8[o + 1], p8[o + 2], p8[o + 3]};
+                    accV[k % DB] = mfma32(fr[i], f.v, accV[k % DB]);
+                }
+            }
+        };
+        // sums of block c - 1 and, between their matrix instructions, the arithmetic of block c (its half CP of a tile; block c - 1 is the
+        // other half)
+        auto sums_probs = [&](auto cpc, int stat) {
+            constexpr int CP = decltype(cpc)::value;
+            constexpr int HALF = CP ? 0 : 1, AH = kReadAhead, N = 4 * DB;
+            const uint32_t(&p8)[8] = pp[CP ^ 1], (&d8)[8] = dd[CP ^ 1];
+            bf16x8 fr[N];
+            f32x4 l4[4];
+            auto rd = [&](int i) {
+                const int k = i >> 1, at = ((i & 1) ? 0 : QTILE) + (HALF * 32 + (k / DB) * 16) * L::ROWB;
+                return lds_tr(smem, at + tr[k % DB][0], at + tr[k % DB][1]);
+            };
+            l4[0] = *(const f32x4 *)(smem + stat + 2 * QTILE + CP * 128);
+#pragma unroll
+            for (int i = 0; i < AH; i++) fr[i] = rd(i);
+            float p0 = 0.f, d0 = 0.f;
+#pragma unroll
+            for (int i = 0; i < N; i++) {
+                if (i + AH < N) fr[i + AH] = rd(i + AH);
+                if (i * 4 % N == 0 && i * 4 / N < 3) l4[i * 4 / N + 1] = *(const f32x4 *)(smem + stat + 2 * QTILE + CP * 128 + 32 * (i * 4 / N + 1));
+                const int k = i >> 1, o = 4 * (k / DB);
+                Frag8 f;
+                if (i & 1) {
+                    f.u = u32x4{d8[o], d8[o + 1], d8[o + 2], d8[o + 3]};
+                    accK[k % DB] = mfma32(fr[i], f.v, accK[k % DB]);
+                } else {
+                    f.u = u32x4{p8[o], p8[o + 1], p8[o + 2], p8[o + 3]};
+                    accV[k % DB] = mfma32(fr[i], f.v, accV[k % DB]);
+                }
+#pragma unroll
+                for (int e = (i * 16) / N; e < ((i + 1) * 16) / N; e++) {
+                    const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sa[e], scale_l2, -l4[e >> 2][e & 3]));
+                    const float ds = p * pa[e];
+                    if (e & 1) {
+                        pp[CP][e >> 1] = pack_bf16x2(p0, p);
+                        dd[CP][e >> 1] = pack_bf16x2(d0, ds);
+                        asm volatile("" : "+v"(pp[CP][e >> 1]), "+v"(dd[CP][e >> 1]));
+                    } else {
+                        p0 = p;
+                        d0 = ds;
+                    }
+                }
+            }
+        };
+        // Tile t + 1 has landed, everybody's share of it, and everybody is done with tile t - 1.  `later`: tile t + 2 is on its
+        // way and may stay there: the NCP copies that were asked for last (behind its row statistics).
+        static_assert(NCP == 4, "the wait below");
+        auto settle = [&](bool later) {
+            if (later)
+                __builtin_amdgcn_s_waitcnt(0x0F74);  // vmcnt(4)
+            else
+                wait_vmem();
+            __syncthreads();
+        };
+        // fill: S, dP of blocks 0 and 1, P, dS of block 0
+        settle(n > 2);  // (tile 0: tile 1 may be waited for as well)
+        if (!empty(q_t)) {
+            scores(0);
+            probs(pp[0], dd[0], q_t, st_t, 0);
+        }
+        if (!empty(q_t + 32)) scores(1);
+        int cur = 0;  // buffer of step t
+        int t = 0, q_n = next_q(q_t), up;
+        // Window t: P, dS of blocks 2 t + 1 and 2 t + 2, S, dP of blocks 2 t + 2 and 2 t + 3, the sums of blocks 2 t and 2 t + 1.
+        auto enter = [&]() {
+            up = cur + 1 == NB ? -(NB - 1) * STEP : STEP;  // from the buffer of step t to that of step t + 1
+#pragma unroll
+            for (int ks = 0; ks < KS; ks++) nat[ks] += up;
+            st_n += up;
+            settle(t + 2 < n);
+            fetch();
+        };
+        auto leave = [&]() {
+#pragma unroll
+            for (int db = 0; db < DB; db++) tr[db][0] += up, tr[db][1] += up;
+            st_t += up;
+            cur = cur + 1 == NB ? 0 : cur + 1;
+            q_t = q_n;
+            q_n = next_q(q_n);
+            t++;
+        };
+        while (t < n) {
+            // windows from here on without an empty block and without a masked one among those whose arithmetic they do
+            const int from = causal ? wk_lo + 31 : 0;  // first row from which a block is not masked
+            int run = q_t + 32 < from || q_t + 64 > s || q_n < from || wk_lo >= s ? 0 : max(0, min(n - 1 - t, (s - q_n) / BQ));
+            for (; run > 0; run--) {
+                enter();
+                sums_probs(std::integral_constant<int, 1>{}, st_t);
+                scores(0);
+                sums_probs(std::integral_constant<int, 0>{}, st_n);
+                scores(1);
+                leave();
+            }
+            if (t >= n) break;
+            enter();
+            const bool more = t + 1 < n;
+            if (!empty(q_t)) sums(pp[0], dd[0], 0);
+            if (!empty(q_t + 32)) {
+                probs(pp[1], dd[1], q_t + 32, st_t, 1);
+                sums(pp[1], dd[1], 1);
+            }
+            if (more && !empty(q_n)) {
+                scores(0);
+                probs(pp[0], dd[0], q_n, st_n, 0);
+            }
+            if (more && !empty(q_n + 32)) scores(1);
+            leave();
+        }
+        KernArgs &e = fresh(args);
+        if (n >= kLateTicketSteps) deal.prefetch();
+        if (nparts > 1) {
+            constexpr int HALF = DB * 16 * kThreads * 4;  // bytes of one of the two sums
+            char *rec = e.pq.split_scratch + (int64_t)(slot + part) * kPartialBytes;
+            split_store<DB>(rec, accV, tid);
+            split_store<DB>(rec + HALF, accK, tid);
+            if (!split_arrive(e.pq.split_flags + slot, nparts, &split_word, tid)) continue;  // a later part finishes the tile
+#pragma unroll
+            for (int d = 0; d < DB; d++) accV[d] = accK[d] = f32x16{};
+            for (int p = 0; p < nparts; p++) {
+                const char *from = e.pq.split_scratch + (int64_t)(slot + p) * kPartialBytes;
+                split_sum<DB>(from, accV, 1.0f, tid);
+                split_sum<DB>(from + HALF, accK, 1.0f, tid);
+            }
+        }
+        if (wk_lo >= s) continue;
+        char *const stage = smem + (n % NB) * STEP + wave * (32 * L::ROWB);  // (nobody reads this buffer after the last window's barrier)
+        const int rows = min(32, s - wk_lo);
+        auto put = [&](void *out, int32_t st, int32_t sh, const f32x16 (&acc)[DB], float mul) {
+            if (e.grad_f32) {
+                RowsF32<DB> f;
+                f.store(stage, (float *)out + (tok0 + wk_lo) * st + (int64_t)g * sh, st, rows, acc, mul, lane);
+            } else {
+                store_rowT_bf16_lds<DB>(stage, (uint16_t *)out + (tok0 + wk_lo) * st + (int64_t)g * sh, st, rows, acc, mul, lane);
+            }
+        };
+        put(e.dv, e.dv_st, e.dv_sh, accV, 1.0f);
+        put(e.dk, e.dk_st, e.dk_sh, accK, e.scale);
+    }
+    deal.finish();
+}
+
 // ------------------------------------------------------------------------------ dQ
 // SHARD = true: the rows' share of dQ that comes from one shard of the keys (see the dK/dV kernel): the
 // log-sum-exp read here is that of the complete attention and `o` the complete output, so delta is the
@@ -678,7 +1002,9 @@ void start_both(const AttnArgs &a, int D, int grid, hipStream_t s)
 
 hipError_t launch_attn_bwd_dkv(const AttnArgs &a, int D, int grid, hipStream_t s)
 {
-    if (a.dq_wg)
+    if (a.wide)
+        launch(attn_bwd_dkv_wide_kernel, a, grid, s);
+    else if (a.dq_wg)
         start_both<false>(a, D, grid, s);
     else if (D == 128)
         launch(attn_bwd_dkv_kernel<128, false>, a, grid, s);

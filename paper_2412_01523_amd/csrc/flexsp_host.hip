@@ -64,6 +64,7 @@ struct flexsp_plan {
     bool kvshard = false;
     std::vector<int32_t> cu_k, shift;
     int64_t Tk = 0;
+    bool wide = false;  // the dK/dV pass's items have kDkvWideBk keys
     HostPass pass[3];
     // device side (null for host-only plans): one allocation, carved up
     void *dev_base;
@@ -505,6 +506,24 @@ void direct_list(HostPass &p, int nq, int n_wg, int spare, int64_t lowest)
     }
 }
 
+// Whether the dK/dV pass takes 128 keys an item (attn_bwd_dkv_wide_kernel; D = 64).  What it gives up: at a walk's start and end, and
+// where blocks are masked, its stages run one after the other, a causal walk begins with up to two steps of that kind, and
+// its items are half as many.  So not where the causal walks of a batch are under five steps on average (sequences
+// of 512 tokens: even; 256: 1 % slower; 64 to 512 tokens with 16 heads on 2: 9 % slower; 1 024: 2 % faster), and not where both passes
+// may run in one launch, which has no such kernel.
+bool wide_keys(const flexsp_plan *p, int n_wg)
+{
+    if (p->D != 64) return false;
+    int64_t steps = 0, walks = 0, items = 0;
+    for (int b = 0; b < p->B; b++) {
+        const int64_t s = p->cu[b + 1] - p->cu[b], tiles = cdiv(s, kDkvWideBk), all = cdiv(s, kDkvBq);
+        walks += tiles;
+        steps += p->causal ? tiles * all - tiles * (tiles - 1) / 2 * (kDkvWideBk / kDkvBq) : tiles * all;
+        items += cdiv(s, kDkvBk) * p->Hkv + cdiv(s, kDqBq) * p->Hq;
+    }
+    return items > n_wg && (!p->causal || steps >= 5 * walks);
+}
+
 int check_attn_common(flexsp_ctx *ctx, flexsp_plan *plan, const int32_t *cu_dev, int32_t head_begin,
                       int32_t head_count, int32_t kv_head_begin, int32_t kv_head_count, int causal)
 {
@@ -649,7 +668,7 @@ bool outputs_apart(const flexsp_plan *p, const AttnArgs &a)
 int both_at_once(const flexsp_ctx *ctx, const flexsp_plan *p, AttnArgs &a)
 {
     const int dkv = (int)p->pass[FLEXSP_PASS_BWD_DKV].direct.size(), dq = (int)p->pass[FLEXSP_PASS_BWD_DQ].direct.size();
-    if (!dkv || !dq || dkv + dq > workgroups_of(ctx) || !outputs_apart(p, a)) return 0;
+    if (p->wide || !dkv || !dq || dkv + dq > workgroups_of(ctx) || !outputs_apart(p, a)) return 0;
     a.pq = p->dq[FLEXSP_PASS_BWD_DKV];
     a.dq_pq = p->dq[FLEXSP_PASS_BWD_DQ];
     a.dkv_items = dkv;
@@ -673,6 +692,7 @@ int grid_for(const flexsp_ctx *ctx, const HostPass &p, int per_cu)
 int bwd_per_cu(const flexsp_ctx *ctx, const flexsp_plan *plan, int pass)
 {
     const HostPass &p = plan->pass[pass];
+    if (plan->wide && pass == FLEXSP_PASS_BWD_DKV) return 2;  // (its registers)
     return plan->D == 64 && 2 * p.longest * workgroups_of(ctx) <= p.steps ? 3 : 2;
 }
 
@@ -841,7 +861,8 @@ int flexsp_plan_create(flexsp_ctx *ctx, const int32_t *cu, int32_t B, int32_t Hq
         p->cu.assign(cu, cu + B + 1);
         const int nq = ctx->num_xcd, n_wg = workgroups_of(ctx);
         build_pass(p->cu, B, Hq, 1, kFwdBq, kFwdBk, causal != 0, false, nq, n_wg, p->pass[FLEXSP_PASS_FWD]);
-        build_pass(p->cu, B, Hkv, Hq / Hkv, kDkvBk, kDkvBq, causal != 0, true, nq, n_wg, p->pass[FLEXSP_PASS_BWD_DKV]);
+        p->wide = wide_keys(p, n_wg);
+        build_pass(p->cu, B, Hkv, Hq / Hkv, p->wide ? kDkvWideBk : kDkvBk, kDkvBq, causal != 0, true, nq, n_wg, p->pass[FLEXSP_PASS_BWD_DKV]);
         build_pass(p->cu, B, Hq, 1, kDqBq, kDqBk, causal != 0, false, nq, n_wg, p->pass[FLEXSP_PASS_BWD_DQ]);
         for (int i = 0; i < 3; i++) direct_list(p->pass[i], nq, n_wg, 0, i == FLEXSP_PASS_FWD ? 0 : kShortPartSteps);
     } catch (const std::bad_alloc &) {
@@ -1415,6 +1436,7 @@ int flexsp_attn_varlen_bwd(flexsp_ctx *ctx, flexsp_plan *plan, flexsp_tensor q, 
         e = launch_attn_bwd_dq(a, plan->D, grid_for(ctx, plan->pass[FLEXSP_PASS_BWD_DQ], bwd_per_cu(ctx, plan, FLEXSP_PASS_BWD_DQ)), s);
     }
     if (e != hipSuccess) return hip_fail(e);
+    a.wide = plan->wide;
     a.lse_in = lse2;
     a.delta_in = plan->delta;
     a.pq = plan->dq[FLEXSP_PASS_BWD_DKV];

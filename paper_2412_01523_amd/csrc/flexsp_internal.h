@@ -18,6 +18,7 @@ constexpr int kFwdBk = 64;     // key rows staged in LDS per forward step
 constexpr int kDqBq = 128;     // query rows per dQ work item
 constexpr int kDqBk = 64;      // key rows per dQ step
 constexpr int kDkvBk = 64;     // key rows per dK/dV work item (2 pairs of waves x 32 rows)
+constexpr int kDkvWideBk = 128;  // ... of attn_bwd_dkv_wide_kernel's (4 waves x 32 rows)
 constexpr int kDkvBq = 64;     // query rows per dK/dV step
 constexpr int kThreads = 256;  // every attention kernel runs 4 wavefronts per workgroup
 constexpr int kMaxQueues = 8;  // one work queue per XCD
@@ -80,6 +81,7 @@ struct AttnArgs {
     // dQ pass's queues, its first workgroup (0: the dK/dV pass alone), the dK/dV pass's items, workgroups per compute unit
     PassQueues dq_pq;
     int32_t dq_wg, dkv_items, per_cu;
+    int32_t wide;  // the dK/dV pass's items have kDkvWideBk keys
     int32_t grid;  // workgroups of the launch (filled in by the launchers)
     // a forward without a list of items: every workgroup finds its own in the lengths (device; null: pq holds a list)
     const int32_t *cu;
