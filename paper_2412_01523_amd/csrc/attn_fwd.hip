@@ -81,7 +81,7 @@ __device__ __forceinline__ bool find_item(const int32_t *cu, int B, int T, int h
 // FIND = true is the variant without a list of items: workgroup w finds the w-th (query tile, head) of the batch in the
 // lengths and leaves when it is done.
 template <int D, bool SHARD, bool FIND>
-__global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const AttnArgs)
+__global__ __launch_bounds__(kThreads, D == 64 && !SHARD ? 3 : 2) void attn_fwd_kernel(const AttnArgs)
 {
     typedef LdsTile<D> L;
     constexpr int KS = D / 16;                  // k steps of the score product

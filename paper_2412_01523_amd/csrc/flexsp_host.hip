@@ -696,6 +696,16 @@ int bwd_per_cu(const flexsp_ctx *ctx, const flexsp_plan *plan, int pass)
     return plan->D == 64 && 2 * p.longest * workgroups_of(ctx) <= p.steps ? 3 : 2;
 }
 
+// ... and of a forward, likewise: with D = 64 three (163 registers, 33 KB of LDS).  Forward and backward of 8 heads, two -> three, causal
+// sequences of 512 tokens 302 -> 290 us, 1 024 434 -> 422, 4 096 1 235 -> 1 218, 16 384 4 398 -> 4 369; not causal 256 142 -> 137, 1 024 331 -> 327,
+// but 2 048 597 -> 602, 16 384 4 395 -> 4 445: long items without a masked or ragged end have no waits that a third could use.
+int fwd_per_cu(const flexsp_ctx *ctx, const flexsp_plan *plan)
+{
+    const HostPass &p = plan->pass[FLEXSP_PASS_FWD];
+    const bool even = 2 * p.longest * workgroups_of(ctx) <= p.steps;
+    return plan->D == 64 && even && (plan->causal || p.steps <= 24 * (int64_t)p.items.size()) ? 3 : 2;
+}
+
 }  // namespace
 
 namespace flexsp {
@@ -1165,7 +1175,7 @@ int flexsp_attn_varlen_fwd(flexsp_ctx *ctx, flexsp_plan *plan, flexsp_tensor q, 
     hipError_t e;
     {
         Timed tm(ctx, FLEXSP_K_FWD, (hipStream_t)stream);
-        e = launch_attn_fwd(a, plan->D, grid_for(ctx, plan->pass[FLEXSP_PASS_FWD], 2), (hipStream_t)stream);
+        e = launch_attn_fwd(a, plan->D, grid_for(ctx, plan->pass[FLEXSP_PASS_FWD], fwd_per_cu(ctx, plan)), (hipStream_t)stream);
     }
     return e == hipSuccess ? FLEXSP_OK : hip_fail(e);
 }
