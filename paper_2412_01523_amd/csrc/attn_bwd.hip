@@ -144,9 +144,11 @@ __device__ __forceinline__ void dkv_pass(KernArgs &args, KernQueues &queues, con
                 h_nxt++;
             }
         };
-        // SELF: 16 rows of O and dO per wavefront and step, whole rows (LPR lanes each), for delta
-        constexpr int LPR = D / 8, RPI = 64 / LPR, NI = 16 / RPI;
-        u32x4 o_raw[SELF ? NI : 1], g_raw[SELF ? NI : 1];
+        // SELF: the pieces of O that correspond to the pieces of dO this lane copies into the tile, and (wavefront 0) a row's log-sum-exp
+        constexpr int NO = SELF ? BQ * L::CH / kThreads : 1;
+        u32x4 o_raw[NO];
+        float lse_raw = 0.f;
+        const uint32_t goffo = SELF ? tile_goff<D>(a.o_st, wave, lane) : 0;
         auto prefetch = [&](int h, int qs, int buf) {
             char *base = smem + buf * STEP;
             const uint16_t *qb = a.q + tok0 * a.q_st + (int64_t)h * a.q_sh;
@@ -158,33 +160,40 @@ __device__ __forceinline__ void dkv_pass(KernArgs &args, KernQueues &queues, con
                 load_tile_async<D, BQ>(base, qb, a.q_st, qs, s - 1, wave, lane);
                 load_tile_async<D, BQ>(base + QTILE, gb, a.do_st, qs, s - 1, wave, lane);
             }
+            const float *const lse = a.lse_in + (int64_t)h * a.T + tok0 + min(qs + lane, s - 1);
             if constexpr (SELF) {
-#pragma unroll
-                for (int i = 0; i < NI; i++) {
-                    const int64_t row = tok0 + min(qs + wave * 16 + i * RPI + lane / LPR, s - 1);
-                    o_raw[i] = *(const u32x4 *)(a.o + row * a.o_st + (int64_t)h * a.o_sh + (lane % LPR) * 8);
-                    g_raw[i] = *(const u32x4 *)(a.dO + row * a.do_st + (int64_t)h * a.do_sh + (lane % LPR) * 8);
-                }
-                if (wave == 0) global_to_lds4(a.lse_in + (int64_t)h * a.T + tok0 + min(qs + lane, s - 1), base + 2 * QTILE);
+                // (rows past the sequence read as zeros: nobody looks at their delta)
+                const uint32_t rowb = (uint32_t)a.o_st * 2u;
+                const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                    (void *)(a.o + (tok0 + qs) * a.o_st + (int64_t)h * a.o_sh), 0, (int)(min(s - qs, BQ) * rowb), 0x00020000);
+    #pragma unroll
+                for (int i = 0; i < NO; i++) o_raw[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, goffo, i * (kThreads / L::CH) * rowb, 0);
+                if (wave == 0) lse_raw = *lse;
             } else if (wave < 2) {  // wavefront 0: lse2 of the 64 rows, wavefront 1: delta
-                const float *src = (wave ? a.delta_in : a.lse_in) + (int64_t)h * a.T + tok0 + min(qs + lane, s - 1);
-                global_to_lds4(src, base + 2 * QTILE + wave * 256);
+                global_to_lds4(wave ? a.delta_in + (lse - a.lse_in) : lse, base + 2 * QTILE + wave * 256);
             }
         };
-        // SELF: -delta of the rows requested last, left where the step in buffer `buf` reads it
+        // SELF: the log-sum-exp to base 2 and -delta of the step in buffer `buf`, left where the step reads them (after this wavefront's own
+        // copies have landed: it reads its pieces of dO from the tile)
         auto put_delta = [&](int buf) {
-            float *to = (float *)(smem + buf * STEP + 2 * QTILE + 256) + wave * 16;
-#pragma unroll
-            for (int i = 0; i < NI; i++) {
+            char *base = smem + buf * STEP;
+            float *to = (float *)(base + 2 * QTILE);
+            u32x4 g_raw[NO];
+    #pragma unroll
+            for (int i = 0; i < NO; i++) g_raw[i] = *(const u32x4 *)(base + QTILE + (i * kThreads + wave * 64 + lane) * 16);
+    #pragma unroll
+            for (int i = 0; i < NO; i++) {
                 float d = 0.f;
-#pragma unroll
+    #pragma unroll
                 for (int e = 0; e < 4; e++) {
                     const uint32_t gw = g_raw[i][e], ow = o_raw[i][e];
                     d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, gw), __builtin_bit_cast(bf16x2, ow), d, false);
                 }
-                d = group_sum<LPR>(d);
-                if (lane % LPR == 0) to[i * RPI + lane / LPR] = -d;
+                d = group_sum<L::CH>(d);
+                if (lane % L::CH == 0) to[64 + (i * kThreads + wave * 64 + lane) / L::CH] = -d;
             }
+            // (SHARD: a row that saw no key anywhere has P = 0)
+            if (wave == 0) to[lane] = SHARD && lse_raw == -INFINITY ? INFINITY : lse_raw * 1.4426950408889634f;
         };
         if (n > 0) prefetch(h_cur, q_cur, 0);
         advance_nxt();
@@ -222,8 +231,8 @@ __device__ __forceinline__ void dkv_pass(KernArgs &args, KernQueues &queues, con
                 return lo_ >= s || (a.causal && lo_ + 31 + sh < wk_lo);
             };
             lo.pin();
-            if constexpr (SELF) put_delta(BUF);
             wait_vmem();
+            if constexpr (SELF) put_delta(BUF);
             __syncthreads();  // tile `step` is in LDS; the previous step's exchange slots are free
             // (the copies of the next tiles go out after phase 1's matrix instructions, not here: a
             // wavefront waits until its copy instructions are accepted, and behind the barrier that wait
@@ -274,11 +283,7 @@ __device__ __forceinline__ void dkv_pass(KernArgs &args, KernQueues &queues, con
                     constexpr bool MASK = decltype(maskc)::value;
 #pragma unroll
                     for (int i4 = 0; i4 < 4; i4++) {
-                        f32x4 l4 = *(const f32x4 *)(sL + j * 32 + 8 * i4 + 4 * hl);
-                        if constexpr (SELF) {  // to base 2, as the dQ pass leaves it
-#pragma unroll
-                            for (int e = 0; e < 4; e++) l4[e] = SHARD && l4[e] == -INFINITY ? INFINITY : l4[e] * 1.4426950408889634f;
-                        }
+                        const f32x4 l4 = *(const f32x4 *)(sL + j * 32 + 8 * i4 + 4 * hl);
                         float p[4], ds[4];
 #pragma unroll
                         for (int e = 0; e < 4; e++) {
@@ -925,11 +930,11 @@ __device__ __forceinline__ void dq_pass(KernArgs &args, KernQueues &queues, cons
 
         KernArgs &e = fresh(args);
         KernQueues &eq = fresh(queues);
-        // delta and the base-2 log-sum-exp are kept for the dK/dV kernel, which runs after this one (beside a
-        // dK/dV pass in one launch nobody reads them)
+        // delta and the base-2 log-sum-exp are kept for the dK/dV kernel, which runs after this one (nowhere beside a
+        // dK/dV pass in one launch: nobody would read them)
         // (stored here, not where they are computed: a store in flight there would be waited for by
         // the first tile's wait for its copy)
-        if (qok && hl == 0) {
+        if (e.delta_out && qok && hl == 0) {
             e.delta_out[(int64_t)h * e.T + tok0 + qrow] = -delta;  // negated: the dK/dV kernel starts its dP accumulator from it
             e.lse_out[(int64_t)h * e.T + tok0 + qrow] = lse2;
         }
@@ -977,8 +982,10 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
 // memory trips and short steps run side by side instead of one after the other; the price is that the dK/dV pass reads
 // O as well.  Forward and backward, two launches -> one: 635 tokens, 1 head 29.6 -> 22.2 us; 808 tokens, 4 heads 42.8 -> 31.7 us;
 // 1 141 tokens, 16 heads on 2 94 -> 76 us; 5 630 tokens, 2 heads 45.0 -> 38.8 us.
-// PER_CU: with D = 128 the rows of O and dO that wait for a step do not fit beside the rest in half the register file (8
-// to 11 spills).  A launch of at most one workgroup per compute unit takes the kernel that has all of it (808 tokens, 4 heads:
+// delta is formed from the piece of dO that the lane has just copied into the tile and the same piece of O, which waits for the step in
+// a register: both rows in registers were 35 spilled ones with D = 128, and dO was fetched twice (1 201 tokens, 16 heads on 4 38.9 -> 37.8
+// us; 5 630 tokens, 2 heads 51.0 -> 50.0).
+// PER_CU: a launch of at most one workgroup per compute unit takes the kernel that has the whole register file (808 tokens, 4 heads:
 // 31.7 against 34.3 us), a larger one the kernel that two workgroups can share a compute unit with (5 630 tokens, 2 heads:
 // 38.8 against 43.4 us).
 template <int D, bool SHARD, int PER_CU>
