@@ -159,60 +159,64 @@ __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70)
 __device__ __forceinline__ void barrier_lds_only() { __builtin_amdgcn_s_barrier(); }
 
 // Copies ROWS rows of a row-major global matrix (row r at g + r*stride elements, D bf16 each)
-// into a swizzled LDS tile, asynchronously, with all 256 threads.  Row `first + r` is clamped to
+// into a swizzled LDS tile, asynchronously, with T threads (wavefronts 0 .. T/64-1).  Row `first + r` is clamped to
 // `last_valid`, so rows past the end of a sequence duplicate its last row (finite data; callers
-// mask them).
-template <int D, int ROWS>
+// mask them).  Pass n of a lane lies T/CH rows below pass n-1.  The swizzle has a period of 16 rows: where a pass covers fewer, its
+// column alternates between the passes.
+template <int D, int T>
+struct TileCopy {
+    typedef LdsTile<D> L;
+    static constexpr int RP = T / L::CH;                // rows per pass
+    static constexpr int P = RP >= 16 ? 1 : 16 / RP;    // passes after which the column repeats
+    static_assert(RP % 16 == 0 || 16 % RP == 0, "the column of a pass must repeat");
+    __device__ static __forceinline__ int row(int wave, int lane) { return (wave * 64 + lane) / L::CH; }
+    __device__ static __forceinline__ int col(int wave, int lane, int n) { return (lane % L::CH) ^ L::sw(row(wave, lane) + (n % P) * RP); }
+};
+template <int D, int ROWS, int T = kThreads>
 __device__ __forceinline__ void load_tile_async(char *tile, const uint16_t *g, int32_t stride, int first,
                                                 int last_valid, int wave, int lane)
 {
-    typedef LdsTile<D> L;
-    constexpr int N = ROWS * L::CH / kThreads;
-    static_assert(N >= 1 && ROWS * L::CH % kThreads == 0, "tile must split evenly over the workgroup");
-    static_assert((kThreads / L::CH) % 16 == 0, "rows per pass must be a multiple of the swizzle period");
-    const int row0 = first + (wave * 64 + lane) / L::CH;  // (the piece's column is the same in every pass)
-    const uint16_t *col = g + ((lane % L::CH) ^ L::sw(row0 - first)) * 8;
+    typedef TileCopy<D, T> C;
+    constexpr int N = ROWS / C::RP;
+    static_assert(N >= 1 && ROWS % C::RP == 0, "tile must split evenly over the threads");
+    const int row0 = first + C::row(wave, lane);
 #pragma unroll
     for (int n = 0; n < N; n++) {
-        const int grow = min(row0 + n * (kThreads / L::CH), last_valid);
-        global_to_lds16(col + (int64_t)grow * stride, tile + (n * kThreads + wave * 64) * 16);
+        const int grow = min(row0 + n * C::RP, last_valid);
+        global_to_lds16(g + (int64_t)grow * stride + C::col(wave, lane, n) * 8, tile + (n * T + wave * 64) * 16);
     }
 }
 
-// The same copy without the clamp, for tiles that lie wholly inside the sequence.  Chunk n of a
-// lane lies kThreads/CH rows below chunk n-1 in the same (swizzled) column, because the swizzle
-// has a period of 16 rows; so one per-lane byte offset (tile_goff, computed once per item) plus
-// wave-uniform addresses describe the whole copy, and it costs no vector address arithmetic.
-template <int D>
-__device__ __forceinline__ uint32_t tile_goff(int32_t stride, int wave, int lane)
+// The same copy without the clamp, for tiles that lie wholly inside the sequence.  One per-lane byte offset (two where the column
+// alternates; tile_goff, computed once per item) plus wave-uniform addresses describe the whole copy, and it costs no vector
+// address arithmetic.
+template <int D, int T = kThreads>
+__device__ __forceinline__ uint32_t tile_goff(int32_t stride, int wave, int lane, int n = 0)
 {
-    typedef LdsTile<D> L;
-    const int row = (wave * 64 + lane) / L::CH;
-    const int c = (lane % L::CH) ^ L::sw(row);
-    return (uint32_t)(row * (uint32_t)stride * 2u + c * 16);
+    typedef TileCopy<D, T> C;
+    return (uint32_t)(C::row(wave, lane) * (uint32_t)stride * 2u + C::col(wave, lane, n) * 16);
 }
 template <int D, int ROWS>
 __device__ __forceinline__ void load_tile_async_fast(char *tile, const uint16_t *g_tile, int32_t stride,
                                                      uint32_t goff, int wave)
 {
-    typedef LdsTile<D> L;
-    static_assert((kThreads / L::CH) % 16 == 0, "rows per pass must be a multiple of the swizzle period");
+    typedef TileCopy<D, kThreads> C;
+    static_assert(C::P == 1, "one offset");
 #pragma unroll
-    for (int n = 0; n < ROWS * L::CH / kThreads; n++)
-        global_to_lds16(g_tile + (int64_t)n * (kThreads / L::CH) * stride, goff, tile + (n * kThreads + wave * 64) * 16);
+    for (int n = 0; n < ROWS / C::RP; n++)
+        global_to_lds16(g_tile + (int64_t)n * C::RP * stride, goff, tile + (n * kThreads + wave * 64) * 16);
 }
 
-// One of the ROWS*CH/kThreads copy instructions of load_tile_async_fast (n is a compile-time
-// constant at every call site).  Lets a kernel place the copies of the next tile one by one
+// One of the ROWS / RP copy instructions of a tile (n is a compile-time
+// constant at every call site; goff: tile_goff of that n).  Lets a kernel place the copies of the next tile one by one
 // between its matrix instructions: issued back to back by all wavefronts right after the
 // barrier they queue up behind the 64 bytes per cycle a compute unit's load path delivers, and
 // every wavefront stalls until its own have been accepted.
-template <int D>
+template <int D, int T = kThreads>
 __device__ __forceinline__ void load_tile_async_fast_one(char *tile, const uint16_t *g_tile, int32_t stride,
                                                          uint32_t goff, int wave, int n)
 {
-    typedef LdsTile<D> L;
-    global_to_lds16(g_tile + (int64_t)n * (kThreads / L::CH) * stride, goff, tile + (n * kThreads + wave * 64) * 16);
+    global_to_lds16(g_tile + (int64_t)n * TileCopy<D, T>::RP * stride, goff, tile + (n * T + wave * 64) * 16);
 }
 
 // Per-lane byte offsets of operand fragments inside a tile (computed once per kernel).

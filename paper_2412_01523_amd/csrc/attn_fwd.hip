@@ -80,24 +80,41 @@ __device__ __forceinline__ bool find_item(const int32_t *cu, int B, int T, int h
 //
 // FIND = true is the variant without a list of items: workgroup w finds the w-th (query tile, head) of the batch in the
 // lengths and leaves when it is done.
-template <int D, bool SHARD, bool FIND>
-__global__ __launch_bounds__(kThreads, D == 64 && !SHARD ? 3 : 2) void attn_fwd_kernel(const AttnArgs)
+//
+// HALVES = 2 is the variant for launches that leave compute units without work: a workgroup is 64 query rows, half an item, and two
+// wavefronts to each block of 32 rows: wavefronts 0 and 1 walk the first half of the key tiles, 2 and 3 the second, each pair with
+// tiles of its own, and hand over through LDS.  Such a launch lasts as long as its longest item's chain of steps, and a step lasts
+// as long as one wavefront's matrix instructions; a hand-over through memory costs what the shorter chain saves.
+template <int D, bool SHARD, bool FIND, int HALVES>
+__global__ __launch_bounds__(kThreads, HALVES == 2 ? 1 : D == 64 && !SHARD ? 3 : 2) void attn_fwd_kernel(const AttnArgs)
 {
+    static_assert(HALVES == 1 || !SHARD, "no list of a shard's launch asks for it");
     typedef LdsTile<D> L;
     constexpr int KS = D / 16;                  // k steps of the score product
     constexpr int DB = D / 32;                  // 32-wide blocks of the head dim
     constexpr int TILE = kFwdBk * L::ROWB;      // bytes of one 64-row tile
-    constexpr int NCP = 2 * kFwdBk * L::CH / kThreads;  // copy instructions per wavefront for a K and a V tile
+    constexpr int NT = kThreads / HALVES;       // threads that share a tile
+    constexpr int BQ = kFwdBq / HALVES;         // query rows of the workgroup
+    constexpr int NCP = 2 * kFwdBk * L::CH / NT;  // copy instructions per wavefront for a K and a V tile
     constexpr int NSLOT = KS + 2 * DB;          // matrix instructions of one pipeline iteration
-    static_assert(NSLOT == 2 * NCP, "one copy instruction per two matrix instructions");
+    static_assert(NSLOT * HALVES == 2 * NCP, "one copy instruction per two matrix instructions, or per one");
     // [K buffer 0 | K buffer 1 | V buffer 0 | V buffer 1]
-    __shared__ __attribute__((aligned(1024))) char smem[4 * TILE];
+    __shared__ __attribute__((aligned(1024))) char smem[HALVES * 4 * TILE];  // (each half of the wavefronts its own)
 
     const int tid = thread_id();
     const int lane0 = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave4 = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = HALVES == 2 ? wave4 & 1 : wave4, half = HALVES == 2 ? wave4 >> 1 : 0;
+    char *const mine = smem + half * 4 * TILE;  // for copies and stores; reads of tiles have the half in their lane offsets:
     LaneOffsets<D> lo;
     lo.init(lane0);
+    if constexpr (HALVES == 2) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) lo.nat[ks] += half * 4 * TILE;
+#pragma unroll
+        for (int db = 0; db < DB; db++) lo.tr[db][0] += half * 4 * TILE, lo.tr[db][1] += half * 4 * TILE;
+    }
+    __shared__ __attribute__((aligned(8))) float stats[HALVES == 2 ? 2 * NT : 2];  // the second half's row maxima and sums
     __shared__ int deal_word, split_word;
     ItemDealer deal;
     KernArgs &args = kernel_args();
@@ -106,7 +123,10 @@ __global__ __launch_bounds__(kThreads, D == 64 && !SHARD ? 3 : 2) void attn_fwd_
     int item;
     if constexpr (FIND) {
         deal.direct = true;
-        item = find_item(args.cu, args.B, args.T, args.Hq, args.causal, workgroup_id(), lane0, found) ? 0 : -1;
+        item = find_item(args.cu, args.B, args.T, args.Hq, args.causal, workgroup_id() / HALVES, lane0, found) ? 0 : -1;
+    } else if constexpr (HALVES == 2) {
+        deal.direct = true;
+        item = workgroup_id() / HALVES;
     } else {
         item = deal.first(args.pq, args.grid, 0, &deal_word, wave, lane0);
     }
@@ -137,9 +157,21 @@ __global__ __launch_bounds__(kThreads, D == 64 && !SHARD ? 3 : 2) void attn_fwd_
         lane &= 63;  // (its range is known again: divisions by the pieces of a row are shifts)
         const int r = lane & 31, hl = lane >> 5;
         const int g = h / a.G;
+        if constexpr (HALVES == 2) {
+            q0 += workgroup_id() % HALVES * BQ;
+            if (q0 >= s) continue;
+        }
         // keys this item needs
-        int kv_end = SHARD ? (a.causal ? max(0, min(sk, q0 + kFwdBq + shift)) : sk)
-                           : (a.causal ? min(s, q0 + kFwdBq) : s);
+        int kv_end = SHARD ? (a.causal ? max(0, min(sk, q0 + BQ + shift)) : sk)
+                           : (a.causal ? min(s, q0 + BQ) : s);
+        // this half's key tiles; windows, and with them barriers, of the first half (the second has no more)
+        int windows = 0;
+        if constexpr (HALVES == 2) {
+            const int n = (kv_end + kFwdBk - 1) / kFwdBk, first = n >= kSplitSteps ? (n + 1) / 2 : n;
+            windows = first;
+            t_lo = half ? first : 0;
+            t_hi = half ? n : first;
+        }
         // The item walks key tiles t_lo .. t_hi-1 (all of them unless the tile was cut).  From here on keys are counted
         // from the part's first one (koff keys are skipped: a multiple of the tile size, so blocks
         // stay aligned and still at most one block per wavefront needs masking); a wavefront whose
@@ -189,23 +221,31 @@ __global__ __launch_bounds__(kThreads, D == 64 && !SHARD ? 3 : 2) void attn_fwd_
         const uint16_t *kbase = a.k + ktok0 * a.k_st + (int64_t)g * a.k_sh;
         const uint16_t *vbase = a.v + ktok0 * a.v_st + (int64_t)g * a.v_sh;
 
-        const uint32_t goffk = tile_goff<D>(a.k_st, wave, lane), goffv = tile_goff<D>(a.v_st, wave, lane);
+        constexpr int CP_ = TileCopy<D, NT>::P;
+        uint32_t goffk[CP_], goffv[CP_];
+#pragma unroll
+        for (int n = 0; n < CP_; n++) goffk[n] = tile_goff<D, NT>(a.k_st, wave, lane, n), goffv[n] = tile_goff<D, NT>(a.v_st, wave, lane, n);
+        auto copy_one = [&](char *dst, const uint16_t *src, int32_t st, const uint32_t (&goff)[CP_], int n) {
+            load_tile_async_fast_one<D, NT>(dst, src, st, goff[n % CP_], wave, n);
+        };
         // whole-tile copies (all of this wavefront's copy instructions back to back)
         auto prefetch_k = [&](int t, int buf) {
-            char *dst = smem + buf * TILE;
+            char *dst = mine + buf * TILE;
             if ((t + 1) * kFwdBk <= sk)  // whole tile inside the sequence
-                load_tile_async_fast<D, kFwdBk>(dst, kbase + (int64_t)t * kFwdBk * a.k_st, a.k_st, goffk, wave);
+#pragma unroll
+                for (int n = 0; n < NCP / 2; n++) copy_one(dst, kbase + (int64_t)t * kFwdBk * a.k_st, a.k_st, goffk, n);
             else
-                load_tile_async<D, kFwdBk>(dst, kbase, a.k_st, t * kFwdBk, sk - 1, wave, lane);
+                load_tile_async<D, kFwdBk, NT>(dst, kbase, a.k_st, t * kFwdBk, sk - 1, wave, lane);
         };
         auto prefetch_v = [&](int t, int buf) {
-            char *dst = smem + (2 + buf) * TILE;
+            char *dst = mine + (2 + buf) * TILE;
             if ((t + 1) * kFwdBk <= sk)
-                load_tile_async_fast<D, kFwdBk>(dst, vbase + (int64_t)t * kFwdBk * a.v_st, a.v_st, goffv, wave);
+#pragma unroll
+                for (int n = 0; n < NCP / 2; n++) copy_one(dst, vbase + (int64_t)t * kFwdBk * a.v_st, a.v_st, goffv, n);
             else
-                load_tile_async<D, kFwdBk>(dst, vbase, a.v_st, t * kFwdBk, sk - 1, wave, lane);
+                load_tile_async<D, kFwdBk, NT>(dst, vbase, a.v_st, t * kFwdBk, sk - 1, wave, lane);
         };
-        prefetch_k(0, 0);
+        if (HALVES == 1 || ntiles > 0) prefetch_k(0, 0);
 
         // ---- Q fragments (B operand: column = query row, k = head dim), kept in registers: the rows
         // are requested here and become fragments just before the barrier below
@@ -394,14 +434,12 @@ __global__ __launch_bounds__(kThreads, D == 64 && !SHARD ? 3 : 2) void attn_fwd_
                     pf.u = u32x4{pp[4 * st], pp[4 * st + 1], pp[4 * st + 2], pp[4 * st + 3]};
                     oacc[(j - KS) % DB] = mfma32(fr[j], pf.v, oacc[(j - KS) % DB]);
                 }
-                if (PF && (j & 1)) {
-                    const int n = j >> 1;
+                if (PF && (HALVES == 2 || (j & 1))) {
+                    const int n = HALVES == 2 ? j : j >> 1;
                     if (n < NCP / 2)
-                        load_tile_async_fast_one<D>(smem + (KB ^ 1) * TILE, kbase + (int64_t)(t + 2) * kFwdBk * a.k_st,
-                                                    a.k_st, goffk, wave, n);
+                        copy_one(mine + (KB ^ 1) * TILE, kbase + (int64_t)(t + 2) * kFwdBk * a.k_st, a.k_st, goffk, n);
                     else
-                        load_tile_async_fast_one<D>(smem + (2 + (VB ^ 1)) * TILE, vbase + (int64_t)(t + 1) * kFwdBk * a.v_st,
-                                                    a.v_st, goffv, wave, n - NCP / 2);
+                        copy_one(mine + (2 + (VB ^ 1)) * TILE, vbase + (int64_t)(t + 1) * kFwdBk * a.v_st, a.v_st, goffv, n - NCP / 2);
                 }
                 {
                     constexpr int NE = NSLOT;  // every slot carries its share of the 16 exponentials
@@ -428,7 +466,7 @@ __global__ __launch_bounds__(kThreads, D == 64 && !SHARD ? 3 : 2) void attn_fwd_
         // ---------------- pipeline fill: K tile 0 -> S(0), then iteration 0 --------------------
         // (the Q rows pass through this wavefront's quarter of the V buffers, which are idle until the
         // barrier: V tile 0 is requested after it)
-        qrows.fragments(smem + 2 * TILE + wave * (32 * L::ROWB), 0, lo, qf, lane);
+        qrows.fragments(smem + 2 * TILE + wave * (32 * L::ROWB), half * 4 * kFwdBk, lo, qf, lane);
         wait_vmem();
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the fragments are in registers
         __syncthreads();
@@ -436,7 +474,7 @@ __global__ __launch_bounds__(kThreads, D == 64 && !SHARD ? 3 : 2) void attn_fwd_
         const int draw_t = ntiles >= kLateTicketSteps ? ntiles - 2 : -1;
         if (draw_t < 0) deal.prefetch();
         if (ntiles > 1) prefetch_k(1, 1);
-        prefetch_v(0, 0);
+        if (HALVES == 1 || ntiles > 0) prefetch_v(0, 0);
         if (cmax >= 0) scores(sacc[0], smem);
         iter_slow(ic<0>{}, 0, smem + 32 * L::ROWB, smem);
 
@@ -491,7 +529,7 @@ __global__ __launch_bounds__(kThreads, D == 64 && !SHARD ? 3 : 2) void attn_fwd_
         // come straight from global memory through this wavefront's quarter of the K buffers (no
         // wavefront reads a K tile after the last window's barrier, and this one is past it).
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(psum_max < 0x1p64f)) != 0, 0)) {
-            char *mine = smem + wave * (32 * L::ROWB);
+            char *block = smem + wave * (32 * L::ROWB);
 #pragma unroll
             for (int db = 0; db < DB; db++)
 #pragma unroll
@@ -501,9 +539,9 @@ __global__ __launch_bounds__(kThreads, D == 64 && !SHARD ? 3 : 2) void attn_fwd_
             for (int c = 0; c <= cmax; c++) {
                 RowBlock<D> blk;
                 blk.load(kbase, a.k_st, c * 32, sk - 1, lane);
-                blk.stage(mine, 0, lane);
+                blk.stage(block, half * 4 * kFwdBk, lane);
                 f32x16 &sa = sacc[0];
-                scores(sa, mine);
+                scores(sa, block);
                 if (SHARD ? c >= cmask : c == cmask) {
 #pragma unroll
                     for (int i = 0; i < 16; i++) {
@@ -522,15 +560,45 @@ __global__ __launch_bounds__(kThreads, D == 64 && !SHARD ? 3 : 2) void attn_fwd_
                     pk[0][i >> 1] = pack_bf16x2(p0, p1);
                 }
                 blk.load(vbase, a.v_st, c * 32, sk - 1, lane);
-                blk.stage(mine, 0, lane);  // (after the reads of the K block: one wavefront's LDS instructions execute in order)
+                blk.stage(block, half * 4 * kFwdBk, lane);  // (after the reads of the K block: one wavefront's LDS instructions execute in order)
                 finish_block(m_new, ps);   // O and the row sum move to the block's reference first
-                pv(pk[0], mine);
+                pv(pk[0], block);
             }
         }
 
         // ---- epilogue: normalise, write O (bf16) and LSE (natural log)
         KernArgs &e = fresh(args);
         float l_tot = halves_sum(l_run);
+        if constexpr (HALVES == 2) {
+            for (int t = ntiles; t < windows; t++) __syncthreads();
+            // the second half's O (not normalised), row maximum and row sum, through its own tiles' LDS
+            __syncthreads();  // (everybody is done with them)
+            f32x4 *const box = (f32x4 *)(smem + 4 * TILE) + wave * (DB * 4 * 64) + lane;
+            float *const st = stats + 2 * (wave * 64 + lane);
+            if (half) {
+#pragma unroll
+                for (int db = 0; db < DB; db++)
+#pragma unroll
+                    for (int i4 = 0; i4 < 4; i4++)
+                        box[(db * 4 + i4) * 64] = f32x4{oacc[db][4 * i4], oacc[db][4 * i4 + 1], oacc[db][4 * i4 + 2], oacc[db][4 * i4 + 3]};
+                st[0] = m_run;
+                st[1] = l_tot;
+            }
+            __syncthreads();
+            if (half) continue;
+            const float m1 = st[0], M = fmaxf(m_run, m1);
+            const float w0 = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run - M) * e.scale_l2);
+            const float w1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m1 - M) * e.scale_l2);
+            l_tot = w0 * l_tot + w1 * st[1];
+            m_run = M;
+            f32x4 o1[DB * 4];
+#pragma unroll
+            for (int i = 0; i < DB * 4; i++) o1[i] = box[i * 64];
+#pragma unroll
+            for (int db = 0; db < DB; db++)
+#pragma unroll
+                for (int i = 0; i < 16; i++) oacc[db][i] = w0 * oacc[db][i] + w1 * o1[db * 4 + i / 4][i % 4];
+        }
         {
             if (nparts > 1) {
                 // hand over (O unnormalised, row maximum, row sum); the part that arrives last merges
@@ -628,23 +696,20 @@ __global__ __launch_bounds__(kThreads, D == 64 && !SHARD ? 3 : 2) void attn_fwd_
 
 hipError_t launch_attn_fwd(const AttnArgs &a, int D, int grid, hipStream_t s)
 {
-    if (D == 128 && a.cu)
-        launch(attn_fwd_kernel<128, false, true>, a, grid, s);
+    if (a.halves && a.cu)
+        launch(D == 128 ? attn_fwd_kernel<128, false, true, 2> : attn_fwd_kernel<64, false, true, 2>, a, 2 * grid, s);
+    else if (a.halves)
+        launch(D == 128 ? attn_fwd_kernel<128, false, false, 2> : attn_fwd_kernel<64, false, false, 2>, a, 2 * grid, s);
     else if (a.cu)
-        launch(attn_fwd_kernel<64, false, true>, a, grid, s);
-    else if (D == 128)
-        launch(attn_fwd_kernel<128, false, false>, a, grid, s);
+        launch(D == 128 ? attn_fwd_kernel<128, false, true, 1> : attn_fwd_kernel<64, false, true, 1>, a, grid, s);
     else
-        launch(attn_fwd_kernel<64, false, false>, a, grid, s);
+        launch(D == 128 ? attn_fwd_kernel<128, false, false, 1> : attn_fwd_kernel<64, false, false, 1>, a, grid, s);
     return hipGetLastError();
 }
 
 hipError_t launch_attn_fwd_kvshard(const AttnArgs &a, int D, int grid, hipStream_t s)
 {
-    if (D == 128)
-        launch(attn_fwd_kernel<128, true, false>, a, grid, s);
-    else
-        launch(attn_fwd_kernel<64, true, false>, a, grid, s);
+    launch(D == 128 ? attn_fwd_kernel<128, true, false, 1> : attn_fwd_kernel<64, true, false, 1>, a, grid, s);
     return hipGetLastError();
 }
 

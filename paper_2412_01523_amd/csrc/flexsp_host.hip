@@ -1173,6 +1173,8 @@ int flexsp_attn_varlen_fwd(flexsp_ctx *ctx, flexsp_plan *plan, flexsp_tensor q, 
     a.T = (int32_t)plan->T; a.Hq = plan->Hq; a.G = plan->Hq / plan->Hkv; a.causal = plan->causal;
     a.scale = scale; a.scale_l2 = scale * 1.4426950408889634f;
     a.pq = plan->dq[FLEXSP_PASS_FWD];
+    const HostPass &fwd = plan->pass[FLEXSP_PASS_FWD];
+    a.halves = !fwd.direct.empty() && fwd.records == 0 && fwd_halves(plan->D, plan->T, plan->B, plan->Hq, ctx->num_cu);
     hipError_t e;
     {
         Timed tm(ctx, FLEXSP_K_FWD, (hipStream_t)stream);

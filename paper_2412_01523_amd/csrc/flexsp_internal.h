@@ -36,6 +36,7 @@ constexpr int kShortPartSteps = 4;  // ... where a backward would leave compute 
 constexpr int kGroupMajorSteps = 24;  // sequences whose longest tile has at most this many steps are queued tile beside tile
 constexpr int kLongPartSteps = 160;  // parts at least this long are aimed at 35 % of an even share instead of 75 %
 constexpr int kMaxParts = 8;
+constexpr int kSplitSteps = 4;  // a forward in halves (attn_fwd_kernel) splits walks of at least this many steps
 constexpr int kMaxSplitRecords = 2048;
 
 // Work item of the key-shard forward: query rows q_start .. q_start+q_len-1 of q / o / lse, shard
@@ -86,6 +87,7 @@ struct AttnArgs {
     // a forward without a list of items: every workgroup finds its own in the lengths (device; null: pq holds a list)
     const int32_t *cu;
     int32_t B;
+    int32_t halves;  // a forward in halves (two workgroups per item, whole tiles; see attn_fwd_kernel)
 };
 
 // Launchers implemented next to their kernels.  All are asynchronous on `s`.
@@ -105,6 +107,19 @@ hipError_t launch_attn_bwd_dkv(const AttnArgs &a, int D, int grid, hipStream_t s
 hipError_t launch_attn_bwd_dq(const AttnArgs &a, int D, int grid, hipStream_t s);
 hipError_t launch_attn_bwd_dkv_kvshard(const AttnArgs &a, int D, int grid, hipStream_t s);  // a.pq.items: flexsp_shard_item;
 hipError_t launch_attn_bwd_dq_kvshard(const AttnArgs &a, int D, int grid, hipStream_t s);   // a.grad_f32 bit 1: add to dq / dk / dv
+
+// Whether a forward of whole tiles runs in halves (attn_fwd_kernel): chains long enough to be worth a hand-over, and room for
+// twice the workgroups, of which a compute unit takes one with D = 128 (128 KiB of LDS), two with D = 64.  Decided from the
+// numbers that both flexsp_attn_varlen_fwd and flexsp_attn_varlen_fwd_static know, so that a batch whose tiles the plan does not cut
+// has the same bits with and without a plan.  Forward without a plan, whole items -> halves, one sequence: 512 tokens, 8 heads 12.2 ->
+// 11.5 us; 1 024, 8 heads 18.2 -> 15.2; 3 000, 4 heads 39.9 -> 28.5; 900, 16 heads (144 possible items) 16.7 -> 15.5; 9 632 tokens of long-tail
+// lengths, 2 heads 61.0 -> 43.3; D = 64: 700, 2 heads 10.4 -> 10.2; 4 000, 4 heads 36.0 -> 26.1.  On the other side: 400 tokens, 16 heads 10.8 ->
+// 11.6; 3 500, 8 heads (232) 46.9 -> 50.3; 1 201 tokens in short sequences, 16 heads 12.1 -> 19.0.
+inline bool fwd_halves(int32_t D, int64_t T, int64_t B, int64_t heads, int num_cu)
+{
+    const int64_t items = ((T + kFwdBq - 1) / kFwdBq + B) * heads;  // at most
+    return T >= 512 * B && (D == 128 ? 3 * items <= 2 * num_cu : items <= num_cu);
+}
 
 // Host helpers shared by the files that hold entry points.
 int ctx_device(const flexsp_ctx *ctx);        // HIP device of a context, -1 for a host-only one

@@ -246,6 +246,7 @@ extern "C" int flexsp_attn_varlen_fwd_static(flexsp_ctx *ctx, flexsp_tensor q, f
     if (!listed) {
         a.cu = cu_seqlens_dev;
         a.B = B;
+        a.halves = fwd_halves(D, T, B, head_count, flexsp_ctx_num_cu(ctx));
         e = launch_attn_fwd(a, D, (int)most_items, s);
         return e == hipSuccess ? FLEXSP_OK : hip_status(e);
     }
