@@ -209,17 +209,18 @@ struct Work {
     flexsp_item it;
     int64_t cost;   // inner-loop steps of this item
     int32_t group;  // (sequence, head) group id
+    int32_t keep;   // what is kept on one queue: the group, or the parts of one number of its cut tiles
 };
 
 void distribute(std::vector<Work> &work, const std::vector<int64_t> &group_cost, int nq, int n_wg, int tile_rows,
-                HostPass &out, int spare = 0);
+                HostPass &out, int spare = 0, int64_t row_bytes = 0, int heads_walked = 1);
 
 // Builds one pass: lists the items, spreads whole (sequence, head) groups over the queues
 // (largest group first onto the least loaded queue, so tiles that read the same K/V run on
 // one XCD and share its L2), then orders each queue by decreasing cost (short sequences: tile beside tile, see distribute) so that the long
 // tail of a batch starts first and short items fill the gaps at the end.
 void build_pass(const std::vector<int32_t> &cu, int B, int heads, int group_mult, int tile_rows,
-                int step_rows, bool causal, bool key_major, int nq, int n_wg, HostPass &out)
+                int step_rows, bool causal, bool key_major, int D, int nq, int n_wg, HostPass &out)
 {
     std::vector<Work> work;
     std::vector<int64_t> group_cost;
@@ -260,7 +261,7 @@ void build_pass(const std::vector<int32_t> &cu, int B, int heads, int group_mult
             group_cost.push_back(gc);
         }
     }
-    distribute(work, group_cost, nq, n_wg, tile_rows, out);
+    distribute(work, group_cost, nq, n_wg, tile_rows, out, 0, 2 * 2 * D, group_mult);  // (two bf16 tensors)
 }
 
 // Cuts tiles that would outlast an even share of the pass into parts (see flexsp_item): with W =
@@ -289,11 +290,19 @@ void cut_part(flexsp_item &it, int64_t c, int p, int k, int32_t slot)
     it.slot = slot;
     it.parts = (p << 16) | k;
 }
-void split_long_items(std::vector<Work> &work, int n_wg, int spare, HostPass &out)
+// Parts of the same number walk about the same rows, parts of one tile do not.  So where a group walks more rows than an XCD's L2 holds
+// beside everything else (`row_bytes` of them each, kPartAffinityBytes in all), the parts of one number are kept on one queue instead of
+// the whole group (`keep`, whose costs are returned).  Forward and backward, by group -> by part: 16 384 tokens, 4 heads 1 274 -> 1 191
+// us; two sequences of 20 000 tokens, 2 heads 1 753 -> 1 700; the 32K-token log-normal step (longest sequence 7 821) 627 -> 608; but
+// sequences of 3 100 to 5 100 tokens, 2 heads 307 -> 318, all of whose rows a group keeps in L2.  One group alone is spread over
+// all queues (32 768 tokens, 1 head 1 246 -> 1 271 by part), unless its parts are its heads (8 192 tokens, 8 heads on 1 720 -> 676).
+std::vector<int64_t> split_long_items(std::vector<Work> &work, std::vector<int64_t> keep_cost, int n_wg, int spare, int64_t row_bytes, int heads_walked,
+                                      HostPass &out)
 {
     out.records = 0;
     int64_t total = 0;
     for (Work &w : work) {
+        w.keep = w.group;
         w.it.step_begin = 0;
         w.it.step_end = (int32_t)w.cost;
         w.it.slot = -1;
@@ -303,10 +312,17 @@ void split_long_items(std::vector<Work> &work, int n_wg, int spare, HostPass &ou
     const int64_t share = total / std::max(n_wg, 1);
     const int64_t target = std::max<int64_t>(part_length(share), kMinPartSteps);
     const size_t n0 = work.size();
+    auto parts_of = [&](int64_t c) { return c <= spare * share ? 1 : part_count(c, target, kMinPartSteps); };
+    std::vector<int32_t> by_part(keep_cost.size(), -1);  // a cut group's first number beyond the groups'
+    int32_t groups_cut = 0;
+    for (const Work &w : work)
+        if (by_part[w.group] < 0 && row_bytes * heads_walked * w.it.seq_len > kPartAffinityBytes && parts_of(w.cost) > 1)
+            by_part[w.group] = (int32_t)keep_cost.size() + groups_cut++ * kMaxParts;
+    if (groups_cut == 1 && heads_walked == 1) std::fill(by_part.begin(), by_part.end(), -1);
+    keep_cost.resize(keep_cost.size() + (size_t)groups_cut * kMaxParts, 0);
     for (size_t i = 0; i < n0; i++) {
         const int64_t c = work[i].cost;
-        if (c <= spare * share) continue;
-        const int k = part_count(c, target, kMinPartSteps);
+        const int k = parts_of(c);
         if (k < 2 || out.records + k > kMaxSplitRecords) continue;
         const int32_t slot = out.records;
         out.records += k;
@@ -314,44 +330,50 @@ void split_long_items(std::vector<Work> &work, int n_wg, int spare, HostPass &ou
             Work w = work[i];
             cut_part(w.it, c, p, k, slot);
             w.cost = w.it.step_end - w.it.step_begin;
+            if (by_part[w.group] >= 0) {
+                keep_cost[w.group] -= w.cost;
+                w.keep = by_part[w.group] + p;
+                keep_cost[w.keep] += w.cost;
+            }
             if (p == 0)
                 work[i] = w;
             else
                 work.push_back(w);
         }
     }
+    return keep_cost;
 }
 
 // Spreads listed work over the queues and orders every queue longest first (see build_pass).
 void distribute(std::vector<Work> &work, const std::vector<int64_t> &group_cost, int nq, int n_wg, int tile_rows,
-                HostPass &out, int spare)
+                HostPass &out, int spare, int64_t row_bytes, int heads_walked)
 {
-    split_long_items(work, n_wg, spare, out);
+    const std::vector<int64_t> keep_cost = split_long_items(work, group_cost, n_wg, spare, row_bytes, heads_walked, out);
     out.steps = out.longest = 0;
     for (const Work &w : work) {
         out.steps += w.cost;
         out.longest = std::max(out.longest, w.cost);
     }
-    // groups -> queues
-    std::vector<int32_t> order(group_cost.size());
+    // what is kept together -> queues
+    std::vector<int32_t> order(keep_cost.size());
     for (size_t i = 0; i < order.size(); i++) order[i] = (int32_t)i;
     std::stable_sort(order.begin(), order.end(),
-                     [&](int32_t a, int32_t b) { return group_cost[a] > group_cost[b]; });
+                     [&](int32_t a, int32_t b) { return keep_cost[a] > keep_cost[b]; });
     std::vector<int64_t> load(nq, 0);
-    std::vector<int32_t> queue_of(group_cost.size(), 0);
+    std::vector<int32_t> queue_of(keep_cost.size(), 0);
     for (int32_t g : order) {
         int best = 0;
         for (int x = 1; x < nq; x++)
             if (load[x] < load[best]) best = x;
         queue_of[g] = best;
-        load[best] += group_cost[g];
+        load[best] += keep_cost[g];
     }
     // item -> queue: its group's queue.  Each queue's members are kept in order of decreasing
     // cost; the order comes from one stable counting sort of all items (costs are small integers),
     // not from comparison sorts: a plan is built per micro-batch, on the host's time.
     const size_t n = work.size();
     std::vector<int32_t> item_queue(n);
-    for (size_t i = 0; i < n; i++) item_queue[i] = queue_of[work[i].group];
+    for (size_t i = 0; i < n; i++) item_queue[i] = queue_of[work[i].keep];
     std::vector<int32_t> by_cost(n);  // item indices, most expensive first, ties in list order
     {
         int64_t maxc = 0;
@@ -871,10 +893,10 @@ int flexsp_plan_create(flexsp_ctx *ctx, const int32_t *cu, int32_t B, int32_t Hq
     try {
         p->cu.assign(cu, cu + B + 1);
         const int nq = ctx->num_xcd, n_wg = workgroups_of(ctx);
-        build_pass(p->cu, B, Hq, 1, kFwdBq, kFwdBk, causal != 0, false, nq, n_wg, p->pass[FLEXSP_PASS_FWD]);
+        build_pass(p->cu, B, Hq, 1, kFwdBq, kFwdBk, causal != 0, false, D, nq, n_wg, p->pass[FLEXSP_PASS_FWD]);
         p->wide = wide_keys(p, n_wg);
-        build_pass(p->cu, B, Hkv, Hq / Hkv, p->wide ? kDkvWideBk : kDkvBk, kDkvBq, causal != 0, true, nq, n_wg, p->pass[FLEXSP_PASS_BWD_DKV]);
-        build_pass(p->cu, B, Hq, 1, kDqBq, kDqBk, causal != 0, false, nq, n_wg, p->pass[FLEXSP_PASS_BWD_DQ]);
+        build_pass(p->cu, B, Hkv, Hq / Hkv, p->wide ? kDkvWideBk : kDkvBk, kDkvBq, causal != 0, true, D, nq, n_wg, p->pass[FLEXSP_PASS_BWD_DKV]);
+        build_pass(p->cu, B, Hq, 1, kDqBq, kDqBk, causal != 0, false, D, nq, n_wg, p->pass[FLEXSP_PASS_BWD_DQ]);
         for (int i = 0; i < 3; i++) direct_list(p->pass[i], nq, n_wg, 0, i == FLEXSP_PASS_FWD ? 0 : kShortPartSteps);
     } catch (const std::bad_alloc &) {
         delete p;

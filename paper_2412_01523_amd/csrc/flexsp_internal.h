@@ -36,6 +36,7 @@ constexpr int kShortPartSteps = 4;  // ... where a backward would leave compute 
 constexpr int kGroupMajorSteps = 24;  // sequences whose longest tile has at most this many steps are queued tile beside tile
 constexpr int kLongPartSteps = 160;  // parts at least this long are aimed at 35 % of an even share instead of 75 %
 constexpr int kMaxParts = 8;
+constexpr int64_t kPartAffinityBytes = (int64_t)7 << 19;  // 3.5 MiB of an XCD's 4 MiB of L2 (see split_long_items)
 constexpr int kSplitSteps = 4;  // a forward in halves (attn_fwd_kernel) splits walks of at least this many steps
 constexpr int kMaxSplitRecords = 2048;
 
