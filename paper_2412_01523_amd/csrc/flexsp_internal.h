@@ -114,12 +114,13 @@ hipError_t launch_attn_bwd_dq_kvshard(const AttnArgs &a, int D, int grid, hipStr
 // numbers that both flexsp_attn_varlen_fwd and flexsp_attn_varlen_fwd_static know, so that a batch whose tiles the plan does not cut
 // has the same bits with and without a plan.  Forward without a plan, whole items -> halves, one sequence: 512 tokens, 8 heads 12.2 ->
 // 11.5 us; 1 024, 8 heads 18.2 -> 15.2; 3 000, 4 heads 39.9 -> 28.5; 900, 16 heads (144 possible items) 16.7 -> 15.5; 9 632 tokens of long-tail
-// lengths, 2 heads 61.0 -> 43.3; D = 64: 700, 2 heads 10.4 -> 10.2; 4 000, 4 heads 36.0 -> 26.1.  On the other side: 400 tokens, 16 heads 10.8 ->
-// 11.6; 3 500, 8 heads (232) 46.9 -> 50.3; 1 201 tokens in short sequences, 16 heads 12.1 -> 19.0.
+// lengths, 2 heads 61.0 -> 43.3; D = 64: 700, 2 heads 10.4 -> 10.2; 4 000, 4 heads 36.0 -> 26.1; 5 000, 8 heads (328) 49.6 -> 47.8.  On the other
+// side: 400 tokens, 16 heads 10.8 -> 11.6; 3 500, 8 heads (232) 46.9 -> 50.3; 1 201 tokens in short sequences, 16 heads 12.1 -> 19.0; D = 64: 3 000,
+// 16 heads (400) 34.5 -> 35.7.
 inline bool fwd_halves(int32_t D, int64_t T, int64_t B, int64_t heads, int num_cu)
 {
     const int64_t items = ((T + kFwdBq - 1) / kFwdBq + B) * heads;  // at most
-    return T >= 512 * B && (D == 128 ? 3 * items <= 2 * num_cu : items <= num_cu);
+    return T >= 512 * B && (D == 128 ? 3 * items <= 2 * num_cu : 2 * items <= 3 * num_cu);
 }
 
 // Host helpers shared by the files that hold entry points.

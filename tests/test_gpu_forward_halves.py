@@ -19,13 +19,23 @@ pytestmark = pytest.mark.gpu
     ([897, 640], 4, 1, None), ([1984], 3, 1, None), ([3000], 1, 1, None), ([1500], 2, 2, (1100, 48.0)), ([1500], 2, 2, (40, 64.0)),
 ], ids=lambda x: str(x).replace(" ", ""))
 def test_forward_in_halves(lens, hq, hkv, outgrow, D, causal):
+    _check(lens, hq, hkv, outgrow, D, causal)
+
+
+def test_forward_in_halves_with_more_items_than_compute_units():
+    """Short rows: a compute unit holds a workgroup and a half of the items' pairs before whole items are the better ones."""
+    _check([1999], 16, 4, None, 64, True)
+
+
+def _check(lens, hq, hkv, outgrow, D, causal):
     import torch
     from paper_2412_01523_amd import binding as fx
     print(f"forward in halves: {lens}, {hq} heads on {hkv}, D={D}, causal={causal}, {outgrow}", flush=True)
     ctx = fx.Context(0)
     cu, T = wl.cu_seqlens(lens), sum(lens)
     # the line the choice is made by (see fwd_halves): the cases lie on its near side
-    assert T >= 512 * len(lens) and 3 * (-(-T // 128) + len(lens)) * hq <= 2 * ctx.num_cu
+    items = (-(-T // 128) + len(lens)) * hq
+    assert T >= 512 * len(lens) and (3 * items <= 2 * ctx.num_cu or D == 64 and ctx.num_cu < items and 2 * items <= 3 * ctx.num_cu)
     q = wl.normal_bf16(941, wl.TID_Q, (T, hq, D))
     k, v = (wl.normal_bf16(941, tid, (T, hkv, D)) for tid in (wl.TID_K, wl.TID_V))
     if outgrow:
