@@ -335,7 +335,8 @@ int flexsp_lse_merge_acc(flexsp_ctx *ctx, flexsp_tensor o_acc, float *lse_acc, f
 
 /*
  * The forward for callers that cannot allocate: code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc.  Same result as flexsp_attn_varlen_fwd, bit for bit, but it takes
+ * harnesses that forbid hipMalloc.  Same result as flexsp_attn_varlen_fwd, bit for bit where the plan
+ * cuts no tile into parts (cut tiles are summed in another order), however many rows beyond cu[B] the tensors hold.  It takes
  * no plan and calls no hipMalloc, hipFree or any other allocating routine: the work is listed
  * on the device from `cu_seqlens_dev` (device pointer, B+1 int32 prefix sums, cu[0] = 0,
  * non-decreasing, cu[B] <= T).  A batch of more possible items, (ceil(T / 128) + B) * head_count, than

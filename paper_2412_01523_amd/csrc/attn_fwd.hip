@@ -72,6 +72,56 @@ __device__ __forceinline__ bool find_item(const int32_t *cu, int B, int T, int h
     return true;
 }
 
+// The lengths of a batch of at most 64 sequences, a lane each, where they also say whether the batch runs in halves: find_item for
+// tiles of either size from one look at them, one chain of exchanges.
+template <int D>
+struct ShortBatch {
+    int lo, hi;
+    uint32_t n, upto;  // tiles of kHalfBq rows | tiles of kFwdBq rows << 16: this lane's, and with those of the earlier ones
+    bool bad, halves;
+
+    __device__ __forceinline__ ShortBatch(KernArgs &a, int lane)
+    {
+        const int32_t *cu = a.cu;
+        const int B = a.B, heads = a.Hq;
+        lo = lane < B ? cu[lane] : 0, hi = lane < B ? cu[lane + 1] : 0;
+        const int first = cu[0], total = cu[B];
+        const bool wrong = lo < 0 || hi < lo || hi > a.T;
+        bad = first != 0 || __builtin_amdgcn_ballot_w64(wrong) != 0;
+        const int len = wrong ? 0 : hi - lo, h = (len + kHalfBq - 1) / kHalfBq;
+        n = upto = h | (len + kFwdBq - 1) / kFwdBq << 16;
+        int steps = a.causal ? h * (h + 1) / 2 : h * h, longest = h;
+#pragma unroll
+        for (int d = 1; d < 64; d *= 2) {
+            const uint32_t x = __shfl_up(upto, d);
+            if (lane >= d) upto += x;
+            steps += __shfl_xor(steps, d);
+            longest = max(longest, __shfl_xor(longest, d));
+        }
+        const int tiles = __builtin_amdgcn_readlane(upto, 63) & 0xffff;
+        steps = __builtin_amdgcn_readfirstlane(steps);
+        longest = __builtin_amdgcn_readfirstlane(longest);
+        halves = fwd_halves(D, {total, B, (int64_t)tiles * heads, (int64_t)steps * heads, longest}, a.num_cu);
+    }
+    __device__ __forceinline__ bool item(KernArgs &a, int n_th, flexsp_item &it) const
+    {
+        const int pair = n_th / a.Hq, shift = halves ? 0 : 16, rows = halves ? kHalfBq : kFwdBq;
+        const int end = upto >> shift & 0xffff, mine = n >> shift & 0xffff;
+        const uint64_t owner = __builtin_amdgcn_ballot_w64(pair >= end - mine && pair < end);
+        if (bad || !owner) return false;
+        const int l = __builtin_ctzll(owner);
+        it.seq_start = __builtin_amdgcn_readlane(lo, l);
+        it.seq_len = __builtin_amdgcn_readlane(hi, l) - it.seq_start;
+        it.tile = pair - __builtin_amdgcn_readlane(end - mine, l);
+        it.head = n_th - pair * a.Hq;
+        it.step_begin = 0;
+        it.step_end = ((a.causal ? min(it.seq_len, (it.tile + 1) * rows) : it.seq_len) + kFwdBk - 1) / kFwdBk;
+        it.slot = -1;
+        it.parts = 1;
+        return true;
+    }
+};
+
 // SHARD = true is the variant for one shard of the keys (context parallelism): a work item then
 // names separate query and key ranges and an offset `shift` between their positions, key j is
 // visible to query row i iff j <= i + shift (when causal), rows may see no key at all (O = 0,
@@ -85,10 +135,24 @@ __device__ __forceinline__ bool find_item(const int32_t *cu, int B, int T, int h
 // wavefronts to each block of 32 rows: wavefronts 0 and 1 walk the first half of the key tiles, 2 and 3 the second, each pair with
 // tiles of its own, and hand over through LDS.  Such a launch lasts as long as its longest item's chain of steps, and a step lasts
 // as long as one wavefront's matrix instructions; a hand-over through memory costs what the shorter chain saves.
-template <int D, bool SHARD, bool FIND, int HALVES>
-__global__ __launch_bounds__(kThreads, HALVES == 2 ? 1 : D == 64 && !SHARD ? 3 : 2) void attn_fwd_kernel(const AttnArgs)
+//
+// BUFS = 1 has one buffer for K and one for V instead of two and waits for every tile: halves with the LDS of whole items, for launches
+// sized for those whose batch turns out to be one for halves.
+template <int D, int HALVES, int BUFS>
+constexpr int fwd_lds()  // bytes of LDS of the pass: [K buffers | V buffers], each half of the wavefronts its own
+{
+    return HALVES * 2 * BUFS * kFwdBk * LdsTile<D>::ROWB;
+}
+template <int HALVES>
+constexpr int fwd_stats()  // floats of LDS for the second half's row maxima and sums
+{
+    return HALVES == 2 ? kThreads : 2;
+}
+template <int D, bool SHARD, bool FIND, int HALVES, int BUFS = 2>
+__device__ __forceinline__ void fwd_pass(KernArgs &args, const flexsp_item &found, char *const smem, float *const stats, int &deal_word, int &split_word)
 {
     static_assert(HALVES == 1 || !SHARD, "no list of a shard's launch asks for it");
+    static_assert(BUFS == 2 || HALVES == 2, "whole items have two buffers");
     typedef LdsTile<D> L;
     constexpr int KS = D / 16;                  // k steps of the score product
     constexpr int DB = D / 32;                  // 32-wide blocks of the head dim
@@ -98,35 +162,31 @@ __global__ __launch_bounds__(kThreads, HALVES == 2 ? 1 : D == 64 && !SHARD ? 3 :
     constexpr int NCP = 2 * kFwdBk * L::CH / NT;  // copy instructions per wavefront for a K and a V tile
     constexpr int NSLOT = KS + 2 * DB;          // matrix instructions of one pipeline iteration
     static_assert(NSLOT * HALVES == 2 * NCP, "one copy instruction per two matrix instructions, or per one");
-    // [K buffer 0 | K buffer 1 | V buffer 0 | V buffer 1]
-    __shared__ __attribute__((aligned(1024))) char smem[HALVES * 4 * TILE];  // (each half of the wavefronts its own)
+    constexpr int REGION = 2 * BUFS * TILE;     // LDS of a half of the wavefronts
+    static_assert(fwd_lds<D, HALVES, BUFS>() == HALVES * REGION && fwd_stats<HALVES>() >= HALVES * NT * (HALVES - 1), "LDS of the pass");
 
     const int tid = thread_id();
     const int lane0 = tid & 63;
     const int wave4 = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave = HALVES == 2 ? wave4 & 1 : wave4, half = HALVES == 2 ? wave4 >> 1 : 0;
-    char *const mine = smem + half * 4 * TILE;  // for copies and stores; reads of tiles have the half in their lane offsets:
+    char *const mine = smem + half * REGION;  // for copies and stores; reads of tiles have the half in their lane offsets:
     LaneOffsets<D> lo;
     lo.init(lane0);
     if constexpr (HALVES == 2) {
 #pragma unroll
-        for (int ks = 0; ks < KS; ks++) lo.nat[ks] += half * 4 * TILE;
+        for (int ks = 0; ks < KS; ks++) lo.nat[ks] += half * REGION;
 #pragma unroll
-        for (int db = 0; db < DB; db++) lo.tr[db][0] += half * 4 * TILE, lo.tr[db][1] += half * 4 * TILE;
+        for (int db = 0; db < DB; db++) lo.tr[db][0] += half * REGION, lo.tr[db][1] += half * REGION;
     }
-    __shared__ __attribute__((aligned(8))) float stats[HALVES == 2 ? 2 * NT : 2];  // the second half's row maxima and sums
-    __shared__ int deal_word, split_word;
     ItemDealer deal;
-    KernArgs &args = kernel_args();
 
-    flexsp_item found;
     int item;
     if constexpr (FIND) {
         deal.direct = true;
-        item = find_item(args.cu, args.B, args.T, args.Hq, args.causal, workgroup_id() / HALVES, lane0, found) ? 0 : -1;
+        item = 0;
     } else if constexpr (HALVES == 2) {
         deal.direct = true;
-        item = workgroup_id() / HALVES;
+        item = workgroup_id();
     } else {
         item = deal.first(args.pq, args.grid, 0, &deal_word, wave, lane0);
     }
@@ -145,7 +205,7 @@ __global__ __launch_bounds__(kThreads, HALVES == 2 ? 1 : D == 64 && !SHARD ? 3 :
         } else {
             flexsp_item it;
             if constexpr (FIND) it = uniform_item(found); else it = load_item(a.pq.items, item);
-            s = it.seq_len; sk = s; shift = 0; h = it.head; q0 = it.tile * kFwdBq;
+            s = it.seq_len; sk = s; shift = 0; h = it.head; q0 = it.tile * BQ;
             tok0 = it.seq_start; ktok0 = tok0;
             part = it.parts >> 16; nparts = it.parts & 0xffff; slot = it.slot;
             t_lo = it.step_begin; t_hi = it.step_end;
@@ -157,10 +217,6 @@ __global__ __launch_bounds__(kThreads, HALVES == 2 ? 1 : D == 64 && !SHARD ? 3 :
         lane &= 63;  // (its range is known again: divisions by the pieces of a row are shifts)
         const int r = lane & 31, hl = lane >> 5;
         const int g = h / a.G;
-        if constexpr (HALVES == 2) {
-            q0 += workgroup_id() % HALVES * BQ;
-            if (q0 >= s) continue;
-        }
         // keys this item needs
         int kv_end = SHARD ? (a.causal ? max(0, min(sk, q0 + BQ + shift)) : sk)
                            : (a.causal ? min(s, q0 + BQ) : s);
@@ -238,7 +294,7 @@ __global__ __launch_bounds__(kThreads, HALVES == 2 ? 1 : D == 64 && !SHARD ? 3 :
                 load_tile_async<D, kFwdBk, NT>(dst, kbase, a.k_st, t * kFwdBk, sk - 1, wave, lane);
         };
         auto prefetch_v = [&](int t, int buf) {
-            char *dst = mine + (2 + buf) * TILE;
+            char *dst = mine + (BUFS + buf) * TILE;
             if ((t + 1) * kFwdBk <= sk)
 #pragma unroll
                 for (int n = 0; n < NCP / 2; n++) copy_one(dst, vbase + (int64_t)t * kFwdBk * a.v_st, a.v_st, goffv, n);
@@ -399,7 +455,7 @@ __global__ __launch_bounds__(kThreads, HALVES == 2 ? 1 : D == 64 && !SHARD ? 3 :
             constexpr bool PF = decltype(pfc)::value != 0;
             constexpr int AH = 4;
             const char *sK = smem + KB * TILE + (CP ? 0 : 32 * L::ROWB);
-            const char *sV = smem + (2 + VB) * TILE + (CP ? 0 : 32 * L::ROWB);
+            const char *sV = smem + (BUFS + VB) * TILE + (CP ? 0 : 32 * L::ROWB);
             f32x16 &sn = sacc[CP ^ 1];
             const f32x16 &sc = sacc[CP];
             const uint32_t(&pp)[8] = pk[CP ^ 1];
@@ -439,7 +495,7 @@ __global__ __launch_bounds__(kThreads, HALVES == 2 ? 1 : D == 64 && !SHARD ? 3 :
                     if (n < NCP / 2)
                         copy_one(mine + (KB ^ 1) * TILE, kbase + (int64_t)(t + 2) * kFwdBk * a.k_st, a.k_st, goffk, n);
                     else
-                        copy_one(mine + (2 + (VB ^ 1)) * TILE, vbase + (int64_t)(t + 1) * kFwdBk * a.v_st, a.v_st, goffv, n - NCP / 2);
+                        copy_one(mine + (BUFS + (VB ^ 1)) * TILE, vbase + (int64_t)(t + 1) * kFwdBk * a.v_st, a.v_st, goffv, n - NCP / 2);
                 }
                 {
                     constexpr int NE = NSLOT;  // every slot carries its share of the 16 exponentials
@@ -466,39 +522,51 @@ __global__ __launch_bounds__(kThreads, HALVES == 2 ? 1 : D == 64 && !SHARD ? 3 :
         // ---------------- pipeline fill: K tile 0 -> S(0), then iteration 0 --------------------
         // (the Q rows pass through this wavefront's quarter of the V buffers, which are idle until the
         // barrier: V tile 0 is requested after it)
-        qrows.fragments(smem + 2 * TILE + wave * (32 * L::ROWB), half * 4 * kFwdBk, lo, qf, lane);
+        qrows.fragments(smem + BUFS * TILE + wave * (32 * L::ROWB), half * (REGION / L::ROWB), lo, qf, lane);
         wait_vmem();
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the fragments are in registers
         __syncthreads();
         // (short items draw their ticket here, long ones near their end: see window())
         const int draw_t = ntiles >= kLateTicketSteps ? ntiles - 2 : -1;
         if (draw_t < 0) deal.prefetch();
-        if (ntiles > 1) prefetch_k(1, 1);
-        if (HALVES == 1 || ntiles > 0) prefetch_v(0, 0);
+        if constexpr (BUFS == 2) {
+            if (ntiles > 1) prefetch_k(1, 1);
+            if (HALVES == 1 || ntiles > 0) prefetch_v(0, 0);
+        }
         if (cmax >= 0) scores(sacc[0], smem);
         iter_slow(ic<0>{}, 0, smem + 32 * L::ROWB, smem);
 
         // ---------------- window t: iterations 2t+1 and 2t+2 ------------------------------------
+        // (BUFS = 1: the tiles of window t, asked for when everybody is done with those before)
+        auto fetch_now = [&](int t) {
+            __syncthreads();
+            if (t + 1 < ntiles) prefetch_k(t + 1, 0);
+            prefetch_v(t, 0);
+        };
         // Steady state: both iterations pipelined, and the copies of K tile t+2 and V tile t+1 (both
         // wholly inside the sequence) ride along with iteration 2t+1.  No branch but the rare rescale.
         auto window_steady = [&](auto vbc, int t) {
-            constexpr int VB = decltype(vbc)::value, KB = VB ^ 1;  // V tile t in VB, K tile t+1 in KB
+            constexpr int VB = decltype(vbc)::value, KB = BUFS == 2 ? VB ^ 1 : 0;  // V tile t in VB, K tile t+1 in KB
             lo.pin();
+            if constexpr (BUFS == 1) fetch_now(t);
             wait_vmem();      // this wavefront's share of K tile t+1 and V tile t has landed
             __syncthreads();  // everybody's has, and everybody is done with K tile t and V tile t-1
-            iter_fast(ic<1>{}, ic<KB>{}, ic<VB>{}, ic<1>{}, t);
+            iter_fast(ic<1>{}, ic<KB>{}, ic<VB>{}, ic<BUFS == 2>{}, t);
             iter_fast(ic<0>{}, ic<KB>{}, ic<VB>{}, ic<0>{}, t);
         };
         // General form (pipeline fill and drain, masked block, ragged last tile): the copies go out in
         // one go after the barrier and the stages of an iteration run one after the other.  One copy
         // of the code for both buffer parities: the tile addresses are run-time values here.
         auto window = [&](int t) {
-            const int vb = t & 1, kb = vb ^ 1;  // V tile t in vb, K tile t+1 in kb
+            const int vb = BUFS == 2 ? t & 1 : 0, kb = BUFS == 2 ? vb ^ 1 : 0;  // V tile t in vb, K tile t+1 in kb
             lo.pin();
+            if constexpr (BUFS == 1) fetch_now(t);
             wait_vmem();      // this wavefront's share of K tile t+1 and V tile t has landed
             __syncthreads();  // everybody's has, and everybody is done with K tile t and V tile t-1
-            if (t + 2 < ntiles) prefetch_k(t + 2, kb ^ 1);
-            if (t + 1 < ntiles) prefetch_v(t + 1, vb ^ 1);
+            if constexpr (BUFS == 2) {
+                if (t + 2 < ntiles) prefetch_k(t + 2, kb ^ 1);
+                if (t + 1 < ntiles) prefetch_v(t + 1, vb ^ 1);
+            }
             // The ticket of the item after a LONG one is drawn in the item's last window but one: late enough
             // that the workgroup commits itself to another item only a few microseconds before it is
             // free for it (a ticket drawn when the item starts reserves the then-largest item for the
@@ -508,7 +576,7 @@ __global__ __launch_bounds__(kThreads, HALVES == 2 ? 1 : D == 64 && !SHARD ? 3 :
             // end, so it draws right after its first barrier (behind its first loads, not in front of
             // them: answers come back in request order).
             if (t == draw_t) deal.prefetch();
-            const char *sK = smem + kb * TILE, *sV = smem + (2 + vb) * TILE;
+            const char *sK = smem + kb * TILE, *sV = smem + (BUFS + vb) * TILE;
             iter_slow(ic<1>{}, 2 * t + 1, sK, sV);
             iter_slow(ic<0>{}, 2 * t + 2, sK + 32 * L::ROWB, sV + 32 * L::ROWB);
         };
@@ -518,7 +586,7 @@ __global__ __launch_bounds__(kThreads, HALVES == 2 ? 1 : D == 64 && !SHARD ? 3 :
         int t = 0;
         for (; t + 1 < tsteady; t += 2) {
             window_steady(ic<0>{}, t);
-            window_steady(ic<1>{}, t + 1);
+            window_steady(ic<BUFS == 2>{}, t + 1);
         }
         for (; t < ntiles; t++) window(t);
 
@@ -539,7 +607,7 @@ __global__ __launch_bounds__(kThreads, HALVES == 2 ? 1 : D == 64 && !SHARD ? 3 :
             for (int c = 0; c <= cmax; c++) {
                 RowBlock<D> blk;
                 blk.load(kbase, a.k_st, c * 32, sk - 1, lane);
-                blk.stage(block, half * 4 * kFwdBk, lane);
+                blk.stage(block, half * (REGION / L::ROWB), lane);
                 f32x16 &sa = sacc[0];
                 scores(sa, block);
                 if (SHARD ? c >= cmask : c == cmask) {
@@ -560,7 +628,7 @@ __global__ __launch_bounds__(kThreads, HALVES == 2 ? 1 : D == 64 && !SHARD ? 3 :
                     pk[0][i >> 1] = pack_bf16x2(p0, p1);
                 }
                 blk.load(vbase, a.v_st, c * 32, sk - 1, lane);
-                blk.stage(block, half * 4 * kFwdBk, lane);  // (after the reads of the K block: one wavefront's LDS instructions execute in order)
+                blk.stage(block, half * (REGION / L::ROWB), lane);  // (after the reads of the K block: one wavefront's LDS instructions execute in order)
                 finish_block(m_new, ps);   // O and the row sum move to the block's reference first
                 pv(pk[0], block);
             }
@@ -570,10 +638,10 @@ __global__ __launch_bounds__(kThreads, HALVES == 2 ? 1 : D == 64 && !SHARD ? 3 :
         KernArgs &e = fresh(args);
         float l_tot = halves_sum(l_run);
         if constexpr (HALVES == 2) {
-            for (int t = ntiles; t < windows; t++) __syncthreads();
+            for (int t = ntiles * (3 - BUFS); t < windows * (3 - BUFS); t++) __syncthreads();  // (BUFS = 1: two a window)
             // the second half's O (not normalised), row maximum and row sum, through its own tiles' LDS
             __syncthreads();  // (everybody is done with them)
-            f32x4 *const box = (f32x4 *)(smem + 4 * TILE) + wave * (DB * 4 * 64) + lane;
+            f32x4 *const box = (f32x4 *)(smem + REGION) + wave * (DB * 4 * 64) + lane;
             float *const st = stats + 2 * (wave * 64 + lane);
             if (half) {
 #pragma unroll
@@ -692,14 +760,59 @@ __global__ __launch_bounds__(kThreads, HALVES == 2 ? 1 : D == 64 && !SHARD ? 3 :
     deal.finish();
 }
 
+template <int D, bool SHARD, bool FIND, int HALVES>
+__global__ __launch_bounds__(kThreads, HALVES == 2 ? 1 : D == 64 && !SHARD ? 3 : 2) void attn_fwd_kernel(const AttnArgs)
+{
+    __shared__ __attribute__((aligned(1024))) char smem[fwd_lds<D, HALVES, 2>()];
+    __shared__ __attribute__((aligned(8))) float stats[fwd_stats<HALVES>()];
+    __shared__ int deal_word, split_word;
+    KernArgs &args = kernel_args();
+    flexsp_item found;
+    if constexpr (FIND) {
+        if (!find_item(args.cu, args.B, args.T, args.Hq, args.causal, workgroup_id(), thread_id() & 63, found)) return;
+    }
+    fwd_pass<D, SHARD, FIND, HALVES>(args, found, smem, stats, deal_word, split_word);
+}
+
+// The forward without a plan where only the lengths on the device tell whether the batch runs in halves: the host knows the rows that the
+// tensors hold, and the batch may be shorter.  Without a list (LIST = false) both kinds of items are found in the lengths; BUFS = 2
+// is for launches of so few items that a compute unit's LDS is theirs.  The builder of a list leaves it empty for a batch in halves.
+template <int D, int BUFS, bool LIST>
+__global__ __launch_bounds__(kThreads, D == 128 && BUFS == 2 ? 1 : 2) void attn_fwd_either_kernel(const AttnArgs)
+{
+    __shared__ __attribute__((aligned(1024))) char smem[fwd_lds<D, 2, BUFS>()];
+    static_assert(fwd_lds<D, 2, BUFS>() >= fwd_lds<D, 1, 2>(), "LDS of either pass");
+    __shared__ __attribute__((aligned(8))) float stats[fwd_stats<2>()];
+    __shared__ int deal_word, split_word;
+    KernArgs &args = kernel_args();
+    flexsp_item found;
+    if constexpr (LIST) {
+        if (args.pq.offsets[args.pq.nq] != 0) {
+            fwd_pass<D, false, false, 1>(args, found, smem, stats, deal_word, split_word);
+            return;
+        }
+    }
+    const ShortBatch<D> batch(args, thread_id() & 63);
+    if (batch.halves) {
+        for (int n = workgroup_id(); batch.item(args, n, found); n += args.grid) {
+            __syncthreads();  // (everybody is done with the LDS of the one before)
+            fwd_pass<D, false, true, 2, BUFS>(args, found, smem, stats, deal_word, split_word);
+        }
+    } else if (!LIST && batch.item(args, workgroup_id(), found)) {
+        fwd_pass<D, false, true, 1>(args, found, smem, stats, deal_word, split_word);
+    }
+}
+
 }  // namespace
 
 hipError_t launch_attn_fwd(const AttnArgs &a, int D, int grid, hipStream_t s)
 {
-    if (a.halves && a.cu)
-        launch(D == 128 ? attn_fwd_kernel<128, false, true, 2> : attn_fwd_kernel<64, false, true, 2>, a, 2 * grid, s);
+    if (a.halves && !a.cu)
+        launch(D == 128 ? attn_fwd_kernel<128, false, false, 2> : attn_fwd_kernel<64, false, false, 2>, a, grid, s);
+    else if (a.halves && a.pq.items)
+        launch(D == 128 ? attn_fwd_either_kernel<128, 1, true> : attn_fwd_either_kernel<64, 1, true>, a, grid, s);
     else if (a.halves)
-        launch(D == 128 ? attn_fwd_kernel<128, false, false, 2> : attn_fwd_kernel<64, false, false, 2>, a, 2 * grid, s);
+        launch(D == 64 ? attn_fwd_either_kernel<64, 2, false> : a.halves == 2 ? attn_fwd_either_kernel<128, 2, false> : attn_fwd_either_kernel<128, 1, false>, a, grid, s);
     else if (a.cu)
         launch(D == 128 ? attn_fwd_kernel<128, false, true, 1> : attn_fwd_kernel<64, false, true, 1>, a, grid, s);
     else

@@ -65,6 +65,7 @@ struct flexsp_plan {
     std::vector<int32_t> cu_k, shift;
     int64_t Tk = 0;
     bool wide = false;  // the dK/dV pass's items have kDkvWideBk keys
+    bool halves = false;  // the forward is launched in halves: its direct list has kHalfBq query rows to an item
     HostPass pass[3];
     // device side (null for host-only plans): one allocation, carved up
     void *dev_base;
@@ -528,6 +529,37 @@ void direct_list(HostPass &p, int nq, int n_wg, int spare, int64_t lowest)
     }
 }
 
+HalvesCount halves_count(const flexsp_plan *p)
+{
+    HalvesCount c = {p->T, p->B, 0, 0, 0};
+    for (int b = 0; b < p->B; b++) {
+        const int64_t n = cdiv(p->cu[b + 1] - p->cu[b], kHalfBq);
+        c.tiles += n * p->Hq;
+        c.steps += (p->causal ? n * (n + 1) / 2 : n * n) * p->Hq;
+        c.longest = std::max(c.longest, n);
+    }
+    return c;
+}
+
+// Whether the forward, launched with one workgroup per item and no tile cut, runs in halves (fwd_halves); if so, its list becomes one of
+// halves, a tile's one after the other.
+bool halve_items(flexsp_plan *p, int num_cu)
+{
+    HostPass &f = p->pass[FLEXSP_PASS_FWD];
+    const HalvesCount c = halves_count(p);
+    if (f.direct.empty() || f.records || !fwd_halves(p->D, c, num_cu)) return false;
+    std::vector<flexsp_item> halves;
+    halves.reserve((size_t)c.tiles);
+    for (flexsp_item it : f.direct)
+        for (int i = 0, first = it.tile * (kFwdBq / kHalfBq); i < kFwdBq / kHalfBq && (first + i) * kHalfBq < it.seq_len; i++) {
+            it.tile = first + i;
+            it.step_end = (int32_t)cdiv(p->causal ? std::min((it.tile + 1) * kHalfBq, it.seq_len) : it.seq_len, kFwdBk);
+            halves.push_back(it);
+        }
+    f.direct.swap(halves);
+    return true;
+}
+
 // Whether the dK/dV pass takes 128 keys an item (attn_bwd_dkv_wide_kernel; D = 64).  What it gives up: at a walk's start and end, and
 // where blocks are masked, its stages run one after the other, a causal walk begins with up to two steps of that kind, and
 // its items are half as many.  So not where the causal walks of a batch are under five steps on average (sequences
@@ -898,6 +930,7 @@ int flexsp_plan_create(flexsp_ctx *ctx, const int32_t *cu, int32_t B, int32_t Hq
         build_pass(p->cu, B, Hkv, Hq / Hkv, p->wide ? kDkvWideBk : kDkvBk, kDkvBq, causal != 0, true, D, nq, n_wg, p->pass[FLEXSP_PASS_BWD_DKV]);
         build_pass(p->cu, B, Hq, 1, kDqBq, kDqBk, causal != 0, false, D, nq, n_wg, p->pass[FLEXSP_PASS_BWD_DQ]);
         for (int i = 0; i < 3; i++) direct_list(p->pass[i], nq, n_wg, 0, i == FLEXSP_PASS_FWD ? 0 : kShortPartSteps);
+        p->halves = halve_items(p, n_wg / 2);
     } catch (const std::bad_alloc &) {
         delete p;
         return FLEXSP_OUT_OF_MEMORY;
@@ -1195,8 +1228,7 @@ int flexsp_attn_varlen_fwd(flexsp_ctx *ctx, flexsp_plan *plan, flexsp_tensor q, 
     a.T = (int32_t)plan->T; a.Hq = plan->Hq; a.G = plan->Hq / plan->Hkv; a.causal = plan->causal;
     a.scale = scale; a.scale_l2 = scale * 1.4426950408889634f;
     a.pq = plan->dq[FLEXSP_PASS_FWD];
-    const HostPass &fwd = plan->pass[FLEXSP_PASS_FWD];
-    a.halves = !fwd.direct.empty() && fwd.records == 0 && fwd_halves(plan->D, plan->T, plan->B, plan->Hq, ctx->num_cu);
+    a.halves = plan->halves;
     hipError_t e;
     {
         Timed tm(ctx, FLEXSP_K_FWD, (hipStream_t)stream);

@@ -85,10 +85,13 @@ struct AttnArgs {
     int32_t dq_wg, dkv_items, per_cu;
     int32_t wide;  // the dK/dV pass's items have kDkvWideBk keys
     int32_t grid;  // workgroups of the launch (filled in by the launchers)
-    // a forward without a list of items: every workgroup finds its own in the lengths (device; null: pq holds a list)
+    // a forward without a plan: the lengths (device), in which every workgroup finds its item unless pq holds a list
     const int32_t *cu;
     int32_t B;
-    int32_t halves;  // a forward in halves (two workgroups per item, whole tiles; see attn_fwd_kernel)
+    // a forward in halves: pq lists tiles of kHalfBq query rows; with cu: in halves if the lengths say so (attn_fwd_either_kernel, with that
+    // many buffers)
+    int32_t halves;
+    int32_t num_cu;  // (for that decision)
 };
 
 // Launchers implemented next to their kernels.  All are asynchronous on `s`.
@@ -109,18 +112,39 @@ hipError_t launch_attn_bwd_dq(const AttnArgs &a, int D, int grid, hipStream_t s)
 hipError_t launch_attn_bwd_dkv_kvshard(const AttnArgs &a, int D, int grid, hipStream_t s);  // a.pq.items: flexsp_shard_item;
 hipError_t launch_attn_bwd_dq_kvshard(const AttnArgs &a, int D, int grid, hipStream_t s);   // a.grad_f32 bit 1: add to dq / dk / dv
 
-// Whether a forward of whole tiles runs in halves (attn_fwd_kernel): chains long enough to be worth a hand-over, and room for
-// twice the workgroups, of which a compute unit takes one with D = 128 (128 KiB of LDS), two with D = 64.  Decided from the
-// numbers that both flexsp_attn_varlen_fwd and flexsp_attn_varlen_fwd_static know, so that a batch whose tiles the plan does not cut
-// has the same bits with and without a plan.  Forward without a plan, whole items -> halves, one sequence: 512 tokens, 8 heads 12.2 ->
-// 11.5 us; 1 024, 8 heads 18.2 -> 15.2; 3 000, 4 heads 39.9 -> 28.5; 900, 16 heads (144 possible items) 16.7 -> 15.5; 9 632 tokens of long-tail
-// lengths, 2 heads 61.0 -> 43.3; D = 64: 700, 2 heads 10.4 -> 10.2; 4 000, 4 heads 36.0 -> 26.1; 5 000, 8 heads (328) 49.6 -> 47.8.  On the other
-// side: 400 tokens, 16 heads 10.8 -> 11.6; 3 500, 8 heads (232) 46.9 -> 50.3; 1 201 tokens in short sequences, 16 heads 12.1 -> 19.0; D = 64: 3 000,
-// 16 heads (400) 34.5 -> 35.7.
-inline bool fwd_halves(int32_t D, int64_t T, int64_t B, int64_t heads, int num_cu)
+// Whether a forward of whole tiles runs in halves (see attn_fwd.hip).  Decided from what the batch itself holds: tokens, sequences, tiles
+// of 64 query rows (kHalfBq) over all heads, their key tiles, and the tiles of the longest sequence.  The plan and a launch without one
+// (on the device: attn_fwd_either_kernel) then agree whatever the tensors have room for, and a batch whose tiles the plan does not
+// cut has the same bits with and without a plan.
+// A walk has to be worth a hand-over (512 tokens a sequence), and all tiles at work at once, one per compute unit: a second turn costs
+// what the halves save.  Where a long sequence's tiles outlast the rest, more of them find room meanwhile: up to a third more tiles
+// with D = 128, three to a unit with D = 64, if all their steps are no more than the units take (D = 128: four fifths; D = 64, whose two
+// workgroups fill each other's waits, five quarters beside 5 120 tokens) while the
+// longest tile lasts whole.
+// Forward without a plan, whole items -> halves, one sequence: 512 tokens, 8 heads 13.0 -> 11.7 us; 1 024, 8 heads 19.3 -> 15.6; 3 000, 4
+// heads 40.8 -> 28.3; 5 248, 4 heads 68.0 -> 56.2; not causal 2 000, 8 heads 32.9 -> 26.4; D = 64: 700, 2 heads 11.1 -> 10.4; 4 000, 4 heads
+// 38.6 -> 26.6; four sequences, one of 15 911, 1 head, not causal 153 -> 95; 261 drawn batches 1.01 to 1.76 times as fast, 1.32 on average.
+// Beyond the lines (in a build whose halves took 5 % longer): not causal 2 176, 8 heads 32.6 -> 46.9; 1 152, 16 heads 20.6 -> 31.9, causal
+// 20.7 -> 24.2; 5 248, 4 heads 73 -> 93; D = 64: 3 600, 8 heads, not causal 37.8 -> 43.1.
+inline constexpr int kHalfBq = 64;
+struct HalvesCount {
+    int64_t tokens, seqs, tiles, steps, longest;
+};
+__host__ __device__ inline int fwd_halves_room(int D, int num_cu) { return D == 128 ? 4 * num_cu / 3 : 3 * num_cu; }
+__host__ __device__ inline bool fwd_halves(int D, const HalvesCount &c, int num_cu)
 {
-    const int64_t items = ((T + kFwdBq - 1) / kFwdBq + B) * heads;  // at most
-    return T >= 512 * B && (D == 128 ? 3 * items <= 2 * num_cu : 2 * items <= 3 * num_cu);
+    if (c.tokens < 512 * c.seqs || c.tiles > fwd_halves_room(D, num_cu)) return false;
+    if (c.tiles <= num_cu) return true;
+    const int64_t while_longest = c.longest * num_cu;
+    return c.longest >= 32 && (D == 128 ? 5 * c.steps <= 4 * while_longest : 4 * c.steps <= (c.longest >= 80 ? 5 : 4) * while_longest);
+}
+// Whether any batch of B sequences and at most T tokens may run in halves (512 tokens, 8 tiles, to a sequence).
+inline bool fwd_may_halve(int64_t T, int64_t B, int64_t heads, int num_cu) { return T >= 512 * B && 8 * B * heads <= num_cu; }
+// ... and the most workgroups it then has.
+inline int64_t fwd_halves_most(int D, int64_t T, int64_t B, int64_t heads, int num_cu)
+{
+    const int64_t all = ((T + kHalfBq - 1) / kHalfBq + B) * heads, room = fwd_halves_room(D, num_cu);
+    return all < room ? all : room;
 }
 
 // Host helpers shared by the files that hold entry points.

@@ -2,7 +2,7 @@
 // allocate (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).
 // It needs no plan: the work queues the forward kernel consumes are built ON THE DEVICE, from the
 // device copy of cu_seqlens, into a file-scope array that every GPU the library runs on holds
-// until the process ends.  The attention kernel itself is the one flexsp_attn_varlen_fwd launches.  A batch small
+// until the process ends.  The attention pass itself is that of flexsp_attn_varlen_fwd.  A batch small
 // enough to be on the chip all at once is launched without queues (see the entry point).
 #include <mutex>
 
@@ -39,7 +39,8 @@ std::mutex g_scratch_mutex;
 // independent).  Lengths are validated here, on the device: a cu_seqlens that is not 0 = cu[0] <=
 // cu[1] <= ... <= cu[B] <= T, a sequence with more than kStaticMaxLevels tiles or a batch with more
 // than kStaticMaxItems items publishes an EMPTY list (the attention kernel then touches nothing)
-// and raises the status word.
+// and raises the status word.  halves_d, if not 0, is the head dim of a forward that may run in halves: if the batch does, the list
+// is empty as well.
 // One workgroup on an idle chip: trips to memory and chains of LDS accesses are what it takes.  Levels are summed 64 at a
 // time by a wavefront, lengths are read 64 sequences at a time, a lane lists a tile.  The whole call, against levels
 // summed one by one and a length read per sequence: 62 852 tokens in 201 sequences, 1 head 29.1 -> 25.1 us; 16 384 tokens
@@ -57,13 +58,13 @@ __device__ __forceinline__ int inclusive_sum(int x, int lane)  // over the wavef
 }
 
 __global__ __launch_bounds__(kBuildThreads) void build_static_queue_kernel(const int32_t *cu, int B, int T, int heads,
-                                                                            int causal, int tile_rows,
+                                                                            int causal, int tile_rows, int halves_d, int num_cu,
                                                                             unsigned char *scr)
 {
     __shared__ int hist[kStaticMaxLevels + 2];   // sequences with exactly n tiles
     __shared__ int start[kStaticMaxLevels + 1];  // first list position of a level
     __shared__ int fill[kStaticMaxLevels + 1];   // (sequence, tile) pairs placed in a level so far
-    __shared__ int s_maxnt, s_bad, s_total;
+    __shared__ int s_maxnt, s_bad, s_total, s_tiles, s_steps, s_longest;  // (the last three: see HalvesCount)
     int32_t *counters = (int32_t *)(scr + kCountersOff);
     int32_t *offsets = (int32_t *)(scr + kOffsetsOff);
     int32_t *status = (int32_t *)(scr + kStatusOff);
@@ -76,6 +77,7 @@ __global__ __launch_bounds__(kBuildThreads) void build_static_queue_kernel(const
         s_maxnt = 0;
         s_bad = (B > 0 && cu[0] != 0) ? 1 : 0;
         s_total = 0;
+        s_tiles = s_steps = s_longest = 0;
     }
     if (tid <= kMaxQueues) counters[tid * kCounterStride] = 0;  // every call starts with clear tickets
     __syncthreads();
@@ -94,6 +96,12 @@ __global__ __launch_bounds__(kBuildThreads) void build_static_queue_kernel(const
         if (nt > 0) {
             atomicAdd(&hist[nt], 1);
             atomicMax(&s_maxnt, nt);
+            if (halves_d) {
+                const int n = (hi - lo + kHalfBq - 1) / kHalfBq;
+                atomicAdd(&s_tiles, n);
+                atomicAdd(&s_steps, causal ? n * (n + 1) / 2 : n * n);
+                atomicMax(&s_longest, n);
+            }
         }
     }
     __syncthreads();
@@ -119,7 +127,9 @@ __global__ __launch_bounds__(kBuildThreads) void build_static_queue_kernel(const
         }
         if (lane == 0) {
             if ((int64_t)pos * heads > kStaticMaxItems) s_bad = 1;
-            s_total = s_bad ? 0 : pos * heads;
+            // (a batch in halves is the other launch's)
+            const bool halves = halves_d && fwd_halves(halves_d, {cu[B], B, (int64_t)s_tiles * heads, (int64_t)s_steps * heads, s_longest}, num_cu);
+            s_total = s_bad || halves ? 0 : pos * heads;
         }
     }
     __syncthreads();
@@ -220,11 +230,17 @@ extern "C" int flexsp_attn_varlen_fwd_static(flexsp_ctx *ctx, flexsp_tensor q, f
     // itself, in the time it would take to read it from a list (402 tokens, 16 heads: 23.0 -> 11.6 us; 1 687 tokens, 16 heads: 31.9 ->
     // 21.9 us; 257 tokens, 2 heads: 18.3 -> 10.4 us).  Larger ones need longest-first queues.
     const int64_t most_items = ((T + kFwdBq - 1) / kFwdBq + B) * (int64_t)head_count;
-    const bool listed = most_items > 2 * flexsp_ctx_num_cu(ctx);
+    const int num_cu = flexsp_ctx_num_cu(ctx);
+    const bool listed = most_items > 2 * num_cu;
+    // Whether it does run in halves the lengths tell, on the device: the rows that the tensors hold beyond the batch change nothing.
+    // (1 000 tokens, 8 heads in 4 096 rows 19.4 -> 18.1 us, 3 000 tokens, 1 head in 65 536 rows 50.9 -> 40.9.  Batches in whole items that
+    // might have been others take what they took, up to 0.6 us more with D = 64.  A second launch for the halves instead, which
+    // leaves at once where it is not wanted, was 2.5 to 4 us for each of them.)
+    const bool may_halve = fwd_may_halve(T, B, head_count, num_cu);
     hipError_t e = hipSuccess;
     if (listed) {
         hipLaunchKernelGGL(build_static_queue_kernel, dim3(1), dim3(kBuildThreads), 0, s, cu_seqlens_dev, (int)B, (int)T,
-                           (int)head_count, causal ? 1 : 0, kFwdBq, scr);
+                           (int)head_count, causal ? 1 : 0, kFwdBq, may_halve ? D : 0, num_cu, scr);
         e = hipGetLastError();
         if (e != hipSuccess) return hip_status(e);
     }
@@ -243,18 +259,23 @@ extern "C" int flexsp_attn_varlen_fwd_static(flexsp_ctx *ctx, flexsp_tensor q, f
     a.lse_out = lse;
     a.T = (int32_t)T; a.Hq = head_count; a.G = head_count / kv_head_count; a.causal = causal ? 1 : 0;
     a.scale = scale; a.scale_l2 = scale * 1.4426950408889634f;
-    if (!listed) {
+    a.num_cu = num_cu;
+    if (!listed || may_halve) {
         a.cu = cu_seqlens_dev;
         a.B = B;
-        a.halves = fwd_halves(D, T, B, head_count, flexsp_ctx_num_cu(ctx));
-        e = launch_attn_fwd(a, D, (int)most_items, s);
-        return e == hipSuccess ? FLEXSP_OK : hip_status(e);
     }
-    a.pq.items = (const flexsp_item *)(scr + kItemsOff);
-    a.pq.offsets = (const int32_t *)(scr + kOffsetsOff);
-    a.pq.counters = (int32_t *)(scr + kCountersOff);
-    a.pq.nq = kMaxQueues;
-    // the item count is known to the device only: a full persistent grid; workgroups without work leave
-    e = launch_attn_fwd(a, D, flexsp_ctx_num_cu(ctx) * 2, s);
+    // the item count is known to the device only.  With a list: a full persistent grid; workgroups without work leave
+    int64_t grid = 2 * (int64_t)num_cu;
+    if (listed) {
+        a.pq.items = (const flexsp_item *)(scr + kItemsOff);
+        a.pq.offsets = (const int32_t *)(scr + kOffsetsOff);
+        a.pq.counters = (int32_t *)(scr + kCountersOff);
+        a.pq.nq = kMaxQueues;
+    } else {
+        grid = may_halve ? std::max(most_items, fwd_halves_most(D, T, B, head_count, num_cu)) : most_items;
+    }
+    // (halves with two buffers where whole items too have the LDS for it: D = 128 one workgroup to a compute unit, D = 64 two)
+    if (may_halve) a.halves = !listed && (D == 64 || most_items <= num_cu) ? 2 : 1;
+    e = launch_attn_fwd(a, D, (int)grid, s);
     return e == hipSuccess ? FLEXSP_OK : hip_status(e);
 }

@@ -88,7 +88,8 @@ static int check_list(const flexsp_plan *p, int pass, const std::vector<std::vec
         CHECK(hp.direct.empty());
         return 0;
     }
-    CHECK(hp.direct.size() >= whole && hp.direct.size() <= 512);
+    const bool halves = pass == FLEXSP_PASS_FWD && p->halves;
+    CHECK(halves ? hp.direct.size() == whole && whole <= (size_t)fwd_halves_room(p->D, 256) : hp.direct.size() >= whole && hp.direct.size() <= 512);
     std::vector<std::vector<std::vector<std::vector<flexsp_item>>>> of(tiles.size());
     for (size_t b = 0; b < tiles.size(); b++) of[b].assign(tiles[b].size(), std::vector<std::vector<flexsp_item>>(heads));
     for (const flexsp_item &it : hp.direct) {
@@ -127,7 +128,7 @@ static int check_direct_lists(flexsp_ctx *ctx)
 {
     unsigned seed = 4711;
     auto rnd = [&](int lo, int hi) { seed = seed * 1664525u + 1013904223u; return lo + (int)((seed >> 8) % (unsigned)(hi - lo + 1)); };
-    int lists = 0, finer = 0, both = 0;
+    int lists = 0, finer = 0, both = 0, halves = 0;
     for (int trial = 0; trial < 600; trial++) {
         const int Hkv = rnd(1, 4), G = rnd(0, 2) ? 1 : rnd(2, 8), Hq = Hkv * G, causal = rnd(0, 3) != 0;
         const int B = rnd(1, rnd(0, 1) ? 4 : 120), top = 1 << rnd(3, 12);
@@ -159,7 +160,14 @@ static int check_direct_lists(flexsp_ctx *ctx)
                 const std::vector<std::vector<int64_t>> &steps = pass == FLEXSP_PASS_BWD_DKV ? keys : rows;
                 const int heads = pass == FLEXSP_PASS_BWD_DKV ? Hkv : Hq;
                 const HostPass &hp = p->pass[pass];
-                if (check_list(p, pass, steps, heads, pass == FLEXSP_PASS_FWD ? kMinPartSteps : kShortPartSteps)) return 1;
+                if (pass == FLEXSP_PASS_FWD && p->halves) {  // (tiles of 64 rows)
+                    CHECK(!shard && hp.records == 0);
+                    std::vector<std::vector<int64_t>> rows64(B);
+                    for (int b = 0; b < B; b++)
+                        for (int64_t t = 0, sq = cu[b + 1] - cu[b]; t * 64 < sq; t++) rows64[b].push_back(((causal ? std::min(sq, (t + 1) * 64) : sq) + 63) / 64);
+                    if (check_list(p, pass, rows64, heads, 0)) return 1;
+                    halves++;
+                } else if (check_list(p, pass, steps, heads, pass == FLEXSP_PASS_FWD ? kMinPartSteps : kShortPartSteps)) return 1;
                 lists += !hp.direct.empty();
                 finer += hp.direct.size() > hp.items.size();
             }
@@ -177,8 +185,50 @@ static int check_direct_lists(flexsp_ctx *ctx)
             flexsp_plan_destroy(p);
         }
     }
-    std::printf("%d lists, %d cut finer than listed, %d single launches\n", lists, finer, both);
-    CHECK(lists > 500 && finer > 100 && both > 200);
+    std::printf("%d lists, %d cut finer than listed, %d single launches, %d in halves\n", lists, finer, both, halves);
+    CHECK(lists > 500 && finer > 100 && both > 200 && halves > 20);
+    return 0;
+}
+
+// Which batches run in halves, either side of each line (256 compute units), that a plan which cuts no tile goes by it, and that a launch
+// without a plan, which knows the rows of its tensors only, looks at the lengths of every batch that does and has workgroups for it.
+static int check_halves(flexsp_ctx *ctx)
+{
+    const struct {
+        std::vector<int> lens;
+        int heads, D, causal;
+        bool halves;
+    } cases[] = {
+        // tokens to a sequence, empty ones counted
+        {{512}, 8, 128, 1, true}, {{511}, 8, 128, 1, false}, {{512}, 1, 64, 0, true}, {{511}, 1, 64, 0, false},
+        {{1, 1700, 65}, 2, 128, 1, true}, {{0, 0, 1535}, 2, 128, 1, false}, {{0, 0, 1536}, 2, 128, 1, true},
+        // one tile to a compute unit, whole tiles counted
+        {{2048}, 8, 128, 0, true}, {{2049}, 8, 128, 0, false}, {{2048}, 8, 64, 0, true}, {{2049}, 8, 64, 0, false},
+        {{1024}, 16, 128, 1, true}, {{1025}, 16, 128, 1, false}, {{960, 1024}, 8, 128, 0, true}, {{961, 1025}, 8, 128, 0, false},
+        // more of them beside a long sequence: its length, all steps, all tiles
+        {{2112}, 8, 128, 1, true}, {{2112}, 8, 128, 0, false}, {{2688}, 8, 128, 1, true}, {{2752}, 8, 128, 1, false}, {{1984, 832}, 6, 128, 1, false},
+        {{1280, 1280}, 8, 128, 1, false}, {{2048, 960}, 7, 128, 1, true}, {{4096}, 5, 128, 0, false}, {{8192, 2048}, 2, 128, 0, false}, {{16384, 640}, 1, 128, 0, false}, {{9600, 2560, 2560, 2560}, 1, 128, 0, true},
+        {{4032}, 8, 64, 1, true}, {{4096}, 8, 64, 1, false}, {{5120}, 7, 64, 1, true}, {{5120}, 8, 64, 1, false}, {{1984, 64}, 12, 64, 1, false},
+        {{8192}, 2, 64, 0, true}, {{8192, 704}, 2, 64, 0, true}, {{20480}, 1, 64, 0, true}, {{20544}, 1, 64, 0, false}, {{32768, 16256}, 1, 64, 1, true},
+    };
+    int plans = 0;
+    for (const auto &c : cases) {
+        std::vector<int32_t> cu(1, 0);
+        for (int s : c.lens) cu.push_back(cu.back() + s);
+        const int B = (int)c.lens.size();
+        flexsp_plan *p = nullptr;
+        CHECK(flexsp_plan_create(ctx, cu.data(), B, c.heads, c.heads, c.D, c.causal, &p) == FLEXSP_OK);
+        const HalvesCount n = halves_count(p);
+        if (fwd_halves(c.D, n, 256) != c.halves) std::fprintf(stderr, "%d tokens, %d sequences, %d heads, D = %d, causal = %d\n", cu[B], B, c.heads, c.D, c.causal);
+        CHECK(fwd_halves(c.D, n, 256) == c.halves);
+        CHECK(p->halves == (c.halves && p->pass[FLEXSP_PASS_FWD].records == 0));
+        plans += p->halves;
+        if (c.halves)
+            for (int64_t rows = cu[B]; rows < 100000; rows = rows * 3 / 2 + 1)
+                CHECK(fwd_may_halve(rows, B, c.heads, 256) && fwd_halves_most(c.D, rows, B, c.heads, 256) >= n.tiles);
+        flexsp_plan_destroy(p);
+    }
+    CHECK(plans >= 5);
     return 0;
 }
 
@@ -186,7 +236,7 @@ int main()
 {
     flexsp_ctx *ctx = nullptr;
     CHECK(flexsp_ctx_create(&ctx, -1) == FLEXSP_OK);
-    if (check_overlap(ctx) || check_direct_lists(ctx)) return 1;
+    if (check_overlap(ctx) || check_direct_lists(ctx) || check_halves(ctx)) return 1;
     flexsp_ctx_destroy(ctx);
     std::puts("launch decisions: ok");
     return 0;

@@ -1,5 +1,5 @@
 """The forward without a plan finds its work on the device: in a list for batches that do not fit the chip at once, every
-workgroup for itself for those that do.  Same bits as the plan's forward around that line and at odd lengths."""
+workgroup for itself for those that do.  Same bits as the plan's forward around that line and at odd lengths, however many rows the tensors hold."""
 import numpy as np
 import pytest
 
@@ -69,3 +69,38 @@ def test_wrong_lengths_compute_nothing(ctx, T, B):
         fx.flexsp_attn_varlen_fwd_static(ctx, t, t, t, cu.cuda(), o, lse)
         torch.cuda.synchronize()
         assert bool((o == 7.0).all()) and bool((lse == 7.0).all()), (at, value)
+
+
+# Tensors with room for more tokens than the batch has, whose lengths alone say how the forward runs: in one launch that takes
+# the batch either way, in two without and with a list, and (the last ones) batches that are not for halves
+@pytest.mark.parametrize("lens,hq,hkv,D,rows", [
+    ([1000], 8, 8, 128, 1000), ([1000], 8, 8, 128, 1900), ([1000], 8, 8, 128, 4096), ([1000], 8, 2, 128, 9000), ([1900], 8, 8, 128, 4096),
+    ([700, 0, 1301], 2, 1, 128, 8192), ([700, 0, 1301], 2, 2, 128, 40000), ([900, 450], 4, 4, 64, 4096), ([1500], 4, 2, 64, 17000),
+    ([8400], 4, 2, 64, 17000), ([0, 0, 700], 4, 4, 64, 2048), ([300, 200], 4, 4, 128, 4096), ([64], 1, 1, 128, 640), ([511], 8, 8, 128, 1000), ([1], 16, 4, 64, 30000),
+], ids=lambda x: str(x).replace(" ", ""))
+@pytest.mark.parametrize("causal", [True, False])
+def test_room_for_more_tokens_changes_nothing(ctx, lens, hq, hkv, D, rows, causal):
+    import torch
+    from paper_2412_01523_amd import binding as fx
+    print(f"static forward: {lens} in {rows} rows, {hq} heads on {hkv}, D={D}, causal={causal}", flush=True)
+    cu, T = wl.cu_seqlens(lens), sum(lens)
+    q, k, v = (torch.full((rows, h, D), float("nan"), dtype=torch.bfloat16, device="cuda") for h in (hq, hkv, hkv))
+    for tid, x in ((0, q), (1, k), (2, v)):
+        x[:T] = to_dev(wl.normal_bf16(772, tid, (T, x.shape[1], D)))
+    cud = torch.from_numpy(cu).cuda()
+    want, want_lse = torch.empty((T, hq, D), dtype=torch.bfloat16, device="cuda"), torch.empty((hq, T), dtype=torch.float32, device="cuda")
+    plan = fx.Plan(ctx, cu, hq, hkv, D, causal)
+    if int(plan.items(fx.PASS_FWD)[0]["nparts"].max()) == 1:
+        fx.flexsp_attn_varlen_fwd(ctx, plan, q[:T], k[:T], v[:T], cud, want, want_lse, causal=causal)
+        torch.cuda.synchronize()
+    else:
+        assert T == 8400  # (cut by the plan; here for the second turn that its halves take)
+        fx.flexsp_attn_varlen_fwd_static(ctx, q[:T], k[:T], v[:T], cud, want, want_lse, causal=causal)
+    plan.close()
+    for _ in range(2):
+        o = torch.full((rows, hq, D), 7.0, dtype=torch.bfloat16, device="cuda")
+        lse = torch.full((hq, rows), 7.0, dtype=torch.float32, device="cuda")
+        fx.flexsp_attn_varlen_fwd_static(ctx, q, k, v, cud, o, lse, causal=causal)
+        torch.cuda.synchronize()
+        assert torch.equal(o[:T].view(torch.int16), want.view(torch.int16)) and torch.equal(lse[:, :T].view(torch.int32), want_lse.view(torch.int32))
+        assert bool((o[T:] == 7.0).all()) and bool((lse[:, T:] == 7.0).all())
