@@ -667,7 +667,7 @@ __device__ __forceinline__ void fwd_pass(KernArgs &args, const flexsp_item &foun
 #pragma unroll
                 for (int i = 0; i < 16; i++) oacc[db][i] = w0 * oacc[db][i] + w1 * o1[db * 4 + i / 4][i % 4];
         }
-        {
+        if constexpr (HALVES == 1) {  // (no list of halves has cut tiles, and here half of the wavefronts have left)
             if (nparts > 1) {
                 // hand over (O unnormalised, row maximum, row sum); the part that arrives last merges
                 // all parts in part order: O = sum_p 2^((m_p - M) scale_l2) O_p, likewise the row sums
