@@ -262,7 +262,7 @@ void build_pass(const std::vector<int32_t> &cu, int B, int heads, int group_mult
             group_cost.push_back(gc);
         }
     }
-    distribute(work, group_cost, nq, n_wg, tile_rows, out, 0, 2 * 2 * D, group_mult);  // (two bf16 tensors)
+    distribute(work, group_cost, nq, n_wg, tile_rows, out, 0, causal ? 2 * 2 * D : 0, group_mult);  // (two bf16 tensors)
 }
 
 // Cuts tiles that would outlast an even share of the pass into parts (see flexsp_item): with W =
@@ -291,12 +291,18 @@ void cut_part(flexsp_item &it, int64_t c, int p, int k, int32_t slot)
     it.slot = slot;
     it.parts = (p << 16) | k;
 }
-// Parts of the same number walk about the same rows, parts of one tile do not.  So where a group walks more rows than an XCD's L2 holds
-// beside everything else (`row_bytes` of them each, kPartAffinityBytes in all), the parts of one number are kept on one queue instead of
-// the whole group (`keep`, whose costs are returned).  Forward and backward, by group -> by part: 16 384 tokens, 4 heads 1 274 -> 1 191
-// us; two sequences of 20 000 tokens, 2 heads 1 753 -> 1 700; the 32K-token log-normal step (longest sequence 7 821) 627 -> 608; but
-// sequences of 3 100 to 5 100 tokens, 2 heads 307 -> 318, all of whose rows a group keeps in L2.  One group alone is spread over
-// all queues (32 768 tokens, 1 head 1 246 -> 1 271 by part), unless its parts are its heads (8 192 tokens, 8 heads on 1 720 -> 676).
+// With a mask, parts of the same number walk about the same rows, parts of one tile do not.  So where a group walks more rows than an
+// XCD's L2 holds beside everything else (`row_bytes` of them each, 0 without a mask, kPartAffinityBytes in all), the parts of one number are
+// kept on one queue instead of the whole group (`keep`, whose costs are returned).  Not where a pass is little more than a few such groups:
+// levelling spreads those over the queues in order of cost, which is the order of their tiles, while parts of one
+// number are of few and unequal costs then.  The line lies at three and a half times the largest group, or two and a half where a group is several
+// heads, whose parts are about its heads; and none where those are cut into as many parts as there are queues.
+// Time of a pass, by group -> by part.  Taken: one sequence of 20 000 tokens, 4 heads, forward 391 -> 373 us, dQ 589 -> 538; 30 721, 12
+// heads on 3, dK/dV 5 959 -> 5 227; 12 000, 8 heads on 1, dK/dV 619 -> 570; a mix of 126 120, 1 head, dK/dV 409 -> 370.  Not taken:
+// 30 721, 2 heads, forward 426 -> 460, dQ 621 -> 680; 20 000, 3 heads, dQ 405 -> 428; 30 721, 8 heads on 2, dK/dV 3 646 -> 3 832; a mix of
+// 68 656 around one of 19 381, 1 head, dQ 195 -> 215; unmasked 6 000, 2 heads on 1, dK/dV 102 -> 116; 12 000, 8 heads, forward 498 -> 530.
+// Rows that fit L2: sequences of 3 100 to 5 100 tokens, 2 heads, forward and backward 307 -> 318.  Of 861 passes, drawn and over single
+// sequences, which take 1.4 % less by this line, 23 take more than 3 % more; all by part 1.0 % less, 95.
 std::vector<int64_t> split_long_items(std::vector<Work> &work, std::vector<int64_t> keep_cost, int n_wg, int spare, int64_t row_bytes, int heads_walked,
                                       HostPass &out)
 {
@@ -316,10 +322,17 @@ std::vector<int64_t> split_long_items(std::vector<Work> &work, std::vector<int64
     auto parts_of = [&](int64_t c) { return c <= spare * share ? 1 : part_count(c, target, kMinPartSteps); };
     std::vector<int32_t> by_part(keep_cost.size(), -1);  // a cut group's first number beyond the groups'
     int32_t groups_cut = 0;
+    int64_t largest = 0, most_parts = 0;
     for (const Work &w : work)
-        if (by_part[w.group] < 0 && row_bytes * heads_walked * w.it.seq_len > kPartAffinityBytes && parts_of(w.cost) > 1)
-            by_part[w.group] = (int32_t)keep_cost.size() + groups_cut++ * kMaxParts;
-    if (groups_cut == 1 && heads_walked == 1) std::fill(by_part.begin(), by_part.end(), -1);
+        if (row_bytes * heads_walked * w.it.seq_len > kPartAffinityBytes && parts_of(w.cost) > 1) {
+            if (by_part[w.group] < 0) by_part[w.group] = (int32_t)keep_cost.size() + groups_cut++ * kMaxParts;
+            largest = std::max(largest, keep_cost[w.group]);
+            most_parts = std::max<int64_t>(most_parts, parts_of(w.cost));
+        }
+    if (2 * total < (heads_walked > 1 ? 5 : 7) * largest && !(heads_walked > 1 && most_parts == kMaxParts)) {
+        std::fill(by_part.begin(), by_part.end(), -1);
+        groups_cut = 0;
+    }
     keep_cost.resize(keep_cost.size() + (size_t)groups_cut * kMaxParts, 0);
     for (size_t i = 0; i < n0; i++) {
         const int64_t c = work[i].cost;

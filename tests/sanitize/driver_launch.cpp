@@ -232,11 +232,65 @@ static int check_halves(flexsp_ctx *ctx)
     return 0;
 }
 
+// Whether a pass keeps the parts of one number of its cut tiles together or whole groups, either side of each line: sequences of the given
+// lengths, `groups` groups (heads, or heads of keys) to each, a group walking `walked` heads, tiles as a forward's under a mask.
+static int check_parts_kept(flexsp_ctx *ctx)
+{
+    const struct {
+        std::vector<int> lens;
+        int groups, walked, row_bytes;
+        bool by_part;
+    } cases[] = {
+        {{20000}, 1, 1, 512, false}, {{20000}, 3, 1, 512, false}, {{20000}, 4, 1, 512, true}, {{20000}, 4, 1, 0, false},  // (0: no mask)
+        {{7168}, 4, 1, 512, false}, {{7296}, 4, 1, 512, true}, {{14336}, 4, 1, 256, false}, {{14464}, 4, 1, 256, true},   // 3.5 MiB
+        {{19381, 9000, 9000}, 1, 1, 512, false}, {{19381, 19381, 19381, 12000}, 1, 1, 512, false}, {{19381, 19381, 19381, 15000}, 1, 1, 512, true},
+        {{30721}, 2, 4, 512, false}, {{12000}, 2, 4, 512, false}, {{30721}, 3, 4, 512, true}, {{8192}, 1, 8, 512, true}, {{3000}, 2, 8, 512, true},
+    };
+    for (const auto &c : cases) {
+        std::vector<Work> work;
+        std::vector<int64_t> cost;
+        for (size_t b = 0; b < c.lens.size(); b++)
+            for (int g = 0; g < c.groups; g++) {
+                const int s = c.lens[b], tile = c.walked > 1 ? 64 : 128;
+                cost.push_back(0);
+                for (int t = 0; t * tile < s; t++) {
+                    Work w;
+                    std::memset(&w, 0, sizeof(w));
+                    w.it.seq_len = s; w.it.tile = t; w.it.head = g;
+                    w.cost = (cdiv(std::min(s, (t + 1) * tile), 64)) * c.walked;
+                    w.group = (int32_t)cost.size() - 1;
+                    cost.back() += w.cost;
+                    work.push_back(w);
+                }
+            }
+        HostPass hp;
+        const size_t groups = cost.size(), tiles = work.size();
+        const std::vector<int64_t> kept = split_long_items(work, cost, workgroups_of(ctx), 0, c.row_bytes, c.walked, hp);
+        CHECK(work.size() > tiles && hp.records > 0);  // (some are cut)
+        std::vector<int64_t> sum(kept.size(), 0);
+        bool by_part = false;
+        for (const Work &w : work) {
+            CHECK(w.keep >= 0 && (size_t)w.keep < kept.size());
+            sum[w.keep] += w.cost;
+            if ((size_t)w.keep >= groups) {  // a number's list: of one group, of one number
+                CHECK((w.it.parts & 0xffff) > 1 && (w.keep - (int)groups) % kMaxParts == w.it.parts >> 16);
+                by_part = true;
+            } else {
+                CHECK(w.keep == w.group);
+            }
+        }
+        CHECK(sum == kept);
+        if (by_part != c.by_part) std::fprintf(stderr, "%d tokens first, %d groups of %d heads\n", c.lens[0], c.groups, c.walked);
+        CHECK(by_part == c.by_part);
+    }
+    return 0;
+}
+
 int main()
 {
     flexsp_ctx *ctx = nullptr;
     CHECK(flexsp_ctx_create(&ctx, -1) == FLEXSP_OK);
-    if (check_overlap(ctx) || check_direct_lists(ctx) || check_halves(ctx)) return 1;
+    if (check_overlap(ctx) || check_direct_lists(ctx) || check_halves(ctx) || check_parts_kept(ctx)) return 1;
     flexsp_ctx_destroy(ctx);
     std::puts("launch decisions: ok");
     return 0;
