@@ -574,21 +574,33 @@ bool halve_items(flexsp_plan *p, int num_cu)
 }
 
 // Whether the dK/dV pass takes 128 keys an item (attn_bwd_dkv_wide_kernel; D = 64).  What it gives up: at a walk's start and end, and
-// where blocks are masked, its stages run one after the other, a causal walk begins with up to two steps of that kind, and
-// its items are half as many.  So not where the causal walks of a batch are under five steps on average (sequences
-// of 512 tokens: even; 256: 1 % slower; 64 to 512 tokens with 16 heads on 2: 9 % slower; 1 024: 2 % faster), and not where both passes
-// may run in one launch, which has no such kernel.
+// where blocks are masked, its stages run one after the other, a causal walk begins with up to two steps of that kind,
+// the last item of a sequence may be half empty, and its items are half as many.  So where walks over the queries are twelve
+// steps or more on average, eight if nothing is masked and next to no key empty.  With shorter ones only where its items, one to a workgroup,
+// are on the chip at once and those of 64 keys would not be: if query heads have key heads of their own (the walks of several are
+// long for so few items), or if nothing is masked and so on.  And not where both passes may run in one launch, which has no such kernel.
+// dK/dV pass, 64 keys -> 128.  Taken: sequences of 1 500 tokens, 4 heads, 12 000 tokens not causal 1.34 times as fast, 39 000 1.15, causal 1.13
+// and 0.99; 40 000 tokens in sequences of 200, 1 head 1.56; 11 904 in 128, 4 heads 1.71; causal 39 501 in 513, 1 head 1.21.  Not
+// taken, in us: 40 000 tokens in 16, 16 heads on 2 97 -> 165; in 129, 8 heads 83 -> 92; in 300, 16 heads on 2 141 -> 168; in 513, 4 heads,
+// causal 0.91 times as fast; 12 000 in 1 000, 4 heads on 1, causal 29 -> 47.  544 batches: 5.6 % faster than with 64 keys, nine of them more
+// than 3 % slower, the slowest 1.11 times; by the line as it was (five steps for causal walks, none for others) 1.9 % and 197.
 bool wide_keys(const flexsp_plan *p, int n_wg)
 {
     if (p->D != 64) return false;
-    int64_t steps = 0, walks = 0, items = 0;
+    int64_t steps = 0, narrow_steps = 0, walks = 0, items = 0;
+    auto walk_steps = [&](int64_t tiles, int64_t all, int64_t skip) { return tiles * all - (p->causal ? tiles * (tiles - 1) / 2 * skip : 0); };
     for (int b = 0; b < p->B; b++) {
-        const int64_t s = p->cu[b + 1] - p->cu[b], tiles = cdiv(s, kDkvWideBk), all = cdiv(s, kDkvBq);
-        walks += tiles;
-        steps += p->causal ? tiles * all - tiles * (tiles - 1) / 2 * (kDkvWideBk / kDkvBq) : tiles * all;
+        const int64_t s = p->cu[b + 1] - p->cu[b], all = cdiv(s, kDkvBq);
+        walks += cdiv(s, kDkvWideBk);
+        steps += walk_steps(cdiv(s, kDkvWideBk), all, kDkvWideBk / kDkvBq);
+        narrow_steps += walk_steps(cdiv(s, kDkvBk), all, kDkvBk / kDkvBq);
         items += cdiv(s, kDkvBk) * p->Hkv + cdiv(s, kDqBq) * p->Hq;
     }
-    return items > n_wg && (!p->causal || steps >= 5 * walks);
+    if (items <= n_wg) return false;
+    const bool full = !p->causal && 40 * steps <= 21 * narrow_steps;
+    if (steps >= (full ? 8 : 12) * walks) return true;
+    const int64_t wide_items = walks * p->Hkv;
+    return 2 * wide_items > n_wg && wide_items <= n_wg && (p->Hq == p->Hkv || full);
 }
 
 int check_attn_common(flexsp_ctx *ctx, flexsp_plan *plan, const int32_t *cu_dev, int32_t head_begin,

@@ -286,11 +286,42 @@ static int check_parts_kept(flexsp_ctx *ctx)
     return 0;
 }
 
+// Which dK/dV passes have items of 128 keys, either side of each line (D = 64, 512 places): equal sequences.
+static int check_wide_keys(flexsp_ctx *ctx)
+{
+    const struct {
+        int n, len, hq, hkv, causal;
+        bool wide;
+    } cases[] = {
+        {40, 740, 8, 8, 0, true}, {40, 704, 8, 8, 0, false}, {60, 512, 8, 8, 0, true}, {60, 384, 8, 8, 0, false}, {30, 1408, 8, 2, 1, true}, {30, 1280, 8, 2, 1, false},  // twelve steps to a walk
+        {85, 200, 3, 3, 0, true}, {86, 200, 3, 3, 0, false}, {64, 200, 2, 2, 0, false}, {65, 200, 2, 2, 0, true},    // 256 and 512 items
+        {100, 500, 1, 1, 1, true}, {100, 500, 4, 1, 1, false}, {100, 500, 4, 1, 0, true}, {100, 160, 8, 2, 0, false}, {100, 256, 8, 2, 0, true},
+        {4, 900, 2, 2, 0, false}, {1, 6000, 1, 1, 1, false}, {1, 16384, 1, 1, 1, false}, {1, 32768, 1, 1, 1, true},  // (both passes in one launch)
+    };
+    for (const auto &c : cases) {
+        std::vector<int32_t> cu(1, 0);
+        for (int i = 0; i < c.n; i++) cu.push_back(cu.back() + c.len);
+        flexsp_plan *p = nullptr;
+        for (int D = 64; D <= 128; D *= 2) {
+            CHECK(flexsp_plan_create(ctx, cu.data(), c.n, c.hq, c.hkv, D, c.causal, &p) == FLEXSP_OK);
+            if (p->wide != (c.wide && D == 64)) std::fprintf(stderr, "%d of %d tokens, %d heads on %d, D = %d, causal = %d\n", c.n, c.len, c.hq, c.hkv, D, c.causal);
+            CHECK(p->wide == (c.wide && D == 64) && p->pass[FLEXSP_PASS_BWD_DKV].tile_rows == (p->wide ? kDkvWideBk : kDkvBk));
+            if (p->wide) {
+                AttnArgs a;
+                std::memset(&a, 0, sizeof(a));
+                CHECK(both_at_once(ctx, p, a) == 0 && bwd_per_cu(ctx, p, FLEXSP_PASS_BWD_DKV) == 2);
+            }
+            flexsp_plan_destroy(p);
+        }
+    }
+    return 0;
+}
+
 int main()
 {
     flexsp_ctx *ctx = nullptr;
     CHECK(flexsp_ctx_create(&ctx, -1) == FLEXSP_OK);
-    if (check_overlap(ctx) || check_direct_lists(ctx) || check_halves(ctx) || check_parts_kept(ctx)) return 1;
+    if (check_overlap(ctx) || check_direct_lists(ctx) || check_halves(ctx) || check_parts_kept(ctx) || check_wide_keys(ctx)) return 1;
     flexsp_ctx_destroy(ctx);
     std::puts("launch decisions: ok");
     return 0;

@@ -14,10 +14,11 @@ EDGES = [1, 31, 32, 33, 63, 64, 65, 127, 128, 129, 191, 192, 193, 255, 256, 257,
 
 
 @pytest.mark.parametrize("lens,hq,hkv,causal,f32,cut", [
-    (EDGES * 2, 4, 4, False, False, False), (EDGES * 2 + [449], 8, 4, False, True, False),
-    ([1025, 1, 960, 1151, 0, 833, 1217] * 2, 4, 4, True, True, False), ([1537, 895, 1280], 8, 8, True, False, False),
+    (EDGES * 3, 4, 4, False, False, False), (EDGES + [2100, 449], 8, 4, False, True, True),
+    ([65, 127, 128, 193, 255, 256, 321, 383, 384] * 4 + [449], 8, 4, False, True, False),
+    ([1025, 1, 960, 1151, 0, 833, 1217] * 2, 4, 4, True, True, False), ([1537, 895, 1280, 700], 8, 8, True, False, False),
     ([4200, 2300, 65], 8, 1, True, False, True), ([2049, 1300, 700, 130], 8, 4, False, True, True),
-], ids=["edges", "edges, grouped", "causal", "causal, more heads", "causal, cut", "cut"])
+], ids=["edges", "edges beside a long one, grouped", "edges, grouped", "causal", "causal, more heads", "causal, cut", "cut"])
 def test_backward_with_128_key_items(lens, hq, hkv, causal, f32, cut):
     from paper_2412_01523_amd import binding as fx
     ctx = fx.Context(0)
