@@ -764,11 +764,12 @@ int grid_for(const flexsp_ctx *ctx, const HostPass &p, int per_cu)
     return p.items.empty() ? 1 : ctx->num_cu * per_cu;
 }
 
-// Workgroups per compute unit of a backward pass.  With D = 64 three fit (160 registers, 42 KB of LDS) and hide more of each
-// other's waits, but each is slower: where the longest item is most of a workgroup's share, the others wait for it.
-// Both passes, two -> three: 30 011 tokens, 12 heads on 4, not causal 1 053 -> 1 004 us with the forward (longest item a third
-// of a share); 44 560 tokens, 4 heads 4 986 -> 4 694 (a third); 59 031 tokens in 296 sequences 415 -> 394 (a third); but 21 751 tokens,
-// 4 heads 263 -> 279 and 125 824 tokens, 2 heads 710 -> 740 (three quarters).  D = 128 needs the registers of two.
+// Workgroups per compute unit of a backward pass.  With D = 64 three fit (dQ 164 registers, dK/dV of 64 keys 147, 42 KB of LDS) and
+// hide more of each other's waits, but each is slower: where the longest item is most of a workgroup's share, the others wait for it.
+// dQ, two -> three: 30 011 tokens, 12 heads on 4, not causal 316 -> 299 us (longest item 0.3 of a share); causal sequences of 4 096 tokens,
+// 8 heads 418 -> 378 (a quarter); 21 751 tokens, 4 heads 66.6 -> 68.8 (a whole share).  dK/dV: 65 536 tokens in causal sequences of 512,
+// 8 heads 152 -> 127; 31 860 tokens in sequences of 300 to 600, 8 heads on 4 72 -> 66 (half a share).  D = 128 and dK/dV of 128 keys need the
+// registers of two.
 int bwd_per_cu(const flexsp_ctx *ctx, const flexsp_plan *plan, int pass)
 {
     const HostPass &p = plan->pass[pass];
@@ -776,14 +777,14 @@ int bwd_per_cu(const flexsp_ctx *ctx, const flexsp_plan *plan, int pass)
     return plan->D == 64 && 2 * p.longest * workgroups_of(ctx) <= p.steps ? 3 : 2;
 }
 
-// ... and of a forward, likewise: with D = 64 three (163 registers, 33 KB of LDS).  Forward and backward of 8 heads, two -> three, causal
-// sequences of 512 tokens 302 -> 290 us, 1 024 434 -> 422, 4 096 1 235 -> 1 218, 16 384 4 398 -> 4 369; not causal 256 142 -> 137, 1 024 331 -> 327,
-// but 2 048 597 -> 602, 16 384 4 395 -> 4 445: long items without a masked or ragged end have no waits that a third could use.
+// ... and of a forward, likewise: with D = 64 three (163 registers, 33 KB of LDS).  65 536 tokens, 8 heads, two -> three: causal sequences of
+// 256 tokens 64 -> 58 us, 1 024 117 -> 105, 4 096 304 -> 289; not causal 256 78 -> 69, 1 024 168 -> 153, 2 048 284 -> 273, 16 384 2 129 -> 2 018
+// (with the backward behind it 8 741 -> 8 658); 30 011 tokens, 12 heads on 4, not causal 237 -> 225.
 int fwd_per_cu(const flexsp_ctx *ctx, const flexsp_plan *plan)
 {
     const HostPass &p = plan->pass[FLEXSP_PASS_FWD];
     const bool even = 2 * p.longest * workgroups_of(ctx) <= p.steps;
-    return plan->D == 64 && even && (plan->causal || p.steps <= 24 * (int64_t)p.items.size()) ? 3 : 2;
+    return plan->D == 64 && even ? 3 : 2;
 }
 
 }  // namespace

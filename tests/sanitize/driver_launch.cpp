@@ -317,11 +317,31 @@ static int check_wide_keys(flexsp_ctx *ctx)
     return 0;
 }
 
+// Where a forward runs three workgroups per compute unit: D = 64 and no item of more than half a workgroup's share.
+static int check_fwd_per_cu(flexsp_ctx *ctx)
+{
+    const struct {
+        int n, len, heads, causal, per_cu;
+    } cases[] = {{128, 512, 8, 1, 3}, {32, 2048, 8, 0, 3}, {2, 16384, 8, 0, 3}, {16, 2048, 4, 0, 3}, {15, 2048, 4, 0, 2}, {16, 2048, 4, 1, 2}, {31, 2048, 4, 1, 3}};
+    for (const auto &c : cases)
+        for (int D = 64; D <= 128; D *= 2) {
+            std::vector<int32_t> cu(1, 0);
+            for (int i = 0; i < c.n; i++) cu.push_back(cu.back() + c.len);
+            flexsp_plan *p = nullptr;
+            CHECK(flexsp_plan_create(ctx, cu.data(), c.n, c.heads, c.heads, D, c.causal, &p) == FLEXSP_OK);
+            const HostPass &f = p->pass[FLEXSP_PASS_FWD];
+            if (fwd_per_cu(ctx, p) != (D == 64 ? c.per_cu : 2)) std::fprintf(stderr, "%d of %d tokens, %d heads: longest %ld of %ld steps\n", c.n, c.len, c.heads, (long)f.longest, (long)f.steps);
+            CHECK(fwd_per_cu(ctx, p) == (D == 64 ? c.per_cu : 2));
+            flexsp_plan_destroy(p);
+        }
+    return 0;
+}
+
 int main()
 {
     flexsp_ctx *ctx = nullptr;
     CHECK(flexsp_ctx_create(&ctx, -1) == FLEXSP_OK);
-    if (check_overlap(ctx) || check_direct_lists(ctx) || check_halves(ctx) || check_parts_kept(ctx) || check_wide_keys(ctx)) return 1;
+    if (check_overlap(ctx) || check_direct_lists(ctx) || check_halves(ctx) || check_parts_kept(ctx) || check_wide_keys(ctx) || check_fwd_per_cu(ctx)) return 1;
     flexsp_ctx_destroy(ctx);
     std::puts("launch decisions: ok");
     return 0;
