@@ -116,18 +116,20 @@ void flexsp_plan_destroy(flexsp_plan *plan);
 
 /* Plan inspection (host logic; works for host-only contexts).
  * A work item is one tile of one (sequence, head): 128 query rows (forward, dQ pass) walking the key
- * tiles they can see, or 64 keys (dK/dV pass) walking the query rows that see them, for every query
- * head of the kv head's group.  When a batch has so few, so long items that the longest would outlast
+ * tiles they can see, or 64 or 128 keys (dK/dV pass) walking the query rows that see them, for every query
+ * head of the kv head's group.  Which of the two is decided per plan (128 only with D = 64):
+ * flexsp_plan_tile_rows tells.  When a batch has so few, so long items that the longest would outlast
  * an even share of the whole pass (few heads, a dominant sequence: the usual case for a large
  * sequence-parallel group), the plan cuts such a tile's inner loop into `nparts` consecutive ranges,
  * one work item each; every part leaves its partial result (fp32) in the plan's scratch and the part
  * that finishes last adds them up in part order and writes the tile, so results do not depend on
  * which part that is.  (A backward of so few items that compute units would be left without work cuts
- * its tiles into shorter parts than listed here, when it is launched.) */
+ * its tiles into shorter parts than listed here, and a forward of few long sequences runs each of its tiles as two
+ * of 64 rows, when they are launched.) */
 typedef struct flexsp_item {
     int32_t seq_start; /* first token of the sequence in the packed stream            */
     int32_t seq_len;   /* its length                                                   */
-    int32_t tile;      /* tile index inside the sequence (query tile or key tile)      */
+    int32_t tile;      /* tile index inside the sequence (query tile or key tile of flexsp_plan_tile_rows rows) */
     int32_t head;      /* query head (forward, dQ pass) or kv head (dK/dV pass)        */
     int32_t step_begin; /* the item walks steps step_begin .. step_end-1 of the tile's inner loop    */
     int32_t step_end;   /* (a step = 64 keys for a query tile; 64 query rows of one head of the group
