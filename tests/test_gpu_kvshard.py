@@ -398,7 +398,9 @@ def test_kvshard_backward_error_paths(ctx):
 
 def test_aligned_shard_equals_the_ordinary_forward_bitwise(ctx):
     """shift = 0 and keys = the whole sequence is ordinary causal attention: same kernel arithmetic,
-    so the key-shard call must reproduce flexsp_attn_varlen_fwd bit for bit."""
+    so the key-shard call must reproduce flexsp_attn_varlen_fwd bit for bit where that runs in whole items (sequences
+    under 512 tokens on average, as here, or more of them than the halves have room for; tests/test_gpu_forward_halves.py tells halves
+    by the bits that differ)."""
     import torch
     from paper_2412_01523_amd import binding as fx
     lens, Hq, Hkv, D = [700, 64, 129, 1], 4, 2, 128

@@ -59,7 +59,8 @@ def test_few_long_items(ctx, lens, hq, hkv, D, causal, grad_f32):
 
 @pytest.mark.parametrize("causal", [True, False])
 def test_three_workgroups_per_unit(ctx, causal):
-    """D = 64 and items that are short against a workgroup's share: the backward passes run three workgroups per compute unit."""
+    """D = 64 and items that are short against a workgroup's share: forward, dQ and dK/dV (of 64 keys: walks are short) run three
+    workgroups per compute unit."""
     # (the flat 2e-2 is a statement about the magnitudes of the configurations: among 7 million dV elements that sum four query
     # heads some are large enough for two or three roundings of P to bf16, 2^-8 of a term each, to pass it (2.1e-2 seen);
     # the budget that is derived element by element from those roundings holds)
