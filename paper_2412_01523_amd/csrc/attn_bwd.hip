@@ -57,7 +57,7 @@ constexpr int dq_lds()  // ... of the dQ pass: two steps (K | V)
 // attention, and the gradients may be added to what dK / dV hold.  Tiles are not cut into parts.
 //
 // SELF = true: the log-sum-exp read is the forward's own and the workgroup forms delta = dO . O of a step's rows itself,
-// from rows of O and dO requested with the step's tiles, so that the pass does not have to come after the dQ pass.
+// from pieces of O requested with the step's tiles and the tile's own dO, so that the pass does not have to come after the dQ pass.
 template <int D, bool SHARD, bool SELF>
 __device__ __forceinline__ void dkv_pass(KernArgs &args, KernQueues &queues, const int first_wg, char *const smem, int &deal_word, int &split_word)
 {
@@ -166,7 +166,7 @@ __device__ __forceinline__ void dkv_pass(KernArgs &args, KernQueues &queues, con
                 const uint32_t rowb = (uint32_t)a.o_st * 2u;
                 const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
                     (void *)(a.o + (tok0 + qs) * a.o_st + (int64_t)h * a.o_sh), 0, (int)(min(s - qs, BQ) * rowb), 0x00020000);
-    #pragma unroll
+#pragma unroll
                 for (int i = 0; i < NO; i++) o_raw[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, goffo, i * (kThreads / L::CH) * rowb, 0);
                 if (wave == 0) lse_raw = *lse;
             } else if (wave < 2) {  // wavefront 0: lse2 of the 64 rows, wavefront 1: delta
@@ -179,12 +179,12 @@ __device__ __forceinline__ void dkv_pass(KernArgs &args, KernQueues &queues, con
             char *base = smem + buf * STEP;
             float *to = (float *)(base + 2 * QTILE);
             u32x4 g_raw[NO];
-    #pragma unroll
+#pragma unroll
             for (int i = 0; i < NO; i++) g_raw[i] = *(const u32x4 *)(base + QTILE + (i * kThreads + wave * 64 + lane) * 16);
-    #pragma unroll
+#pragma unroll
             for (int i = 0; i < NO; i++) {
                 float d = 0.f;
-    #pragma unroll
+#pragma unroll
                 for (int e = 0; e < 4; e++) {
                     const uint32_t gw = g_raw[i][e], ow = o_raw[i][e];
                     d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, gw), __builtin_bit_cast(bf16x2, ow), d, false);
@@ -409,7 +409,8 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dkv_kernel
 // barriers and for LDS).  Here the matrix unit is busy for 50 %, other waits fall from 27 to 21 % of the waves' time: 30 011 tokens, 12
 // heads on 4, not causal 532 -> 465 us (counters on); forward and backward of 8 heads, 64 keys -> 128: 65 536 tokens
 // causal in sequences of 16 384 4 710 -> 4 465 us, 4 096 1 324 -> 1 251, 1 024 451 -> 443, 512 299 -> 297, 256 241 -> 244; 32 768
-// tokens not causal 4 096 1 228 -> 1 149, 1 024 351 -> 327, 256 144 -> 136.  Same bits, the sums are formed in the same order.
+// tokens not causal 4 096 1 228 -> 1 149, 1 024 351 -> 327, 256 144 -> 136.  Same bits where no tile is cut (parts begin elsewhere): the
+// sums are formed in the same order.
 // (D = 128 needs 390 registers, one wavefront per SIMD; two 64-key workgroups are as fast or faster.)
 __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dkv_wide_kernel(const AttnArgs)
 {

@@ -31,7 +31,7 @@ __device__ __forceinline__ int workgroup_id() { return __builtin_amdgcn_workgrou
 
 // A kernel's arguments where the launch left them.  Taken as an ordinary parameter they are all loaded when the kernel starts, and
 // the dozens of scalars that only an item's first and last instructions need are kept for its whole life, most of them
-// spilled into lanes of vector registers (78 to 139 in the D = 128 kernels, 14 to 60 now).  Here a member is a scalar load where it is
+// spilled into lanes of vector registers (78 to 139 in the D = 128 kernels; 0 to 63 now).  Here a member is a scalar load where it is
 // used, and fresh() makes the compiler forget what it has loaded so far.  What an item does once is bound by the instructions it issues: a
 // wavefront has its SIMD's issue slots to itself for most of them.  With this, divisions by the pieces of a row that are shifts, and
 // epilogues through buffer stores, the start of a dK/dV item fell from 399 to 241 instructions and no forward kernel spills a

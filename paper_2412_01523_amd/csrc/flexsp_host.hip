@@ -747,6 +747,7 @@ bool outputs_apart(const flexsp_plan *p, const AttnArgs &a)
 int both_at_once(const flexsp_ctx *ctx, const flexsp_plan *p, AttnArgs &a)
 {
     const int dkv = (int)p->pass[FLEXSP_PASS_BWD_DKV].direct.size(), dq = (int)p->pass[FLEXSP_PASS_BWD_DQ].direct.size();
+    // (a plan of 128 keys an item may fit here, because its items are half as many, but the single launch has no such kernel)
     if (p->wide || !dkv || !dq || dkv + dq > workgroups_of(ctx) || !outputs_apart(p, a)) return 0;
     a.pq = p->dq[FLEXSP_PASS_BWD_DKV];
     a.dq_pq = p->dq[FLEXSP_PASS_BWD_DQ];
