@@ -46,8 +46,8 @@ HBM_PEAK = 8.0e12           # MI355X HBM3E, B/s
 # counter values and the algorithmic bytes beside them are in profiles/attention_hbm_traffic.md).
 # bench.py cannot run the profiler on itself: these are the figures of that summary.
 MEASURED_HBM_TRAFFIC = {
-    ("pareto-64k", "fwd"): 1109401063, ("pareto-64k", "bwd_dq"): 1347854523, ("pareto-64k", "bwd_dkv"): 1284704310,
-    ("single-128k", "fwd"): 11779112005, ("single-128k", "bwd_dq"): 25981247295, ("single-128k", "bwd_dkv"): 10197784226,
+    ("pareto-64k", "fwd"): 1029537792, ("pareto-64k", "bwd_dq"): 1342912326, ("pareto-64k", "bwd_dkv"): 1302433775,
+    ("single-128k", "fwd"): 11535943471, ("single-128k", "bwd_dq"): 22814568822, ("single-128k", "bwd_dkv"): 39482724607,
 }
 
 
