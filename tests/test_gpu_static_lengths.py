@@ -56,7 +56,7 @@ def test_odd_shapes(ctx, lens, hq, hkv, D):
     both(ctx, lens, hq, hkv, D, True)
 
 
-@pytest.mark.parametrize("T,B", [(1024, 3), (65536, 200)])
+@pytest.mark.parametrize("T,B", [(1024, 3), (65536, 200), (4096, 2), (65536, 2)])  # (the last two: batches that might run in halves)
 def test_wrong_lengths_compute_nothing(ctx, T, B):
     import torch
     from paper_2412_01523_amd import binding as fx
@@ -104,3 +104,38 @@ def test_room_for_more_tokens_changes_nothing(ctx, lens, hq, hkv, D, rows, causa
         torch.cuda.synchronize()
         assert torch.equal(o[:T].view(torch.int16), want.view(torch.int16)) and torch.equal(lse[:, :T].view(torch.int32), want_lse.view(torch.int32))
         assert bool((o[T:] == 7.0).all()) and bool((lse[:, T:] == 7.0).all())
+
+
+@pytest.mark.parametrize("rows,hq,D", [(2000, 8, 128), (4096, 8, 128), (9000, 8, 128), (4096, 4, 64), (17000, 4, 64)])
+def test_replayed_with_other_lengths(ctx, rows, hq, D):
+    """One captured call, the lengths changed between the replays: each runs as its lengths say, with the plan's bits."""
+    import torch
+    from paper_2412_01523_amd import binding as fx
+    print(f"static forward, captured: {rows} rows, {hq} heads, D={D}", flush=True)
+    q, k, v = (to_dev(wl.normal_bf16(773, tid, (rows, hq, D))) for tid in (0, 1, 2))
+    cud = torch.tensor([0, 300, 700], dtype=torch.int32).cuda()
+    o, lse = torch.empty((rows, hq, D), dtype=torch.bfloat16, device="cuda"), torch.empty((hq, rows), dtype=torch.float32, device="cuda")
+    call = lambda: fx.flexsp_attn_varlen_fwd_static(ctx, q, k, v, cud, o, lse)  # noqa: E731
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        call()
+    stream.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        call()
+    for lens in ([1000, 200], [300, 400], [0, 1900], [900, 900], [64, 1]):
+        cu, T = wl.cu_seqlens(lens), sum(lens)
+        cud.copy_(torch.from_numpy(cu))
+        o.fill_(7.0)
+        lse.fill_(7.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        plan = fx.Plan(ctx, cu, hq, hq, D)
+        assert int(plan.items(fx.PASS_FWD)[0]["nparts"].max()) == 1
+        want, want_lse = torch.empty((T, hq, D), dtype=torch.bfloat16, device="cuda"), torch.empty((hq, T), dtype=torch.float32, device="cuda")
+        fx.flexsp_attn_varlen_fwd(ctx, plan, q[:T], k[:T], v[:T], cud, want, want_lse)
+        torch.cuda.synchronize()
+        plan.close()
+        assert torch.equal(o[:T].view(torch.int16), want.view(torch.int16)) and torch.equal(lse[:, :T], want_lse), lens
+        assert bool((o[T:] == 7.0).all()) and bool((lse[:, T:] == 7.0).all()), lens
