@@ -216,6 +216,12 @@ struct Work {
 void distribute(std::vector<Work> &work, const std::vector<int64_t> &group_cost, int nq, int n_wg, int tile_rows,
                 HostPass &out, int spare = 0, int64_t row_bytes = 0, int heads_walked = 1);
 
+// Groups of one cost go round the queues in the order they are listed in: the n-th head listed of a sequence.  Where every queue gets several
+// of its heads it gets neighbours, which share their key head's rows in the XCD's L2 if heads are grouped: 262 144 tokens in
+// sequences of up to 65 536, 16 heads on 2, forward and backward 151.7 -> 150.3 ms.  (Same bits; nothing changes for the caches with as many
+// key heads as heads, nor with no more heads than queues.)
+int nth_head(int n, int heads, int nq) { return heads % nq ? n : n % nq * (heads / nq) + n / nq; }
+
 // Builds one pass: lists the items, spreads whole (sequence, head) groups over the queues
 // (largest group first onto the least loaded queue, so tiles that read the same K/V run on
 // one XCD and share its L2), then orders each queue by decreasing cost (short sequences: tile beside tile, see distribute) so that the long
@@ -235,7 +241,8 @@ void build_pass(const std::vector<int32_t> &cu, int B, int heads, int group_mult
         int32_t s = cu[b + 1] - cu[b];
         if (s <= 0) continue;
         int32_t nt = (int32_t)cdiv(s, tile_rows);
-        for (int h = 0; h < heads; h++) {
+        for (int n = 0; n < heads; n++) {
+            const int h = nth_head(n, heads, nq);
             int32_t gid = (int32_t)group_cost.size();
             int64_t gc = 0;
             for (int32_t t = 0; t < nt; t++) {
@@ -1008,7 +1015,8 @@ int flexsp_plan_create_kvshard(flexsp_ctx *ctx, const int32_t *cu_q, const int32
                 const int32_t sq = cu_q[b + 1] - cu_q[b], sk = cu_k[b + 1] - cu_k[b];
                 if (sq <= 0) continue;
                 const int32_t nt = (int32_t)cdiv(sq, kFwdBq);
-                for (int h = 0; h < Hq; h++) {
+                for (int n = 0; n < Hq; n++) {
+                    const int h = nth_head(n, Hq, ctx->num_xcd);
                     const int32_t gid = (int32_t)group_cost.size();
                     int64_t gc = 0;
                     for (int32_t t = 0; t < nt; t++) {

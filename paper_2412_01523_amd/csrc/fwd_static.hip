@@ -36,7 +36,9 @@ std::mutex g_scratch_mutex;
 // key tiles an item walks: tile index + 1 when causal (level = tile index), the sequence's tile
 // count otherwise (level = tile count - 1).  Levels are bucket-sorted with LDS counters; the order
 // of items inside a level is whatever the atomics give, which does not affect any result (items are
-// independent).  Lengths are validated here, on the device: a cu_seqlens that is not 0 = cu[0] <=
+// independent).  Where the heads are a multiple of the queues, a queue gets the same neighbouring heads of every tile instead of
+// every eighth item: as level, and with grouped heads an XCD reads few key heads' rows (16 384 tokens in 15 sequences, 16 heads on
+// 2: 154.4 -> 150.2 us).  Lengths are validated here, on the device: a cu_seqlens that is not 0 = cu[0] <=
 // cu[1] <= ... <= cu[B] <= T, a sequence with more than kStaticMaxLevels tiles or a batch with more
 // than kStaticMaxItems items publishes an EMPTY list (the attention kernel then touches nothing)
 // and raises the status word.  halves_d, if not 0, is the head dim of a forward that may run in halves: if the batch does, the list
@@ -175,9 +177,10 @@ __global__ __launch_bounds__(kBuildThreads) void build_static_queue_kernel(const
             it.slot = -1;
             it.parts = 1;
             for (int h = 0; h < heads; h++) {
-                const int p = p0 + h, x = p % nq;
+                const int p = p0 + h, x = heads % nq ? p % nq : h / (heads / nq);
                 it.head = h;
-                items[x * (total / nq) + min(x, total % nq) + p / nq] = it;
+                const int at = heads % nq ? p / nq : p0 / nq + h % (heads / nq);
+                items[x * (total / nq) + min(x, total % nq) + at] = it;
             }
         }
     }
