@@ -265,8 +265,8 @@ int flexsp_attn_varlen_bwd(flexsp_ctx *ctx, flexsp_plan *plan, flexsp_tensor q, 
  *   flexsp_attn_varlen_fwd_kvshard (_acc) and flexsp_attn_varlen_bwd_kvshard only (the other attention calls
  *   answer PLAN_MISMATCH); it is destroyed by flexsp_plan_destroy and inspected by flexsp_plan_num_items /
  *   _get_items, where an item's seq_start holds the sequence INDEX b (and, in FLEXSP_PASS_BWD_DKV, tile
- *   counts 64-key tiles of the SHARD).  Long query tiles are cut into parts as in flexsp_plan_create (a
- *   step = 64 shard keys); key tiles are not.  Hq <= 65 535, else UNSUPPORTED.
+ *   counts 64-key tiles of the SHARD).  Long tiles are cut into parts as in flexsp_plan_create (a step = 64
+ *   shard keys, or 64 query rows of one head, and one more for the tile).  Hq <= 65 535, else UNSUPPORTED.
  *
  * flexsp_attn_varlen_fwd_kvshard - per query row, softmax over the visible shard keys only:
  *   O = sum_j P_j v_j (bf16), LSE = log sum_j exp(scale q.k_j) (fp32, natural log, [head_count, Tq]).

@@ -54,7 +54,7 @@ constexpr int dq_lds()  // ... of the dQ pass: two steps (K | V)
 // SHARD = true is the variant for one shard of the keys (context parallelism; see the forward kernel):
 // an item names 64 keys of the shard and the query rows of its sequence on this device, key j is
 // visible to query row i iff j <= i + shift, the rows' log-sum-exp and delta are those of the COMPLETE
-// attention, and the gradients may be added to what dK / dV hold.  Tiles are not cut into parts.
+// attention, and the gradients may be added to what dK / dV hold.  Part p of a tile cut into k parts walks the p-th k-th of its steps.
 //
 // SELF = true: the log-sum-exp read is the forward's own and the workgroup forms delta = dO . O of a step's rows itself,
 // from pieces of O requested with the step's tiles and the tile's own dO, so that the pass does not have to come after the dQ pass.
@@ -104,7 +104,13 @@ __device__ __forceinline__ void dkv_pass(KernArgs &args, KernQueues &queues, con
             // steps at all when no row of the device sees these keys
             qfirst = a.causal ? (max(0, kv0 - sh) & ~(BQ - 1)) : 0;
             nsteps = max(0, (s - qfirst + BQ - 1) / BQ);
-            first = 0; total = nsteps * a.G; nparts = 1; part = 0; slot = -1;
+            first = 0; total = nsteps * a.G;
+            part = (it.head_parts >> 16) & 0xff; nparts = it.head_parts >> 24; slot = it.slot;
+            if (nparts > 1) {
+                const int all = total;
+                first = part * all / nparts;
+                total = (part + 1) * all / nparts;
+            }
         } else {
             const flexsp_item it = load_item(pq.items, item);
             s = it.seq_len; sk = s; sh = 0; g = it.head; kv0 = it.tile * kDkvBk;
@@ -135,7 +141,11 @@ __device__ __forceinline__ void dkv_pass(KernArgs &args, KernQueues &queues, con
         // it, does not show).
         if (n < kLateTicketSteps) deal.prefetch();
         const int q_end = qfirst + nsteps * BQ;
-        int h_cur = g * a.G + (SHARD ? 0 : first / nsteps), q_cur = qfirst + (SHARD ? 0 : (first % nsteps) * BQ);
+        int h_cur = g * a.G, q_cur = qfirst;
+        if (!SHARD || first > 0) {  // (a shard's tile may have no steps)
+            h_cur += first / nsteps;
+            q_cur += first % nsteps * BQ;
+        }
         int h_nxt = h_cur, q_nxt = q_cur;
         auto advance_nxt = [&]() {
             q_nxt += BQ;

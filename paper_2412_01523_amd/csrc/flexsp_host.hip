@@ -683,10 +683,12 @@ int plan_upload(flexsp_ctx *ctx, flexsp_plan *p)
                     const flexsp_item &it = items[n];
                     const int b = it.seq_start;
                     // a part of a cut tile: the keys of its steps only, positions counted from its first key
-                    const int32_t np = it.parts & 0xffff, part = it.parts >> 16;  // (whole tiles only in the dK/dV pass)
-                    const int32_t skip = np > 1 ? it.step_begin * kFwdBk : 0;
+                    // (the dK/dV pass finds a part's steps itself)
+                    const int32_t np = it.parts & 0xffff, part = it.parts >> 16;
+                    const bool by_keys = np > 1 && i != FLEXSP_PASS_BWD_DKV;
+                    const int32_t skip = by_keys ? it.step_begin * kFwdBk : 0;
                     int32_t k_len = p->cu_k[b + 1] - p->cu_k[b];
-                    if (np > 1 && part + 1 < np) k_len = std::min(k_len, it.step_end * kFwdBk);
+                    if (by_keys && part + 1 < np) k_len = std::min(k_len, it.step_end * kFwdBk);
                     d[n] = flexsp_shard_item{p->cu[b], p->cu[b + 1] - p->cu[b], p->cu_k[b] + skip, k_len - skip,
                                              p->shift[b] - skip, it.tile, it.head | (part << 16) | (np << 24), it.slot};
                 }
@@ -1041,7 +1043,7 @@ int flexsp_plan_create_kvshard(flexsp_ctx *ctx, const int32_t *cu_q, const int32
             distribute(work, group_cost, ctx->num_xcd, workgroups_of(ctx), kFwdBq, p->pass[pass], 2);
         }
         // dK/dV kernel: items (sequence index, key tile of the shard, kv head); cost = steps of 64 query rows
-        // from the first row that sees the tile, for every query head of the group.  Not cut into parts.
+        // from the first row that sees the tile, for every query head of the group.
         {
             std::vector<Work> work;
             std::vector<int64_t> group_cost;
@@ -1069,11 +1071,14 @@ int flexsp_plan_create_kvshard(flexsp_ctx *ctx, const int32_t *cu_q, const int32
                     group_cost.push_back(gc);
                 }
             }
-            // (one "workgroup" whose share no tile exceeds: nothing is cut)
-            distribute(work, group_cost, ctx->num_xcd, 1, kDkvBk, p->pass[FLEXSP_PASS_BWD_DKV], 1);
+            // Cut like the query tiles.  (They were not: few key heads with several query heads each, or one long sequence,
+            // are fewer tiles than workgroups, and a tile is a chain of all its group's heads.  One device's ring pass, whole tiles ->
+            // cut: 14 514 tokens over four devices, 16 heads on 2 1 222 -> 622 us; 2 517, 8 heads on 1 199 -> 132; 4 912 over two, 2
+            // heads, D = 64 158 -> 102; 35 804 over eight, 16 heads on 4 4 949 -> 4 563; 5 306 over four, 2 heads 180 -> 162.)
+            distribute(work, group_cost, ctx->num_xcd, workgroups_of(ctx), kDkvBk, p->pass[FLEXSP_PASS_BWD_DKV], 2, 0, G);
         }
-        for (int i = 0; i < 3; i++)  // (whole tiles only in the dK/dV pass)
-            direct_list(p->pass[i], ctx->num_xcd, workgroups_of(ctx), 2, i == FLEXSP_PASS_BWD_DQ ? kShortPartSteps : 0);
+        for (int i = 0; i < 3; i++)
+            direct_list(p->pass[i], ctx->num_xcd, workgroups_of(ctx), 2, i == FLEXSP_PASS_FWD ? 0 : kShortPartSteps);
     } catch (const std::bad_alloc &) {
         delete p;
         return FLEXSP_OUT_OF_MEMORY;
