@@ -996,9 +996,9 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
 // delta is formed from the piece of dO that the lane has just copied into the tile and the same piece of O, which waits for the step in
 // a register: both rows in registers were 35 spilled ones with D = 128, and dO was fetched twice (1 201 tokens, 16 heads on 4 38.9 -> 37.8
 // us; 5 630 tokens, 2 heads 51.0 -> 50.0).
-// PER_CU: a launch of at most one workgroup per compute unit takes the kernel that has the whole register file (808 tokens, 4 heads:
-// 31.7 against 34.3 us), a larger one the kernel that two workgroups can share a compute unit with (5 630 tokens, 2 heads:
-// 38.8 against 43.4 us).
+// PER_CU: a launch of at most one workgroup per compute unit takes the kernel that has the whole register file, a larger one the kernel
+// that two workgroups can share a compute unit with (5 630 tokens, 2 heads: 38.8 against 43.4 us; since results of matrix
+// instructions stay in vector registers, see build.py, the former needs 251 and the two differ by less than 1 % where either would do).
 template <int D, bool SHARD, int PER_CU>
 __global__ __launch_bounds__(kThreads, PER_CU) void attn_bwd_both_kernel(const AttnArgs)
 {
