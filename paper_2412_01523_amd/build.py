@@ -19,7 +19,7 @@ INCLUDE = PKG.parent / "include"
 OBJ = CSRC / "_build"
 LIB = PKG / "libflexsp.so"
 
-SOURCES = ["flexsp_host.hip", "pack.hip", "attn_fwd.hip", "attn_bwd.hip", "planner.hip", "fwd_static.hip",
+SOURCES = ["flexsp_host.hip", "pack.hip", "attn_fwd.hip", "attn_fwd_search.hip", "attn_bwd.hip", "planner.hip", "fwd_static.hip",
            "lse_merge.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
@@ -44,7 +44,7 @@ SOURCE_ORDER = ["-mllvm", "-pre-RA-sched=source", "-mllvm", "-enable-misched=fal
 # 112, with 904 copies): forward and backward of 200 tokens, 4 heads 20.1 -> 19.5 us, 440, 16 heads on 4 28.5 -> 27.7, 2 000, 2 heads on 1
 # 31.6 -> 30.7, same bits; the kernels that share a compute unit are compiled the same either way.
 VECTOR_RESULTS = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-PER_SOURCE = {"attn_fwd.hip": SOURCE_ORDER + VECTOR_RESULTS, "attn_bwd.hip": SOURCE_ORDER + VECTOR_RESULTS}
+PER_SOURCE = {"attn_fwd.hip": SOURCE_ORDER + VECTOR_RESULTS, "attn_fwd_search.hip": SOURCE_ORDER + VECTOR_RESULTS, "attn_bwd.hip": SOURCE_ORDER + VECTOR_RESULTS}
 
 
 def _hipcc() -> str:

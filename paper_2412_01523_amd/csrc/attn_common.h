@@ -623,8 +623,11 @@ __device__ __forceinline__ flexsp_shard_item load_shard_item(const flexsp_shard_
 // in front of the descriptor, the ticket, the look at all counters at the end, the count of those that left are
 // four trips to memory one after the other in a kernel that otherwise takes a dozen.  Measured, forward
 // and backward: 436 tokens in four sequences, 4 heads, D = 64: 30.8 -> 25.7 us; batches of 80 and 92 us: 6 and 8 % less.
-struct ItemDealer {
+// LISTED = false: there is no list, place l of queue q is place l * nq + q of all, and the caller says how many there are (`total`).
+template <bool LISTED = true>
+struct Dealer {
     const int32_t *offsets;
+    int total;
     int32_t *counters;  // kCounterStride apart (a line of their own each: they are hammered from all
                         // compute dies at once): [q] tickets drawn beyond the static ones, [nq] workgroups that left
     int *slot;          // LDS word
@@ -633,6 +636,8 @@ struct ItemDealer {
     bool direct;        // one workgroup per item
 
     __device__ __forceinline__ int wgs_of(int qq) const { return (grid - qq + nq - 1) / nq; }
+    __device__ __forceinline__ int place(int qq, int l) const { return LISTED ? offsets[qq] + l : l * nq + qq; }
+    __device__ __forceinline__ int end(int qq) const { return LISTED ? offsets[qq + 1] : total; }
     __device__ __forceinline__ int draw(int qq)  // wavefront 0 only; waits for the answer
     {
         int tk = 0;
@@ -657,7 +662,7 @@ struct ItemDealer {
             int key = 0;
             if (l < nq) {
                 const int drawn = __hip_atomic_load(counters + l * kCounterStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const int left = offsets[l + 1] - offsets[l] - wgs_of(l) - drawn;
+                const int left = (LISTED ? offsets[l + 1] - offsets[l] : (total - l + nq - 1) / nq) - wgs_of(l) - drawn;
                 const int dist = l > q ? l - q : l - q + nq;  // 1 .. nq
                 key = left > 0 ? (min(left, 0xFFFFF) << 8) | ((8 - dist) << 4) | l : 0;
             }
@@ -668,8 +673,8 @@ struct ItemDealer {
             key = __builtin_amdgcn_readfirstlane(key);
             if (key == 0) return -1;
             q = key & 15;
-            const int idx = offsets[q] + wgs_of(q) + draw(q);
-            if (idx < offsets[q + 1]) return idx;
+            const int idx = place(q, wgs_of(q) + draw(q));
+            if (idx < end(q)) return idx;
         }
         return -1;
     }
@@ -684,9 +689,9 @@ struct ItemDealer {
     }
     __device__ __forceinline__ int first(KernQueues &pq, int grid_, int first_wg, int *lds_word, int wave_, int lane_)  // first_wg: the launch's first workgroup of this pass
     {
-        direct = pq.direct != 0;
-        if (direct) return workgroup_id() - first_wg;
-        offsets = pq.offsets;
+        direct = LISTED ? pq.direct != 0 : total <= grid_;
+        if (direct) return LISTED || workgroup_id() < total ? workgroup_id() - first_wg : -1;
+        if (LISTED) offsets = pq.offsets;
         counters = pq.counters;
         slot = lds_word;
         nq = pq.nq;
@@ -697,8 +702,8 @@ struct ItemDealer {
         pending = 0;
         int idx = -1;
         if (wave == 0) {
-            idx = offsets[q] + workgroup_id() / pq.nq;
-            if (idx >= offsets[q + 1]) idx = steal();
+            idx = place(q, workgroup_id() / pq.nq);
+            if (idx >= end(q)) idx = steal();
         }
         return publish(idx);
     }
@@ -714,8 +719,8 @@ struct ItemDealer {
         if (direct) return -1;
         int idx = -1;
         if (wave == 0) {
-            idx = offsets[q] + wgs_of(q) + __builtin_amdgcn_readfirstlane(pending);
-            if (idx >= offsets[q + 1]) idx = steal();
+            idx = place(q, wgs_of(q) + __builtin_amdgcn_readfirstlane(pending));
+            if (idx >= end(q)) idx = steal();
         }
         return publish(idx);
     }
@@ -734,5 +739,6 @@ struct ItemDealer {
         }
     }
 };
+typedef Dealer<> ItemDealer;
 
 }  // namespace flexsp

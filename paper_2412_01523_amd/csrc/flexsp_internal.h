@@ -39,6 +39,8 @@ constexpr int kMaxParts = 8;
 constexpr int64_t kPartAffinityBytes = (int64_t)7 << 19;  // 3.5 MiB of an XCD's 4 MiB of L2 (see split_long_items)
 constexpr int kSplitSteps = 4;  // a forward in halves (attn_fwd_kernel) splits walks of at least this many steps
 constexpr int kMaxSplitRecords = 2048;
+constexpr int kSearchSeqs = 256;      // a forward without a plan finds its items in the lengths of up to so many sequences (attn_fwd_search.hip)
+constexpr int kStaticRecords = 1024;  // ... and has so many partial-result records
 
 // Work item of the key-shard forward: query rows q_start .. q_start+q_len-1 of q / o / lse, shard
 // keys k_start .. k_start+k_len-1 of k / v, shift = position of the first query in its sequence
@@ -100,6 +102,7 @@ hipError_t launch_pack(const void *src, void *dst, int64_t T, int H, int D, int 
 hipError_t launch_pack_many(int n, const void *const *src, void *const *dst, int64_t T, const int32_t *H, int D,
                             int P, int eb, bool unpack, hipStream_t s);
 hipError_t launch_attn_fwd(const AttnArgs &a, int D, int grid, hipStream_t s);
+hipError_t launch_attn_fwd_search(const AttnArgs &a, int D, int grid, hipStream_t s);  // a.cu, a.pq.counters, split_flags and split_scratch: no list
 hipError_t launch_attn_fwd_kvshard(const AttnArgs &a, int D, int grid, hipStream_t s);  // a.pq.items: flexsp_shard_item
 hipError_t launch_lse_merge(const uint16_t *oa, const float *la, const uint16_t *ob, const float *lb, uint16_t *oo,
                             float *lo, int64_t T, int H, int D, int32_t oa_st, int32_t oa_sh, int32_t ob_st,

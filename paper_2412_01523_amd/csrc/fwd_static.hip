@@ -1,9 +1,9 @@
 // flexsp_attn_varlen_fwd_static: the forward of packed attention for callers that cannot
 // allocate (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).
-// It needs no plan: the work queues the forward kernel consumes are built ON THE DEVICE, from the
-// device copy of cu_seqlens, into a file-scope array that every GPU the library runs on holds
-// until the process ends.  The attention pass itself is that of flexsp_attn_varlen_fwd.  A batch small
-// enough to be on the chip all at once is launched without queues (see the entry point).
+// It needs no plan: the forward kernel finds its items in the device copy of cu_seqlens (attn_fwd_search.h), and deals them by
+// counters in a file-scope array that every GPU the library runs on holds until the process ends.  For batches of very many sequences
+// work queues are built ON THE DEVICE, into the same array, by a kernel in front.  The attention pass itself is that of
+// flexsp_attn_varlen_fwd.  A batch small enough to be on the chip all at once shares nothing with other calls (see the entry point).
 #include <mutex>
 
 #include "flexsp_internal.h"
@@ -19,7 +19,9 @@ constexpr int kCountersOff = 0;          // kMaxQueues ticket counters + "workgr
 constexpr int kOffsetsOff = (kMaxQueues + 1) * kCounterStride * 4;  // int32[16]: kMaxQueues + 1 queue boundaries
 constexpr int kStatusOff = kOffsetsOff + 64;  // int32[2], to look at when debugging: items listed by the last call that had queues, 1 if it rejected its lengths
 constexpr int kItemsOff = kStatusOff + 64;
-constexpr size_t kScratchBytes = kItemsOff + (size_t)kStaticMaxItems * sizeof(flexsp_item);
+constexpr size_t kFlagsOff = kItemsOff + (size_t)kStaticMaxItems * sizeof(flexsp_item);  // int32[kStaticRecords]: arrival counters, clear between calls
+constexpr size_t kRecordsOff = kFlagsOff + (size_t)kStaticRecords * 4;                     // partial results of cut tiles
+constexpr size_t kScratchBytes = kRecordsOff + (size_t)kStaticRecords * kPartialBytes;
 
 // One copy per GPU, at its own address.  In host code this name is only a handle for
 // hipGetSymbolAddress; kernels and copies use the resolved pointer (g_scratch_ptr).
@@ -38,11 +40,10 @@ std::mutex g_scratch_mutex;
 // of items inside a level is whatever the atomics give, which does not affect any result (items are
 // independent).  Where the heads are a multiple of the queues, a queue gets the same neighbouring heads of every tile instead of
 // every eighth item: as level, and with grouped heads an XCD reads few key heads' rows (16 384 tokens in 15 sequences, 16 heads on
-// 2: 154.4 -> 150.2 us).  Lengths are validated here, on the device: a cu_seqlens that is not 0 = cu[0] <=
+// 2: 154.4 -> 150.2 us, when that batch had a list).  Lengths are validated here, on the device: a cu_seqlens that is not 0 = cu[0] <=
 // cu[1] <= ... <= cu[B] <= T, a sequence with more than kStaticMaxLevels tiles or a batch with more
 // than kStaticMaxItems items publishes an EMPTY list (the attention kernel then touches nothing)
-// and raises the status word.  halves_d, if not 0, is the head dim of a forward that may run in halves: if the batch does, the list
-// is empty as well.
+// and raises the status word.
 // One workgroup on an idle chip: trips to memory and chains of LDS accesses are what it takes.  Levels are summed 64 at a
 // time by a wavefront, lengths are read 64 sequences at a time, a lane lists a tile.  The whole call, against levels
 // summed one by one and a length read per sequence: 62 852 tokens in 201 sequences, 1 head 29.1 -> 25.1 us; 16 384 tokens
@@ -60,13 +61,12 @@ __device__ __forceinline__ int inclusive_sum(int x, int lane)  // over the wavef
 }
 
 __global__ __launch_bounds__(kBuildThreads) void build_static_queue_kernel(const int32_t *cu, int B, int T, int heads,
-                                                                            int causal, int tile_rows, int halves_d, int num_cu,
-                                                                            unsigned char *scr)
+                                                                            int causal, int tile_rows, unsigned char *scr)
 {
     __shared__ int hist[kStaticMaxLevels + 2];   // sequences with exactly n tiles
     __shared__ int start[kStaticMaxLevels + 1];  // first list position of a level
     __shared__ int fill[kStaticMaxLevels + 1];   // (sequence, tile) pairs placed in a level so far
-    __shared__ int s_maxnt, s_bad, s_total, s_tiles, s_steps, s_longest;  // (the last three: see HalvesCount)
+    __shared__ int s_maxnt, s_bad, s_total;
     int32_t *counters = (int32_t *)(scr + kCountersOff);
     int32_t *offsets = (int32_t *)(scr + kOffsetsOff);
     int32_t *status = (int32_t *)(scr + kStatusOff);
@@ -79,7 +79,6 @@ __global__ __launch_bounds__(kBuildThreads) void build_static_queue_kernel(const
         s_maxnt = 0;
         s_bad = (B > 0 && cu[0] != 0) ? 1 : 0;
         s_total = 0;
-        s_tiles = s_steps = s_longest = 0;
     }
     if (tid <= kMaxQueues) counters[tid * kCounterStride] = 0;  // every call starts with clear tickets
     __syncthreads();
@@ -98,12 +97,6 @@ __global__ __launch_bounds__(kBuildThreads) void build_static_queue_kernel(const
         if (nt > 0) {
             atomicAdd(&hist[nt], 1);
             atomicMax(&s_maxnt, nt);
-            if (halves_d) {
-                const int n = (hi - lo + kHalfBq - 1) / kHalfBq;
-                atomicAdd(&s_tiles, n);
-                atomicAdd(&s_steps, causal ? n * (n + 1) / 2 : n * n);
-                atomicMax(&s_longest, n);
-            }
         }
     }
     __syncthreads();
@@ -129,9 +122,7 @@ __global__ __launch_bounds__(kBuildThreads) void build_static_queue_kernel(const
         }
         if (lane == 0) {
             if ((int64_t)pos * heads > kStaticMaxItems) s_bad = 1;
-            // (a batch in halves is the other launch's)
-            const bool halves = halves_d && fwd_halves(halves_d, {cu[B], B, (int64_t)s_tiles * heads, (int64_t)s_steps * heads, s_longest}, num_cu);
-            s_total = s_bad || halves ? 0 : pos * heads;
+            s_total = s_bad ? 0 : pos * heads;
         }
     }
     __syncthreads();
@@ -240,10 +231,13 @@ extern "C" int flexsp_attn_varlen_fwd_static(flexsp_ctx *ctx, flexsp_tensor q, f
     // might have been others take what they took, up to 0.6 us more with D = 64.  A second launch for the halves instead, which
     // leaves at once where it is not wanted, was 2.5 to 4 us for each of them.)
     const bool may_halve = fwd_may_halve(T, B, head_count, num_cu);
+    // (Cut tiles need records, and tickets counters, that calls share: batches of fewer items, which may run side by side, have neither.  A
+    // batch that may run in halves is one of at most 32 sequences.)
+    const bool search = listed && B <= kSearchSeqs;
     hipError_t e = hipSuccess;
-    if (listed) {
+    if (listed && !search) {
         hipLaunchKernelGGL(build_static_queue_kernel, dim3(1), dim3(kBuildThreads), 0, s, cu_seqlens_dev, (int)B, (int)T,
-                           (int)head_count, causal ? 1 : 0, kFwdBq, may_halve ? D : 0, num_cu, scr);
+                           (int)head_count, causal ? 1 : 0, kFwdBq, scr);
         e = hipGetLastError();
         if (e != hipSuccess) return hip_status(e);
     }
@@ -263,22 +257,26 @@ extern "C" int flexsp_attn_varlen_fwd_static(flexsp_ctx *ctx, flexsp_tensor q, f
     a.T = (int32_t)T; a.Hq = head_count; a.G = head_count / kv_head_count; a.causal = causal ? 1 : 0;
     a.scale = scale; a.scale_l2 = scale * 1.4426950408889634f;
     a.num_cu = num_cu;
-    if (!listed || may_halve) {
+    if (!listed || search) {
         a.cu = cu_seqlens_dev;
         a.B = B;
     }
     // the item count is known to the device only.  With a list: a full persistent grid; workgroups without work leave
     int64_t grid = 2 * (int64_t)num_cu;
     if (listed) {
-        a.pq.items = (const flexsp_item *)(scr + kItemsOff);
-        a.pq.offsets = (const int32_t *)(scr + kOffsetsOff);
+        if (!search) {
+            a.pq.items = (const flexsp_item *)(scr + kItemsOff);
+            a.pq.offsets = (const int32_t *)(scr + kOffsetsOff);
+        }
         a.pq.counters = (int32_t *)(scr + kCountersOff);
         a.pq.nq = kMaxQueues;
+        a.pq.split_flags = (int32_t *)(scr + kFlagsOff);
+        a.pq.split_scratch = (char *)scr + kRecordsOff;
     } else {
         grid = may_halve ? std::max(most_items, fwd_halves_most(D, T, B, head_count, num_cu)) : most_items;
     }
     // (halves with two buffers where whole items too have the LDS for it: D = 128 one workgroup to a compute unit, D = 64 two)
-    if (may_halve) a.halves = !listed && (D == 64 || most_items <= num_cu) ? 2 : 1;
-    e = launch_attn_fwd(a, D, (int)grid, s);
+    if (may_halve) a.halves = !search && (D == 64 || most_items <= num_cu) ? 2 : 1;
+    e = search && !may_halve ? launch_attn_fwd_search(a, D, (int)grid, s) : launch_attn_fwd(a, D, (int)grid, s);
     return e == hipSuccess ? FLEXSP_OK : hip_status(e);
 }
