@@ -351,7 +351,8 @@ int flexsp_lse_merge_acc(flexsp_ctx *ctx, flexsp_tensor o_acc, float *lse_acc, f
  * The lengths are read on the device only, so they cannot be checked by the host: if the device
  * array is not a valid prefix-sum list inside [0, T], NOTHING is computed (o and lse keep their
  * contents).  Calls with queues share the GPU's array: those that may overlap in time on one
- * GPU (different streams, or graph replays running concurrently) race; order them.  Sequences are
+ * GPU (different streams, or graph replays running concurrently) race; order them.  What calls that did
+ * overlap wrote is undefined; ordered calls after them are right again.  Sequences are
  * served longest tile first like a plan's queues, but without the plan's grouping of a head's tiles
  * onto one XCD, so it is somewhat slower than the plan-based call; nothing synchronises the host.
  * Errors: INVALID_ARGUMENT, UNSUPPORTED, NO_DEVICE, HIP_ERROR.

@@ -732,11 +732,30 @@ struct Dealer {
     // leaving workgroup: the workgroups still running then find their tiles gone from the cache.)
     __device__ __forceinline__ void finish()
     {
+        static_assert(LISTED, "counters that calls share: finish_shared");
         if (direct) return;
         if (wave == 0 && lane == 0) {
             if (atomicAdd(counters + nq * kCounterStride, 1) == grid - 1)
                 for (int i = 0; i <= nq; i++) __hip_atomic_store(counters + i * kCounterStride, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+    }
+    // ... where the counters are not a plan's: clears the arrival counters behind them too.  They are clear already unless launches have
+    // overlapped, see last_to_leave.
+    __device__ __forceinline__ void finish_shared()
+    {
+        if (direct || wave != 0) return;
+        struct Left {
+            int32_t *word;
+            __device__ __forceinline__ unsigned add(unsigned n) { return atomicAdd((unsigned *)word, n); }
+        };
+        int last = 0;
+        if (lane == 0) last = last_to_leave(Left{counters + nq * kCounterStride}, (unsigned)grid);
+        if (!__builtin_amdgcn_readfirstlane(last)) return;
+        if (lane < nq) __hip_atomic_store(counters + lane * kCounterStride, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        static_assert(kStaticFlagsAt % 2 == 0 && kStaticRecords % 128 == 0, "two at a time");
+        uint64_t *const flags = (uint64_t *)(counters + kStaticFlagsAt);
+#pragma unroll
+        for (int i = 0; i < kStaticRecords / 128; i++) __hip_atomic_store(flags + i * 64 + lane, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 };
 typedef Dealer<> ItemDealer;

@@ -766,7 +766,7 @@ __device__ __forceinline__ void fwd_pass(KernArgs &args, const flexsp_item &foun
                                     (SHARD && !(l_tot > 0.f)) ? 0.f : 1.0f / l_tot, lane);
         // deal.advance() holds the barrier after which the LDS buffers are reused by the next item
     }
-    deal.finish();
+    if constexpr (SEARCH) deal.finish_shared(); else deal.finish();
 }
 
 }  // namespace

@@ -41,6 +41,22 @@ constexpr int kSplitSteps = 4;  // a forward in halves (attn_fwd_kernel) splits 
 constexpr int kMaxSplitRecords = 2048;
 constexpr int kSearchSeqs = 256;      // a forward without a plan finds its items in the lengths of up to so many sequences (attn_fwd_search.hip)
 constexpr int kStaticRecords = 1024;  // ... and has so many partial-result records
+constexpr int kStaticFlagsAt = (kMaxQueues + 1) * kCounterStride;  // ... whose arrival counters stand so many int32 behind its ticket counters
+
+// One workgroup's leave from a launch whose counters calls without a plan share: true for the one that has to clear them.  Such calls have
+// to be ordered, but if two overlap all the same nothing of it may stay for the calls after them, which have no plan of their own to
+// start from.  So leaves are never overwritten: they are counted over all launches (of one grid size each) and taken off by the
+// `grid`, however those mix, and once every workgroup of all of them has left, the count is 0 and the last one has cleared what they drew and
+// counted.  (A count set to 0 by whoever finds the others there lost the leaves that came in between.)  WORD: add(n) returns the
+// value before.
+template <class WORD>
+__host__ __device__ inline bool last_to_leave(WORD &&left, unsigned grid)
+{
+    const unsigned n = left.add(1u) + 1u;
+    if (n < grid || (n > grid && n % grid)) return false;
+    left.add(0u - grid);
+    return true;
+}
 
 // Work item of the key-shard forward: query rows q_start .. q_start+q_len-1 of q / o / lse, shard
 // keys k_start .. k_start+k_len-1 of k / v, shift = position of the first query in its sequence

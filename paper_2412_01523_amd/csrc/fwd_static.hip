@@ -16,11 +16,11 @@ namespace {
 constexpr int kStaticMaxItems = 65536;   // work items (128 query rows of one head each) per call
 constexpr int kStaticMaxLevels = 4096;   // query tiles per sequence: sequences up to 524 288 tokens
 constexpr int kCountersOff = 0;          // kMaxQueues ticket counters + "workgroups done", kCounterStride int32 apart
-constexpr int kOffsetsOff = (kMaxQueues + 1) * kCounterStride * 4;  // int32[16]: kMaxQueues + 1 queue boundaries
+constexpr int kFlagsOff = kStaticFlagsAt * 4;  // int32[kStaticRecords]: arrival counters, clear between calls
+constexpr int kOffsetsOff = kFlagsOff + kStaticRecords * 4;  // int32[16]: kMaxQueues + 1 queue boundaries
 constexpr int kStatusOff = kOffsetsOff + 64;  // int32[2], to look at when debugging: items listed by the last call that built queues, 1 if it rejected its lengths
 constexpr int kItemsOff = kStatusOff + 64;
-constexpr size_t kFlagsOff = kItemsOff + (size_t)kStaticMaxItems * sizeof(flexsp_item);  // int32[kStaticRecords]: arrival counters, clear between calls
-constexpr size_t kRecordsOff = kFlagsOff + (size_t)kStaticRecords * 4;                     // partial results of cut tiles
+constexpr size_t kRecordsOff = kItemsOff + (size_t)kStaticMaxItems * sizeof(flexsp_item);  // partial results of cut tiles
 constexpr size_t kScratchBytes = kRecordsOff + (size_t)kStaticRecords * kPartialBytes;
 
 // One copy per GPU, at its own address.  In host code this name is only a handle for

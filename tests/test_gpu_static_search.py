@@ -29,6 +29,8 @@ CASES = {
     "last-tile-of-one-step": ([128 * 9 + 1, 128 * 9, 128 * 9 + 64, 128 * 9 + 65] * 8, 0, 8, 2, 128, True, False),
     "heads-16": ([2000, 1000, 3, 700] * 2 + [90] * 20, 0, 16, 2, 64, True, "by the plan only"),
     "heads-12-not-causal": ([700, 0, 513, 512, 1] * 5, 0, 12, 4, 128, False, False),
+    "heads-8-cut": ([4300] + [30] * 31, 0, 8, 4, 128, True, True),
+    "heads-16-cut-d64": ([2500, 1] + [30] * 31, 3, 16, 2, 64, True, True),
     "64-sequences": ([130, 128] * 32, 0, 8, 8, 128, True, False),
     "65-sequences": ([257] * 64 + [1], 0, 8, 8, 64, False, False),
     "256-sequences": ([i % 300 for i in range(256)], 5, 4, 2, 128, True, False),
@@ -87,3 +89,40 @@ def test_wrong_or_no_lengths_touch_nothing(ctx, cu):
         good = lens is not cu
         assert bool((o == 7.0).all()) != good and bool((lse == 7.0).all()) != good
         assert not good or bool(torch.isfinite(lse).all())
+
+
+def test_replayed_dealt_and_cut(ctx):
+    """One captured call whose batches are dealt whole, dealt with tiles cut, and small enough for neither, in turn: each replay starts from the
+    counters that the one before left, and has the plan's bits."""
+    import torch
+    from paper_2412_01523_amd import binding as fx
+    rows, hq, hkv, D, B = 8192, 8, 4, 128, 32
+    q, k, v = (to_dev(wl.normal_bf16(883, tid, (rows, h, D))) for tid, h in ((0, hq), (1, hkv), (2, hkv)))
+    cud = torch.from_numpy(wl.cu_seqlens([128] * B)).cuda()
+    o, lse = torch.empty((rows, hq, D), dtype=torch.bfloat16, device="cuda"), torch.empty((hq, rows), dtype=torch.float32, device="cuda")
+    call = lambda: fx.flexsp_attn_varlen_fwd_static(ctx, q, k, v, cud, o, lse)  # noqa: E731
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        call()
+    stream.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        call()
+    whole, cut, short = [260] * 31 + [1], [4300] + [30] * 31, [64] * 32
+    for lens in (whole, cut, cut, short, cut, whole, whole, cut):
+        cu, T = wl.cu_seqlens(lens), sum(lens)
+        print(f"static forward, captured: {lens[0]} tokens in the first of {B} sequences", flush=True)
+        cud.copy_(torch.from_numpy(cu))
+        o.fill_(7.0)
+        lse.fill_(7.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        plan = fx.Plan(ctx, cu, hq, hkv, D)
+        assert (plan.items(fx.PASS_FWD)[0]["nparts"] > 1).any() == (lens is cut)
+        want, want_lse = torch.empty((T, hq, D), dtype=torch.bfloat16, device="cuda"), torch.empty((hq, T), dtype=torch.float32, device="cuda")
+        fx.flexsp_attn_varlen_fwd(ctx, plan, q[:T], k[:T], v[:T], cud, want, want_lse)
+        torch.cuda.synchronize()
+        plan.close()
+        assert torch.equal(o[:T].view(torch.int16), want.view(torch.int16)) and torch.equal(lse[:, :T].view(torch.int32), want_lse.view(torch.int32))
+        assert bool((o[T:] == 7.0).all()) and bool((lse[:, T:] == 7.0).all())
