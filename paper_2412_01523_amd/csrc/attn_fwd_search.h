@@ -35,9 +35,14 @@ __device__ __forceinline__ int lanes_max(int x)
 // come from counts of set bits.  Whole call, list -> search: 2 759 tokens, 16 heads on 2 27.0 -> 22.9 us; 16 384 tokens in 15
 // sequences, 16 heads on 2 152.5 -> 150.3; 31 875, 8 heads 523 -> 518.
 // And tiles that outlast the rest are cut into parts as a plan cuts them (split_long_items; the same parts, as long as the records of
-// partial results suffice), which a list of whole tiles did not: 63 259 tokens, 1 head 167 -> 112 us; 9 009, 8 heads on 4 43.6 ->
-// 38.3; 51 606, 2 heads on 1 146.3 -> 143.3.  Only where the longest tile lasts 1.4 even shares: parts are not kept to an XCD here, and
-// at 1.34 (14 604 tokens, 8 heads) cut 129.4 -> 131.9, whole 128.8 -> 126.1, at 0.9 (31 875) cut 524 -> 535.
+// partial results suffice), which a list of whole tiles did not: 63 259 tokens, 1 head 167 -> 112 us; 51 606, 2 heads on 1 146.3 -> 143.3.
+// Only where the longest tile outlasts the rest by more than the hand-over costs.  A workgroup whose neighbour on the compute unit has run out
+// of work goes nearly twice as fast, so a longest tile that is alone there costs time from about two even shares on, and beyond that must be worth
+// the hand-over's steps; without a mask all tiles of the longest sequence are equally long, and where they are more than the compute
+// units two of them share one.  Whole call, whole -> cut: 6 208 tokens in four sequences, 16 heads on 4 (a share of 34 steps, the longest
+// 59) 80 -> 88 us; 10 994 in 171, 12 heads, D = 64 (48, 86) 83 -> 91; a share of 64 to 96 steps and 2 to 2.3 of it 0.94 of the time, up to 48 steps 1.04 to 1.09;
+// unmasked 38 098, 2 heads, D = 64 (233, 338, on 338 tiles) 319 -> 270; 6 773, 6 heads on 3 (20, 58, on 174 tiles) 55 -> 70.  Of 618 batches whose longest
+// tile lasts a share or more, cut by this line, eight take over 2 % more than whole (cut from 1.4 shares on, 186).
 template <int CHUNKS>
 struct SearchBatch {
     static constexpr int kWhole = 1 << 24;  // a part length that no tile reaches
@@ -111,8 +116,15 @@ struct SearchBatch {
         maxnt = lanes_max(longest);
         // (no parts where a call on tensors of the batch's own size would be one of few items, which has none: the room in the tensors
         // changes no bits)
-        const int share = (int)((int64_t)lanes_sum(cost) * heads / (2 * a.num_cu));
-        if (((__builtin_amdgcn_readfirstlane(last) + kFwdBq - 1) / kFwdBq + a.B) * (int64_t)heads > 2 * a.num_cu && 5 * 2 * maxnt > 7 * share) {
+        const int share = (int)((int64_t)lanes_sum(cost) * heads / (2 * a.num_cu)), steps = 2 * maxnt;
+        int longs = 0;  // without a mask: tiles of three quarters of the longest's steps or more
+        if (!causal) {
+#pragma unroll
+            for (int c = 0; c < CHUNKS; c++) longs += 4 * l[c].nt >= 3 * maxnt ? l[c].nt : 0;
+            longs = lanes_sum(longs) * heads;
+        }
+        const bool outlasts = causal ? 4 * steps > 7 * share + 80 : longs <= a.num_cu ? steps > 2 * share + 20 : 3 * steps > 4 * share + 42;
+        if (((__builtin_amdgcn_readfirstlane(last) + kFwdBq - 1) / kFwdBq + a.B) * (int64_t)heads > 2 * a.num_cu && outlasts) {
             target = max(min(share * 3 / 4, max((int)((int64_t)share * 35 / 100), (int)kLongPartSteps)), kMinPartSteps);
         }
         // (every cut tile stands at a level from first_level(2) on: a record for each place down to there)

@@ -30,7 +30,7 @@ CASES = {
     "heads-16": ([2000, 1000, 3, 700] * 2 + [90] * 20, 0, 16, 2, 64, True, "by the plan only"),
     "heads-12-not-causal": ([700, 0, 513, 512, 1] * 5, 0, 12, 4, 128, False, False),
     "heads-8-cut": ([4300] + [30] * 31, 0, 8, 4, 128, True, True),
-    "heads-16-cut-d64": ([2500, 1] + [30] * 31, 3, 16, 2, 64, True, True),
+    "heads-8-cut-d64": ([4100, 1] + [30] * 31, 3, 8, 2, 64, True, True),
     "64-sequences": ([130, 128] * 32, 0, 8, 8, 128, True, False),
     "65-sequences": ([257] * 64 + [1], 0, 8, 8, 64, False, False),
     "256-sequences": ([i % 300 for i in range(256)], 5, 4, 2, 128, True, False),
@@ -69,6 +69,25 @@ def test_same_bits_as_with_a_plan(ctx, name):
             assert torch.equal(o[:T].view(torch.int16), want.view(torch.int16))
             assert torch.equal(lse[:, :T].view(torch.int32), want_lse.view(torch.int32))
         assert bool((o[T:] == 7.0).all()) and bool((lse[:, T:] == 7.0).all())
+
+
+# (a longest tile of 59 steps beside an even share of 34; unmasked, 58 beside 18 on fewer tiles than compute units)
+@pytest.mark.parametrize("lens,hq,hkv,D,causal", [([3776, 507, 1386, 539], 16, 4, 128, True), ([3700] + [77] * 52, 6, 3, 128, False)])
+def test_tiles_that_do_not_outlast_the_rest_stay_whole(ctx, lens, hq, hkv, D, causal):
+    """The first sequence has the bits of a call of its own, which has too few items to be dealt and cuts nothing."""
+    import torch
+    from paper_2412_01523_amd import binding as fx
+    print(f"static forward, whole tiles: {lens[0]} tokens beside {len(lens) - 1} sequences, {hq} heads", flush=True)
+    T, n = sum(lens), lens[0]
+    q, k, v = (to_dev(wl.normal_bf16(884, tid, (T, h, D))) for tid, h in ((0, hq), (1, hkv), (2, hkv)))
+    outs = []
+    for x in (lens, [n]):
+        t = sum(x)
+        o, lse = torch.empty((t, hq, D), dtype=torch.bfloat16, device="cuda"), torch.empty((hq, t), dtype=torch.float32, device="cuda")
+        fx.flexsp_attn_varlen_fwd_static(ctx, q[:t], k[:t], v[:t], torch.from_numpy(wl.cu_seqlens(x)).cuda(), o, lse, causal=causal)
+        outs.append((o[:n], lse[:, :n].contiguous()))
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0][0].view(torch.int16), outs[1][0].view(torch.int16)) and torch.equal(outs[0][1].view(torch.int32), outs[1][1].view(torch.int32))
 
 
 @pytest.mark.parametrize("cu", [[1, 8000], [0, 9000, 8000], [0, 8000, 8000 + 4097], [0, -1, 8000], [0, 0, 0]])
