@@ -15,9 +15,10 @@ namespace {
 // ---------------------------------------------------------------------------- the scratch
 constexpr int kStaticMaxItems = 65536;   // work items (128 query rows of one head each) per call
 constexpr int kStaticMaxLevels = 4096;   // query tiles per sequence: sequences up to 524 288 tokens
-constexpr int kCountersOff = 0;          // kMaxQueues ticket counters + "workgroups done", kCounterStride int32 apart
-constexpr int kFlagsOff = kStaticFlagsAt * 4;  // int32[kStaticRecords]: arrival counters, clear between calls
-constexpr int kOffsetsOff = kFlagsOff + kStaticRecords * 4;  // int32[16]: kMaxQueues + 1 queue boundaries
+constexpr int kCountersOff = 0;          // kMaxQueues ticket counters + "workgroups done", kCounterStride int32 apart: clear between calls (last_to_leave)
+constexpr int kFlagsOff = kStaticFlagsAt * 4;  // int32[kStaticRecords]: arrival counters, likewise
+constexpr int kListCountersOff = kFlagsOff + kStaticRecords * 4;  // the same for calls whose queues are listed, which a kernel in front of each clears: calls that overlapped must leave nothing in the others'
+constexpr int kOffsetsOff = kListCountersOff + kStaticFlagsAt * 4;  // int32[16]: kMaxQueues + 1 queue boundaries
 constexpr int kStatusOff = kOffsetsOff + 64;  // int32[2], to look at when debugging: items listed by the last call that built queues, 1 if it rejected its lengths
 constexpr int kItemsOff = kStatusOff + 64;
 constexpr size_t kRecordsOff = kItemsOff + (size_t)kStaticMaxItems * sizeof(flexsp_item);  // partial results of cut tiles
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(kBuildThreads) void build_static_queue_kernel(const
     __shared__ int start[kStaticMaxLevels + 1];  // first list position of a level
     __shared__ int fill[kStaticMaxLevels + 1];   // (sequence, tile) pairs placed in a level so far
     __shared__ int s_maxnt, s_bad, s_total;
-    int32_t *counters = (int32_t *)(scr + kCountersOff);
+    int32_t *counters = (int32_t *)(scr + kListCountersOff);
     int32_t *offsets = (int32_t *)(scr + kOffsetsOff);
     int32_t *status = (int32_t *)(scr + kStatusOff);
     flexsp_item *items = (flexsp_item *)(scr + kItemsOff);
@@ -268,7 +269,7 @@ extern "C" int flexsp_attn_varlen_fwd_static(flexsp_ctx *ctx, flexsp_tensor q, f
             a.pq.items = (const flexsp_item *)(scr + kItemsOff);
             a.pq.offsets = (const int32_t *)(scr + kOffsetsOff);
         }
-        a.pq.counters = (int32_t *)(scr + kCountersOff);
+        a.pq.counters = (int32_t *)(scr + (search ? kCountersOff : kListCountersOff));
         a.pq.nq = kMaxQueues;
         a.pq.split_flags = (int32_t *)(scr + kFlagsOff);
         a.pq.split_scratch = (char *)scr + kRecordsOff;
