@@ -341,10 +341,10 @@ int flexsp_lse_merge_acc(flexsp_ctx *ctx, flexsp_tensor o_acc, float *lse_acc, f
  * cuts no tile into parts (cut tiles are summed in another order), however many rows beyond cu[B] the tensors hold.  It takes
  * no plan and calls no hipMalloc, hipFree or any other allocating routine: the attention kernel's workgroups find their work
  * in `cu_seqlens_dev` (device pointer, B+1 int32 prefix sums, cu[0] = 0, non-decreasing, cu[B] <= T).  A batch
- * of more possible items, (ceil(T / 128) + B) * head_count, than two per compute unit has work queues, whose counters and partial
+ * of more possible items, (ceil(T / 128) + B) * head_count, than two per compute unit has work queues, whose counters, items and partial
  * results of tiles that outlast the rest lie in a fixed array of about 70 MiB that each GPU the library runs on holds from
- * library load until the process ends (its address on the context's device is resolved by flexsp_ctx_create).  With more than
- * 256 sequences the queues are listed there by a small kernel in front, and no tile is cut.
+ * library load until the process ends (its address on the context's device is resolved by flexsp_ctx_create).  With many more
+ * items, or more than 256 sequences, a small kernel in front lists the queues there; with more than 256 no tile is cut.
  *   B, T            sequences in the batch; tokens the q / k / v / o tensors hold (rows of lse)
  *   D               head dim, 64 or 128; the remaining arguments are those of flexsp_attn_varlen_fwd
  * Limits: T <= 524 288 and (ceil(T / 128) + B) * head_count <= 65 536, else FLEXSP_UNSUPPORTED.

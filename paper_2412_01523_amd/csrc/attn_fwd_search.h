@@ -30,10 +30,10 @@ __device__ __forceinline__ int lanes_max(int x)
 // The list that a small kernel in front of this one would write (build_static_queue_kernel), without writing it: items in decreasing order of the key tiles
 // their query tile walks, which a level stands for (the tile's number if causal, else the sequence's number of tiles less one),
 // levels from the highest down.  A place in it is found by halving over the levels, with the lengths in the lanes, 64 sequences at a
-// time: as many trips to memory as reading the item from a list, and a few hundred instructions.  What it saves is the other kernel, 6 to 8 us; what it
-// costs are those instructions, item by item, so it is a level search of one pass where lanes and sequences are few, and prefixes
-// come from counts of set bits.  Whole call, list -> search: 2 759 tokens, 16 heads on 2 27.0 -> 22.9 us; 16 384 tokens in 15
-// sequences, 16 heads on 2 152.5 -> 150.3; 31 875, 8 heads 523 -> 518.
+// time: as many trips to memory as reading the item from a list, and a few hundred instructions.  What it saves is a kernel in front; what it
+// costs are those instructions, item by item (where they cost more, a kernel makes the list after all, list_items_kernel), so it is a level
+// search of one pass where lanes and sequences are few, and prefixes come from counts of set bits.  Whole call, against the list of a
+// single workgroup: 2 759 tokens, 16 heads on 2 27.0 -> 22.9 us; 16 384 tokens in 15 sequences, 16 heads on 2 152.5 -> 150.3.
 // And tiles that outlast the rest are cut into parts as a plan cuts them (split_long_items; the same parts, as long as the records of
 // partial results suffice), which a list of whole tiles did not: 63 259 tokens, 1 head 167 -> 112 us; 51 606, 2 heads on 1 146.3 -> 143.3.
 // Only where the longest tile outlasts the rest by more than the hand-over costs.  A workgroup whose neighbour on the compute unit has run out
@@ -153,7 +153,7 @@ struct SearchBatch {
     }
     __device__ __forceinline__ flexsp_item find(KernArgs &a, int place, int lane) const
     {
-        const int causal = a.causal, heads = a.Hq, group = heads / kMaxQueues;
+        const int heads = a.Hq, group = heads / kMaxQueues;
         int pos, h;
         if (heads % kMaxQueues) {
             pos = place / heads;
@@ -163,6 +163,24 @@ struct SearchBatch {
             pos = l / group;
             h = place % kMaxQueues * group + l - pos * group;
         }
+        return head_of(tile(a, pos, lane), h);
+    }
+    // ... and the other way round: the queue of position pos of head h, and the place there
+    __device__ __forceinline__ static int2 queue_place(int heads, int pos, int h)
+    {
+        const int group = heads / kMaxQueues, place = pos * heads + h;
+        return heads % kMaxQueues ? int2{place % kMaxQueues, place / kMaxQueues} : int2{h / group, pos * group + h % group};
+    }
+    __device__ __forceinline__ static flexsp_item head_of(flexsp_item it, int h)
+    {
+        it.head = h;
+        if (it.slot >= 0) it.slot += h * (it.parts & 0xffff);
+        return it;
+    }
+    // What stands at a position, the same for every head: a tile of the first, or a part of one
+    __device__ __forceinline__ flexsp_item tile(KernArgs &a, int pos, int lane) const
+    {
+        const int causal = a.causal, heads = a.Hq;
         Lens l[CHUNKS];
         int all[CHUNKS];
 #pragma unroll
@@ -226,11 +244,10 @@ struct SearchBatch {
                     it.tile = part / np;
                     part -= it.tile * np;
                 }
-                it.head = h;
                 const int steps = ((causal ? min(it.seq_len, (it.tile + 1) * kFwdBq) : it.seq_len) + kFwdBk - 1) / kFwdBk;
                 it.step_begin = np > 1 ? part * steps / np : 0;
                 it.step_end = np > 1 ? (part + 1) * steps / np : steps;
-                it.slot = np > 1 ? (pos - part) * heads + h * np : -1;
+                it.slot = np > 1 ? (pos - part) * heads : -1;
                 it.parts = part << 16 | np;
                 rem = -1;
             }

@@ -40,6 +40,8 @@ constexpr int64_t kPartAffinityBytes = (int64_t)7 << 19;  // 3.5 MiB of an XCD's
 constexpr int kSplitSteps = 4;  // a forward in halves (attn_fwd_kernel) splits walks of at least this many steps
 constexpr int kMaxSplitRecords = 2048;
 constexpr int kSearchSeqs = 256;      // a forward without a plan finds its items in the lengths of up to so many sequences (attn_fwd_search.hip)
+constexpr int kSearchItems = 7;       // ... each workgroup by itself, up to so many items per compute unit; of more a kernel in front makes a list
+constexpr int kSearchFewItems = 9;    // ... with at most 64 sequences, a lane each
 constexpr int kStaticRecords = 1024;  // ... and has so many partial-result records
 constexpr int kStaticFlagsAt = (kMaxQueues + 1) * kCounterStride;  // ... whose arrival counters stand so many int32 behind its ticket counters
 
@@ -119,6 +121,7 @@ hipError_t launch_pack_many(int n, const void *const *src, void *const *dst, int
                             int P, int eb, bool unpack, hipStream_t s);
 hipError_t launch_attn_fwd(const AttnArgs &a, int D, int grid, hipStream_t s);
 hipError_t launch_attn_fwd_search(const AttnArgs &a, int D, int grid, hipStream_t s);  // a.cu, a.pq.counters, split_flags and split_scratch: no list
+hipError_t launch_list_items(const AttnArgs &a, int positions, hipStream_t s);  // ... which this writes: a.pq.items, offsets, and clear counters and split_flags; positions: wavefronts
 hipError_t launch_attn_fwd_kvshard(const AttnArgs &a, int D, int grid, hipStream_t s);  // a.pq.items: flexsp_shard_item
 hipError_t launch_lse_merge(const uint16_t *oa, const float *la, const uint16_t *ob, const float *lb, uint16_t *oo,
                             float *lo, int64_t T, int H, int D, int32_t oa_st, int32_t oa_sh, int32_t ob_st,

@@ -1,8 +1,8 @@
 // flexsp_attn_varlen_fwd_static: the forward of packed attention for callers that cannot
 // allocate (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).
 // It needs no plan: the forward kernel finds its items in the device copy of cu_seqlens (attn_fwd_search.h), and deals them by
-// counters in a file-scope array that every GPU the library runs on holds until the process ends.  For batches of very many sequences
-// work queues are built ON THE DEVICE, into the same array, by a kernel in front.  The attention pass itself is that of
+// counters in a file-scope array that every GPU the library runs on holds until the process ends.  For batches of many items or very many
+// sequences work queues are listed ON THE DEVICE, in the same array, by a kernel in front.  The attention pass itself is that of
 // flexsp_attn_varlen_fwd.  A batch small enough to be on the chip all at once shares nothing with other calls (see the entry point).
 #include <mutex>
 
@@ -13,15 +13,16 @@ using namespace flexsp;
 namespace {
 
 // ---------------------------------------------------------------------------- the scratch
-constexpr int kStaticMaxItems = 65536;   // work items (128 query rows of one head each) per call
+constexpr int kStaticMaxItems = 65536;   // tiles (128 query rows of one head each) per call: room for them in a list, and a limit of the call whether it has one or not
 constexpr int kStaticMaxLevels = 4096;   // query tiles per sequence: sequences up to 524 288 tokens
 constexpr int kCountersOff = 0;          // kMaxQueues ticket counters + "workgroups done", kCounterStride int32 apart: clear between calls (last_to_leave)
 constexpr int kFlagsOff = kStaticFlagsAt * 4;  // int32[kStaticRecords]: arrival counters, likewise
 constexpr int kListCountersOff = kFlagsOff + kStaticRecords * 4;  // the same for calls whose queues are listed, which a kernel in front of each clears: calls that overlapped must leave nothing in the others'
-constexpr int kOffsetsOff = kListCountersOff + kStaticFlagsAt * 4;  // int32[16]: kMaxQueues + 1 queue boundaries
-constexpr int kStatusOff = kOffsetsOff + 64;  // int32[2], to look at when debugging: items listed by the last call that built queues, 1 if it rejected its lengths
+constexpr int kListFlagsOff = kListCountersOff + kStaticFlagsAt * 4;
+constexpr int kOffsetsOff = kListFlagsOff + kStaticRecords * 4;  // int32[16]: kMaxQueues + 1 queue boundaries
+constexpr int kStatusOff = kOffsetsOff + 64;  // int32[2], to look at when debugging: items listed by the last call of more than kSearchSeqs sequences, 1 if it rejected its lengths
 constexpr int kItemsOff = kStatusOff + 64;
-constexpr size_t kRecordsOff = kItemsOff + (size_t)kStaticMaxItems * sizeof(flexsp_item);  // partial results of cut tiles
+constexpr size_t kRecordsOff = kItemsOff + (size_t)(kStaticMaxItems + kStaticRecords) * sizeof(flexsp_item);  // partial results of cut tiles (whose parts are more items)
 constexpr size_t kScratchBytes = kRecordsOff + (size_t)kStaticRecords * kPartialBytes;
 
 // One copy per GPU, at its own address.  In host code this name is only a handle for
@@ -212,7 +213,7 @@ extern "C" int flexsp_attn_varlen_fwd_static(flexsp_ctx *ctx, flexsp_tensor q, f
     if (!view_ok(q) || !view_ok(k) || !view_ok(v) || !view_ok(o) || !std::isfinite(scale))
         return FLEXSP_INVALID_ARGUMENT;
     if (D != 64 && D != 128) return FLEXSP_UNSUPPORTED;
-    // the scratch array bounds the batch: every sequence adds at most one partial tile
+    // (every sequence adds at most one partial tile)
     if (T > (int64_t)kStaticMaxLevels * kFwdBq ||
         ((T + kFwdBq - 1) / kFwdBq + B) * (int64_t)head_count > kStaticMaxItems)
         return FLEXSP_UNSUPPORTED;
@@ -226,7 +227,7 @@ extern "C" int flexsp_attn_varlen_fwd_static(flexsp_ctx *ctx, flexsp_tensor q, f
     // 21.9 us; 257 tokens, 2 heads: 18.3 -> 10.4 us).  Larger ones need longest-first queues.
     const int64_t most_items = ((T + kFwdBq - 1) / kFwdBq + B) * (int64_t)head_count;
     const int num_cu = flexsp_ctx_num_cu(ctx);
-    const bool listed = most_items > 2 * num_cu;
+    const bool dealt = most_items > 2 * num_cu;
     // Whether it does run in halves the lengths tell, on the device: the rows that the tensors hold beyond the batch change nothing.
     // (1 000 tokens, 8 heads in 4 096 rows 19.4 -> 18.1 us, 3 000 tokens, 1 head in 65 536 rows 50.9 -> 40.9.  Batches in whole items that
     // might have been others take what they took, up to 0.6 us more with D = 64.  A second launch for the halves instead, which
@@ -234,9 +235,15 @@ extern "C" int flexsp_attn_varlen_fwd_static(flexsp_ctx *ctx, flexsp_tensor q, f
     const bool may_halve = fwd_may_halve(T, B, head_count, num_cu);
     // (Cut tiles need records, and tickets counters, that calls share: batches of fewer items, which may run side by side, have neither.  A
     // batch that may run in halves is one of at most 32 sequences.)
-    const bool search = listed && B <= kSearchSeqs;
+    const bool found = dealt && B <= kSearchSeqs;
+    // What the search costs it costs for every item, 0.5 to 2 us of a workgroup; a list of the same items costs a launch in front, about 4 us, so it is
+    // the faster way from three and a half possible items to a workgroup on, four and a half where a lane has one sequence.  Whole call, search -> list: 256
+    // sequences of 256 tokens, 16 heads on 2, D = 64 191 -> 145 us; 128 of 512, 8 heads, D = 64 103 -> 93; 24 of 1 000, 16 heads on 2 (6.6 items) 144 -> 136;
+    // not taken: 12 of 1 000, 16 heads on 2, D = 64, unmasked (3.6) 85 -> 91; 64 of 256, 4 heads (1.5) 24.0 -> 26.8.  Of 1 914 batches, drawn and over
+    // lengths, heads and sequences, 53 take over 2 % more by this line than by the better way.  (The choice changes no bits.)
+    const bool search = found && (may_halve || most_items <= (B <= 64 ? kSearchFewItems : kSearchItems) * num_cu);
     hipError_t e = hipSuccess;
-    if (listed && !search) {
+    if (dealt && !found) {
         hipLaunchKernelGGL(build_static_queue_kernel, dim3(1), dim3(kBuildThreads), 0, s, cu_seqlens_dev, (int)B, (int)T,
                            (int)head_count, causal ? 1 : 0, kFwdBq, scr);
         e = hipGetLastError();
@@ -258,23 +265,28 @@ extern "C" int flexsp_attn_varlen_fwd_static(flexsp_ctx *ctx, flexsp_tensor q, f
     a.T = (int32_t)T; a.Hq = head_count; a.G = head_count / kv_head_count; a.causal = causal ? 1 : 0;
     a.scale = scale; a.scale_l2 = scale * 1.4426950408889634f;
     a.num_cu = num_cu;
-    if (!listed || search) {
+    if (!dealt || found) {
         a.cu = cu_seqlens_dev;
         a.B = B;
     }
-    // the item count is known to the device only.  With a list: a full persistent grid; workgroups without work leave
+    // the item count is known to the device only.  Dealt items: a full persistent grid; workgroups without work leave
     int64_t grid = 2 * (int64_t)num_cu;
-    if (listed) {
+    if (dealt) {
         if (!search) {
             a.pq.items = (const flexsp_item *)(scr + kItemsOff);
             a.pq.offsets = (const int32_t *)(scr + kOffsetsOff);
         }
         a.pq.counters = (int32_t *)(scr + (search ? kCountersOff : kListCountersOff));
         a.pq.nq = kMaxQueues;
-        a.pq.split_flags = (int32_t *)(scr + kFlagsOff);
+        a.pq.split_flags = (int32_t *)(scr + (search ? kFlagsOff : kListFlagsOff));
         a.pq.split_scratch = (char *)scr + kRecordsOff;
     } else {
         grid = may_halve ? std::max(most_items, fwd_halves_most(D, T, B, head_count, num_cu)) : most_items;
+    }
+    if (found && !search) {
+        e = launch_list_items(a, (int)(most_items / head_count), s);
+        if (e != hipSuccess) return hip_status(e);
+        a.cu = nullptr;  // (the attention kernel has a list)
     }
     // (halves with two buffers where whole items too have the LDS for it: D = 128 one workgroup to a compute unit, D = 64 two)
     if (may_halve) a.halves = !search && (D == 64 || most_items <= num_cu) ? 2 : 1;

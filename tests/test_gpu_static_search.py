@@ -1,4 +1,4 @@
-"""The forward without a plan where its workgroups find more items than there are workgroups in the lengths: against the plan's forward, bit
+"""The forward without a plan where more items than there are workgroups are found in the lengths, by the workgroups or by a kernel in front that lists them: against the plan's forward, bit
 for bit, also where both cut long tiles into the same parts (where only the plan does, or there are not records enough for its parts, to
 within the rounding of fp32 sums and of the bf16 store); up to and beyond as many sequences as are searched; wrong lengths; call after call."""
 import numpy as np
@@ -24,6 +24,7 @@ CASES = {
     "one-sequence-cut": ([33000], 0, 2, 1, 128, True, True),
     "one-sequence-cut-d64": ([33001], 7, 2, 2, 64, True, True),
     "more-parts-than-records": ([36001], 0, 2, 2, 64, True, "other parts"),
+    "fewer-parts-for-the-records": ([34501], 0, 2, 2, 64, True, "other parts"),
     "cut-beside-short-ones": ([9001, 1, 0, 128, 129, 127, 64, 65] * 2 + [300] * 150, 0, 3, 3, 128, True, True),
     "not-causal-cut": ([70, 4000, 0, 3969] + [500] * 150, 100, 1, 1, 128, False, True),
     "last-tile-of-one-step": ([128 * 9 + 1, 128 * 9, 128 * 9 + 64, 128 * 9 + 65] * 8, 0, 8, 2, 128, True, False),
@@ -31,6 +32,12 @@ CASES = {
     "heads-12-not-causal": ([700, 0, 513, 512, 1] * 5, 0, 12, 4, 128, False, False),
     "heads-8-cut": ([4300] + [30] * 31, 0, 8, 4, 128, True, True),
     "heads-8-cut-d64": ([4100, 1] + [30] * 31, 3, 8, 2, 64, True, True),
+    "heads-8-cut-listed": ([30] * 100 + [4300] + [30] * 100, 0, 8, 4, 128, True, True),
+    "heads-8-cut-in-many-rows": ([4300] + [30] * 31, 31000, 8, 4, 128, True, True),
+    "1792-items": ([130] * 100, 2872, 8, 2, 64, True, False),
+    "1800-items": ([130] * 100, 2873, 8, 2, 64, True, False),
+    "listed-not-causal": ([1, 700, 0, 129, 513] * 20, 3, 12, 3, 64, False, False),
+    "listed-9-heads": ([260] * 80, 0, 9, 9, 128, True, False),
     "64-sequences": ([130, 128] * 32, 0, 8, 8, 128, True, False),
     "65-sequences": ([257] * 64 + [1], 0, 8, 8, 64, False, False),
     "256-sequences": ([i % 300 for i in range(256)], 5, 4, 2, 128, True, False),
@@ -110,12 +117,13 @@ def test_wrong_or_no_lengths_touch_nothing(ctx, cu):
         assert not good or bool(torch.isfinite(lse).all())
 
 
-def test_replayed_dealt_and_cut(ctx):
+@pytest.mark.parametrize("rows", [8192, 36000])  # (items found by the workgroups; listed in front)
+def test_replayed_dealt_and_cut(ctx, rows):
     """One captured call whose batches are dealt whole, dealt with tiles cut, and small enough for neither, in turn: each replay starts from the
     counters that the one before left, and has the plan's bits."""
     import torch
     from paper_2412_01523_amd import binding as fx
-    rows, hq, hkv, D, B = 8192, 8, 4, 128, 32
+    hq, hkv, D, B = 8, 4, 128, 32
     q, k, v = (to_dev(wl.normal_bf16(883, tid, (rows, h, D))) for tid, h in ((0, hq), (1, hkv), (2, hkv)))
     cud = torch.from_numpy(wl.cu_seqlens([128] * B)).cuda()
     o, lse = torch.empty((rows, hq, D), dtype=torch.bfloat16, device="cuda"), torch.empty((hq, rows), dtype=torch.float32, device="cuda")
