@@ -169,11 +169,21 @@ __global__ __launch_bounds__(kBuildThreads) void build_static_queue_kernel(const
             it.step_end = ((causal ? min(len, (t + 1) * tile_rows) : len) + kFwdBk - 1) / kFwdBk;
             it.slot = -1;
             it.parts = 1;
-            for (int h = 0; h < heads; h++) {
-                const int p = p0 + h, x = heads % nq ? p % nq : h / (heads / nq);
-                it.head = h;
-                const int at = heads % nq ? p / nq : p0 / nq + h % (heads / nq);
-                items[x * (total / nq) + min(x, total % nq) + at] = it;
+            // (no division per head: this workgroup's time is the call's)
+            if (heads % nq == 0) {  // (so is the total)
+                const int group = heads / nq;
+                for (int x = 0; x < nq; x++)
+                    for (int i = 0; i < group; i++) {
+                        it.head = x * group + i;
+                        items[x * (total / nq) + p0 / nq + i] = it;
+                    }
+            } else {
+                int x = p0 % nq, at = p0 / nq;
+                for (int h = 0; h < heads; h++) {
+                    it.head = h;
+                    items[x * (total / nq) + min(x, total % nq) + at] = it;
+                    if (++x == nq) x = 0, at++;
+                }
             }
         }
     }

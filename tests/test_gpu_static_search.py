@@ -41,6 +41,8 @@ CASES = {
     "64-sequences": ([130, 128] * 32, 0, 8, 8, 128, True, False),
     "65-sequences": ([257] * 64 + [1], 0, 8, 8, 64, False, False),
     "256-sequences": ([i % 300 for i in range(256)], 5, 4, 2, 128, True, False),
+    "300-sequences-16-heads": ([i % 300 for i in range(300)], 7, 16, 4, 64, True, False),
+    "300-sequences-8-heads": ([i % 200 for i in range(300)], 0, 8, 8, 128, False, False),
     "257-sequences": ([i % 300 for i in range(257)], 5, 4, 2, 128, True, False),
 }
 
