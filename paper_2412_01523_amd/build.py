@@ -40,11 +40,10 @@ SOURCE_ORDER = ["-mllvm", "-pre-RA-sched=source", "-mllvm", "-enable-misched=fal
 # A kernel whose LDS leaves room for one workgroup per compute unit may use all 512 registers, and the compiler then keeps the results of
 # matrix instructions in the half that the vector unit cannot read: every score is copied before its exponential.  The
 # forward's such kernels need 219 and 253 registers without that half (one had 187 and 96 of it); forwards in halves
-# take 5 % less time, whole items in the same kernel 10 % less.  The single launch of a small backward needs 251 (it had 203 and
-# 112, with 904 copies): forward and backward of 200 tokens, 4 heads 20.1 -> 19.5 us, 440, 16 heads on 4 28.5 -> 27.7, 2 000, 2 heads on 1
-# 31.6 -> 30.7, same bits; the kernels that share a compute unit are compiled the same either way.
+# take 5 % less time, whole items in the same kernel 10 % less.  (Kernels that share a compute unit, among them all of the
+# backward, are compiled the same either way.)
 VECTOR_RESULTS = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-PER_SOURCE = {"attn_fwd.hip": SOURCE_ORDER + VECTOR_RESULTS, "attn_fwd_search.hip": SOURCE_ORDER + VECTOR_RESULTS, "attn_bwd.hip": SOURCE_ORDER + VECTOR_RESULTS}
+PER_SOURCE = {"attn_fwd.hip": SOURCE_ORDER + VECTOR_RESULTS, "attn_fwd_search.hip": SOURCE_ORDER + VECTOR_RESULTS, "attn_bwd.hip": SOURCE_ORDER}
 
 
 def _hipcc() -> str:

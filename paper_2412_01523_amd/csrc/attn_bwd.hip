@@ -996,11 +996,10 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
 // delta is formed from the piece of dO that the lane has just copied into the tile and the same piece of O, which waits for the step in
 // a register: both rows in registers were 35 spilled ones with D = 128, and dO was fetched twice (1 201 tokens, 16 heads on 4 38.9 -> 37.8
 // us; 5 630 tokens, 2 heads 51.0 -> 50.0).
-// PER_CU: a launch of at most one workgroup per compute unit takes the kernel that has the whole register file, a larger one the kernel
-// that two workgroups can share a compute unit with (5 630 tokens, 2 heads: 38.8 against 43.4 us; since results of matrix
-// instructions stay in vector registers, see build.py, the former needs 251 and the two differ by less than 1 % where either would do).
-template <int D, bool SHARD, int PER_CU>
-__global__ __launch_bounds__(kThreads, PER_CU) void attn_bwd_both_kernel(const AttnArgs)
+// (A variant with the whole register file for launches of at most one workgroup per compute unit was worth 0.2 % over 156 drawn passes of up to
+// 3e10 operations with D = 128, 1.6 % at the most, and nothing over 76 rings.)
+template <int D, bool SHARD>
+__global__ __launch_bounds__(kThreads, 2) void attn_bwd_both_kernel(const AttnArgs)
 {
     KernArgs &a = kernel_args();
     constexpr int LDS = dkv_lds<D>() > dq_lds<D>() ? dkv_lds<D>() : dq_lds<D>();
@@ -1015,12 +1014,7 @@ __global__ __launch_bounds__(kThreads, PER_CU) void attn_bwd_both_kernel(const A
 template <bool SHARD>
 void start_both(const AttnArgs &a, int D, int grid, hipStream_t s)
 {
-    if (D == 64)
-        launch(attn_bwd_both_kernel<64, SHARD, 2>, a, grid, s);
-    else if (a.per_cu == 1)
-        launch(attn_bwd_both_kernel<128, SHARD, 1>, a, grid, s);
-    else
-        launch(attn_bwd_both_kernel<128, SHARD, 2>, a, grid, s);
+    launch(D == 64 ? attn_bwd_both_kernel<64, SHARD> : attn_bwd_both_kernel<128, SHARD>, a, grid, s);
 }
 
 }  // namespace

@@ -786,7 +786,6 @@ int both_at_once(const flexsp_ctx *ctx, const flexsp_plan *p, AttnArgs &a)
     a.dq_wg = (int)cdiv(dkv, ctx->num_xcd) * ctx->num_xcd;
     const int grid = a.dq_wg + dq;
     a.delta_out = a.lse_out = nullptr;  // (the dK/dV pass forms its own)
-    a.per_cu = grid <= ctx->num_cu ? 1 : 2;
     return grid;
 }
 

@@ -100,9 +100,9 @@ struct AttnArgs {
     float scale_l2;  // scale * log2(e)
     PassQueues pq;
     // a launch that runs both backward passes (launch_attn_bwd_dkv*, both passes direct, lse_in as the caller gave it): the
-    // dQ pass's queues, its first workgroup (0: the dK/dV pass alone), the dK/dV pass's items, workgroups per compute unit
+    // dQ pass's queues, its first workgroup (0: the dK/dV pass alone), the dK/dV pass's items
     PassQueues dq_pq;
-    int32_t dq_wg, dkv_items, per_cu;
+    int32_t dq_wg, dkv_items;
     int32_t wide;  // the dK/dV pass's items have kDkvWideBk keys
     int32_t grid;  // workgroups of the launch (filled in by the launchers)
     // a forward without a plan: the lengths (device), in which every workgroup finds its item unless pq holds a list
