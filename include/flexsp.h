@@ -148,7 +148,8 @@ int flexsp_plan_get_items(const flexsp_plan *plan, int pass, flexsp_item *items,
                           int64_t capacity, int64_t *queue_offsets);
 /* Rows per tile used by a pass (query rows for FWD and BWD_DQ, key rows for BWD_DKV). */
 int flexsp_plan_tile_rows(const flexsp_plan *plan, int pass);
-/* Bytes of device scratch the plan holds for the backward pass. */
+/* Bytes of device scratch the plan holds for the rows of the backward pass (delta and log-sum-exp).  Its work lists and the partial
+ * results of tiles that it cuts, up to 2 048 of 66 KiB for each of the three passes, are not counted; a key shard's plan has the same. */
 size_t flexsp_attn_bwd_workspace_bytes(const flexsp_plan *plan);
 
 /*
@@ -347,14 +348,15 @@ int flexsp_lse_merge_acc(flexsp_ctx *ctx, flexsp_tensor o_acc, float *lse_acc, f
  * items, or more than 256 sequences, a small kernel in front lists the queues there; with more than 256 no tile is cut.
  *   B, T            sequences in the batch; tokens the q / k / v / o tensors hold (rows of lse)
  *   D               head dim, 64 or 128; the remaining arguments are those of flexsp_attn_varlen_fwd
- * Limits: T <= 524 288 and (ceil(T / 128) + B) * head_count <= 65 536, else FLEXSP_UNSUPPORTED.
+ * Limits: T <= 524 288 and (ceil(T / 128) + B) * head_count <= 65 536 (the items a list has room for, whether the batch is
+ * listed or not), else FLEXSP_UNSUPPORTED.
  * The lengths are read on the device only, so they cannot be checked by the host: if the device
  * array is not a valid prefix-sum list inside [0, T], NOTHING is computed (o and lse keep their
  * contents).  Calls with queues share the GPU's array: those that may overlap in time on one
  * GPU (different streams, or graph replays running concurrently) race; order them.  What calls that did
- * overlap wrote is undefined; ordered calls after them are right again.  Sequences are
- * served longest tile first like a plan's queues, but without the plan's grouping of a head's tiles
- * onto one XCD, so it is somewhat slower than the plan-based call; nothing synchronises the host.
+ * overlap wrote is undefined; ordered calls after them are right again.  Tiles are
+ * served longest first like a plan's; a head's tiles share an XCD only where head_count is a multiple of 8, and fewer are cut, so it is
+ * somewhat slower than the plan-based call; nothing synchronises the host.
  * Errors: INVALID_ARGUMENT, UNSUPPORTED, NO_DEVICE, HIP_ERROR.
  */
 int flexsp_attn_varlen_fwd_static(flexsp_ctx *ctx, flexsp_tensor q, flexsp_tensor k, flexsp_tensor v,

@@ -127,7 +127,8 @@ struct SearchBatch {
         if (((__builtin_amdgcn_readfirstlane(last) + kFwdBq - 1) / kFwdBq + a.B) * (int64_t)heads > 2 * a.num_cu && outlasts) {
             target = max(min(share * 3 / 4, max((int)((int64_t)share * 35 / 100), (int)kLongPartSteps)), kMinPartSteps);
         }
-        // (every cut tile stands at a level from first_level(2) on: a record for each place down to there)
+        // (every cut tile stands at a level from first_level(2) on: a record for each place down to there.  Too few: longer parts for all tiles,
+        // which keeps what a place holds a matter of its tile alone)
         for (;; target *= 2) {
             const int cut_level = first_level(2), cut_below = below(cut_level);
             int all = 0, cut = 0;

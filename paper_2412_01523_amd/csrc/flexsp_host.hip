@@ -219,7 +219,7 @@ void distribute(std::vector<Work> &work, const std::vector<int64_t> &group_cost,
 // Groups of one cost go round the queues in the order they are listed in: the n-th head listed of a sequence.  Where every queue gets several
 // of its heads it gets neighbours, which share their key head's rows in the XCD's L2 if heads are grouped: 262 144 tokens in
 // sequences of up to 65 536, 16 heads on 2, forward and backward 151.7 -> 150.3 ms.  (Same bits; nothing changes for the caches with as many
-// key heads as heads, nor with no more heads than queues.)
+// key heads as heads, nor with no more heads than queues.  The key heads of a shard's dK/dV pass, which share no rows, are listed as they come.)
 int nth_head(int n, int heads, int nq) { return heads % nq ? n : n % nq * (heads / nq) + n / nq; }
 
 // Builds one pass: lists the items, spreads whole (sequence, head) groups over the queues
@@ -1098,7 +1098,7 @@ int flexsp_plan_create_kvshard(flexsp_ctx *ctx, const int32_t *cu_q, const int32
             // are fewer tiles than workgroups, and a tile is a chain of all its group's heads.  One device's ring pass, whole tiles ->
             // cut: 14 514 tokens over four devices, 16 heads on 2 1 222 -> 622 us; 2 517, 8 heads on 1 199 -> 132; 4 912 over two, 2
             // heads, D = 64 158 -> 102; 35 804 over eight, 16 heads on 4 4 949 -> 4 563; 5 306 over four, 2 heads 180 -> 162.)
-            distribute(work, group_cost, ctx->num_xcd, workgroups_of(ctx), kDkvBk, p->pass[FLEXSP_PASS_BWD_DKV], 2, 0, G);
+            distribute(work, group_cost, ctx->num_xcd, workgroups_of(ctx), kDkvBk, p->pass[FLEXSP_PASS_BWD_DKV], 2);
         }
         for (int i = 0; i < 3; i++)
             direct_list(p->pass[i], ctx->num_xcd, workgroups_of(ctx), 2, i == FLEXSP_PASS_FWD ? 0 : kShortPartSteps);

@@ -39,10 +39,13 @@ constexpr int kMaxParts = 8;
 constexpr int64_t kPartAffinityBytes = (int64_t)7 << 19;  // 3.5 MiB of an XCD's 4 MiB of L2 (see split_long_items)
 constexpr int kSplitSteps = 4;  // a forward in halves (attn_fwd_kernel) splits walks of at least this many steps
 constexpr int kMaxSplitRecords = 2048;
-constexpr int kSearchSeqs = 256;      // a forward without a plan finds its items in the lengths of up to so many sequences (attn_fwd_search.hip)
+constexpr int kSearchSeqs = 256;      // a forward without a plan finds its items in the lengths of up to so many sequences (attn_fwd_search.hip), four to a lane in registers
 constexpr int kSearchItems = 7;       // ... each workgroup by itself, up to so many items per compute unit; of more a kernel in front makes a list
 constexpr int kSearchFewItems = 9;    // ... with at most 64 sequences, a lane each
-constexpr int kStaticRecords = 1024;  // ... and has so many partial-result records
+// ... and has so many partial-result records.  Parts are 0.35 to 0.75 even shares, so up to some 750 in all suffice unless a few heads' long tiles are
+// cut at 0.35 shares and 160 steps: of 7 440 drawn batches 249 have cut tiles, half of those need 600 records, nine in ten 726, seven over 1 024 (up to 1 650).  Those are
+// cut into fewer parts (SearchBatch); 512 would do for 75.
+constexpr int kStaticRecords = 1024;
 constexpr int kStaticFlagsAt = (kMaxQueues + 1) * kCounterStride;  // ... whose arrival counters stand so many int32 behind its ticket counters
 
 // One workgroup's leave from a launch whose counters calls without a plan share: true for the one that has to clear them.  Such calls have

@@ -1,5 +1,5 @@
-"""The forward without a plan finds its work on the device: in a list for batches that do not fit the chip at once, every
-workgroup for itself for those that do.  Same bits as the plan's forward around that line and at odd lengths, however many rows the tensors hold."""
+"""The forward without a plan finds its work on the device: every workgroup one item for itself where the batch fits the chip at once, dealt
+items (test_gpu_static_search.py) or a list where it does not.  Same bits as the plan's forward around that line and at odd lengths, however many rows the tensors hold."""
 import numpy as np
 import pytest
 
@@ -72,7 +72,7 @@ def test_wrong_lengths_compute_nothing(ctx, T, B):
 
 
 # Tensors with room for more tokens than the batch has, whose lengths alone say how the forward runs: in one launch that takes
-# the batch either way, in two without and with a list, and (the last ones) batches that are not for halves
+# the batch either way, with items found one to a workgroup or dealt, and (the last ones) batches that are not for halves
 @pytest.mark.parametrize("lens,hq,hkv,D,rows", [
     ([1000], 8, 8, 128, 1000), ([1000], 8, 8, 128, 1900), ([1000], 8, 8, 128, 4096), ([1000], 8, 2, 128, 9000), ([1900], 8, 8, 128, 4096),
     ([700, 0, 1301], 2, 1, 128, 8192), ([700, 0, 1301], 2, 2, 128, 40000), ([900, 450], 4, 4, 64, 4096), ([1500], 4, 2, 64, 17000),
