@@ -353,8 +353,9 @@ int flexsp_lse_merge_acc(flexsp_ctx *ctx, flexsp_tensor o_acc, float *lse_acc, f
  * The lengths are read on the device only, so they cannot be checked by the host: if the device
  * array is not a valid prefix-sum list inside [0, T], NOTHING is computed (o and lse keep their
  * contents).  Calls with queues share the GPU's array: those that may overlap in time on one
- * GPU (different streams, or graph replays running concurrently) race; order them.  What calls that did
- * overlap wrote is undefined; ordered calls after them are right again.  Tiles are
+ * GPU (different streams, or graph replays running concurrently) race; order them.  Calls that
+ * overlap all the same have undefined results, and with a listed queue may use one another's lengths on their own tensors (memory
+ * outside them, if those are shorter); ordered calls after them are right again.  Tiles are
  * served longest first like a plan's; a head's tiles share an XCD only where head_count is a multiple of 8, and fewer are cut, so it is
  * somewhat slower than the plan-based call; nothing synchronises the host.
  * Errors: INVALID_ARGUMENT, UNSUPPORTED, NO_DEVICE, HIP_ERROR.
