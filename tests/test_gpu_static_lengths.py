@@ -56,7 +56,7 @@ def test_odd_shapes(ctx, lens, hq, hkv, D):
     both(ctx, lens, hq, hkv, D, True)
 
 
-@pytest.mark.parametrize("T,B", [(1024, 3), (65536, 200), (4096, 2), (65536, 2)])  # (the last two: batches that might run in halves)
+@pytest.mark.parametrize("T,B", [(1024, 3), (65536, 200), (4096, 2), (65536, 2), (200000, 100), (30000, 300)])  # (the third and fourth: batches that might run in halves; the last two: listed)
 def test_wrong_lengths_compute_nothing(ctx, T, B):
     import torch
     from paper_2412_01523_amd import binding as fx
