@@ -19,7 +19,7 @@ INCLUDE = PKG.parent / "include"
 OBJ = CSRC / "_build"
 LIB = PKG / "libflexsp.so"
 
-SOURCES = ["flexsp_host.hip", "pack.hip", "attn_fwd.hip", "attn_fwd_search.hip", "attn_bwd.hip", "planner.hip", "fwd_static.hip",
+SOURCES = ["flexsp_host.hip", "pack.hip", "attn_fwd.hip", "attn_fwd_search.hip", "attn_bwd.hip", "attn_bwd_chain.hip", "planner.hip", "fwd_static.hip",
            "lse_merge.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
@@ -43,7 +43,7 @@ SOURCE_ORDER = ["-mllvm", "-pre-RA-sched=source", "-mllvm", "-enable-misched=fal
 # take 5 % less time, whole items in the same kernel 10 % less.  (Kernels that share a compute unit, among them all of the
 # backward, are compiled the same either way.)
 VECTOR_RESULTS = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-PER_SOURCE = {"attn_fwd.hip": SOURCE_ORDER + VECTOR_RESULTS, "attn_fwd_search.hip": SOURCE_ORDER + VECTOR_RESULTS, "attn_bwd.hip": SOURCE_ORDER}
+PER_SOURCE = {"attn_fwd.hip": SOURCE_ORDER + VECTOR_RESULTS, "attn_fwd_search.hip": SOURCE_ORDER + VECTOR_RESULTS, "attn_bwd.hip": SOURCE_ORDER, "attn_bwd_chain.hip": SOURCE_ORDER}
 
 
 def _hipcc() -> str:

@@ -11,7 +11,8 @@
 //           the group and over the query rows that see those keys; dK^T, dV^T stay in
 //           registers, so grouped-query heads are summed without a reduction pass.
 // With D = 64 and long enough walks a dK/dV item is 128 keys (attn_bwd_dkv_wide_kernel).
-// Small backwards run both as one launch (attn_bwd_both_kernel); the dK/dV pass then forms delta itself.
+// Small backwards run both as one launch (attn_bwd_both_kernel); the dK/dV pass then forms delta itself.  Large ones with D = 128 do not come
+// here (attn_bwd_chain.hip).
 // The 32x32 accumulator keeps one COLUMN per lane, and only its ROW index can be contracted
 // in a following MFMA.  Hence dK/dV computes S = Q K^T (rows = queries) and dQ computes
 // S^T = K Q^T (rows = keys).  Operands whose contraction index runs along the rows of a
@@ -1021,6 +1022,7 @@ void start_both(const AttnArgs &a, int D, int grid, hipStream_t s)
 
 hipError_t launch_attn_bwd_dkv(const AttnArgs &a, int D, int grid, hipStream_t s)
 {
+    if (a.chain) return launch_attn_bwd_chain(a, grid, s);
     if (a.wide)
         launch(attn_bwd_dkv_wide_kernel, a, grid, s);
     else if (a.dq_wg)
@@ -1034,6 +1036,7 @@ hipError_t launch_attn_bwd_dkv(const AttnArgs &a, int D, int grid, hipStream_t s
 
 hipError_t launch_attn_bwd_dq(const AttnArgs &a, int D, int grid, hipStream_t s)
 {
+    if (a.chain) return launch_attn_bwd_delta(a, s);
     if (D == 128)
         launch(attn_bwd_dq_kernel<128, false>, a, grid, s);
     else

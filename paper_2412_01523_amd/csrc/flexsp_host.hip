@@ -29,7 +29,8 @@ struct PlanSlab {
 };
 constexpr size_t kSlabPoolMax = 16;  // free slabs kept by a context
 constexpr size_t kSlabEager = 4;     // slabs a context makes rather than wait for a busy one ...
-constexpr size_t kSlabEagerBytes = (size_t)1 << 30;  // ... while they hold less device memory than this
+constexpr size_t kSlabEagerBytes = (size_t)8 << 30;  // ... while they hold less device memory than this (a backward in one pass keeps 512 bytes a token and head)
+constexpr size_t kSlabPoolBytes = (size_t)16 << 30;  // free slabs hold no more device memory than this, the one released last apart
 
 struct flexsp_ctx {
     int device;  // -1: host-only
@@ -67,6 +68,10 @@ struct flexsp_plan {
     bool wide = false;  // the dK/dV pass's items have kDkvWideBk keys
     bool halves = false;  // the forward is launched in halves: its direct list has kHalfBq query rows to an item
     HostPass pass[3];
+    std::vector<flexsp_item> chain;        // items of the backward in one pass (attn_bwd_chain.hip); empty: it runs in two
+    std::vector<int32_t> chain_bundles;    // ... boundaries of its bundles
+    int64_t chain_tiles = 0;  // tiles of kDkvBq query rows it keeps partial sums of, over all heads
+    PassQueues chain_dq;
     // device side (null for host-only plans): one allocation, carved up
     void *dev_base;
     size_t dev_bytes;
@@ -632,6 +637,93 @@ bool wide_keys(const flexsp_plan *p, int n_wg)
     return 2 * wide_items > n_wg && wide_items <= n_wg && (p->Hq == p->Hkv || full);
 }
 
+// Whether a backward runs in one pass (attn_bwd_chain.hip): D = 128 and
+// - at least two items of 128 keys per compute unit, three steps of 64 query rows an item and head, twelve without a mask: a delta launch in
+//   front and the start of an item, during which its compute unit does nothing else, have to be made up for;
+// - no item longer than an even share of the steps (0.4 of one where several heads share their keys, whose items are long and few): all
+//   compute units wait for the last;
+// - no (sequence, kv head) of more than a quarter of the steps: each of its items starts a step or two behind the one before.
+// Backward, two kernels -> one pass, us.  Taken: 17 433 tokens, 4 heads, up to 1 290 a sequence 114 -> 88; 28 916 in one, 4 heads 2 776 -> 2 480; 82 128,
+// 4 heads, up to 23 445 2 971 -> 2 693; 66 564 in sequences of 757, 8 heads, unmasked (9.9 steps an item, not taken) 738 -> 741; 26 644 in 441, 16 heads on 8 290 ->
+// 279.  Not taken: 130 077 in one, 1 head 14 965 -> 16 098; 84 931, 1 head, up to 21 776 732 -> 854; 9 400 in 460, 16 heads on 8
+// 129 -> 140; 41 048 in 65, 16 heads on 2 321 -> 342; 95 093, 8 heads on 1, unmasked 5 220 -> 6 520; 24 348 in 99, 1 head 19 -> 30.
+bool chain_pays(const flexsp_plan *p, int64_t steps, int64_t longest, int64_t largest, int64_t items, int n_cu)
+{
+    const int64_t G = p->Hq / p->Hkv;
+    return items >= 2 * n_cu && steps >= (p->causal ? 3 : 12) * G * items && longest * n_cu * (G > 1 ? 5 : 2) <= 2 * steps && 4 * largest <= steps;
+}
+
+// Lists a backward in one pass, if it is one.  The list's bundles (see ChainDealer) are what a compute die's workgroups, one per compute
+// unit, work on at a time, and what they share should stay in its L2: the rows of dQ that are added to, Q and dO, 64 KB a step.  So a long
+// sequence's key tiles are bundles of up to kChainTeam, one to a workgroup, which go through the steps one behind the other; heads and
+// sequences of fewer tiles are put together, kChainSpan items or a little more, and lie in a bundle as their walks' lengths say, so that
+// an item does not stand right behind the one that it follows.  Bundles, too, stand dearest first.  Items of a (sequence, kv head) then stand in the
+// order of their keys, which is what they wait for.
+// Backward by kChainSpan, us, 1 / 32 / 64 / 128 / 256 / no bound: sequences of 4 096 tokens, 8 heads 1 744 / 1 744 / 1 700 / 1 695 / 1 797 / 2 006;
+// 1 024 514 / 476 / 462 / 459 / 490 / 521; a 64K-token long-tail batch 1 263 / 1 247 / 1 244 / 1 266 / 1 274 / 1 274.
+// An item's fields here: step_begin the bundle's first key tile of this (sequence, kv head), step_end its steps, slot the first of its
+// sequence's query tiles among all that several key tiles add to, parts whether the next key tile is in another bundle.
+void build_chain(flexsp_plan *p, int n_cu)
+{
+    if (p->D != 128) return;
+    const int G = p->Hq / p->Hkv, skip = p->causal ? kChainBk / kDkvBq : 0;  // steps a walk is shorter than that of the key tile in front
+    struct Seq {
+        int64_t cost;
+        int32_t b, base;
+    };
+    std::vector<Seq> seqs;
+    int64_t tiles = 0, steps = 0, longest = 0, largest = 0, items = 0;
+    for (int b = 0; b < p->B; b++) {
+        const int64_t s = p->cu[b + 1] - p->cu[b], nt = cdiv(s, kDkvBq), nb = cdiv(s, kChainBk);
+        if (s <= 0) continue;
+        const int64_t cost = (nb * nt - nb * (nb - 1) / 2 * skip) * G;
+        seqs.push_back(Seq{cost, b, (int32_t)tiles});
+        if (nb > 1) tiles += nt;  // (rows that one key tile sees alone are not kept)
+        steps += cost * p->Hkv;
+        items += nb * p->Hkv;
+        longest = std::max(longest, nt * G);
+        largest = std::max(largest, cost);
+    }
+    if (!chain_pays(p, steps, longest, largest, items, n_cu) || tiles * p->Hq > kChainMostTiles) return;
+    std::stable_sort(seqs.begin(), seqs.end(), [](const Seq &a, const Seq &b) { return a.cost > b.cost; });
+    struct Bundle {
+        int32_t cost, team, first, end;
+    };
+    std::vector<Bundle> bundles;
+    std::vector<flexsp_item> list;
+    list.reserve((size_t)items);
+    int32_t open = 0;  // first item of the bundle that is being filled
+    auto close = [&](int32_t team) {
+        if ((size_t)open == list.size()) return;
+        std::stable_sort(list.begin() + open, list.end(), [](const flexsp_item &a, const flexsp_item &b) { return a.step_end > b.step_end; });
+        bundles.push_back(Bundle{list[open].step_end, team, open, (int32_t)list.size()});
+        open = (int32_t)list.size();
+    };
+    for (const Seq &q : seqs)
+        for (int32_t g = 0; g < p->Hkv; g++) {
+            const int32_t s = p->cu[q.b + 1] - p->cu[q.b], nt = (int32_t)cdiv(s, kDkvBq), nb = (int32_t)cdiv(s, kChainBk);
+            const int32_t teams = (int32_t)cdiv(nb, kChainTeam);
+            if (teams > 1) close(0);
+            for (int32_t t = 0; t < teams; t++) {
+                const int32_t from = (int32_t)((int64_t)t * nb / teams), to = (int32_t)((int64_t)(t + 1) * nb / teams);
+                for (int32_t i = from; i < to; i++)
+                    list.push_back(flexsp_item{p->cu[q.b], s, i, g, from, (nt - i * skip) * G, q.base, i + 1 == to && to < nb});
+                if (teams > 1) close(t);
+            }
+            if ((int64_t)list.size() - open >= kChainSpan) close(0);
+        }
+    close(0);
+    std::stable_sort(bundles.begin(), bundles.end(), [](const Bundle &a, const Bundle &b) { return a.cost != b.cost ? a.cost > b.cost : a.team < b.team; });
+    p->chain.reserve(list.size());
+    p->chain_bundles.reserve(bundles.size() + 1);
+    for (const Bundle &b : bundles) {
+        p->chain_bundles.push_back((int32_t)p->chain.size());
+        p->chain.insert(p->chain.end(), list.begin() + b.first, list.begin() + b.end);
+    }
+    p->chain_bundles.push_back((int32_t)p->chain.size());
+    p->chain_tiles = tiles * p->Hq;
+}
+
 int check_attn_common(flexsp_ctx *ctx, flexsp_plan *plan, const int32_t *cu_dev, int32_t head_begin,
                       int32_t head_count, int32_t kv_head_begin, int32_t kv_head_count, int causal)
 {
@@ -648,8 +740,8 @@ int check_attn_common(flexsp_ctx *ctx, flexsp_plan *plan, const int32_t *cu_dev,
 }
 
 // Puts a freshly built plan's queues on the device (nothing to do for a host-only context): one
-// slab, carved into [items x3][offsets x3][counters x3][delta, lse2].  Items of a key-shard plan are
-// written in their wider device form.  On failure the plan is deleted and a status returned.
+// slab, carved into [items x3][offsets x3][counters x3][delta, lse2], and what a backward in one pass needs instead of the two
+// passes'.  Items of a key-shard plan are written in their wider device form.  On failure the plan is deleted and a status returned.
 int plan_upload(flexsp_ctx *ctx, flexsp_plan *p)
 {
     for (int i = 0; i < 3; i++) std::memset(&p->dq[i], 0, sizeof(PassQueues));
@@ -659,11 +751,12 @@ int plan_upload(flexsp_ctx *ctx, flexsp_plan *p)
 
         // one allocation: [items x3][offsets x3][counters x3][delta]
         int nq = ctx->num_xcd;
+        auto on_device = [&](int i) { return i == FLEXSP_PASS_FWD || p->chain.empty(); };
         size_t off = 0, item_off[3], offs_off[3], ctr_off[3];
         auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
         for (int i = 0; i < 3; i++) {
             item_off[i] = off;
-            off = align(off + std::max(p->pass[i].items.size(), p->pass[i].direct.size()) * item_bytes);
+            if (on_device(i)) off = align(off + std::max(p->pass[i].items.size(), p->pass[i].direct.size()) * item_bytes);
         }
         for (int i = 0; i < 3; i++) {
             offs_off[i] = off;
@@ -676,17 +769,32 @@ int plan_upload(flexsp_ctx *ctx, flexsp_plan *p)
         size_t flag_off[3], part_off[3];
         for (int i = 0; i < 3; i++) {
             flag_off[i] = off;
-            off = align(off + (size_t)p->pass[i].records * sizeof(int32_t));
+            if (on_device(i)) off = align(off + (size_t)p->pass[i].records * sizeof(int32_t));
         }
+        // (a chain's dealer and flags are cleared by the launch in front of it)
+        const size_t chain_tiles = p->chain.empty() ? 0 : (size_t)p->chain_tiles;
+        const size_t chain_items_off = off;
+        off = align(off + p->chain.size() * sizeof(flexsp_item));
+        const size_t chain_offs_off = off;
+        off = align(off + (p->chain.empty() ? 0 : p->chain_bundles.size()) * sizeof(int32_t));
         size_t head_bytes = off;
+        const size_t chain_ctr_off = off, chain_flag_off = off + (1 + kChainDies) * kCounterStride * sizeof(int32_t);
+        if (!p->chain.empty()) off = align(chain_flag_off + chain_tiles * sizeof(int32_t));
+        const size_t chain_rows_off = off;
+        off = align(off + chain_tiles * kChainTileBytes);
         size_t delta_off = off;
         off = align(off + p->delta_bytes + 512);  // the dK/dV kernel reads up to 63 floats past a row's end
         for (int i = 0; i < 3; i++) {
             part_off[i] = off;
-            off = align(off + (size_t)p->pass[i].records * kPartialBytes);
+            if (on_device(i)) off = align(off + (size_t)p->pass[i].records * kPartialBytes);
         }
         hipError_t e = hipSetDevice(ctx->device);
         if (e == hipSuccess) e = slab_get(ctx, off ? off : 256, head_bytes ? head_bytes : 256, p->slab);
+        if (e == hipErrorOutOfMemory && !p->chain.empty()) {  // two passes need less
+            (void)hipGetLastError();
+            p->chain.clear();
+            return plan_upload(ctx, p);
+        }
         if (e != hipSuccess) {
             delete p;
             return hip_fail(e);
@@ -696,6 +804,7 @@ int plan_upload(flexsp_ctx *ctx, flexsp_plan *p)
         char *stage = (char *)p->slab.host;
         std::memset(stage, 0, head_bytes);  // also the ticket counters: every plan starts with them clear
         for (int i = 0; i < 3; i++) {
+            if (!on_device(i)) continue;
             const bool direct = !p->pass[i].direct.empty();
             const std::vector<flexsp_item> &items = direct ? p->pass[i].direct : p->pass[i].items;
             if (p->kvshard) {
@@ -726,6 +835,17 @@ int plan_upload(flexsp_ctx *ctx, flexsp_plan *p)
             p->dq[i].direct = direct ? 1 : 0;
             p->dq[i].split_flags = (int32_t *)((char *)p->dev_base + flag_off[i]);
             p->dq[i].split_scratch = (char *)p->dev_base + part_off[i];
+        }
+        if (!p->chain.empty()) {
+            std::memcpy(stage + chain_items_off, p->chain.data(), p->chain.size() * sizeof(flexsp_item));
+            std::memcpy(stage + chain_offs_off, p->chain_bundles.data(), p->chain_bundles.size() * sizeof(int32_t));
+            std::memset(&p->chain_dq, 0, sizeof(PassQueues));
+            p->chain_dq.items = (const flexsp_item *)((char *)p->dev_base + chain_items_off);
+            p->chain_dq.offsets = (const int32_t *)((char *)p->dev_base + chain_offs_off);
+            p->chain_dq.counters = (int32_t *)((char *)p->dev_base + chain_ctr_off);
+            p->chain_dq.nq = (int32_t)p->chain_bundles.size() - 1;
+            p->chain_dq.split_flags = (int32_t *)((char *)p->dev_base + chain_flag_off);
+            p->chain_dq.split_scratch = (char *)p->dev_base + chain_rows_off;
         }
         // asynchronous upload on the context's own stream, after the kernels of the slab's previous
         // plan; the hot calls make their stream wait for `ready` (or find it complete already)
@@ -989,6 +1109,7 @@ int flexsp_plan_create(flexsp_ctx *ctx, const int32_t *cu, int32_t B, int32_t Hq
         p->pass[FLEXSP_PASS_BWD_DQ] = p->pass[FLEXSP_PASS_FWD];
         for (int i = 0; i < 3; i++) direct_list(p->pass[i], nq, n_wg, 0, i == FLEXSP_PASS_FWD ? 0 : kShortPartSteps);
         p->halves = halve_items(p, n_wg / 2);
+        build_chain(p, n_wg / 2);
     } catch (const std::bad_alloc &) {
         delete p;
         return FLEXSP_OUT_OF_MEMORY;
@@ -1129,22 +1250,28 @@ void flexsp_plan_destroy(flexsp_plan *plan)
             else
                 s.done_valid = true;
         }
+        auto give_back = [&](PlanSlab &slab) {
+            if (slab.done_valid) (void)hipEventSynchronize(slab.done);
+            (void)hipEventSynchronize(slab.ready);
+            ctx->slab_bytes -= slab.dev_bytes;
+            slab_free(slab);
+            ctx->slabs_owned--;
+        };
+        size_t pooled = s.dev_bytes;
+        for (const PlanSlab &x : ctx->slabs) pooled += x.dev_bytes;
+        while (!ctx->slabs.empty() && pooled > kSlabPoolBytes) {  // the one released longest ago first
+            pooled -= ctx->slabs.front().dev_bytes;
+            give_back(ctx->slabs.front());
+            ctx->slabs.erase(ctx->slabs.begin());
+        }
         if (ctx->slabs.size() < kSlabPoolMax) {
             try {
                 ctx->slabs.push_back(s);
             } catch (const std::bad_alloc &) {
-                if (s.done_valid) (void)hipEventSynchronize(s.done);
-                (void)hipEventSynchronize(s.ready);
-                ctx->slab_bytes -= s.dev_bytes;
-                slab_free(s);
-                ctx->slabs_owned--;
+                give_back(s);
             }
         } else {
-            if (s.done_valid) (void)hipEventSynchronize(s.done);
-            (void)hipEventSynchronize(s.ready);
-            ctx->slab_bytes -= s.dev_bytes;
-            slab_free(s);
-            ctx->slabs_owned--;
+            give_back(s);
         }
     }
     delete plan;
@@ -1552,6 +1679,23 @@ int flexsp_attn_varlen_bwd(flexsp_ctx *ctx, flexsp_plan *plan, flexsp_tensor q, 
     a.lse_in = lse;
     a.lse_out = lse2;
     a.delta_out = plan->delta;
+    // (dq over o, dk and dv over k and v come out right here too: O is read in front of the chain, a key tile's rows by its own item
+    // before it writes them)
+    if (!plan->chain.empty()) {
+        a.pq = plan->chain_dq;
+        a.chain = 1;
+        a.chain_flags = (int32_t)plan->chain_tiles;
+        {
+            Timed tm(ctx, FLEXSP_K_BWD_DELTA, s);
+            e = launch_attn_bwd_dq(a, plan->D, 0, s);
+        }
+        if (e != hipSuccess) return hip_fail(e);
+        a.lse_in = lse2;
+        a.delta_in = plan->delta;
+        Timed tm(ctx, FLEXSP_K_BWD_DKV, s);
+        e = launch_attn_bwd_dkv(a, plan->D, ctx->num_cu, s);
+        return e == hipSuccess ? FLEXSP_OK : hip_fail(e);
+    }
     if (const int grid = both_at_once(ctx, plan, a)) {
         Timed tm(ctx, FLEXSP_K_BWD_DKV, s);
         e = launch_attn_bwd_dkv(a, plan->D, grid, s);

@@ -20,6 +20,7 @@ constexpr int kDqBk = 64;      // key rows per dQ step
 constexpr int kDkvBk = 64;     // key rows per dK/dV work item (2 pairs of waves x 32 rows)
 constexpr int kDkvWideBk = 128;  // ... of attn_bwd_dkv_wide_kernel's (4 waves x 32 rows)
 constexpr int kDkvBq = 64;     // query rows per dK/dV step
+constexpr int kChainBk = 128;  // key rows per item of a backward in one pass (8 waves: 4 blocks of 32 rows, dK and dV apart)
 constexpr int kThreads = 256;  // every attention kernel runs 4 wavefronts per workgroup
 constexpr int kMaxQueues = 8;  // one work queue per XCD
 constexpr int kCounterStride = 32;  // int32 from one queue's ticket counter to the next: a 128-byte line each
@@ -62,6 +63,13 @@ __host__ __device__ inline bool last_to_leave(WORD &&left, unsigned grid)
     left.add(0u - grid);
     return true;
 }
+
+// A backward in one pass (attn_bwd_chain.hip, build_chain).
+constexpr int kChainDies = 16;   // compute dies, each of which draws from a word of its own
+constexpr int kChainTeam = 32;   // a long sequence's key tiles are bundles of up to so many, a workgroup of the die each
+constexpr int kChainSpan = 64;   // shorter ones are put together until a bundle has so many items
+constexpr size_t kChainTileBytes = (size_t)kDkvBq * 128 * sizeof(float);        // partial sums of dQ: 64 query rows of a head, D = 128
+constexpr int64_t kChainMostTiles = ((int64_t)4 << 30) / (int64_t)kChainTileBytes;  // a plan keeps up to 4 GiB of them
 
 // Work item of the key-shard forward: query rows q_start .. q_start+q_len-1 of q / o / lse, shard
 // keys k_start .. k_start+k_len-1 of k / v, shift = position of the first query in its sequence
@@ -115,6 +123,8 @@ struct AttnArgs {
     // many buffers)
     int32_t halves;
     int32_t num_cu;  // (for that decision)
+    // a backward in one pass (the dQ launcher then starts what runs in front of it); its flags, which that clears
+    int32_t chain, chain_flags;
 };
 
 // Launchers implemented next to their kernels.  All are asynchronous on `s`.
@@ -134,6 +144,8 @@ hipError_t launch_lse_merge_acc(float *oacc, float *lacc, const uint16_t *ob, co
                                 int32_t o16_sh, hipStream_t s);
 hipError_t launch_attn_bwd_dkv(const AttnArgs &a, int D, int grid, hipStream_t s);
 hipError_t launch_attn_bwd_dq(const AttnArgs &a, int D, int grid, hipStream_t s);
+hipError_t launch_attn_bwd_delta(const AttnArgs &a, hipStream_t s);
+hipError_t launch_attn_bwd_chain(const AttnArgs &a, int grid, hipStream_t s);
 hipError_t launch_attn_bwd_dkv_kvshard(const AttnArgs &a, int D, int grid, hipStream_t s);  // a.pq.items: flexsp_shard_item;
 hipError_t launch_attn_bwd_dq_kvshard(const AttnArgs &a, int D, int grid, hipStream_t s);   // a.grad_f32 bit 1: add to dq / dk / dv
 

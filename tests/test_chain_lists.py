@@ -1,0 +1,35 @@
+"""CPU: the list of a backward in one pass and when there is one (tests/sanitize/driver_chain.cpp includes the host source), under the
+sanitizers; what the compiler says about its kernels' registers."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2412_01523_amd import build
+from test_sanitizers import OUT, ROOT, SAN, _run
+
+
+def test_lists_under_asan_ubsan():
+    hipcc = "/opt/rocm/bin/hipcc" if os.path.exists("/opt/rocm/bin/hipcc") else shutil.which("hipcc")
+    if not hipcc:
+        pytest.skip("hipcc not found")
+    OUT.mkdir(exist_ok=True)
+    exe = OUT / "driver_chain"
+    _run([hipcc, "--offload-arch=gfx950", "-O1", "-g", "-std=c++17", "-fno-omit-frame-pointer",
+          "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined", "-fno-gpu-rdc",
+          f"-I{ROOT / 'include'}", f"-I{ROOT / 'paper_2412_01523_amd' / 'csrc'}", "-o", str(exe),
+          str(SAN / "driver_chain.cpp"), "-fsanitize=address", "-fsanitize=undefined"])
+    assert "ok" in _run([str(exe)])
+
+
+def test_registers():
+    """Two wavefronts to a SIMD, nothing spilled to memory."""
+    src = "attn_bwd_chain.hip"
+    r = subprocess.run([build._hipcc(), *build.FLAGS, *build.PER_SOURCE[src], "-Rpass-analysis=kernel-resource-usage",
+                        "--cuda-device-only", "-c", str(build.CSRC / src), "-o", "/dev/null"], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    use = [[int(n) for n in re.findall(rf" {what}: (\d+)", r.stderr)]
+           for what in ("VGPRs Spill", r"ScratchSize \[bytes/lane\]", "AGPRs", r"Occupancy \[waves/SIMD\]")]
+    assert use[:3] == [[0, 0]] * 3 and len(use[3]) == 2 and min(use[3]) >= 2, use

@@ -1,0 +1,129 @@
+"""The backward in one pass over the key tiles: against the CPU fp64 oracle at the edges of its tiles and bundles, both gradient modes, in
+place, in a graph, and two of them at once."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2412_01523_amd import workloads as wl
+
+from gpu_util import bf16_f64, check_against_budget, to_bits, to_dev
+from test_gpu_backward_routes import inputs
+
+pytestmark = pytest.mark.gpu
+
+# sequences around the edges of query tiles (64), key tiles (128) and bundles (32 key tiles: 4 096 tokens), empty and one-token ones;
+# one of several bundles beside short ones; grouped heads; without a mask
+CASES = {
+    "edges": ([4097, 1, 64, 65, 127, 0, 128, 129, 191, 255, 256, 257, 640, 4224, 2048], 8, 8, True),
+    "short": ([130, 257, 383, 511, 300, 256] * 12, 8, 8, True),
+    "grouped": ([900, 77, 1009, 128, 600, 881, 700, 870, 1, 936, 1000, 955, 640, 1024, 1, 961, 897] + [800] * 14, 16, 8, True),
+    "unmasked": ([769, 1000, 833, 900, 1024, 961, 800, 895, 4100, 1025, 950], 8, 8, False),
+}
+
+
+def batch(name, seed=931):
+    lens, hq, hkv, causal = CASES[name]
+    T = sum(lens)
+    return wl.cu_seqlens(lens), hq, hkv, causal, inputs(seed, T, T, hq, hkv, 128)
+
+
+class Backward:
+    """A batch on the GPU, forward done; run() is its backward."""
+
+    def __init__(self, ctx, name, seed=931):
+        import torch
+        from paper_2412_01523_amd import binding as fx
+        self.ctx, self.fx = ctx, fx
+        self.cu, self.hq, self.hkv, self.causal, bits = batch(name, seed)
+        self.bits = bits
+        self.q, self.k, self.v, self.g = (to_dev(x) for x in bits)
+        self.cud = torch.from_numpy(self.cu).cuda()
+        self.plan = fx.Plan(ctx, self.cu, self.hq, self.hkv, 128, self.causal)
+        self.o, self.lse = torch.empty_like(self.q), torch.empty((self.hq, int(self.cu[-1])), dtype=torch.float32, device="cuda")
+        fx.flexsp_attn_varlen_fwd(ctx, self.plan, self.q, self.k, self.v, self.cud, self.o, self.lse, causal=self.causal)
+        torch.cuda.synchronize()
+
+    def outputs(self, dtype):
+        import torch
+        return [torch.full(x.shape, float("nan"), dtype=dtype, device="cuda") for x in (self.q, self.k, self.v)]
+
+    def run(self, out, **kw):
+        self.fx.flexsp_attn_varlen_bwd(self.ctx, self.plan, self.q, self.k, self.v, self.o, self.g, self.lse, self.cud, *out, causal=self.causal, **kw)
+        return out
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2412_01523_amd import binding as fx
+    c = fx.Context(0)
+    yield c
+    c.close()
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_against_the_oracle(ctx, name):
+    import torch
+    print(f"chain: {name}", flush=True)
+    b = Backward(ctx, name)
+    o, _, dq, dk, dv = oracle.attn_fwd_bwd(*b.bits, b.cu, b.causal)
+    ref = {"O": o, "dQ": dq, "dK": dk, "dV": dv}
+    f32 = b.outputs(torch.float32)
+    ctx.profile_start(16)
+    b.run(f32)
+    p = ctx.profile_stop()
+    assert [p[k][1] for k in ("bwd_delta", "bwd_dkv", "bwd_dq")] == [1, 1, 0]
+    out = {"O": bf16_f64(to_bits(b.o))}
+    out.update(zip(("dQ", "dK", "dV"), (x.double().cpu().numpy() for x in f32)))
+    # (the budget that the roundings allow, element by element; the flat 2e-2 is a statement about other magnitudes: sums over a group's
+    # heads and rows that see few keys pass it, by either backward)
+    check_against_budget(f"{name} fp32", out, ref, *b.bits, b.cu, b.causal, None, True, stated=False)
+    again = b.run(b.outputs(torch.float32))
+    bf16 = b.run(b.outputs(torch.bfloat16))
+    for n, x, y, z in zip(("dQ", "dK", "dV"), f32, again, bf16):
+        assert torch.equal(x, y), f"{n} is not reproducible"
+        assert torch.equal(x.to(torch.bfloat16), z), f"{n}: bf16 is not the fp32 result rounded once"
+    # dq over o, dk and dv over k and v: read before they are overwritten
+    over = b.run([b.o, b.k, b.v])
+    for n, x, y in zip(("dQ", "dK", "dV"), bf16, over):
+        assert torch.equal(x, y), f"{n} over an input"
+    b.plan.close()
+
+
+def test_replayed_from_a_graph(ctx):
+    import torch
+    b = Backward(ctx, "edges")
+    ref = [x.clone() for x in b.run(b.outputs(torch.bfloat16))]
+    torch.cuda.synchronize()
+    out = b.outputs(torch.bfloat16)
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=side):
+        b.run(out, stream=torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    for rep in range(3):
+        for t in out:
+            t.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for x, y in zip(ref, out):
+            assert torch.equal(x, y), f"replay {rep}"
+        b.run(b.outputs(torch.bfloat16))  # the program's own eager work between replays
+        torch.cuda.synchronize()
+    b.plan.close()
+
+
+def test_two_at_once(ctx):
+    """Two plans on two streams: their workgroups take each other's compute units, and what either waits for is always running."""
+    import torch
+    pair = [Backward(ctx, "edges", 941), Backward(ctx, "short", 942)]
+    refs = [[x.clone() for x in b.run(b.outputs(torch.bfloat16))] for b in pair]
+    outs = [b.outputs(torch.bfloat16) for b in pair]
+    streams = [torch.cuda.Stream() for _ in pair]
+    torch.cuda.synchronize()
+    for _ in range(10):
+        for b, out, s in zip(pair, outs, streams):
+            b.run(out, stream=s)
+    torch.cuda.synchronize()
+    for b, ref, out in zip(pair, refs, outs):
+        assert all(torch.equal(x, y) for x, y in zip(ref, out))
+        b.plan.close()
