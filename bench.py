@@ -44,17 +44,17 @@ HBM_PEAK = 8.0e12           # MI355X HBM3E, B/s
 # HBM bytes per launch of the attention kernels (FETCH_SIZE + WRITE_SIZE from two rocprofv3 --pmc runs,
 # each scaled by what the same counter reads for a plain copy of known size; the commands, the raw
 # counter values and the algorithmic bytes beside them are in profiles/attention_hbm_traffic.md).
-# bench.py cannot run the profiler on itself: these are the figures of that summary.
+# bench.py cannot run the profiler on itself: these are the figures of that summary (bwd_dkv: the one pass over the key tiles).
 MEASURED_HBM_TRAFFIC = {
-    ("pareto-64k", "fwd"): 1029537792, ("pareto-64k", "bwd_dq"): 1342912326, ("pareto-64k", "bwd_dkv"): 1302433775,
-    ("single-128k", "fwd"): 11535943471, ("single-128k", "bwd_dq"): 22814568822, ("single-128k", "bwd_dkv"): 39482724607,
+    ("pareto-64k", "fwd"): 1034448790, ("pareto-64k", "bwd_delta"): 274796210, ("pareto-64k", "bwd_dkv"): 3195276271,
+    ("single-128k", "fwd"): 11122565611, ("single-128k", "bwd_delta"): 549618520, ("single-128k", "bwd_dkv"): 105326908086,
 }
 
 
 def kernel_flops(d, pairs_heads, launched):
     """Algorithmic FLOPs of a launch by kernel, per (query, key) pair and head: fwd 2 products; dK/dV kernel 4 (S, dP, dV,
-    dK); dQ kernel 1 (its S and dP are recomputation, counted as zero).  A small backward runs both passes in one launch, which
-    the library counts as bwd_dkv: without a bwd_dq among the `launched` kernels all 5 products are that launch's."""
+    dK); dQ kernel 1 (its S and dP are recomputation, counted as zero).  A backward in one pass over the key tiles and a small one are one
+    launch, which the library counts as bwd_dkv: without a bwd_dq among the `launched` kernels all 5 products are that launch's."""
     flops = {"fwd": 4 * d * pairs_heads, "bwd_dkv": 8 * d * pairs_heads, "bwd_dq": 2 * d * pairs_heads}
     if "bwd_dq" not in launched:
         flops["bwd_dkv"] += flops.pop("bwd_dq")
@@ -275,11 +275,11 @@ def length_sweep_leg(ctx, fx, wl, torch, np):
         torch.cuda.synchronize()
         pr = ctx.profile_stop()
         plan.close()
-        ms = {n: pr[n][0] / max(pr[n][1], 1) for n in ("fwd", "bwd_dq", "bwd_dkv")}
+        ms = {n: pr[n][0] / max(pr[n][1], 1) for n in ("fwd", "bwd_delta", "bwd_dq", "bwd_dkv")}
         f_fwd, f_bwd = wl.attn_flops(lens, H, D, True)
         total = sum(ms.values())
         io = 2 * T * H * D          # bytes of one bf16 [T, H, D] tensor
-        out.append({"batch": name, "tokens": T, "sequences": len(lens), "fwd_ms": ms["fwd"], "bwd_dq_ms": ms["bwd_dq"],
+        out.append({"batch": name, "tokens": T, "sequences": len(lens), "fwd_ms": ms["fwd"], "bwd_delta_ms": ms["bwd_delta"], "bwd_dq_ms": ms["bwd_dq"],
                     "bwd_dkv_ms": ms["bwd_dkv"], "tflops": (f_fwd + f_bwd) / (total * 1e-3) / 1e12,
                     "frac_of_bf16_mfma_peak": (f_fwd + f_bwd) / (total * 1e-3) / BF16_MFMA_PEAK,
                     "fwd_flop_per_byte": f_fwd / (4 * io), "fwd_ms_of_its_bytes_at_6TBps": 4 * io / 6e12 * 1e3,
@@ -378,6 +378,9 @@ def main() -> int:
         alg = {"fwd": (T * (2 * Hq + 2 * Hkv) * D) * e + 4 * Hq * T,
                "bwd_dq": (T * (4 * Hq + 2 * Hkv) * D) * e + 3 * 4 * Hq * T,
                "bwd_dkv": (T * (2 * Hq + 4 * Hkv) * D) * e + 2 * 4 * Hq * T,
+               # one pass over the key tiles: q k v dO, delta and lse2 in, dq dk dv out; o dO lse in, delta and lse2 out in front of it
+               "bwd_chain": (T * (3 * Hq + 4 * Hkv) * D) * e + 2 * 4 * Hq * T,
+               "bwd_delta": (T * 2 * Hq * D) * e + 3 * 4 * Hq * T,
                # a small backward's one launch: q k v o dO lse in, dq dk dv out, delta and lse2 written
                "bwd_both": (T * (4 * Hq + 4 * Hkv) * D) * e + 3 * 4 * Hq * T}
         print(json.dumps({"traffic_probe": cfg.name, "copy_bytes_each_way": c1.tokens * c1.hq * c1.sp_degree * c1.d * 2,

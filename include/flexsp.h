@@ -96,14 +96,17 @@ int flexsp_ctx_num_xcd(const flexsp_ctx *ctx);
  * backward, one 66 KiB record per part of a cut tile), so the hot calls allocate nothing.  Where the finer
  * cut of a small backward applies (see flexsp_item) there are at most two records per compute unit and
  * backward pass, 69 MB for both passes on 256 compute units; a new buffer is made a quarter larger than asked.
+ * Where the backward runs in one pass over the key tiles (D = 128 and enough items for the device) the plan holds its items in place of
+ * the two passes', and partial sums of dQ, 512 bytes per token and query head of sequences of more than 128 tokens, 4 GiB at most: a
+ * batch that needs more, or finds less memory, runs in two passes.
  * Everything is copied before the call returns; the caller keeps ownership of
  * cu_seqlens_host.  On a device context the queues go to the GPU with an asynchronous copy on
  * a stream of the context's own, and the first forward / backward call that uses the plan
  * makes its stream wait for that copy (a call made under stream capture should find the copy
  * finished: create the plan, let work that follows it complete, then capture).  Device and
  * pinned memory of destroyed plans is kept by the context (up to 16 buffers) and handed to new
- * plans (a buffer whose kernels have finished is preferred; a context makes at most four, 1 GiB
- * in all, before it reuses a busy one), so a plan per micro-batch costs neither an allocation
+ * plans (a buffer whose kernels have finished is preferred; a context makes at most four, 8 GiB
+ * in all, before it reuses a busy one, and keeps no more than 16 GiB in free ones, one apart), so a plan per micro-batch costs neither an allocation
  * nor a device-wide synchronisation after the first steps.  When every buffer is still in use
  * by kernels, THIS CALL BLOCKS THE HOST until those of the buffer released first have finished:
  * a caller that makes a plan per step runs at most four steps ahead of the GPU.  A context, and
@@ -123,7 +126,7 @@ void flexsp_plan_destroy(flexsp_plan *plan);
  * sequence-parallel group), the plan cuts such a tile's inner loop into `nparts` consecutive ranges,
  * one work item each; every part leaves its partial result (fp32) in the plan's scratch and the part
  * that finishes last adds them up in part order and writes the tile, so results do not depend on
- * which part that is.  (A backward of so few items that compute units would be left without work cuts
+ * which part that is.  (The items of a backward in one pass are not listed here; a backward of so few items that compute units would be left without work cuts
  * its tiles into shorter parts than listed here, and a forward of few long sequences runs each of its tiles as two
  * of 64 rows, when they are launched.) */
 typedef struct flexsp_item {
@@ -148,8 +151,8 @@ int flexsp_plan_get_items(const flexsp_plan *plan, int pass, flexsp_item *items,
                           int64_t capacity, int64_t *queue_offsets);
 /* Rows per tile used by a pass (query rows for FWD and BWD_DQ, key rows for BWD_DKV). */
 int flexsp_plan_tile_rows(const flexsp_plan *plan, int pass);
-/* Bytes of device scratch the plan holds for the rows of the backward pass (delta and log-sum-exp).  Its work lists and the partial
- * results of tiles that it cuts, up to 2 048 of 66 KiB for each of the three passes, are not counted; a key shard's plan has the same. */
+/* Bytes of device scratch the plan holds for the rows of the backward pass (delta and log-sum-exp).  Its work lists, the partial
+ * sums of a backward in one pass and the partial results of tiles that it cuts, up to 2 048 of 66 KiB for each of the three passes, are not counted; a key shard's plan has the same. */
 size_t flexsp_attn_bwd_workspace_bytes(const flexsp_plan *plan);
 
 /*
@@ -234,8 +237,8 @@ int flexsp_attn_varlen_fwd(flexsp_ctx *ctx, flexsp_plan *plan, flexsp_tensor q, 
  * Backward of Eq. 3 for the loss L = sum(O * dO): writes dq [T,*,D] (query heads as in q)
  * and dk, dv [T,*,D] (kv heads as in k; summed over the query heads of each group).
  * o and lse are the forward's outputs.  Softmax is recomputed from lse (no second
- * reduction); delta = rowsum(dO * O) is formed in fp32 and kept in the plan's scratch between the two
- * passes (a small backward runs them in one launch, in which each forms it itself).
+ * reduction); delta = rowsum(dO * O) is formed in fp32 and kept in the plan's scratch for the pass or the
+ * two passes behind it (a small backward runs both in one launch, in which each forms it itself).
  * grad_dtype selects the element type of dq, dk and dv (their strides count elements of that
  * type): FLEXSP_BF16 rounds the fp32 accumulators to bf16 once; FLEXSP_F32 stores them as
  * they are (useful when grouped-query sums grow past the range where bf16's spacing is fine
@@ -411,8 +414,8 @@ enum {
     FLEXSP_K_PACK = 0,
     FLEXSP_K_UNPACK = 1,
     FLEXSP_K_FWD = 2,
-    FLEXSP_K_BWD_DELTA = 3, /* reserved: the row-dot preprocessing is part of the dQ kernel, never launched */
-    FLEXSP_K_BWD_DKV = 4,   /* a small backward runs both passes in one launch, counted here            */
+    FLEXSP_K_BWD_DELTA = 3, /* the rows' delta, in front of a backward in one pass over the key tiles  */
+    FLEXSP_K_BWD_DKV = 4,   /* that pass, and the one launch of a small backward, are counted here     */
     FLEXSP_K_BWD_DQ = 5,
     FLEXSP_K_COUNT = 6
 };

@@ -15,8 +15,10 @@
 // What bounds it: the matrix unit is busy for half of the cycles, and the chip is at 1.8 GHz (zero inputs: 2.3).  A workgroup of
 // eight wavefronts has a compute unit to itself, two to a SIMD with 256 registers each.  While one of the two does matrix work alone
 // (sums) the other forms S, dP and their exponentials (scores): wavefronts 0 .. 3 in this order, 4 .. 7 in the other.
-// Backward, two kernels -> this, us: one sequence of 131 072 tokens, 8 heads 101 339 -> 88 770, 32 768 6 576 -> 5 637; sequences of 4 096 1 898 ->
-// 1 679, 2 048 812 -> 742, 1 024 481 -> 466; a 64K-token long-tail batch 1 320 -> 1 252; 262 144 tokens, 16 heads on 2 122 988 -> 112 100.
+// Of the rows' stores 28 % leave the L2 on long sequences all the same: what 32 workgroups two steps apart are busy with is as large as it.
+// Backward, two kernels -> this, us: one sequence of 131 072 tokens, 8 heads 101 280 -> 89 180, 32 768 6 581 -> 5 576; sequences of 4 096 1 874 ->
+// 1 668, 2 048 805 -> 739, 1 024 476 -> 457; 49 152 tokens, up to 1 024 a sequence 390 -> 383; a 64K-token long-tail batch 1 329 -> 1 246;
+// 262 144 tokens, 16 heads on 2 122 170 -> 111 100.
 // Tried on the way: both wavefronts of a SIMD in the same phase, two barriers a step (as fast as two kernels); the exponentials between the
 // sums' matrix instructions of the same wavefront (56 registers too many).
 #include <type_traits>
