@@ -127,3 +127,20 @@ def test_two_at_once(ctx):
     for b, ref, out in zip(pair, refs, outs):
         assert all(torch.equal(x, y) for x, y in zip(ref, out))
         b.plan.close()
+
+
+def test_plans_behind_a_full_pool(ctx):
+    """A larger plan than any of those that fill the context's pool is kept like they were: the next one takes its memory over."""
+    import torch
+    from paper_2412_01523_amd import binding as fx
+    few = [fx.Plan(ctx, wl.cu_seqlens([300]), 2, 2, 64, True) for _ in range(17)]
+    for p in few:
+        p.close()
+    free = []
+    for _ in range(3):
+        p = fx.Plan(ctx, wl.cu_seqlens([2048] * 32), 8, 8, 128, True)  # 256 MB of dQ's rows
+        torch.cuda.synchronize()
+        free.append(torch.cuda.mem_get_info()[0])
+        p.close()
+        free.append(torch.cuda.mem_get_info()[0])
+    assert max(free) - min(free) < 64 << 20, free
