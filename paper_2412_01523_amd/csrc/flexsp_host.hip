@@ -653,6 +653,29 @@ bool chain_pays(const flexsp_plan *p, int64_t steps, int64_t longest, int64_t la
     return items >= 2 * n_cu && steps >= (p->causal ? 3 : 12) * G * items && longest * n_cu * (G > 1 ? 5 : 2) <= 2 * steps && 4 * largest <= steps;
 }
 
+struct ChainBundle {
+    int32_t cost, team, first, end;
+};
+
+// Whether the dies, which take the bundles in this order as they come to an end with one, all have about an even share of the steps: with few
+// bundles as dear as each other some take one more than the rest, and everything waits for them.
+// Backward, two kernels -> one pass, us, by the largest share over the even one, no mask: 1.00 (32 768 tokens in sequences of 2 048, 8 heads) 881 -> 795; 1.04 (131 072 in
+// 1 000, 8 heads) 1 965 -> 1 895; 1.08 (49 352 in one, 16 heads on 4) 60 230 -> 60 950; 1.2 (65 536 in 1 600, 4 heads) 721 -> 728, (20 000 in 1 500, 8 heads)
+// 413 -> 495; 1.3 (40 000 in 3 000, 12 heads on 4) 2 270 -> 2 680.  With a mask later bundles are cheaper, and the pass gains more: forward, backward and permutes
+// at 1.08 (121 707, up to 1 606 a sequence, 2 heads) 469 -> 451, at 1.12 (124 314 in 433, 4 heads on 2) 739 -> 739.
+bool dies_even(const std::vector<flexsp_item> &list, const std::vector<ChainBundle> &bundles, int dies, bool causal)
+{
+    std::vector<int64_t> share((size_t)dies, 0);
+    int64_t all = 0;
+    for (const ChainBundle &b : bundles) {
+        int64_t steps = 0;
+        for (int32_t i = b.first; i < b.end; i++) steps += list[i].step_end;
+        *std::min_element(share.begin(), share.end()) += steps;
+        all += steps;
+    }
+    return 100 * *std::max_element(share.begin(), share.end()) * dies <= (causal ? 111 : 106) * all;
+}
+
 // Lists a backward in one pass, if it is one.  The list's bundles (see ChainDealer) are what a compute die's workgroups, one per compute
 // unit, work on at a time, and what they share should stay in its L2: the rows of dQ that are added to, Q and dO, 64 KB a step.  So a long
 // sequence's key tiles are bundles of up to kChainTeam, one to a workgroup, which go through the steps one behind the other; heads and
@@ -686,17 +709,14 @@ void build_chain(flexsp_plan *p, int n_cu)
     }
     if (!chain_pays(p, steps, longest, largest, items, n_cu) || tiles * p->Hq > kChainMostTiles) return;
     std::stable_sort(seqs.begin(), seqs.end(), [](const Seq &a, const Seq &b) { return a.cost > b.cost; });
-    struct Bundle {
-        int32_t cost, team, first, end;
-    };
-    std::vector<Bundle> bundles;
+    std::vector<ChainBundle> bundles;
     std::vector<flexsp_item> list;
     list.reserve((size_t)items);
     int32_t open = 0;  // first item of the bundle that is being filled
     auto close = [&](int32_t team) {
         if ((size_t)open == list.size()) return;
         std::stable_sort(list.begin() + open, list.end(), [](const flexsp_item &a, const flexsp_item &b) { return a.step_end > b.step_end; });
-        bundles.push_back(Bundle{list[open].step_end, team, open, (int32_t)list.size()});
+        bundles.push_back(ChainBundle{list[open].step_end, team, open, (int32_t)list.size()});
         open = (int32_t)list.size();
     };
     for (const Seq &q : seqs)
@@ -713,10 +733,11 @@ void build_chain(flexsp_plan *p, int n_cu)
             if ((int64_t)list.size() - open >= kChainSpan) close(0);
         }
     close(0);
-    std::stable_sort(bundles.begin(), bundles.end(), [](const Bundle &a, const Bundle &b) { return a.cost != b.cost ? a.cost > b.cost : a.team < b.team; });
+    std::stable_sort(bundles.begin(), bundles.end(), [](const ChainBundle &a, const ChainBundle &b) { return a.cost != b.cost ? a.cost > b.cost : a.team < b.team; });
+    if (!dies_even(list, bundles, std::max(1, n_cu / kChainTeam), p->causal)) return;
     p->chain.reserve(list.size());
     p->chain_bundles.reserve(bundles.size() + 1);
-    for (const Bundle &b : bundles) {
+    for (const ChainBundle &b : bundles) {
         p->chain_bundles.push_back((int32_t)p->chain.size());
         p->chain.insert(p->chain.end(), list.begin() + b.first, list.begin() + b.end);
     }

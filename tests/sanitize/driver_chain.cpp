@@ -104,6 +104,7 @@ int main()
         {64, 768, 8, 8, 0, 128, 1}, {64, 704, 8, 8, 0, 128, 0},    // twelve steps an item, eleven, unmasked
         {8, 1024, 8, 8, 1, 128, 1}, {4, 2048, 8, 8, 1, 128, 1}, {2, 4096, 8, 8, 1, 128, 1},  // shares of 18, 34 and 66 steps, walks of 16, 32 and 64
         {1, 8192, 8, 8, 1, 128, 1}, {1, 8064, 8, 8, 1, 128, 0},   // 512 items and 504
+        {32, 2048, 8, 8, 0, 128, 1}, {13, 1500, 8, 8, 0, 128, 0}, {41, 1600, 4, 4, 0, 128, 0},  // as many bundles for each die, or one more for some
         {5, 8192, 16, 4, 1, 128, 1}, {4, 8192, 16, 4, 1, 128, 0},  // 0.39 and 0.49 of a share: several heads to a key head
     };
     for (const auto &c : cases) {

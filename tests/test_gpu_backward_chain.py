@@ -14,10 +14,10 @@ pytestmark = pytest.mark.gpu
 # sequences around the edges of query tiles (64), key tiles (128) and bundles (32 key tiles: 4 096 tokens), empty and one-token ones;
 # one of several bundles beside short ones; grouped heads; without a mask
 CASES = {
-    "edges": ([4097, 1, 64, 65, 127, 0, 128, 129, 191, 255, 256, 257, 640, 4224, 2048], 8, 8, True),
+    "edges": ([4097, 1, 64, 65, 127, 0, 128, 129, 191, 255, 256, 257, 640, 4224, 2048] + [896] * 12, 8, 8, True),
     "short": ([130, 257, 383, 511, 300, 256] * 12, 8, 8, True),
     "grouped": ([900, 77, 1009, 128, 600, 881, 700, 870, 1, 936, 1000, 955, 640, 1024, 1, 961, 897] + [800] * 14, 16, 8, True),
-    "unmasked": ([769, 1000, 833, 900, 1024, 961, 800, 895, 4100, 1025, 950], 8, 8, False),
+    "unmasked": ([769, 1000, 833, 900, 1024, 961, 800, 895, 4100, 1025, 950] + [896] * 8, 8, 8, False),
 }
 
 
@@ -129,18 +129,20 @@ def test_two_at_once(ctx):
         b.plan.close()
 
 
-def test_plans_behind_a_full_pool(ctx):
+def test_plans_behind_a_full_pool():
     """A larger plan than any of those that fill the context's pool is kept like they were: the next one takes its memory over."""
     import torch
     from paper_2412_01523_amd import binding as fx
+    ctx = fx.Context(0)
     few = [fx.Plan(ctx, wl.cu_seqlens([300]), 2, 2, 64, True) for _ in range(17)]
     for p in few:
         p.close()
     free = []
     for _ in range(3):
-        p = fx.Plan(ctx, wl.cu_seqlens([2048] * 32), 8, 8, 128, True)  # 256 MB of dQ's rows
+        p = fx.Plan(ctx, wl.cu_seqlens([2048] * 32), 8, 8, 128, True)  # 256 MB of dQ's rows, a quarter more as allocated
         torch.cuda.synchronize()
         free.append(torch.cuda.mem_get_info()[0])
         p.close()
         free.append(torch.cuda.mem_get_info()[0])
-    assert max(free) - min(free) < 64 << 20, free
+    ctx.close()
+    assert max(free) - min(free) < 160 << 20, free  # (one of the few, under 100 MB, is given back at first)
