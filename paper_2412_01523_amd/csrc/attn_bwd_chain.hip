@@ -11,7 +11,12 @@
 // at that time: plain stores, loads that pass by the compute unit's own cache (sc1).  Measured on a buffer that a die's 32 compute units
 // hand round: every such load sees the store, 12 TB/s read and as much written over the chip.  From die to die both go through
 // memory (2.8 TB/s), so that only the last item of a bundle (see ChainDealer) stores its rows that way.
-//
+// What the hand-over relies on.  Within a die: a plain store that has been counted (vmcnt) is in the die's L2, and an sc1 load asks there; a
+// wavefront that reads its own store back like that has to see it, and the L2 does not tell one unit's stores from another's.  From die to die: rows
+// and flag are stored and loaded with sc1, which is what relaxed atomic accesses of agent scope are made of; such a load may not return an older copy
+// that its die's L2 still holds (whoever waits for a flag of another die's would wait for good), so it does not matter which versions of
+// a row a die has seen before.  The flag is stored when the rows have been counted.  Nobody reads rows of dQ in any other way, nor before the
+// flag says that they are there: no load ahead of time, plain or not.
 // What bounds it: the matrix unit is busy for half of the cycles, and the chip is at 1.8 GHz (zero inputs: 2.3).  A workgroup of
 // eight wavefronts has a compute unit to itself, two to a SIMD with 256 registers each.  While one of the two does matrix work alone
 // (sums) the other forms S, dP and their exponentials (scores): wavefronts 0 .. 3 in this order, 4 .. 7 in the other.
@@ -328,20 +333,17 @@ __global__ __launch_bounds__(kChainThreads, 2) void attn_bwd_chain_kernel(const 
                 }
             };
             // The first block of a bundle would meet every tile in memory, and the others keep its pace.  So the n-th block after
-            // it touches the n-th sixteenth of a tile's lines (Q, dO, then dQ's where another bundle has added to it) before it gets there.
+            // it touches the n-th eighth of a tile's lines (Q, dO) before it gets there.  (Not the lines of dQ that another bundle has added
+            // to: whether that has added for the last time is what the flag says, and nobody reads a row of dQ before the flag.)
             const int nth = b - it.step_begin, reach = (2 * nth + 5) / G + 1;  // in tiles
             auto touch = [&]() {
                 const int t = t_x - reach;
-                if (nth < 1 || nth > (it.step_begin ? 16 : 8) || t < (causal ? it.step_begin * (kChainBk / BQ) : 0)) return;
+                if (nth < 1 || nth > 8 || t < (causal ? it.step_begin * (kChainBk / BQ) : 0)) return;
                 int l = lane;
                 asm volatile("" : "+v"(l));
-                if (nth > 8) {
-                    global_to_lds4(a.pq.split_scratch + (int64_t)(i_x - reach) * (int64_t)kChainTileBytes + (nth - 9) * 4096 + l * 64, smem + NOBODY);
-                } else {
-                    const bool is_q = nth <= 4;
-                    const int64_t row = tok0 + t * BQ + (nth - 1 & 3) * 16 + (l >> 2);
-                    global_to_lds4((const char *)((is_q ? a.q : a.dO) + row * (is_q ? a.q_st : a.do_st) + (int64_t)h_x * (is_q ? a.q_sh : a.do_sh)) + (l & 3) * 64, smem + NOBODY);
-                }
+                const bool is_q = nth <= 4;
+                const int64_t row = tok0 + t * BQ + (nth - 1 & 3) * 16 + (l >> 2);
+                global_to_lds4((const char *)((is_q ? a.q : a.dO) + row * (is_q ? a.q_st : a.do_st) + (int64_t)h_x * (is_q ? a.q_sh : a.do_sh)) + (l & 3) * 64, smem + NOBODY);
             };
             auto ask = [&]() {
                 int l = lane;
