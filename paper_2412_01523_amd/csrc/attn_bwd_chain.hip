@@ -4,7 +4,8 @@
 // One work item = 128 keys of one (sequence, kv head), as there: dK^T and dV^T stay in registers while the query rows go by, 64 a
 // step.  dQ of those rows is a sum over the key tiles, so it travels: the item of key tile b reads what tile b - 1 has left, adds its
 // own dS K in fp32 and leaves it for tile b + 1; the last one to see the rows scales, rounds and writes dq.  The order of the
-// additions is that of the keys, whoever runs when: results are bitwise reproducible, no float atomics.  A flag per (64 query rows,
+// additions is that of the keys, whoever runs when: results are bitwise reproducible, no float atomics, and dQ has the two kernels' bits where they cut no tile
+// (dK and dV are summed from the last query rows to the first here).  A flag per (64 query rows,
 // head) says how many key tiles have added.  Every item walks its query tiles from the last one down, so that the items of a sequence
 // start together, each a step or two behind the one before, and with a mask the later, shorter walks end first.
 // The rows in between (32 KB per step and item, read and written) stay in the L2 of the compute die that runs the neighbouring key tiles
@@ -36,38 +37,49 @@ namespace {
 // LDS fragments are read this many matrix instructions ahead (the file is compiled in source order); 4 takes 2 % longer, 2 the same
 constexpr int kReadAhead = 3;
 constexpr int kChainThreads = 512;
+constexpr int kDeltaRows = kThreads / 64 * 32;
 
 // ------------------------------------------------------------------------------ delta
-// -delta = -(dO . O) and the base-2 log-sum-exp of every row, and a clear dealer and flags for the launch behind it.  One workgroup: 64
-// rows of one head.  Bound by reading O and dO: 65 536 tokens, 8 heads 53 us, 5 TB/s.  (The key tiles all need delta, none before the
+// -delta = -(dO . O) and the base-2 log-sum-exp of every row, and a clear dealer and flags for the launch behind it.  One wavefront: 32
+// rows of one head, read as whole rows and summed in the order of the dQ kernel (attn_bwd.hip): half a row's head dims in turn by a lane, then
+// the other half's sum, so that dQ has the bits it has there.  Bound by reading O and dO: 65 536 tokens, 8 heads 61 us between events (53
+// with pieces summed by whichever lanes read them, and rounded differently).  (The key tiles all need delta, none before the
 // others, so no item of theirs can form it for the rest.)
 __global__ __launch_bounds__(kThreads) void attn_bwd_delta_kernel(const AttnArgs)
 {
-    constexpr int D = 128, CH = D / 8, RP = kThreads / CH, N = 64 / RP;
+    constexpr int D = 128, KS = D / 16;
+    typedef LdsTile<D> L;
+    __shared__ __attribute__((aligned(1024))) char smem[kThreads / 64 * 32 * L::ROWB];
     KernArgs &a = kernel_args();
-    const int tid = thread_id(), wg = workgroup_id();
-    const int h = wg % a.Hq, t0 = wg / a.Hq * 64;
-    const int row = tid / CH, ch = tid % CH;
-    u32x4 o[N], g[N];
+    const int tid = thread_id(), wg = workgroup_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int h = wg % a.Hq, t0 = wg / a.Hq * kDeltaRows + wave * 32;
+    LaneOffsets<D> lo;
+    lo.init(lane);
+    RowBlock<D> orows, grows;
+    orows.load(a.o + (int64_t)h * a.o_sh, a.o_st, t0, a.T - 1, lane);
+    grows.load(a.dO + (int64_t)h * a.do_sh, a.do_st, t0, a.T - 1, lane);
+    char *const region = smem + wave * (32 * L::ROWB);
+    bf16x8 of[KS], gf[KS];
+    orows.fragments(region, 0, lo, of, lane);
+    grows.fragments(region, 0, lo, gf, lane);
+    float d = 0.f;
 #pragma unroll
-    for (int n = 0; n < N; n++) {
-        const int64_t t = min(t0 + n * RP + row, a.T - 1);
-        o[n] = *(const u32x4 *)(a.o + t * a.o_st + (int64_t)h * a.o_sh + ch * 8);
-        g[n] = *(const u32x4 *)(a.dO + t * a.do_st + (int64_t)h * a.do_sh + ch * 8);
-    }
+    for (int ks = 0; ks < KS; ks++) {
+        Frag8 fg, fo;
+        fg.v = gf[ks];
+        fo.v = of[ks];
 #pragma unroll
-    for (int n = 0; n < N; n++) {
-        float d = 0.f;
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-            const uint32_t gw = g[n][e], ow = o[n][e];
+        for (int i = 0; i < 4; i++) {
+            const uint32_t gw = fg.u[i], ow = fo.u[i];
             d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, gw), __builtin_bit_cast(bf16x2, ow), d, false);
         }
-        d = group_sum<CH>(d);
-        const int t = t0 + n * RP + row;
-        if (ch == 0 && t < a.T) a.delta_out[(int64_t)h * a.T + t] = -d;
     }
-    if (tid < 64 && t0 + tid < a.T) a.lse_out[(int64_t)h * a.T + t0 + tid] = a.lse_in[(int64_t)h * a.T + t0 + tid] * 1.4426950408889634f;
+    d = halves_sum(d);
+    const int64_t at = (int64_t)h * a.T + t0 + lane;
+    if (lane < 32 && t0 + lane < a.T) {
+        a.delta_out[at] = -d;
+        a.lse_out[at] = a.lse_in[at] * 1.4426950408889634f;
+    }
     for (int i = wg * kThreads + tid; i < a.chain_flags; i += a.grid * kThreads) a.pq.split_flags[i] = 0;
     if (wg == 0 && tid <= kChainDies) *(unsigned long long *)(a.pq.counters + tid * kCounterStride) = 0;
 }
@@ -587,7 +599,7 @@ __global__ __launch_bounds__(kChainThreads, 2) void attn_bwd_chain_kernel(const 
 
 hipError_t launch_attn_bwd_delta(const AttnArgs &a, hipStream_t s)
 {
-    launch(attn_bwd_delta_kernel, a, (int)((a.T + 63) / 64) * a.Hq, s);
+    launch(attn_bwd_delta_kernel, a, (int)((a.T + kDeltaRows - 1) / kDeltaRows) * a.Hq, s);
     return hipGetLastError();
 }
 
