@@ -27,6 +27,9 @@ def batch(name, seed=931, cases=CASES):
     return wl.cu_seqlens(lens), hq, hkv, causal, inputs(seed, T, T, hq, hkv, 128)
 
 
+PLANS = []  # closed in front of their context, also those of a test that failed
+
+
 class Backward:
     """A batch on the GPU, forward done; run() is its backward."""
 
@@ -39,6 +42,7 @@ class Backward:
         self.q, self.k, self.v, self.g = (to_dev(x) for x in bits)
         self.cud = torch.from_numpy(self.cu).cuda()
         self.plan = fx.Plan(ctx, self.cu, self.hq, self.hkv, 128, self.causal)
+        PLANS.append(self.plan)
         self.o, self.lse = torch.empty_like(self.q), torch.empty((self.hq, int(self.cu[-1])), dtype=torch.float32, device="cuda")
         fx.flexsp_attn_varlen_fwd(ctx, self.plan, self.q, self.k, self.v, self.cud, self.o, self.lse, causal=self.causal)
         torch.cuda.synchronize()
@@ -57,6 +61,8 @@ def ctx():
     from paper_2412_01523_amd import binding as fx
     c = fx.Context(0)
     yield c
+    while PLANS:
+        PLANS.pop().close()
     c.close()
 
 
@@ -106,6 +112,7 @@ def test_rows_handed_from_die_to_die(ctx, name):
     b = Backward(ctx, name, 951, {**CASES, **LONG})
     lens = np.diff(b.cu)
     plan = fx.ShardPlan(ctx, b.cu, b.cu, [0] * len(lens), b.hq, b.hkv, 128, b.causal)
+    PLANS.append(plan)
     assert (plan.items(fx.PASS_BWD_DQ)[0]["nparts"] <= 1).all()  # (a cut tile's sums are formed apart)
     ref = b.outputs(torch.float32)
     fx.flexsp_attn_varlen_bwd_kvshard(ctx, plan, b.q, b.k, b.v, b.o, b.g, b.lse, *ref, causal=b.causal)
@@ -124,6 +131,50 @@ def test_rows_handed_from_die_to_die(ctx, name):
             rel = ((x - y).double().norm() / y.double().norm()).item()
             assert rel <= n ** 0.5 * 2.0 ** -24, f"{what}: {rel:.1e}"
     plan.close()
+    b.plan.close()
+
+
+# (sequences whose last tile of query rows is half a tile)
+NONFINITE = {"one pass": ([800, 992, 416] * 20, 8, 8, True), "two": ([800, 992, 416] * 20, 1, 1, True)}
+
+
+@pytest.mark.parametrize("name", NONFINITE)
+def test_a_row_that_is_not_finite(ctx, name):
+    """A row of k, v, q or dO with an infinity or a NaN: what shares no visible pair's block of 32 rows and 32 keys with it keeps its bits."""
+    import torch
+    print(f"not finite: {name}", flush=True)
+    b = Backward(ctx, name, 961, NONFINITE)
+    clean = b.run(b.outputs(torch.float32))
+    ctx.profile_start(16)
+    b.run(b.outputs(torch.float32))
+    assert (ctx.profile_stop()["bwd_delta"][1] == 1) == (name == "one pass")
+    end = int(b.cu[-1])
+    everywhere = torch.ones(end, dtype=torch.bool, device="cuda")
+
+    def but(first, stop):
+        keep = everywhere.clone()
+        keep[first:stop] = False
+        return keep
+
+    for seq, row in ((0, 100), (1, 205), (4, 430), (16, 991), (17, 37), (3, 799), (2, 0)):
+        start, stop = int(b.cu[seq]), int(b.cu[seq + 1])
+        first = start + row // 32 * 32
+        last = min(first + 32, stop)
+        for which, x in (("k", b.k), ("v", b.v), ("q", b.q), ("dO", b.g)):
+            # rows of dQ that see a key of the block, keys that are seen from a row of it
+            if which in "kv":
+                keep = but(first, stop), but(first, last), but(first, last)
+            else:
+                keep = but(first, last), but(start, last), but(start, last)
+            for value in (float("inf"), float("nan")):
+                old = x[start + row].clone()
+                x[start + row, :, 5:9] = value
+                out = b.run(b.outputs(torch.float32))
+                for n, got, want, rows in zip(("dQ", "dK", "dV"), out, clean, keep):
+                    assert torch.equal(got[rows], want[rows]), f"{which}[{seq}, {row}] = {value}: {n}"
+                if which == "dO" and row == 799 and value > 0:  # a last half tile: nothing but P times infinity, P > 0
+                    assert (out[2][start:stop, :, 5:9] == value).all(), "dV"
+                x[start + row] = old
     b.plan.close()
 
 
