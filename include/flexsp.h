@@ -98,7 +98,9 @@ int flexsp_ctx_num_xcd(const flexsp_ctx *ctx);
  * backward pass, 69 MB for both passes on 256 compute units; a new buffer is made a quarter larger than asked.
  * Where the backward runs in one pass over the key tiles (D = 128 and enough items for the device) the plan holds its items in place of
  * the two passes', and partial sums of dQ, 512 bytes per token and query head of sequences of more than 128 tokens, 4 GiB at most: a
- * batch that needs more, or finds less memory, runs in two passes.
+ * batch that needs more, or finds less memory, runs in two passes.  (The bits of dk and dv then differ, whose sums over the rows run the other way,
+ * and of dq where the two passes cut tiles: results are reproducible as long as that memory is there or is not.  The memory is taken when the plan is made,
+ * also if it is only used forward; flexsp_attn_varlen_fwd_static needs no plan.)
  * Everything is copied before the call returns; the caller keeps ownership of
  * cu_seqlens_host.  On a device context the queues go to the GPU with an asynchronous copy on
  * a stream of the context's own, and the first forward / backward call that uses the plan
@@ -106,7 +108,8 @@ int flexsp_ctx_num_xcd(const flexsp_ctx *ctx);
  * finished: create the plan, let work that follows it complete, then capture).  Device and
  * pinned memory of destroyed plans is kept by the context (up to 16 buffers) and handed to new
  * plans (a buffer whose kernels have finished is preferred; a context makes at most four, 8 GiB
- * in all, before it reuses a busy one, and keeps no more than 16 GiB in free ones, one apart), so a plan per micro-batch costs neither an allocation
+ * in all, before it reuses a busy one, keeps no more than 16 GiB in free ones, one apart, hands none to a plan that needs less than a quarter of it less
+ * 64 MiB, and gives free ones back when the device has no memory for a new one), so a plan per micro-batch costs neither an allocation
  * nor a device-wide synchronisation after the first steps.  When every buffer is still in use
  * by kernels, THIS CALL BLOCKS THE HOST until those of the buffer released first have finished:
  * a caller that makes a plan per step runs at most four steps ahead of the GPU.  A context, and

@@ -31,6 +31,7 @@ constexpr size_t kSlabPoolMax = 16;  // free slabs kept by a context
 constexpr size_t kSlabEager = 4;     // slabs a context makes rather than wait for a busy one ...
 constexpr size_t kSlabEagerBytes = (size_t)8 << 30;  // ... while they hold less device memory than this (a backward in one pass keeps 512 bytes a token and head)
 constexpr size_t kSlabPoolBytes = (size_t)16 << 30;  // free slabs hold no more device memory than this, the one released last apart
+constexpr size_t kSlabWaste = (size_t)64 << 20;      // a plan takes no slab of more than four times what it asks for and this
 
 struct flexsp_ctx {
     int device;  // -1: host-only
@@ -109,6 +110,31 @@ void slab_free(PlanSlab &s)
     s = PlanSlab();
 }
 
+// Gives a free slab's memory back, behind its kernels and its upload.
+void slab_give_back(flexsp_ctx *ctx, PlanSlab &s)
+{
+    if (s.done_valid) (void)hipEventSynchronize(s.done);
+    (void)hipEventSynchronize(s.ready);
+    ctx->slab_bytes -= s.dev_bytes;
+    slab_free(s);
+    ctx->slabs_owned--;
+}
+
+hipError_t slab_make(PlanSlab &s)
+{
+    hipError_t e = hipMalloc(&s.dev, s.dev_bytes);
+    if (e == hipSuccess) e = hipHostMalloc(&s.host, s.host_bytes, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&s.ready, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&s.done, hipEventDisableTiming);
+    if (e != hipSuccess) {
+        const size_t dev_bytes = s.dev_bytes, host_bytes = s.host_bytes;
+        slab_free(s);
+        s.dev_bytes = dev_bytes;
+        s.host_bytes = host_bytes;
+    }
+    return e;
+}
+
 // A slab with at least the given sizes.  Among the adequate ones in the pool, one whose last
 // kernels have already finished is preferred (the smallest such): its queues can be uploaded at
 // once, while the kernels of the plan destroyed a moment ago still run.  Taking back the slab just
@@ -124,12 +150,14 @@ void slab_free(PlanSlab &s)
 // slab's kernels with an event on the upload stream (the first such cross-stream waits after an
 // idle period).  With the host-side wait, allocations end with the first kSlabEager plans of a run
 // and no stream ever waits for an event that is not complete yet.
+// A slab that is far too large stays in the pool for a plan that needs it: a small plan would hold gigabytes for its life, and the next large one
+// would make another.  Where there is no memory for a new one, the free ones are given back first, those whose kernels have finished before others.
 hipError_t slab_get(flexsp_ctx *ctx, size_t dev_bytes, size_t host_bytes, PlanSlab &out)
 {
     int best = -1, best_busy = -1;
     for (size_t i = 0; i < ctx->slabs.size(); i++) {
         const PlanSlab &s = ctx->slabs[i];
-        if (s.dev_bytes < dev_bytes || s.host_bytes < host_bytes) continue;
+        if (s.dev_bytes < dev_bytes || s.host_bytes < host_bytes || s.dev_bytes > 4 * dev_bytes + kSlabWaste) continue;
         const bool idle = !s.done_valid || hipEventQuery(s.done) == hipSuccess;
         // idle: the smallest adequate one; busy: the first in the list, which was released first
         if (idle) {
@@ -154,14 +182,21 @@ hipError_t slab_get(flexsp_ctx *ctx, size_t dev_bytes, size_t host_bytes, PlanSl
     PlanSlab s;
     s.dev_bytes = dev_bytes + dev_bytes / 4 + 256;
     s.host_bytes = host_bytes + host_bytes / 4 + 256;
-    hipError_t e = hipMalloc(&s.dev, s.dev_bytes);
-    if (e == hipSuccess) e = hipHostMalloc(&s.host, s.host_bytes, hipHostMallocDefault);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&s.ready, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&s.done, hipEventDisableTiming);
-    if (e != hipSuccess) {
-        slab_free(s);
-        return e;
+    hipError_t e = slab_make(s);
+    while (e == hipErrorOutOfMemory && !ctx->slabs.empty()) {
+        (void)hipGetLastError();
+        size_t room = 0, total = 0;
+        if (hipMemGetInfo(&room, &total) != hipSuccess) return e;
+        for (const PlanSlab &x : ctx->slabs) room += x.dev_bytes;
+        if (room < s.dev_bytes) return e;  // in vain (the next, smaller request may find what it needs in the pool)
+        size_t i = 0;
+        while (i + 1 < ctx->slabs.size() && ctx->slabs[i].done_valid && hipEventQuery(ctx->slabs[i].done) != hipSuccess) i++;
+        if (ctx->slabs[i].done_valid && hipEventQuery(ctx->slabs[i].done) != hipSuccess) i = 0;  // none has finished: the one released first
+        slab_give_back(ctx, ctx->slabs[i]);
+        ctx->slabs.erase(ctx->slabs.begin() + i);
+        e = slab_make(s);
     }
+    if (e != hipSuccess) return e;
     ctx->slabs_owned++;
     ctx->slab_bytes += s.dev_bytes;
     out = s;
@@ -1271,26 +1306,19 @@ void flexsp_plan_destroy(flexsp_plan *plan)
             else
                 s.done_valid = true;
         }
-        auto give_back = [&](PlanSlab &slab) {
-            if (slab.done_valid) (void)hipEventSynchronize(slab.done);
-            (void)hipEventSynchronize(slab.ready);
-            ctx->slab_bytes -= slab.dev_bytes;
-            slab_free(slab);
-            ctx->slabs_owned--;
-        };
         size_t pooled = s.dev_bytes;
         for (const PlanSlab &x : ctx->slabs) pooled += x.dev_bytes;
         // the one released longest ago first: were the pool closed to the plan at hand once it is full, every plan of a larger batch to
         // come would be a hipMalloc and a hipFree (a step of 44 874 tokens, 3 heads behind 16 smaller plans 453 -> 2 200 us)
         while (!ctx->slabs.empty() && (pooled > kSlabPoolBytes || ctx->slabs.size() >= kSlabPoolMax)) {
             pooled -= ctx->slabs.front().dev_bytes;
-            give_back(ctx->slabs.front());
+            slab_give_back(ctx, ctx->slabs.front());
             ctx->slabs.erase(ctx->slabs.begin());
         }
         try {
             ctx->slabs.push_back(s);
         } catch (const std::bad_alloc &) {
-            give_back(s);
+            slab_give_back(ctx, s);
         }
     }
     delete plan;

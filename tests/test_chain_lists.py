@@ -1,5 +1,5 @@
-"""CPU: the list of a backward in one pass and when there is one (tests/sanitize/driver_chain.cpp includes the host source), under the
-sanitizers; what the compiler says about its kernels' registers."""
+"""CPU: the list of a backward in one pass and when there is one, and the memory plans take, keep and give back (tests/sanitize/driver_chain.cpp
+and driver_pool.cpp include the host source), under the sanitizers; what the compiler says about its kernels' registers."""
 import os
 import re
 import shutil
@@ -11,17 +11,25 @@ from paper_2412_01523_amd import build
 from test_sanitizers import OUT, ROOT, SAN, _run
 
 
-def test_lists_under_asan_ubsan():
+def _run_driver(name):
     hipcc = "/opt/rocm/bin/hipcc" if os.path.exists("/opt/rocm/bin/hipcc") else shutil.which("hipcc")
     if not hipcc:
         pytest.skip("hipcc not found")
     OUT.mkdir(exist_ok=True)
-    exe = OUT / "driver_chain"
+    exe = OUT / name
     _run([hipcc, "--offload-arch=gfx950", "-O1", "-g", "-std=c++17", "-fno-omit-frame-pointer",
           "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined", "-fno-gpu-rdc",
           f"-I{ROOT / 'include'}", f"-I{ROOT / 'paper_2412_01523_amd' / 'csrc'}", "-o", str(exe),
-          str(SAN / "driver_chain.cpp"), "-fsanitize=address", "-fsanitize=undefined"])
+          str(SAN / f"{name}.cpp"), "-fsanitize=address", "-fsanitize=undefined"])
     assert "ok" in _run([str(exe)])
+
+
+def test_lists_under_asan_ubsan():
+    _run_driver("driver_chain")
+
+
+def test_plan_memory_under_asan_ubsan():
+    _run_driver("driver_pool")
 
 
 def test_registers():
