@@ -178,6 +178,39 @@ def test_a_row_that_is_not_finite(ctx, name):
     b.plan.close()
 
 
+@pytest.mark.parametrize("name", ["edges", "grouped", "unmasked"])
+@pytest.mark.parametrize("f32", [False, True])
+def test_views_and_head_subsets(ctx, name, f32):
+    """Some heads of wider tensors whose rows and heads lie apart, each tensor its own way: the dense tensors' bits, and nothing beside them."""
+    import torch
+    print(f"chain, views: {name}, f32={f32}", flush=True)
+    b = Backward(ctx, name)
+    T, dtype = int(b.cu[-1]), torch.float32 if f32 else torch.bfloat16
+    ref = b.run(b.outputs(dtype))
+    first_q, first_kv = 3, 1
+
+    def wide(x, first, heads, d):  # rows of `heads` heads of d elements, the first 128 of each
+        t = torch.full((T + 2, first + heads, d), 7.0, dtype=x.dtype, device="cuda")
+        v = t[1:-1, :, :128]
+        v[:, first:first + x.shape[1]] = x
+        return t, v
+
+    q, g, o = (wide(x, first_q, b.hq + n, d)[1] for x, n, d in ((b.q, 0, 136), (b.g, 2, 128), (b.o, 1, 192)))
+    k, v = (wide(x, first_kv, b.hkv + n, d)[1] for x, n, d in ((b.k, 3, 144), (b.v, 0, 128)))
+    outs = [wide(torch.full_like(x, 7.0), first, x.shape[1] + n, d)
+            for x, first, n, d in zip(ref, (first_q, first_kv, first_kv), (1, 0, 2), (160, 128, 136))]
+    ctx.profile_start(16)
+    b.fx.flexsp_attn_varlen_bwd(ctx, b.plan, q, k, v, o, g, b.lse, b.cud, *(x for _, x in outs), causal=b.causal,
+                                head_begin=first_q, head_count=b.hq, kv_head_begin=first_kv, kv_head_count=b.hkv)
+    assert ctx.profile_stop()["bwd_delta"][1] == 1
+    for n, (t, view), want, first in zip(("dQ", "dK", "dV"), outs, ref, (first_q, first_kv, first_kv)):
+        mine = view[:, first:first + want.shape[1]]
+        assert torch.equal(mine, want), n
+        mine.fill_(7.0)
+        assert (t == 7).all(), f"{n}: written beside"
+    b.plan.close()
+
+
 def test_replayed_from_a_graph(ctx):
     import torch
     b = Backward(ctx, "edges")
