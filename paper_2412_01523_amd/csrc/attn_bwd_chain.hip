@@ -11,7 +11,7 @@
 // The rows in between (32 KB per step and item, read and written) stay in the L2 of the compute die that runs the neighbouring key tiles
 // at that time: plain stores, loads that pass by the compute unit's own cache (sc1).  Measured on a buffer that a die's 32 compute units
 // hand round: every such load sees the store, 12 TB/s read and as much written over the chip.  From die to die both go through
-// memory (2.8 TB/s), so that only the last item of a bundle (see ChainDealer) stores its rows that way.
+// memory (2.8 TB/s), so that only the last item of a bundle (see chain_take) stores its rows that way.
 // What the hand-over relies on.  Within a die: a plain store that has been counted (vmcnt) is in the die's L2, and an sc1 load asks there; a
 // wavefront that reads its own store back like that has to see it, and the L2 does not tell one unit's stores from another's.  From die to die: rows
 // and flag are stored and loaded with sc1, which is what relaxed atomic accesses of agent scope are made of; such a load may not return an older copy
@@ -85,20 +85,11 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_delta_kernel(const AttnArgs
 }
 
 // ------------------------------------------------------------------------------ work
-// The list is cut into bundles (build_chain).  A compute die takes a bundle at a time, in the order of the list, and its workgroups draw the
-// bundle's items one by one: what a bundle shares meets in the die's L2.  A die's word holds the next item and the end of its bundle;
-// whoever draws the item at the end takes the next bundle for the die, the others wait for that.
-// Every wait ends, however few workgroups are resident.  An item waits for items in front of it in the list only.  Of all items that are not
-// done, take the first: what it waits for is done.  If it has been drawn, a running workgroup has it, and finishes it.  If not, but its
-// bundle has been taken, the workgroups of that die have drawn only from what stands in front of it (a die takes a bundle when the one
-// before has been drawn to the end), all of it done, so they are free and draw it; there is such a workgroup, for whoever takes a
-// bundle draws from it.  If its bundle has not been taken, neither has any behind it: everybody who runs is free, or holds something that is
-// done, and takes it.  A workgroup that waits for a bundle to be taken waits for one that waits for nobody.
+// The workgroups' side of chain_take.
 struct ChainDealer {
-    static constexpr uint32_t kDone = 0x80000000u;
     const int32_t *offsets;
     uint32_t *next;            // bundles taken
-    unsigned long long *word;  // end << 32 | next item
+    unsigned long long *word;  // this die's
     typedef volatile __attribute__((address_space(3))) int Word;
     Word *slot;
     int bundles, wave, lane;
@@ -110,29 +101,23 @@ struct ChainDealer {
         if (lane == 0) w = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return w;
     }
-    __device__ __forceinline__ int take(unsigned long long w)  // wavefront 0: the item drawn, or -1 when there are no more
+    __device__ __forceinline__ unsigned long long look() { return __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ void put(unsigned long long w)
     {
-        for (;;) {
-            const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)w), end = __builtin_amdgcn_readfirstlane((uint32_t)(w >> 32));
-            if (at & kDone) return -1;
-            if (at < end) return (int)at;
-            if (at == end) {
-                uint32_t b = 0;
-                if (lane == 0) b = __hip_atomic_fetch_add(next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                b = __builtin_amdgcn_readfirstlane(b);
-                const bool more = b < (uint32_t)bundles;
-                const uint32_t first = more ? (uint32_t)offsets[b] : 0, stop = more ? (uint32_t)offsets[b + 1] : 0;
-                if (lane == 0) __hip_atomic_store(word, more ? (unsigned long long)stop << 32 | (first + 1) : (unsigned long long)kDone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                return more ? __builtin_amdgcn_readfirstlane((int)first) : -1;
-            }
-            for (uint32_t e = end;;) {
-                const unsigned long long v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                e = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-                if (e != end || (__builtin_amdgcn_readfirstlane((uint32_t)v) & kDone)) break;
-                __builtin_amdgcn_s_sleep(1);
-            }
-            w = draw();
-        }
+        if (lane == 0) __hip_atomic_store(word, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ uint32_t bundle()
+    {
+        uint32_t b = 0;
+        if (lane == 0) b = __hip_atomic_fetch_add(next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return __builtin_amdgcn_readfirstlane(b);
+    }
+    __device__ __forceinline__ uint32_t low(unsigned long long w) { return __builtin_amdgcn_readfirstlane((uint32_t)w); }
+    __device__ __forceinline__ uint32_t high(unsigned long long w) { return __builtin_amdgcn_readfirstlane((uint32_t)(w >> 32)); }
+    __device__ __forceinline__ void rest() { __builtin_amdgcn_s_sleep(1); }
+    __device__ __forceinline__ int take(unsigned long long w)  // wavefront 0
+    {
+        return __builtin_amdgcn_readfirstlane(chain_take(*this, w, offsets, bundles));
     }
     __device__ __forceinline__ int publish(int idx)
     {

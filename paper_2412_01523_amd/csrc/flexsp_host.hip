@@ -711,7 +711,7 @@ bool dies_even(const std::vector<flexsp_item> &list, const std::vector<ChainBund
     return 100 * *std::max_element(share.begin(), share.end()) * dies <= (causal ? 111 : 106) * all;
 }
 
-// Lists a backward in one pass, if it is one.  The list's bundles (see ChainDealer) are what a compute die's workgroups, one per compute
+// Lists a backward in one pass, if it is one.  The list's bundles (see chain_take) are what a compute die's workgroups, one per compute
 // unit, work on at a time, and what they share should stay in its L2: the rows of dQ that are added to, Q and dO, 64 KB a step.  So a long
 // sequence's key tiles are bundles of up to kChainTeam, one to a workgroup, which go through the steps one behind the other; heads and
 // sequences of fewer tiles are put together, kChainSpan items or a little more, and lie in a bundle as their walks' lengths say, so that

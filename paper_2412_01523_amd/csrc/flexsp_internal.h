@@ -71,6 +71,42 @@ constexpr int kChainSpan = 64;   // shorter ones are put together until a bundle
 constexpr size_t kChainTileBytes = (size_t)kDkvBq * 128 * sizeof(float);        // partial sums of dQ: 64 query rows of a head, D = 128
 constexpr int64_t kChainMostTiles = ((int64_t)4 << 30) / (int64_t)kChainTileBytes;  // a plan keeps up to 4 GiB of them
 
+// How a chain's workgroups get their items.  The list is cut into bundles (build_chain).  A compute die takes a bundle at a time, in the order of the
+// list, and its workgroups draw the bundle's items one by one: what a bundle shares meets in the die's L2.  A die's word holds the next item and the end
+// of its bundle (end << 32 | next); whoever draws the item at the end takes the next bundle for the die, the others wait for that.  Returns the
+// item that a draw of the word's value `w` stands for, or -1 when there are no more.
+// Every wait ends, however few workgroups are resident.  An item waits for items in front of it in the list only.  Of all items that are not
+// done, take the first: what it waits for is done.  If it has been drawn, a running workgroup has it, and finishes it.  If not, but its
+// bundle has been taken, the workgroups of that die have drawn only from what stands in front of it (a die takes a bundle when the one
+// before has been drawn to the end), all of it done, so they are free and draw it; there is such a workgroup, for whoever takes a
+// bundle draws from it.  If its bundle has not been taken, neither has any behind it: everybody who runs is free, or holds something that is
+// done, and takes it.  A workgroup that waits for a bundle to be taken waits for one that waits for nobody.
+// DIE: draw() adds one to the word and returns what it was, look() reads it, put(w) replaces it, bundle() counts bundles taken (of all dies), low(w) and
+// high(w) are a word's halves, rest() passes some time.
+constexpr uint32_t kChainDone = 0x80000000u;
+template <class DIE>
+__host__ __device__ __forceinline__ int chain_take(DIE &&die, unsigned long long w, const int32_t *offsets, int bundles)
+{
+    for (;;) {
+        const uint32_t at = die.low(w), end = die.high(w);
+        if (at & kChainDone) return -1;
+        if (at < end) return (int)at;
+        if (at == end) {
+            const uint32_t b = die.bundle();
+            const bool more = b < (uint32_t)bundles;
+            const uint32_t first = more ? (uint32_t)offsets[b] : 0, stop = more ? (uint32_t)offsets[b + 1] : 0;
+            die.put(more ? (unsigned long long)stop << 32 | (first + 1) : (unsigned long long)kChainDone);
+            return more ? (int)first : -1;
+        }
+        for (;;) {
+            const unsigned long long v = die.look();
+            if (die.high(v) != end || (die.low(v) & kChainDone)) break;
+            die.rest();
+        }
+        w = die.draw();
+    }
+}
+
 // Work item of the key-shard forward: query rows q_start .. q_start+q_len-1 of q / o / lse, shard
 // keys k_start .. k_start+k_len-1 of k / v, shift = position of the first query in its sequence
 // minus position of the shard's first key.  `tile` counts 128-row query tiles.

@@ -1,5 +1,5 @@
-"""CPU: the list of a backward in one pass and when there is one, and the memory plans take, keep and give back (tests/sanitize/driver_chain.cpp
-and driver_pool.cpp include the host source), under the sanitizers; what the compiler says about its kernels' registers."""
+"""CPU: the list of a backward in one pass and when there is one, who draws which item of it, and the memory plans take, keep and give back
+(tests/sanitize/driver_chain.cpp, driver_dealer.cpp and driver_pool.cpp include the host source), under the sanitizers; what the compiler says about its kernels' registers."""
 import os
 import re
 import shutil
@@ -30,6 +30,10 @@ def test_lists_under_asan_ubsan():
 
 def test_plan_memory_under_asan_ubsan():
     _run_driver("driver_pool")
+
+
+def test_every_item_once_and_every_wait_ends():
+    _run_driver("driver_dealer")
 
 
 def test_registers():
