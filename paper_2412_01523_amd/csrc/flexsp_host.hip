@@ -67,8 +67,9 @@ struct flexsp_plan {
     std::vector<int32_t> cu_k, shift;
     int64_t Tk = 0;
     bool wide = false;  // the dK/dV pass's items have kDkvWideBk keys
+    mutable bool two_listed = true;  // the two backward passes are listed (a plan that runs in one lists them when somebody asks)
     bool halves = false;  // the forward is launched in halves: its direct list has kHalfBq query rows to an item
-    HostPass pass[3];
+    mutable HostPass pass[3];
     std::vector<flexsp_item> chain;        // items of the backward in one pass (attn_bwd_chain.hip); empty: it runs in two
     std::vector<int32_t> chain_bundles;    // ... boundaries of its bundles
     int64_t chain_tiles = 0;  // tiles of kDkvBq query rows it keeps partial sums of, over all heads
@@ -672,6 +673,37 @@ bool wide_keys(const flexsp_plan *p, int n_wg)
     return 2 * wide_items > n_wg && wide_items <= n_wg && (p->Hq == p->Hkv || full);
 }
 
+// Lists the dK/dV and the dQ pass; `forward`: the forward's list, if it is as build_pass has left it.
+void list_two_passes(const flexsp_plan *p, const HostPass *forward)
+{
+    const int nq = p->ctx->num_xcd, n_wg = workgroups_of(p->ctx);
+    const bool causal = p->causal != 0;
+    static_assert(kFwdBq == kDqBq && kFwdBk == kDqBk, "the forward's and the dQ kernel's items are listed alike");
+    HostPass &dkv = p->pass[FLEXSP_PASS_BWD_DKV], &dq = p->pass[FLEXSP_PASS_BWD_DQ];
+    build_pass(p->cu, p->B, p->Hkv, p->Hq / p->Hkv, p->wide ? kDkvWideBk : kDkvBk, kDkvBq, causal, true, p->D, nq, n_wg, dkv);
+    if (forward)
+        dq = *forward;
+    else
+        build_pass(p->cu, p->B, p->Hq, 1, kDqBq, kDqBk, causal, false, p->D, nq, n_wg, dq);
+    direct_list(dkv, nq, n_wg, 0, kShortPartSteps);
+    direct_list(dq, nq, n_wg, 0, kShortPartSteps);
+}
+
+// The lists of a plan that runs in one pass, when they are asked for (they took most of the time of making it, us: one sequence of 131 072 tokens, 8
+// heads 727 -> 251, 49 152 tokens in short ones 337 -> 165, a 64K-token long-tail batch 410 -> 180).
+int need_two_passes(const flexsp_plan *p)
+{
+    if (p->two_listed) return FLEXSP_OK;
+    try {
+        list_two_passes(p, nullptr);
+    } catch (const std::bad_alloc &) {
+        p->pass[FLEXSP_PASS_BWD_DKV] = p->pass[FLEXSP_PASS_BWD_DQ] = HostPass{};
+        return FLEXSP_OUT_OF_MEMORY;
+    }
+    p->two_listed = true;
+    return FLEXSP_OK;
+}
+
 // Whether a backward runs in one pass (attn_bwd_chain.hip): D = 128 and
 // - at least two items of 128 keys per compute unit, three steps of 64 query rows an item and head, twelve without a mask: a delta launch in
 //   front and the start of an item, during which its compute unit does nothing else, have to be made up for;
@@ -679,8 +711,8 @@ bool wide_keys(const flexsp_plan *p, int n_wg)
 //   compute units wait for the last;
 // - no (sequence, kv head) of more than a quarter of the steps: each of its items starts a step or two behind the one before.
 // Backward, two kernels -> one pass, us.  Taken: 17 433 tokens, 4 heads, up to 1 290 a sequence 114 -> 88; 28 916 in one, 4 heads 2 776 -> 2 480; 82 128,
-// 4 heads, up to 23 445 2 971 -> 2 693; 66 564 in sequences of 757, 8 heads, unmasked (9.9 steps an item, not taken) 738 -> 741; 26 644 in 441, 16 heads on 8 290 ->
-// 279.  Not taken: 130 077 in one, 1 head 14 965 -> 16 098; 84 931, 1 head, up to 21 776 732 -> 854; 9 400 in 460, 16 heads on 8
+// 4 heads, up to 23 445 2 971 -> 2 693; 26 644 in 441, 16 heads on 8 290 -> 279.  Not taken: 66 564 in sequences of 757, 8 heads, unmasked (9.9 steps
+// an item) 738 -> 741; 130 077 in one, 1 head 14 965 -> 16 098; 84 931, 1 head, up to 21 776 732 -> 854; 9 400 in 460, 16 heads on 8
 // 129 -> 140; 41 048 in 65, 16 heads on 2 321 -> 342; 95 093, 8 heads on 1, unmasked 5 220 -> 6 520; 24 348 in 99, 1 head 19 -> 30.
 bool chain_pays(const flexsp_plan *p, int64_t steps, int64_t longest, int64_t largest, int64_t items, int n_cu)
 {
@@ -849,6 +881,10 @@ int plan_upload(flexsp_ctx *ctx, flexsp_plan *p)
         if (e == hipErrorOutOfMemory && !p->chain.empty()) {  // two passes need less
             (void)hipGetLastError();
             p->chain.clear();
+            if (const int rc = need_two_passes(p)) {
+                delete p;
+                return rc;
+            }
             return plan_upload(ctx, p);
         }
         if (e != hipSuccess) {
@@ -1160,12 +1196,11 @@ int flexsp_plan_create(flexsp_ctx *ctx, const int32_t *cu, int32_t B, int32_t Hq
         const int nq = ctx->num_xcd, n_wg = workgroups_of(ctx);
         build_pass(p->cu, B, Hq, 1, kFwdBq, kFwdBk, causal != 0, false, D, nq, n_wg, p->pass[FLEXSP_PASS_FWD]);
         p->wide = wide_keys(p, n_wg);
-        build_pass(p->cu, B, Hkv, Hq / Hkv, p->wide ? kDkvWideBk : kDkvBk, kDkvBq, causal != 0, true, D, nq, n_wg, p->pass[FLEXSP_PASS_BWD_DKV]);
-        static_assert(kFwdBq == kDqBq && kFwdBk == kDqBk, "the forward's and the dQ kernel's items are listed alike");
-        p->pass[FLEXSP_PASS_BWD_DQ] = p->pass[FLEXSP_PASS_FWD];
-        for (int i = 0; i < 3; i++) direct_list(p->pass[i], nq, n_wg, 0, i == FLEXSP_PASS_FWD ? 0 : kShortPartSteps);
-        p->halves = halve_items(p, n_wg / 2);
         build_chain(p, n_wg / 2);
+        p->two_listed = p->chain.empty();
+        if (p->two_listed) list_two_passes(p, &p->pass[FLEXSP_PASS_FWD]);
+        direct_list(p->pass[FLEXSP_PASS_FWD], nq, n_wg, 0, 0);
+        p->halves = halve_items(p, n_wg / 2);
     } catch (const std::bad_alloc &) {
         delete p;
         return FLEXSP_OUT_OF_MEMORY;
@@ -1327,6 +1362,8 @@ void flexsp_plan_destroy(flexsp_plan *plan)
 int64_t flexsp_plan_num_items(const flexsp_plan *plan, int pass)
 {
     if (!plan || pass < 0 || pass > 2) return FLEXSP_INVALID_ARGUMENT;
+    if (pass != FLEXSP_PASS_FWD)
+        if (const int rc = need_two_passes(plan)) return rc;
     return (int64_t)plan->pass[pass].items.size();
 }
 
@@ -1334,6 +1371,8 @@ int flexsp_plan_get_items(const flexsp_plan *plan, int pass, flexsp_item *items,
                           int64_t *queue_offsets)
 {
     if (!plan || pass < 0 || pass > 2) return FLEXSP_INVALID_ARGUMENT;
+    if (pass != FLEXSP_PASS_FWD)
+        if (const int rc = need_two_passes(plan)) return rc;
     const HostPass &hp = plan->pass[pass];
     if (capacity < (int64_t)hp.items.size() || (!items && !hp.items.empty())) return FLEXSP_INVALID_ARGUMENT;
     if (!hp.items.empty()) std::memcpy(items, hp.items.data(), hp.items.size() * sizeof(flexsp_item));
@@ -1345,6 +1384,7 @@ int flexsp_plan_get_items(const flexsp_plan *plan, int pass, flexsp_item *items,
 int flexsp_plan_tile_rows(const flexsp_plan *plan, int pass)
 {
     if (!plan || pass < 0 || pass > 2) return FLEXSP_INVALID_ARGUMENT;
+    if (!plan->two_listed && pass != FLEXSP_PASS_FWD) return pass == FLEXSP_PASS_BWD_DKV ? (plan->wide ? kDkvWideBk : kDkvBk) : kDqBq;
     return plan->pass[pass].tile_rows;
 }
 

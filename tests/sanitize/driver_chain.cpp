@@ -26,6 +26,28 @@ hipError_t static_scratch_init(int) { return hipErrorUnknown; }
 
 #define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "FAILED: %s (line %d)\n", #c, __LINE__); return 1; } } while (0)
 
+// The two passes' lists of a plan that runs in one: made when they are asked for, and then what they would have been at once.
+static int check_two_passes(flexsp_plan *p, int nq, int n_wg)
+{
+    for (int pass : {FLEXSP_PASS_BWD_DKV, FLEXSP_PASS_BWD_DQ}) CHECK(p->pass[pass].items.empty());
+    CHECK(flexsp_plan_tile_rows(p, FLEXSP_PASS_BWD_DKV) == kDkvBk && flexsp_plan_tile_rows(p, FLEXSP_PASS_BWD_DQ) == kDqBq);
+    for (int pass : {FLEXSP_PASS_BWD_DQ, FLEXSP_PASS_BWD_DKV}) {
+        HostPass want;
+        if (pass == FLEXSP_PASS_BWD_DKV)
+            build_pass(p->cu, p->B, p->Hkv, p->Hq / p->Hkv, kDkvBk, kDkvBq, p->causal != 0, true, p->D, nq, n_wg, want);
+        else
+            build_pass(p->cu, p->B, p->Hq, 1, kDqBq, kDqBk, p->causal != 0, false, p->D, nq, n_wg, want);
+        CHECK(flexsp_plan_num_items(p, pass) == (int64_t)want.items.size());
+        std::vector<flexsp_item> got(want.items.size());
+        int64_t offsets[kMaxQueues + 1];
+        CHECK(flexsp_plan_get_items(p, pass, got.data(), (int64_t)got.size(), offsets) == FLEXSP_OK);
+        CHECK(std::memcmp(got.data(), want.items.data(), got.size() * sizeof(flexsp_item)) == 0);
+        for (int x = 0; x <= nq; x++) CHECK(offsets[x] == want.offsets[x]);
+        CHECK(flexsp_plan_tile_rows(p, pass) == want.tile_rows);
+    }
+    return 0;
+}
+
 static int check_list(const flexsp_plan *p)
 {
     const int G = p->Hq / p->Hkv;
@@ -89,7 +111,7 @@ int main()
         CHECK(flexsp_plan_create(ctx, cu.data(), B, hq, hkv, 128, causal, &p) == FLEXSP_OK);
         if (!p->chain.empty()) {
             taken++;
-            if (check_list(p)) return 1;
+            if (check_list(p) || check_two_passes(p, ctx->num_xcd, workgroups_of(ctx))) return 1;
         }
         flexsp_plan_destroy(p);
     }
