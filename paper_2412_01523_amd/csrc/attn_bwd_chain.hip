@@ -22,9 +22,9 @@
 // eight wavefronts has a compute unit to itself, two to a SIMD with 256 registers each.  While one of the two does matrix work alone
 // (sums) the other forms S, dP and their exponentials (scores): wavefronts 0 .. 3 in this order, 4 .. 7 in the other.
 // Of the rows' stores 28 % leave the L2 on long sequences all the same: what 32 workgroups two steps apart are busy with is as large as it.
-// Backward, two kernels -> this, us: one sequence of 131 072 tokens, 8 heads 101 280 -> 89 180, 32 768 6 581 -> 5 576; sequences of 4 096 1 874 ->
-// 1 668, 2 048 805 -> 739, 1 024 476 -> 457; 49 152 tokens, up to 1 024 a sequence 390 -> 383; a 64K-token long-tail batch 1 329 -> 1 246;
-// 262 144 tokens, 16 heads on 2 122 170 -> 111 100.
+// Backward, two kernels -> this, us: 8 heads, one sequence of 131 072 tokens 100 070 -> 90 840, 32 768 6 465 -> 5 510; 65 536 tokens in sequences of 4 096
+// 1 871 -> 1 645, 2 048 1 095 -> 986, 1 024 625 -> 617; 49 152 tokens, up to 1 024 a sequence 393 -> 381; a 64K-token long-tail batch 1 313 -> 1 231;
+// 262 144 tokens, 16 heads on 2 121 140 -> 108 990.
 // Tried on the way: both wavefronts of a SIMD in the same phase, two barriers a step (as fast as two kernels); the exponentials between the
 // sums' matrix instructions of the same wavefront (56 registers too many).
 #include <type_traits>
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(kChainThreads, 2) void attn_bwd_chain_kernel(const 
                     same();
                     window(w + 1);
                     // (first of all: asked for in scores, their time beyond that is all waiting for the block that meets them in memory; and the
-                    // block in front is everybody's pace.  32 768 tokens 5 717 -> 5 517 us, sequences of 4 096 1 682 -> 1 655, 1 024 463 -> 453)
+                    // block in front is everybody's pace: 2 to 4 %)
                     if (w + 2 < n) copy_all();
                     copied();
                     ask();

@@ -711,8 +711,8 @@ int need_two_passes(const flexsp_plan *p)
 //   compute units wait for the last;
 // - no (sequence, kv head) of more than a quarter of the steps: each of its items starts a step or two behind the one before.
 // Backward, two kernels -> one pass, us.  Taken: 17 433 tokens, 4 heads, up to 1 290 a sequence 114 -> 88; 28 916 in one, 4 heads 2 776 -> 2 480; 82 128,
-// 4 heads, up to 23 445 2 971 -> 2 693; 26 644 in 441, 16 heads on 8 290 -> 279.  Not taken: 66 564 in sequences of 757, 8 heads, unmasked (9.9 steps
-// an item) 738 -> 741; 130 077 in one, 1 head 14 965 -> 16 098; 84 931, 1 head, up to 21 776 732 -> 854; 9 400 in 460, 16 heads on 8
+// 4 heads, up to 23 445 2 971 -> 2 693; 26 644 in 441, 16 heads on 8 290 -> 279; 66 564 in 757, 8 heads, unmasked (twelve steps an item) 863 -> 823.
+// Not taken: 130 077 in one, 1 head 14 965 -> 16 098; 84 931, 1 head, up to 21 776 732 -> 854; 9 400 in 460, 16 heads on 8
 // 129 -> 140; 41 048 in 65, 16 heads on 2 321 -> 342; 95 093, 8 heads on 1, unmasked 5 220 -> 6 520; 24 348 in 99, 1 head 19 -> 30.
 bool chain_pays(const flexsp_plan *p, int64_t steps, int64_t longest, int64_t largest, int64_t items, int n_cu)
 {
