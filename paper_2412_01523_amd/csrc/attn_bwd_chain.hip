@@ -157,11 +157,24 @@ __device__ __forceinline__ void flag_to_lds(const int32_t *g, void *lds)
 // As global_to_lds16 with a base in scalar registers.  A scalar register that a vector instruction has written (v_readlane: this kernel's scalars do not all
 // fit, and wait in lanes of a vector register) may be a memory instruction's address five wait states later at the earliest; the hardware does
 // not wait, and the compiler does not count for an inline assembly statement.  So the statement counts itself (the write of m0 is one of
-// them).  32 768 tokens, 8 heads 5 608 -> 5 618 us, shorter sequences the same.
+// them).
 __device__ __forceinline__ void scalar_to_lds16(const void *base, uint32_t lane_off, void *lds)
 {
     const uint32_t dst = (uint32_t)(uintptr_t)lds;
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base), "s"(dst) : "memory");
+}
+// A wavefront's share of two tiles in one statement, which counts once: `a0`, `a1` of `a` to lds and GAP bytes behind, `b0`, `b1` of `b` to 2 and 3 GAP
+// behind.  The wavefronts that copy right behind the barrier hold everybody up meanwhile: one sequence of 131 072 tokens, 8 heads 90 960 -> 89 130 us
+// against four statements, shorter ones the same.
+template <int GAP>
+__device__ __forceinline__ void scalar_to_lds16(const void *a, uint32_t a0, uint32_t a1, const void *b, uint32_t b0, uint32_t b1, void *lds)
+{
+    const uint32_t dst = (uint32_t)(uintptr_t)lds;
+    asm volatile("s_mov_b32 m0, %6\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %4\n\t"
+                 "s_add_u32 m0, %6, %7\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %4\n\t"
+                 "s_add_u32 m0, %6, %8\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %5\n\t"
+                 "s_add_u32 m0, %6, %9\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %5" ::"v"(a0), "v"(a1), "v"(b0), "v"(b1), "s"(a), "s"(b), "s"(dst),
+                 "n"(GAP), "n"(2 * GAP), "n"(3 * GAP) : "memory", "scc");
 }
 __device__ __forceinline__ void scalar_to_lds4(const void *base, uint32_t lane_off, void *lds)
 {
@@ -246,10 +259,7 @@ __global__ __launch_bounds__(kChainThreads, 2) void attn_bwd_chain_kernel(const 
         };
         auto copy_all = [&]() {
             copy_stats();
-            copy(0);
-            copy(1);
-            copy(2);
-            copy(3);
+            scalar_to_lds16<QTILE / 2>(q_f, oq0, oq1, g_f, og0, og1, smem + base_f + wave * 1024);
         };
         auto copied = [&]() {  // (the heads of a tile one after the other, then the tile in front)
             base_f = base_f == (NB - 1) * STEP ? 0 : base_f + STEP;

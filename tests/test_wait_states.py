@@ -64,4 +64,8 @@ def test_scalar_addresses(src):
         copies = [at for at, (op, operands) in enumerate(code) if op.startswith("global_load_lds") and scalars(operands)]
         assert len(copies) >= 20
         for at in copies:
-            assert code[at - 2][0] == "s_mov_b32" and code[at - 1][0] == "s_nop" and int(code[at - 1][1][0]) + 2 >= NEEDED, code[at - 2:at + 1]
+            waits, before = 0, at
+            while waits < NEEDED and (code[before - 1][0] in ("s_nop", "global_load_lds_dwordx4") or "m0" in code[before - 1][1][:1]):
+                before -= 1
+                waits += int(code[before][1][0]) + 1 if code[before][0] == "s_nop" else 1
+            assert waits >= NEEDED, code[before - 1:at + 1]
