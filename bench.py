@@ -46,8 +46,8 @@ HBM_PEAK = 8.0e12           # MI355X HBM3E, B/s
 # counter values and the algorithmic bytes beside them are in profiles/attention_hbm_traffic.md).
 # bench.py cannot run the profiler on itself: these are the figures of that summary (bwd_dkv: the one pass over the key tiles).
 MEASURED_HBM_TRAFFIC = {
-    ("pareto-64k", "fwd"): 1034448790, ("pareto-64k", "bwd_delta"): 274796210, ("pareto-64k", "bwd_dkv"): 3195276271,
-    ("single-128k", "fwd"): 11122565611, ("single-128k", "bwd_delta"): 549618520, ("single-128k", "bwd_dkv"): 105326908086,
+    ("pareto-64k", "fwd"): 1029050361, ("pareto-64k", "bwd_delta"): 274765133, ("pareto-64k", "bwd_dkv"): 3159890728,
+    ("single-128k", "fwd"): 11470496655, ("single-128k", "bwd_delta"): 549476366, ("single-128k", "bwd_dkv"): 86816250632,
 }
 
 

@@ -18,13 +18,14 @@
 // that its die's L2 still holds (whoever waits for a flag of another die's would wait for good), so it does not matter which versions of
 // a row a die has seen before.  The flag is stored when the rows have been counted.  Nobody reads rows of dQ in any other way, nor before the
 // flag says that they are there: no load ahead of time, plain or not.
-// What bounds it: the matrix unit is busy for half of the cycles, and the chip is at 1.8 GHz (zero inputs: 2.3).  A workgroup of
+// What bounds it: on long sequences the matrix unit is busy for half of the cycles (counters: 49 %, short ones 26), and the chip is at 1.8 to 1.95 GHz
+// (zero inputs: 2.3).  A workgroup of
 // eight wavefronts has a compute unit to itself, two to a SIMD with 256 registers each.  While one of the two does matrix work alone
 // (sums) the other forms S, dP and their exponentials (scores): wavefronts 0 .. 3 in this order, 4 .. 7 in the other.
-// Of the rows' stores 28 % leave the L2 on long sequences all the same: what 32 workgroups two steps apart are busy with is as large as it.
-// Backward, two kernels -> this, us: 8 heads, one sequence of 131 072 tokens 100 070 -> 90 840, 32 768 6 465 -> 5 510; 65 536 tokens in sequences of 4 096
-// 1 871 -> 1 645, 2 048 1 095 -> 986, 1 024 625 -> 617; 49 152 tokens, up to 1 024 a sequence 393 -> 381; a 64K-token long-tail batch 1 313 -> 1 231;
-// 262 144 tokens, 16 heads on 2 121 140 -> 108 990.
+// Of the rows' stores 24 % leave the L2 on long sequences all the same: what 32 workgroups two steps apart are busy with is as large as it.
+// Backward, two kernels -> this, us: 8 heads, one sequence of 131 072 tokens 99 470 -> 88 610, 32 768 6 436 -> 5 530; 65 536 tokens in sequences of 4 096
+// 1 853 -> 1 659, 2 048 1 089 -> 982, 1 024 622 -> 615; 49 152 tokens, up to 1 024 a sequence 393 -> 380; a 64K-token long-tail batch 1 305 -> 1 228;
+// 262 144 tokens, 16 heads on 2 120 650 -> 108 680.
 // Tried on the way: both wavefronts of a SIMD in the same phase, two barriers a step (as fast as two kernels); the exponentials between the
 // sums' matrix instructions of the same wavefront (56 registers too many).
 #include <type_traits>
